@@ -9,7 +9,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libensi_hip.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["api.hip", "api_keys.hip", "api_static.hip", "api_matmul.hip", "api_pmult.hip", "api_ccmm.hip", "ntt.hip", "ntt16.hip", "keyswitch16.hip", "pmult.hip", "ccmm.hip", "kernels.hip",
-           "accumulate_mfma.hip"]
+           "accumulate_mfma.hip"] + ["keyswitch16_ring.hip:%d" % s for s in range(5)]  # file:s -- compiled with -DKS_RING=s
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
@@ -20,6 +20,9 @@ FLAGS = [
 
 
 def compile_one(src, out, extra=(), verbose=False):
+    src, _, ring = src.partition(":")
+    if ring:
+        extra = list(extra) + ["-DKS_RING=" + ring]
     cmd = [HIPCC] + FLAGS + list(extra) + ["-I" + os.path.join(CSRC, "inc"), "-c", os.path.join(CSRC, src), "-o", out]
     if verbose:
         print(" ".join(cmd))
@@ -32,7 +35,7 @@ def build(verbose=False, lib=LIB, defines=None):
     os.makedirs(OBJ_DIR, exist_ok=True)
     defines = defines or {}
     tag = os.path.splitext(os.path.basename(lib))[0]
-    jobs = [(s, os.path.join(OBJ_DIR, "%s.%s.o" % (tag, os.path.splitext(s)[0])), defines.get(s, ())) for s in SOURCES]
+    jobs = [(s, os.path.join(OBJ_DIR, "%s.%s.o" % (tag, s.replace(".hip", "").replace(":", ""))), defines.get(s, ())) for s in reversed(SOURCES)]
     with ThreadPoolExecutor(max_workers=min(8, len(jobs))) as pool:
         objs = list(pool.map(lambda j: compile_one(j[0], j[1], j[2], verbose), jobs))
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-fno-gpu-rdc"] + objs + ["-o", lib]
@@ -48,7 +51,7 @@ def build_sanitized(lib=None):
     lib = lib or os.path.join(OBJ_DIR, "libensi_hip_san.so")
     os.makedirs(OBJ_DIR, exist_ok=True)
     san = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined", "-Xarch_host", "-fno-omit-frame-pointer", "-g"]
-    jobs = [(s, os.path.join(OBJ_DIR, "san.%s.o" % os.path.splitext(s)[0])) for s in SOURCES]
+    jobs = [(s, os.path.join(OBJ_DIR, "san.%s.o" % s.replace(".hip", "").replace(":", ""))) for s in reversed(SOURCES)]
     with ThreadPoolExecutor(max_workers=min(8, len(jobs))) as pool:
         objs = list(pool.map(lambda j: compile_one(j[0], j[1], san), jobs))
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-fno-gpu-rdc", "-fsanitize=address", "-fsanitize=undefined",

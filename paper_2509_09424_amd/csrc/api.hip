@@ -152,6 +152,16 @@ extern "C" int ensi_ctx_create(const ensi_params *prm, ensi_ctx **out) {
     ctx->primes = qs;
     ctx->primes.insert(ctx->primes.end(), ps.begin(), ps.end());
     const int np = ctx->L + ctx->K;
+    for (u64 q : ctx->primes)
+        ctx->kind.push_back(ctx->log_n < 12              ? PRIME_INT
+                            : q < ((u64)1 << 50)         ? PRIME_FP
+                            : q < ((u64)1 << 60) && q > ((u64)1 << 60) - ((u64)1 << 26) ? PRIME_WIDE
+                                                         : PRIME_INT);
+    // the key-switch kernels take one arithmetic for all special primes
+    ctx->special_kind = ctx->kind[ctx->L];
+    for (int k = 1; k < ctx->K; k++)
+        if (ctx->kind[ctx->L + k] != ctx->special_kind) ctx->special_kind = PRIME_INT;
+    for (int k = 0; k < ctx->K; k++) ctx->kind[ctx->L + k] = ctx->special_kind;
 
     std::vector<PrimeConst> pcs(np);
     std::vector<u64> tw((size_t)np * 4 * N);
@@ -175,13 +185,18 @@ extern "C" int ensi_ctx_create(const ensi_params *prm, ensi_ctx **out) {
         pc.r2 = hm_mulmod(r, r, q);
         pc.n_inv = hm_invmod((u64)N % q, q);
         pc.n_inv_s = hm_shoup(pc.n_inv, q);
-        // N = 2^16 rings transform limbs with primes below 2^50 in fp64 (see ntt16.hip)
-        const bool fp = ctx->log_n == 16 && q < ((u64)1 << 50);
+        // rings from 2^12 on transform limbs with primes below 2^50 in fp64, primes just below 2^60 in signed integers (see ntt16_core.h)
+        const bool fp = ctx->kind[i] == PRIME_FP, wide = ctx->kind[i] == PRIME_WIDE;
         if (fp) {
             const double qi = 1.0 / (double)q, nq = (double)pc.n_inv / (double)q;
-            pc.pad[0] = 1;
-            memcpy(&pc.pad[1], &qi, 8);
-            memcpy(&pc.pad[2], &nq, 8);
+            pc.kind = PRIME_FP;
+            memcpy(&pc.aux0, &qi, 8);
+            memcpy(&pc.aux1, &nq, 8);
+        } else if (wide) {
+            pc.kind = PRIME_WIDE;
+            pc.aux0 = ((u64)1 << 60) - q;
+            pc.n_inv_s = hm_wide_pack(hm_mulmod(pc.n_inv, (u64)1 << 32, q), q);
+            pc.n_inv = hm_wide_pack(pc.n_inv, q);
         }
         // powers of psi and psi^{-1}, then bit-reversed tables
         std::vector<u64> pw(N), ipw(N);
@@ -203,6 +218,11 @@ extern "C" int ensi_ctx_create(const ensi_params *prm, ensi_ctx **out) {
                 memcpy(&t[N + k], &wq, 8);
                 memcpy(&t[2 * N + k], &wi, 8);
                 memcpy(&t[3 * N + k], &wiq, 8);
+            } else if (wide) {
+                t[k] = hm_wide_pack(pw[rk], q);
+                t[N + k] = hm_wide_pack(hm_mulmod(pw[rk], (u64)1 << 32, q), q);
+                t[2 * N + k] = hm_wide_pack(ipw[rk], q);
+                t[3 * N + k] = hm_wide_pack(hm_mulmod(ipw[rk], (u64)1 << 32, q), q);
             } else {
                 t[k] = pw[rk];
                 t[N + k] = hm_shoup(pw[rk], q);
@@ -212,8 +232,8 @@ extern "C" int ensi_ctx_create(const ensi_params *prm, ensi_ctx **out) {
         }
     }
     // the fused key-switching kernels need every ciphertext prime on the fp64 path
-    ctx->ks16 = ctx->log_n == 16;
-    for (int i = 0; i < ctx->L; i++) ctx->ks16 = ctx->ks16 && pcs[i].pad[0] != 0;
+    ctx->ks16 = ctx->log_n >= 12;
+    for (int i = 0; i < ctx->L; i++) ctx->ks16 = ctx->ks16 && pcs[i].kind == PRIME_FP;
     std::vector<double> cs(2 * (size_t)N);
     for (size_t e = 0; e < cs.size(); e++) cs[e] = (double)cosl(M_PIl * (long double)e / (long double)N);
     ctx->rot_exp.resize(N / 2);
@@ -252,7 +272,8 @@ extern "C" int ensi_ctx_create(const ensi_params *prm, ensi_ctx **out) {
 
 static void free_modconst(ensi_ctx *ctx) {
     for (auto &kv : ctx->ks16c) {
-        (void)hipFree((void *)kv.second.hat_fp);
+        (void)hipFree((void *)kv.second.hat_sp);
+        (void)hipFree((void *)kv.second.down_h);
         (void)hipFree((void *)kv.second.pmod_fp);
         (void)hipFree((void *)kv.second.down_p);
         (void)hipFree((void *)kv.second.down_p_fp);
@@ -284,7 +305,6 @@ extern "C" void ensi_ctx_free(ensi_ctx *ctx) {
     if (ctx->ws_digits) (void)hipFree(ctx->ws_digits);
     if (ctx->ws_u) (void)hipFree(ctx->ws_u);
     if (ctx->ws_y) (void)hipFree(ctx->ws_y);
-    if (ctx->ws_ysp) (void)hipFree(ctx->ws_ysp);
     if (ctx->ws_virt) (void)hipFree(ctx->ws_virt);
     if (ctx->ws_desc) (void)hipFree(ctx->ws_desc);
     if (ctx->ws_plan) (void)hipFree(ctx->ws_plan);
@@ -423,21 +443,23 @@ int get_ks16(ensi_ctx *ctx, int l1, const Ks16Const **out) {
         kc.hat_mont = mu->hat;
         const u64 n_ring = (u64)ctx->N;
         auto prime_of = [&](int e) { return ctx->primes[e < l1 ? e : L + (e - l1)]; };
-        auto is_fp = [&](u64 t) { return t < ((u64)1 << 50); };
-        std::vector<double> hat_fp((size_t)kc.beta * ext * alpha * 2, 0.0), pmod((size_t)l1 * 2), down_p_fp((size_t)K * 2, 0.0),
-            down_q((size_t)l1 * (2 + 4 * K));
-        std::vector<u64> down_p((size_t)K * 2);
+        auto kind_of = [&](int e) { return ctx->kind[e < l1 ? e : L + (e - l1)]; };
+        const bool fp_special = ctx->special_kind == PRIME_FP, wide_special = ctx->special_kind == PRIME_WIDE;
+        std::vector<double> pmod((size_t)l1 * 2), down_p_fp((size_t)K * 2, 0.0), down_q((size_t)l1 * 2);
+        std::vector<u64> hat_sp((size_t)kc.beta * ext * alpha * 2, 0), down_p((size_t)K * 2), down_h((size_t)l1 * K * 2);
         for (int j = 0; j < kc.beta; j++) {
             const int first = j * alpha, ns = kc.n_src[j];
             for (int e = 0; e < ext; e++) {
                 const u64 t = prime_of(e);
-                if ((e >= first && e < first + ns) || !is_fp(t)) continue;
+                if ((e >= first && e < first + ns) || kind_of(e) == PRIME_INT) continue;
                 for (int a = 0; a < ns; a++) {
                     u64 h = 1;
                     for (int b = 0; b < ns; b++)
                         if (b != a) h = hm_mulmod(h, ctx->primes[first + b] % t, t);
-                    hat_fp[(((size_t)j * ext + e) * alpha + a) * 2] = (double)h;
-                    hat_fp[(((size_t)j * ext + e) * alpha + a) * 2 + 1] = (double)h / (double)t;
+                    const u64 h25 = hm_mulmod(h, ((u64)1 << 25) % t, t);
+                    u64 *hs = &hat_sp[(((size_t)j * ext + e) * alpha + a) * 2];
+                    hs[0] = kind_of(e) == PRIME_FP ? hm_split((int64_t)h, 25) : hm_split(hm_centred(h, t), 30);
+                    hs[1] = kind_of(e) == PRIME_FP ? hm_split((int64_t)h25, 25) : hm_split(hm_centred(h25, t), 30);
                 }
             }
         }
@@ -447,17 +469,15 @@ int get_ks16(ensi_ctx *ctx, int l1, const Ks16Const **out) {
             for (int b = 0; b < K; b++) P = hm_mulmod(P, ctx->primes[L + b] % q, q);
             pmod[2 * i] = (double)P;
             pmod[2 * i + 1] = (double)P / (double)q;
-            double *dq = &down_q[(size_t)i * (2 + 4 * K)];
+            double *dq = &down_q[(size_t)i * 2];
             const u64 sc = hm_mulmod(hm_invmod(n_ring % q, q), hm_invmod(P, q), q);
             dq[0] = (double)sc;
             dq[1] = (double)sc / (double)q;
             for (int k = 0; k < K; k++) {
                 const u64 h = hm_invmod(ctx->primes[L + k] % q, q);
                 const u64 h30 = hm_mulmod(h, ((u64)1 << 30) % q, q);
-                dq[2 + 4 * k] = (double)h;
-                dq[3 + 4 * k] = (double)h / (double)q;
-                dq[4 + 4 * k] = (double)h30;
-                dq[5 + 4 * k] = (double)h30 / (double)q;
+                down_h[((size_t)i * K + k) * 2] = hm_split((int64_t)h, 25);
+                down_h[((size_t)i * K + k) * 2 + 1] = hm_split((int64_t)h30, 25);
             }
         }
         for (int k = 0; k < K; k++) {
@@ -466,19 +486,20 @@ int get_ks16(ensi_ctx *ctx, int l1, const Ks16Const **out) {
             for (int b = 0; b < K; b++)
                 if (b != k) prod = hm_mulmod(prod, ctx->primes[L + b] % pk, pk);
             const u64 cs = hm_mulmod(hm_invmod(n_ring % pk, pk), hm_invmod(prod, pk), pk);
-            down_p[2 * k] = cs;
-            down_p[2 * k + 1] = hm_shoup(cs, pk);
-            if (is_fp(pk)) {
+            down_p[2 * k] = wide_special ? hm_wide_pack(cs, pk) : cs;
+            down_p[2 * k + 1] = wide_special ? hm_wide_pack(hm_mulmod(cs, (u64)1 << 32, pk), pk) : hm_shoup(cs, pk);
+            if (fp_special) {
                 down_p_fp[2 * k] = (double)cs;
                 down_p_fp[2 * k + 1] = (double)cs / (double)pk;
             }
         }
-        double *d_hat = nullptr, *d_pmod = nullptr, *d_dpf = nullptr, *d_dq = nullptr;
-        u64 *d_dp = nullptr;
-        if (upload(&d_hat, hat_fp) != hipSuccess || upload(&d_pmod, pmod) != hipSuccess || upload(&d_dp, down_p) != hipSuccess ||
+        double *d_pmod = nullptr, *d_dpf = nullptr, *d_dq = nullptr;
+        u64 *d_dp = nullptr, *d_hat = nullptr, *d_dh = nullptr;
+        if (upload(&d_hat, hat_sp) != hipSuccess || upload(&d_dh, down_h) != hipSuccess || upload(&d_pmod, pmod) != hipSuccess || upload(&d_dp, down_p) != hipSuccess ||
             upload(&d_dpf, down_p_fp) != hipSuccess || upload(&d_dq, down_q) != hipSuccess)
             ENSI_FAIL(ctx, ENSI_E_HIP, "uploading key-switch constants failed");
-        kc.hat_fp = d_hat;
+        kc.hat_sp = d_hat;
+        kc.down_h = d_dh;
         kc.pmod_fp = d_pmod;
         kc.down_p = d_dp;
         kc.down_p_fp = d_dpf;
@@ -742,15 +763,14 @@ size_t raised_words(const ensi_ctx *ctx, int l1) {
 // n_ct * raised_words).
 // ws: where the intermediates go; nullptr = the context's own workspaces (ws_digits sized by the caller, the rest
 // grown here).  With an explicit workspace nothing is allocated.
-int raise_cts(ensi_ctx *ctx, int l1, const u64 *ct_base, size_t ct_stride_words, int limb_stride, int n_ct, hipStream_t st,
+int raise_cts(ensi_ctx *ctx, int l1, const u64 *ct_base, size_t ct_stride_words, int limb_stride, int n_ct, RaiseUse use, hipStream_t st,
               const KsWorkspace *ws) {
     int rc;
     u64 *digits = ws ? ws->digits : ctx->ws_digits;
     if (ctx->ks16) {
         const Ks16Const *kc;
         if ((rc = get_ks16(ctx, l1, &kc))) return rc;
-        if (!ws && (rc = grow(ctx, &ctx->ws_y, &ctx->ws_y_words, (size_t)n_ct * l1 * ctx->N))) return rc;
-        launch_ks16_raise(ctx, *kc, ct_base, ct_stride_words, limb_stride, n_ct, ws ? ws->y : ctx->ws_y, digits, st);
+        launch_ks16_raise(ctx, *kc, ct_base, ct_stride_words, limb_stride, n_ct, digits, use == RAISE_SHARED, st);
         return ENSI_OK;
     }
     const ModUpConst *mu;
@@ -766,15 +786,14 @@ int raise_cts(ensi_ctx *ctx, int l1, const u64 *ct_base, size_t ct_stride_words,
 // destination); a group's inner products are added over the extended basis and brought back by one inverse
 // transform and one ModDown, and the destination receives sum_k phi_{g_k}(c0) with it.  h_desc: host copy of the
 // descriptors (needed by the unfused path of a grouped call only).
-int run_rotations(ensi_ctx *ctx, const RotDesc *d_desc, int n_rot, int l1, int limb_stride_in, int limb_stride_out, hipStream_t st,
+int run_rotations(ensi_ctx *ctx, const RotDesc *d_desc, int n_rot, int l1, int limb_stride_in, int limb_stride_out, RaiseUse use, hipStream_t st,
                   int members, const RotDesc *h_desc, const KsWorkspace *ws) {
     int rc;
     u64 *u = ws ? ws->u : ctx->ws_u;
     if (ctx->ks16) {
         const Ks16Const *kc;
         if ((rc = get_ks16(ctx, l1, &kc))) return rc;
-        if (!ws && (rc = grow(ctx, &ctx->ws_ysp, &ctx->ws_ysp_words, (size_t)(n_rot / members) * 2 * ctx->K * ctx->N))) return rc;
-        launch_ks16_switch(ctx, *kc, d_desc, n_rot, u, ws ? ws->ysp : ctx->ws_ysp, limb_stride_out, st, members);
+        launch_ks16_switch(ctx, *kc, d_desc, n_rot, u, limb_stride_out, use == RAISE_ONE, st, members);
         return ENSI_OK;
     }
     const ModDownConst *md;
@@ -807,10 +826,10 @@ int run_rotations(ensi_ctx *ctx, const RotDesc *d_desc, int n_rot, int l1, int l
 }
 
 // Ciphertexts per group of a batched rotation: bounds the workspace (about 31 MiB of raised digits per
-// ciphertext at 13 limbs).  Smaller groups were measured slower: the kernels are not limited by HBM alone,
+// ciphertext at N = 2^16 and 13 limbs; smaller rings take as many more).  Smaller groups were measured slower: the kernels are not limited by HBM alone,
 // so keeping the intermediates of a group inside the memory-side cache gains less than the shorter
 // launches lose.
-int rot_chunk() { return 64; }
+int rot_chunk(const ensi_ctx *ctx) { return ctx->log_n < 12 ? 1024 : 64 << (16 - ctx->log_n); }
 
 int ensure_desc(ensi_ctx *ctx, size_t n) {
     if (ctx->ws_desc_n >= n) return ENSI_OK;
@@ -832,7 +851,7 @@ extern "C" int ensi_rotate(ensi_ctx *ctx, const ensi_gk *gk, const ensi_ct *in, 
     const int N = ctx->N, l1 = in->limbs, ext = l1 + ctx->K, n = in->n;
     std::vector<RotDesc> desc(n);
     const size_t in_ct = (size_t)2 * in->limbs_alloc * N, out_ct = (size_t)2 * out->limbs_alloc * N;
-    const int chunk = std::min(n, ctx->ks16 ? rot_chunk() : n);
+    const int chunk = std::min(n, ctx->ks16 ? rot_chunk(ctx) : n);
     const size_t rw = raised_words(ctx, l1);
     int rc;
     if ((rc = grow(ctx, &ctx->ws_digits, &ctx->ws_digits_words, (size_t)chunk * rw))) return rc;
@@ -858,8 +877,8 @@ extern "C" int ensi_rotate(ensi_ctx *ctx, const ensi_gk *gk, const ensi_ct *in, 
     ENSI_HIP(ctx, host_to_device(ctx, ctx->ws_desc, desc.data(), n * sizeof(RotDesc), st));
     for (int c0 = 0; c0 < n; c0 += chunk) {
         const int cnt = std::min(chunk, n - c0);
-        if ((rc = raise_cts(ctx, l1, in->d + (size_t)c0 * in_ct, in_ct, in->limbs_alloc, cnt, st))) return rc;
-        if ((rc = run_rotations(ctx, ctx->ws_desc + c0, cnt, l1, in->limbs_alloc, out->limbs_alloc, st))) return rc;
+        if ((rc = raise_cts(ctx, l1, in->d + (size_t)c0 * in_ct, in_ct, in->limbs_alloc, cnt, RAISE_ONE, st))) return rc;
+        if ((rc = run_rotations(ctx, ctx->ws_desc + c0, cnt, l1, in->limbs_alloc, out->limbs_alloc, RAISE_ONE, st))) return rc;
     }
     out->scale = in->scale;
     ENSI_HIP(ctx, hipGetLastError());

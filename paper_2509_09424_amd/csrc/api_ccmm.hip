@@ -38,7 +38,7 @@ static int mult_core(ensi_ctx *ctx, const u64 *rkey, const std::vector<MmTerm> &
     // one that enters several products is gathered and transformed once), at most 65535 products, at least one output
     const size_t max_ops = std::max<size_t>(2, ((size_t)3 << 30) / ((size_t)2 * l1 * N));
     // (a grid of up to 256 outputs is kept in one group, so that the tiled multiply-add applies)
-    const int max_out = (grid_x > 0 && grid_x * grid_y == n_out && n_out <= 256) ? std::max(n_out, 64) : ctx->ks16 ? rot_chunk() : 64;
+    const int max_out = (grid_x > 0 && grid_x * grid_y == n_out && n_out <= 256) ? std::max(n_out, 64) : ctx->ks16 ? rot_chunk(ctx) : 64;
     if (a_pre && limb_stride_a != l1) ENSI_FAIL(ctx, ENSI_E_LEVEL, "prepared operands have %d limbs, the product runs at %d", limb_stride_a, l1);
     std::vector<int> cut(1, 0);
     std::vector<MmOperand> ops;
@@ -148,8 +148,8 @@ static int mult_core(ensi_ctx *ctx, const u64 *rkey, const std::vector<MmTerm> &
             desc[c].g_inv = 1;
         }
         ENSI_HIP(ctx, host_to_device(ctx, ctx->ws_desc, desc.data(), cnt * sizeof(RotDesc), st));
-        if ((rc = raise_cts(ctx, l1, ctx->ws_md, (size_t)3 * l1 * N, l1, cnt, st))) return rc;
-        if ((rc = run_rotations(ctx, ctx->ws_desc, cnt, l1, l1, l1, st))) return rc;
+        if ((rc = raise_cts(ctx, l1, ctx->ws_md, (size_t)3 * l1 * N, l1, cnt, RAISE_ONE, st))) return rc;
+        if ((rc = run_rotations(ctx, ctx->ws_desc, cnt, l1, l1, l1, RAISE_ONE, st))) return rc;
         launch_mm_add_d1(ctx, g, st);
         if (rescale) launch_rescale(ctx, ctx->ws_me, cnt, l1, l1, d_consts, fp ? d_fconsts : nullptr, st);
         launch_mm_scatter(ctx, g, st);
@@ -238,7 +238,7 @@ static int doubling_steps(ensi_ctx *ctx, const ensi_gk *gk, ensi_ct *t, int r_be
     if (groups.empty()) return ENSI_OK;
     int rc;
     const bool fused = ctx->ks16;
-    const int chunk = std::min(n, fused ? rot_chunk() : 16);
+    const int chunk = std::min(n, fused ? rot_chunk(ctx) : 16);
     const size_t rw = raised_words(ctx, l1), ct_words = (size_t)2 * t->limbs_alloc * N, tmp_words = (size_t)2 * l1 * N;
     if ((rc = grow(ctx, &ctx->ws_digits, &ctx->ws_digits_words, (size_t)chunk * rw))) return rc;
     if ((rc = grow(ctx, &ctx->ws_u, &ctx->ws_u_words, (size_t)chunk * 3 * 2 * ext * N))) return rc;
@@ -275,10 +275,11 @@ static int doubling_steps(ensi_ctx *ctx, const ensi_gk *gk, ensi_ct *t, int r_be
     size_t k = 0;
     for (const auto &grp : groups) {
         const int members = (int)grp.size();
+        const RaiseUse use = members == 1 ? RAISE_ONE : RAISE_SHARED;
         for (int c0 = 0; c0 < n; c0 += chunk, k++) {
             const int cnt = std::min(chunk, n - c0);
-            if ((rc = raise_cts(ctx, l1, t->d + (size_t)c0 * ct_words, ct_words, t->limbs_alloc, cnt, st))) return rc;
-            if ((rc = run_rotations(ctx, ctx->ws_desc + base[k], cnt * members, l1, t->limbs_alloc, fused ? t->limbs_alloc : l1, st, members,
+            if ((rc = raise_cts(ctx, l1, t->d + (size_t)c0 * ct_words, ct_words, t->limbs_alloc, cnt, use, st))) return rc;
+            if ((rc = run_rotations(ctx, ctx->ws_desc + base[k], cnt * members, l1, t->limbs_alloc, fused ? t->limbs_alloc : l1, use, st, members,
                                     desc.data() + base[k])))
                 return rc;
             if (!fused) launch_ct_add(ctx, t->d + (size_t)c0 * ct_words, t->limbs_alloc, ctx->ws_rtmp, l1, l1, cnt, st);
@@ -426,7 +427,7 @@ extern "C" int ensi_block_start_mask(ensi_ctx *ctx, int32_t s, int32_t limbs, en
 static int rotate_columns(ensi_ctx *ctx, const ensi_gk *gk, const ensi_ct *B, const int32_t *cols, int cnt, u64 *out, hipStream_t st) {
     const int N = ctx->N, d = B->n, l1 = B->limbs, ext = l1 + ctx->K;
     const size_t b_ct = (size_t)2 * B->limbs_alloc * N, o_ct = (size_t)2 * l1 * N, rw = raised_words(ctx, l1);
-    const int GS = std::min(d, 16), per = std::max(1, rot_chunk() * 2 / GS);  // rotation amounts per launch
+    const int GS = std::min(d, 16), per = std::max(1, rot_chunk(ctx) * 2 / GS);  // rotation amounts per launch
     int rc;
     if ((rc = grow(ctx, &ctx->ws_digits, &ctx->ws_digits_words, (size_t)GS * rw))) return rc;
     if ((rc = grow(ctx, &ctx->ws_u, &ctx->ws_u_words, (size_t)GS * per * 2 * ext * N))) return rc;
@@ -466,11 +467,11 @@ static int rotate_columns(ensi_ctx *ctx, const ensi_gk *gk, const ensi_ct *B, co
                 }
             if (desc.empty()) continue;
             if (!raised) {
-                if ((rc = raise_cts(ctx, l1, B->d + (size_t)j0 * b_ct, b_ct, B->limbs_alloc, gs, st))) return rc;
+                if ((rc = raise_cts(ctx, l1, B->d + (size_t)j0 * b_ct, b_ct, B->limbs_alloc, gs, RAISE_SHARED, st))) return rc;
                 raised = true;
             }
             ENSI_HIP(ctx, host_to_device(ctx, ctx->ws_desc, desc.data(), desc.size() * sizeof(RotDesc), st));
-            if ((rc = run_rotations(ctx, ctx->ws_desc, (int)desc.size(), l1, B->limbs_alloc, l1, st))) return rc;
+            if ((rc = run_rotations(ctx, ctx->ws_desc, (int)desc.size(), l1, B->limbs_alloc, l1, RAISE_SHARED, st))) return rc;
         }
     }
     return ENSI_OK;
@@ -560,7 +561,7 @@ static int rotate_jobs(ensi_ctx *ctx, const ensi_gk *gk, const u64 *src, size_t 
                        std::vector<RotJob> jobs, hipStream_t st) {
     const int N = ctx->N, ext = l1 + ctx->K;
     const size_t rw = raised_words(ctx, l1);
-    const int GS = 16, per = std::max(1, rot_chunk() * 2 / GS);
+    const int GS = 16, per = std::max(1, rot_chunk(ctx) * 2 / GS);
     int rc;
     if ((rc = grow(ctx, &ctx->ws_digits, &ctx->ws_digits_words, (size_t)GS * rw))) return rc;
     if ((rc = grow(ctx, &ctx->ws_u, &ctx->ws_u_words, (size_t)GS * per * 2 * ext * N))) return rc;
@@ -584,13 +585,13 @@ static int rotate_jobs(ensi_ctx *ctx, const ensi_gk *gk, const u64 *src, size_t 
             }
             k1++;
         }
-        if (any && (rc = raise_cts(ctx, l1, src + (size_t)lo * src_ct, src_ct, limb_stride_in, hi - lo + 1, st))) return rc;
+        if (any && (rc = raise_cts(ctx, l1, src + (size_t)lo * src_ct, src_ct, limb_stride_in, hi - lo + 1, RAISE_SHARED, st))) return rc;
         std::vector<RotDesc> desc;
         auto flush = [&]() -> int {
             if (desc.empty()) return ENSI_OK;
             if (host_to_device(ctx, ctx->ws_desc, desc.data(), desc.size() * sizeof(RotDesc), st) != hipSuccess)
                 ENSI_FAIL(ctx, ENSI_E_HIP, "descriptor copy failed");
-            const int r = run_rotations(ctx, ctx->ws_desc, (int)desc.size(), l1, limb_stride_in, l1, st);
+            const int r = run_rotations(ctx, ctx->ws_desc, (int)desc.size(), l1, limb_stride_in, l1, RAISE_SHARED, st);
             desc.clear();
             return r;
         };

@@ -331,7 +331,7 @@ extern "C" int ensi_pk_export(ensi_ctx *ctx, const ensi_pk *pk, uint64_t *words)
     if (d_t.alloc(bytes) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in pk_export");
     ENSI_HIP(ctx, hipDeviceSynchronize());
     ENSI_HIP(ctx, hipMemcpy(d_t.p, pk->d_pk, bytes, hipMemcpyDeviceToDevice));
-    launch_key_to_plain(ctx, d_t.as<u64>(), 2 * L, mq, false, nullptr);
+    launch_from_mont(ctx, d_t.as<u64>(), 2 * L, mq, nullptr);
     launch_ntt(ctx, d_t.as<u64>(), 2 * L, mq, true, nullptr);
     ENSI_HIP(ctx, hipMemcpy(words, d_t.p, bytes, hipMemcpyDeviceToHost));
     return ENSI_OK;
@@ -384,7 +384,8 @@ extern "C" int ensi_gk_export(ensi_ctx *ctx, const ensi_gk *gk, int32_t step, ui
     if (d_t.alloc(bytes) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in gk_export");
     ENSI_HIP(ctx, hipDeviceSynchronize());
     ENSI_HIP(ctx, hipMemcpy(d_t.p, it->second, bytes, hipMemcpyDeviceToDevice));
-    launch_key_to_plain(ctx, d_t.as<u64>(), beta * 2 * ext, mext, ctx->ks16, nullptr);
+    if (ctx->ks16) launch_ks16_key_plain(ctx, d_t.as<u64>(), beta * 2 * ext, nullptr);
+    else launch_from_mont(ctx, d_t.as<u64>(), beta * 2 * ext, mext, nullptr);
     launch_ntt(ctx, d_t.as<u64>(), beta * 2 * ext, mext, true, nullptr);
     ENSI_HIP(ctx, hipMemcpy(words, d_t.p, bytes, hipMemcpyDeviceToHost));
     return ENSI_OK;

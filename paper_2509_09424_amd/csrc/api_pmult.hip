@@ -238,7 +238,7 @@ extern "C" int ensi_rope(ensi_ctx *ctx, const ensi_gk *gk, const ensi_ct *in, co
         if (it == gk->keys.end()) ENSI_FAIL(ctx, ENSI_E_NOKEY, "rope: no Galois key for step %d", steps[e]);
         key[e] = it->second;
     }
-    const int chunk = std::min(n, rot_chunk() / 2);
+    const int chunk = std::min(n, rot_chunk(ctx) / 2);
     const size_t rw = raised_words(ctx, l1), ct_words = (size_t)2 * ls * N;
     int rc;
     if ((rc = grow(ctx, &ctx->ws_digits, &ctx->ws_digits_words, (size_t)chunk * rw))) return rc;
@@ -263,8 +263,8 @@ extern "C" int ensi_rope(ensi_ctx *ctx, const ensi_gk *gk, const ensi_ct *in, co
                 d.g_inv = inv_mod_2n(g[e], N);
             }
         ENSI_HIP(ctx, host_to_device(ctx, ctx->ws_desc, desc.data(), desc.size() * sizeof(RotDesc), st));
-        if ((rc = raise_cts(ctx, l1, in->d + (size_t)c0 * ct_words, ct_words, ls, cnt, st))) return rc;
-        if ((rc = run_rotations(ctx, ctx->ws_desc, 2 * cnt, l1, ls, ls, st))) return rc;
+        if ((rc = raise_cts(ctx, l1, in->d + (size_t)c0 * ct_words, ct_words, ls, cnt, RAISE_SHARED, st))) return rc;
+        if ((rc = run_rotations(ctx, ctx->ws_desc, 2 * cnt, l1, ls, ls, RAISE_SHARED, st))) return rc;
         // y = q (x) cos + Rot(q; 1) (x) (neg sin) + Rot(q; -1) (x) (pos sin), rescaled once
         std::vector<PmTerm> terms(3 * cnt);
         std::vector<int32_t> begin(cnt + 1);

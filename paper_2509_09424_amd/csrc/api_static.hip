@@ -49,8 +49,10 @@ extern "C" int ensi_rotate_static(ensi_ctx *ctx, const ensi_gk *gk, const ensi_c
     // workspace layout inside the static array: descriptors, then the four arrays of the key switch
     const size_t rw = raised_words(ctx, l1);
     const size_t desc_bytes = (((size_t)n * sizeof(RotDesc)) + 255) & ~(size_t)255;
-    const size_t w_digits = (size_t)n * rw, w_u = (size_t)n * 2 * ext * N, w_y = (size_t)n * l1 * N, w_ysp = (size_t)n * 2 * ctx->K * N;
-    const size_t need = desc_bytes + (w_digits + w_u + w_y + w_ysp) * sizeof(u64);
+    const size_t w_digits = (size_t)n * rw, w_u = (size_t)n * 2 * ext * N;
+    // (the documented limit also counts inner factors and special residues, which the kernels of every ring now keep in registers)
+    const size_t w_more = (size_t)n * (l1 + 2 * ctx->K) * N;
+    const size_t need = desc_bytes + (w_digits + w_u + w_more) * sizeof(u64);
     if (n > ENSI_STATIC_MAX_BATCH || need > ctx->static_scratch_bytes)
         ENSI_FAIL(ctx, ENSI_E_SHAPE, "rotate_static: %d ciphertexts at %d limbs need %zu bytes of workspace; the static workspace holds %zu (at most %d per call)",
                   n, l1, need, ctx->static_scratch_bytes, ENSI_STATIC_MAX_BATCH);
@@ -62,8 +64,6 @@ extern "C" int ensi_rotate_static(ensi_ctx *ctx, const ensi_gk *gk, const ensi_c
     KsWorkspace ws;
     ws.digits = (u64 *)(base + desc_bytes);
     ws.u = ws.digits + w_digits;
-    ws.y = ws.u + w_u;
-    ws.ysp = ws.y + w_y;
     RotDesc desc[ENSI_STATIC_MAX_BATCH];
     const size_t in_ct = (size_t)2 * in->limbs_alloc * N, out_ct = (size_t)2 * out->limbs_alloc * N;
     for (int c = 0; c < n; c++) {
@@ -82,10 +82,10 @@ extern "C" int ensi_rotate_static(ensi_ctx *ctx, const ensi_gk *gk, const ensi_c
     if ((size_t)n * sizeof(RotDesc) > ctx->stage[ctx->stage_next].cap) ENSI_FAIL(ctx, ENSI_E_SHAPE, "descriptor table larger than a staging slot");
     ENSI_HIP(ctx, host_to_device(ctx, d_desc, desc, (size_t)n * sizeof(RotDesc), st));
     int rc;
-    // every word of the workspace that a kernel reads is written earlier in this same call (digits and inner factors by the
-    // raise, accumulators by the inner product, special-limb residues by the first ModDown kernel): nothing has to start at zero
-    if ((rc = raise_cts(ctx, l1, in->d, in_ct, in->limbs_alloc, n, st, &ws))) return rc;
-    if ((rc = run_rotations(ctx, d_desc, n, l1, in->limbs_alloc, out->limbs_alloc, st, 1, nullptr, &ws))) return rc;
+    // every word of the workspace that a kernel reads is written earlier in this same call (digits by the raise, accumulators
+    // by the inner product): nothing has to start at zero
+    if ((rc = raise_cts(ctx, l1, in->d, in_ct, in->limbs_alloc, n, RAISE_ONE, st, &ws))) return rc;
+    if ((rc = run_rotations(ctx, d_desc, n, l1, in->limbs_alloc, out->limbs_alloc, RAISE_ONE, st, 1, nullptr, &ws))) return rc;
     out->scale = in->scale;
     ENSI_HIP(ctx, hipGetLastError());
     return ENSI_OK;

@@ -70,18 +70,20 @@ hipError_t host_to_device(ensi_ctx *ctx, void *dst, const void *src, size_t byte
 
 // ---- key switching, shared by the entry points (api.hip) -------------------------------------------------
 // Intermediates of a batch of key switches: raised digits (raised_words per ciphertext), accumulators
-// (2 (l1+K) N words per rotation), inner factors of the basis conversion (l1 N per ciphertext, fused path),
-// centred special-limb residues (2 K N per rotation, fused path).
+// (2 (l1+K) N words per rotation).
 struct KsWorkspace {
-    u64 *digits, *u, *y, *ysp;
+    u64 *digits, *u;
 };
+// Whether each raised ciphertext serves one rotation (the fused path then leaves its digits after their column pass, and the
+// inner product runs their row passes) or several.
+enum RaiseUse { RAISE_ONE, RAISE_SHARED };
 size_t raised_words(const ensi_ctx *ctx, int l1);
 int get_modup(ensi_ctx *ctx, int l1, const ModUpConst **out);
 int get_moddown(ensi_ctx *ctx, int l1, const ModDownConst **out);
 int get_ks16(ensi_ctx *ctx, int l1, const Ks16Const **out);
-int raise_cts(ensi_ctx *ctx, int l1, const u64 *ct_base, size_t ct_stride_words, int limb_stride, int n_ct, hipStream_t st,
+int raise_cts(ensi_ctx *ctx, int l1, const u64 *ct_base, size_t ct_stride_words, int limb_stride, int n_ct, RaiseUse use, hipStream_t st,
               const KsWorkspace *ws = nullptr);
-int run_rotations(ensi_ctx *ctx, const RotDesc *d_desc, int n_rot, int l1, int limb_stride_in, int limb_stride_out, hipStream_t st,
+int run_rotations(ensi_ctx *ctx, const RotDesc *d_desc, int n_rot, int l1, int limb_stride_in, int limb_stride_out, RaiseUse use, hipStream_t st,
                   int members = 1, const RotDesc *h_desc = nullptr, const KsWorkspace *ws = nullptr);
 
 // Resolves the device address of the statically linked workspace for the context's device (api_static.hip).
@@ -93,7 +95,7 @@ int stage_prealloc(ensi_ctx *ctx);
 // api.hip
 int encode_window(ensi_ctx *ctx, const double *slots, int n_pt, int n_slots, int slot0, int slot_step, int limbs, double scale,
                   ensi_pt **out);
-int rot_chunk();                           // ciphertexts per group of a batched rotation
+int rot_chunk(const ensi_ctx *ctx);        // ciphertexts per group of a batched rotation
 int ensure_desc(ensi_ctx *ctx, size_t n);  // grows the context's descriptor table to n entries
 // api_matmul.hip
 void free_plan(MatmulPlan *p);

@@ -167,7 +167,7 @@ void launch_mm_tensor(ensi_ctx *ctx, const MmGroup &g, hipStream_t st) {
     const int N = ctx->N, nb = (N + MM_THREADS - 1) / MM_THREADS;
     const LimbMap map = mm_map(g.l1);
     if (g.n_ops > 0) {
-        if (ctx->log_n == 16) {
+        if (ctx->log_n >= 12) {
             // the forward column pass reads the operands where they lie
             launch_ntt16_gather(ctx, g.ws_a, g.ops, g.n_ops, g.l1, st);
         } else {

@@ -21,9 +21,16 @@ struct PrimeConst {
     u64 q;
     u64 qneg_inv;   // -q^{-1} mod 2^64
     u64 r2;         // 2^128 mod q   (to Montgomery form: mont_mul(x, r2))
-    u64 n_inv;      // N^{-1} mod q
-    u64 n_inv_s;    // its Shoup companion
-    u64 pad[3];     // [0] 1 if this prime's transform tables hold doubles (fp64 path), [1] bits of 1/q, [2] bits of n_inv/q
+    u64 n_inv;      // N^{-1} mod q          (PRIME_WIDE: packed as a multiplier, see wide_pack)
+    u64 n_inv_s;    // its Shoup companion   (PRIME_WIDE: N^{-1} 2^32 mod q, packed)
+    u64 kind;       // PRIME_*: the arithmetic of the register transform (N >= 2^12), and with it the format of the prime's transform tables
+    u64 aux0;       // PRIME_FP: bits of 1/q      PRIME_WIDE: 2^60 - q
+    u64 aux1;       // PRIME_FP: bits of n_inv/q
+};
+enum {
+    PRIME_INT = 0,   // any prime: 64-bit Shoup / Montgomery integers
+    PRIME_FP = 1,    // q < 2^50: exact integers in doubles
+    PRIME_WIDE = 2,  // 2^60 - 2^26 < q < 2^60: signed 64-bit integers, products reduced by 2^60 = 2^60 - q
 };
 
 // Which prime each limb row of a kernel's operand uses.
@@ -51,17 +58,19 @@ struct ModDownConst {
     u64 *negtab;   // [l1][K+1]  j * (P mod q_i) mod q_i: what j negative centred residues add to the conversion
 };
 
-// Constants of the fused N = 2^16 key switch at one level (limbs = l1); all pointers device memory.
+// Constants of the fused key switch at one level (limbs = l1); all pointers device memory.
 struct Ks16Const {
     int32_t l1, K, L, alpha, beta;
     int32_t n_src[8];          // limbs in digit j
     const u64 *inv, *inv_s;    // [l1]               (Q_j/q_a)^{-1} mod q_a of the digit that holds limb a, and its Shoup companion
     const u64 *hat_mont;       // [beta][ext][alpha] (Q_j/q_a) mod t, Montgomery form
-    const double *hat_fp;      // [beta][ext][alpha][2]  the same value and value/t as doubles (targets below 2^50 only)
+    const u64 *hat_sp;         // [beta][ext][alpha][2]  h = (Q_j/q_a) mod t and h 2^25 mod t, each split into two halves:
+                               //   t < 2^50: high * 2^25 + low; PRIME_WIDE: high * 2^30 + low (halves are int32, low centred)
     const double *pmod_fp;     // [l1][2]            P mod q_i and (P mod q_i)/q_i
-    const u64 *down_p;         // [K][2]             N^{-1} (P/p_k)^{-1} mod p_k and its Shoup companion
+    const u64 *down_p;         // [K][2]             N^{-1} (P/p_k)^{-1} mod p_k and its Shoup companion (PRIME_WIDE: packed multiplier)
     const double *down_p_fp;   // [K][2]             the same value and value/p_k (special primes below 2^50 only)
-    const double *down_q;      // [l1][2 + 4K]       N^{-1} P^{-1} mod q_i, /q_i; per k: p_k^{-1}, /q_i, 2^30 p_k^{-1}, /q_i
+    const double *down_q;      // [l1][2]            N^{-1} P^{-1} mod q_i, /q_i
+    const u64 *down_h;         // [l1][K][2]         p_k^{-1} mod q_i and 2^30 p_k^{-1} mod q_i, each split as high * 2^25 + low
 };
 
 // One product of a plaintext multiplication: source ciphertext ([2][limb_stride][N] words) and plaintext index.
@@ -135,7 +144,7 @@ struct RotDesc {
     u64 *out;           // destination ciphertext: [2][limb_stride_out][N]
     u32 g;              // Galois element
     u32 g_inv;          // its inverse mod 2N
-    u32 accumulate;     // fused N = 2^16 kernels only: add the result to what `out` holds instead of overwriting it
+    u32 accumulate;     // fused kernels only: add the result to what `out` holds instead of overwriting it
     u32 pad;
 };
 
@@ -174,6 +183,8 @@ struct ensi_ctx {
     int log_n, N, L, K, alpha;
     double scale;
     int device;
+    std::vector<u64> kind;          // PRIME_* by prime
+    u64 special_kind = PRIME_INT;   // the kind of all special primes (one kind for all of them)
     std::vector<u64> primes;        // L + K
     std::vector<u64> psi;           // chosen 2N-th roots
     PrimeConst *d_pc = nullptr;     // [L+K]
@@ -183,10 +194,9 @@ struct ensi_ctx {
     std::vector<u32> rot_exp;
     std::map<int, ModUpConst> modup;      // by l1
     std::map<int, ModDownConst> moddown;  // by l1
-    bool ks16 = false;                    // N = 2^16 and every ciphertext prime below 2^50: fused key-switching kernels
+    bool ks16 = false;                    // N = 2^12 .. 2^16 and every ciphertext prime below 2^50: fused key-switching kernels
     std::map<int, Ks16Const> ks16c;       // by l1
-    u64 *ws_y = nullptr; size_t ws_y_words = 0;   // inner factors of the basis conversion (ModUp)
-    u64 *ws_ysp = nullptr; size_t ws_ysp_words = 0;  // centred special-limb residues (ModDown)
+    u64 *ws_y = nullptr; size_t ws_y_words = 0;   // automorphism of one polynomial (grouped rotations of the unfused path)
     // scratch for key switching, grown on demand
     u64 *ws_digits = nullptr; size_t ws_digits_words = 0;
     u64 *ws_u = nullptr; size_t ws_u_words = 0;
@@ -249,7 +259,7 @@ struct ensi_pt {
     u64 *d;  // [n][limbs][N] coefficient form
     // multiplier forms, built on first use by a plaintext multiplication
     mutable u64 *d_mont = nullptr;  // transform domain, Montgomery form
-    mutable u64 *d_fp = nullptr;    // transform domain, doubles in [0,q), register order of the row pass (N = 2^16)
+    mutable u64 *d_fp = nullptr;    // transform domain, doubles in [0,q), register order of the row pass (N >= 2^12)
 };
 struct ensi_ct {
     ensi_ctx *ctx;
@@ -294,18 +304,21 @@ struct ScopedTimer {
 // ---- launchers (defined in the .hip files) ---------------------------------
 // Transform n_inst limb rows in place; row r uses prime map.prime[r % map.n].
 void launch_ntt(ensi_ctx *ctx, u64 *data, int n_inst, const LimbMap &map, bool inverse, hipStream_t st);
-void launch_ntt16(ensi_ctx *ctx, u64 *data, int n_inst, const LimbMap &map, bool inverse, hipStream_t st);  // N = 2^16 only
-void launch_ntt16_gather(ensi_ctx *ctx, u64 *data, const MmOperand *ops, int n_ops, int l1, hipStream_t st);  // N = 2^16 only
+void launch_ntt16(ensi_ctx *ctx, u64 *data, int n_inst, const LimbMap &map, bool inverse, hipStream_t st);  // N >= 2^12
+void launch_ntt16_gather(ensi_ctx *ctx, u64 *data, const MmOperand *ops, int n_ops, int l1, hipStream_t st);  // N >= 2^12
 
-// fused key switch for N = 2^16 (keyswitch16.hip)
+// fused key switch (keyswitch16.hip)
 void launch_ks16_key_format(ensi_ctx *ctx, u64 *key, int beta_full, hipStream_t st);
-// raises n_ct ciphertexts: dig [n_ct][beta*ext + l1][N] receives the transformed digits of c1 and P*c0
+void launch_ks16_key_plain(ensi_ctx *ctx, u64 *key, int n_rows, hipStream_t st);  // rows of L + K limbs, in place: the stored format -> residues
+// raises n_ct ciphertexts: dig [n_ct][beta*ext + l1][N] receives the digits of c1 and P*c0, transformed (rows) or after their
+// column pass only
 void launch_ks16_raise(ensi_ctx *ctx, const Ks16Const &kc, const u64 *ct_base, size_t ct_stride_words, int limb_stride, int n_ct,
-                       u64 *ybuf, u64 *dig, hipStream_t st);
+                       u64 *dig, bool rows, hipStream_t st);
 // inner product + inverse transform + ModDown for n_rot descriptors (desc.digits = the ciphertext's block of dig)
 // members > 1: the descriptors come in groups of `members` rotations of one ciphertext (same digits and destination);
 // a group's inner products are added before one inverse transform and one ModDown
-void launch_ks16_switch(ensi_ctx *ctx, const Ks16Const &kc, const RotDesc *d_desc, int n_rot, u64 *u, u64 *ysp, int limb_stride_out,
+// raw: the digits have been through their column pass only
+void launch_ks16_switch(ensi_ctx *ctx, const Ks16Const &kc, const RotDesc *d_desc, int n_rot, u64 *u, int limb_stride_out, bool raw,
                         hipStream_t st, int members = 1);
 
 void launch_modup(ensi_ctx *ctx, const ModUpConst &mc, const u64 *ct_base, size_t ct_stride_words, int limb_stride,
@@ -330,7 +343,7 @@ int launch_accumulate_mfma(ensi_ctx *ctx, const u64 *xbase, size_t xstride, int 
 int launch_matrix_rate(ensi_ctx *ctx, double seconds, double *ops_per_second, hipStream_t st);
 
 // plaintext multiplication (pmult.hip).  The generic pair works for every ring size and prime; the fused one needs
-// N = 2^16 and ciphertext primes below 2^50.
+// N >= 2^12 and ciphertext primes below 2^50.
 void launch_pm_generic(ensi_ctx *ctx, const PmGroup &g, const u64 *d_consts, const double *d_fconsts, hipStream_t st);
 void launch_pm16(ensi_ctx *ctx, const PmGroup &g, const PmRescale &rs, hipStream_t st);
 void launch_pm16_pt_format(ensi_ctx *ctx, const u64 *ntt_form, int n_rows, u64 *out, hipStream_t st);
@@ -350,8 +363,7 @@ void launch_mul_mont(ensi_ctx *ctx, u64 *out, const u64 *a, const u64 *b_mont, i
                      hipStream_t st);
 void launch_add(ensi_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int n_rows, const LimbMap &map, hipStream_t st);
 void launch_to_mont(ensi_ctx *ctx, u64 *data, int n_rows, const LimbMap &map, hipStream_t st);
-// stored key words (Montgomery form, or doubles on the limbs the fused N = 2^16 kernels read as such) -> ordinary residues
-void launch_key_to_plain(ensi_ctx *ctx, u64 *data, int n_rows, const LimbMap &map, bool fp_format, hipStream_t st);
+void launch_from_mont(ensi_ctx *ctx, u64 *data, int n_rows, const LimbMap &map, hipStream_t st);
 // *d_bad += number of words >= their prime
 void launch_count_noncanonical(ensi_ctx *ctx, const u64 *data, int n_rows, const LimbMap &map, unsigned int *d_bad, hipStream_t st);
 // d_sums[c] += wrap-around sum of the active limb words of ciphertext c

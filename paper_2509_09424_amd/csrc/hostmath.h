@@ -27,6 +27,17 @@ static inline u64 hm_neg_inv64(u64 q) {
     for (int i = 0; i < 6; i++) x *= 2 - q * x;
     return (u64)0 - x;
 }
+// Two int32 halves of v packed into one word, v = high * 2^bits + low with low in [-2^(bits-1), 2^(bits-1)] (slightly
+// beyond where the high half would leave 31 bits).
+static inline u64 hm_split(int64_t v, int bits) {
+    int64_t hi = (v + ((int64_t)1 << (bits - 1))) >> bits;
+    if (hi > 0x7fffffff) hi = 0x7fffffff;
+    const int64_t lo = v - hi * ((int64_t)1 << bits);
+    return ((u64)(u32)(int32_t)hi << 32) | (u32)(int32_t)lo;
+}
+static inline int64_t hm_centred(u64 w, u64 q) { return w > q / 2 ? (int64_t)w - (int64_t)q : (int64_t)w; }
+// multiplier of the PRIME_WIDE arithmetic: the centred residue, split at 28 bits
+static inline u64 hm_wide_pack(u64 w, u64 q) { return hm_split(hm_centred(w, q), 28); }
 static inline bool hm_is_prime(u64 n) {
     if (n < 2) return false;
     static const u64 bases[] = {2, 3, 5, 7, 11, 13, 17, 19, 23, 29, 31, 37};

@@ -415,24 +415,19 @@ void launch_to_mont(ensi_ctx *ctx, u64 *data, int n_rows, const LimbMap &map, hi
     hipLaunchKernelGGL(k_to_mont, grid, dim3(EW_THREADS), 0, st, data, map, ctx->d_pc, ctx->N);
 }
 
-// Stored key words back to ordinary residues, in place: limbs that the fused N = 2^16 kernels keep as doubles in
-// [0,p) (fp_format, primes below 2^50) are converted, every other word leaves Montgomery form.
-__global__ __launch_bounds__(EW_THREADS) void k_key_to_plain(u64 *data, LimbMap map, const PrimeConst *pc, int N, int fp_format) {
+// Words out of Montgomery form, in place.
+__global__ __launch_bounds__(EW_THREADS) void k_from_mont(u64 *data, LimbMap map, const PrimeConst *pc, int N) {
     const int idx = blockIdx.x * EW_THREADS + threadIdx.x;
     if (idx >= N) return;
     const int row = blockIdx.y;
     const PrimeConst p = pc[map.prime[row % map.n]];
     const size_t o = (size_t)row * N + idx;
-    if (fp_format && p.pad[0]) {
-        data[o] = (u64)__longlong_as_double((long long)data[o]);
-    } else {
-        acc128 t = {data[o], 0};
-        data[o] = mont_reduce(t, p.q, p.qneg_inv);
-    }
+    acc128 t = {data[o], 0};
+    data[o] = mont_reduce(t, p.q, p.qneg_inv);
 }
-void launch_key_to_plain(ensi_ctx *ctx, u64 *data, int n_rows, const LimbMap &map, bool fp_format, hipStream_t st) {
+void launch_from_mont(ensi_ctx *ctx, u64 *data, int n_rows, const LimbMap &map, hipStream_t st) {
     dim3 grid((ctx->N + EW_THREADS - 1) / EW_THREADS, n_rows);
-    hipLaunchKernelGGL(k_key_to_plain, grid, dim3(EW_THREADS), 0, st, data, map, ctx->d_pc, ctx->N, fp_format ? 1 : 0);
+    hipLaunchKernelGGL(k_from_mont, grid, dim3(EW_THREADS), 0, st, data, map, ctx->d_pc, ctx->N);
 }
 
 // Number of words of a batch of limb rows that are not canonical residues (>= their prime), added to *bad.

@@ -1,0 +1,662 @@
+// Rotation (paper, Preliminaries: Rot) for the rings N = 2^12 .. 2^16 with ciphertext primes below 2^50:
+// automorphism plus hybrid key switching in three kernels (four where several rotations share one raised
+// ciphertext) that keep every intermediate in the layout and number format of the transform passes around it.
+//
+//   k_ks16_fcols   ModUp fused into the forward column pass.  A block holds the inner factors
+//                  y_a = c1_a (Q_j/q_a)^-1 mod q_a of one digit on one column tile in registers and walks the
+//                  limbs of the extended basis: it forms  sum_a y_a (Q_j/q_a) mod t  (or takes the limb inside its
+//                  own digit), runs the column pass on it and writes it.  Further blocks do the same for P * c0, so
+//                  that phi_g(c0) can be added in the transform domain (ModDown divides it by P again, exactly)
+//   k_ks16_frows   forward row pass of the raised digits and of P * c0, where several rotations read them
+//   k_ks16_inner   automorphism (a permutation of transform-domain positions that maps rows onto rows, applied
+//                  between two registers-to-LDS exchanges) + inner product with the key + P * phi_g(c0) + inverse
+//                  row pass.  A raised ciphertext that only one rotation reads is taken after its column
+//                  pass and the row passes of its digits are run here: the transformed digits never reach memory
+//   k_ks16_icols   inverse column pass fused with ModDown.  A block brings the K special limbs of one column tile
+//                  to centred residues y_k = [u (P/p_k)^-1]_{p_k}, held in registers, and then walks the
+//                  ciphertext limbs:  u P^-1 - sum_k y_k p_k^-1  mod q_i
+//
+// What bounds them: a row or column pass costs 40 to 60 instructions per word, the memory system about as much, so
+// neither can be wasted.  Holding y (fcols) and y_k (icols) in registers while the block walks the limbs is what
+// removed the re-reads: with a block per limb each word of y was fetched through L2 once per target limb and the
+// kernels waited on those loads, whatever their arithmetic cost.
+//
+// Number formats between the kernels (workspaces only, never visible outside the library), by
+// the prime's kind:
+//   PRIME_FP    doubles (exact integers, |x| <= p/2); key: doubles in [0,p)
+//   PRIME_WIDE  signed 64-bit integers, |x| <= q/2 + 8 (2^60 - q); transformed digits and the key as two
+//               int32 halves high * 2^30 + low, so that the inner product is multiply-adds of 32-bit words
+//   PRIME_INT   canonical 64-bit residues; key: Montgomery residues
+// Transformed digits and the key are stored in the order a wave holds them in the row pass ("register order"): within
+// the four rows of a wave, value i of lane (rho, j) -- position 16 j + i of row rho -- at i * 64 + lane, so that reading
+// them needs no exchange and is contiguous.
+// All results that leave the last kernel are canonical residues and equal, word for word, what the unfused sequence
+// (ModUp, transform, inner product, inverse transform, ModDown, + phi_g(c0)) gives.
+#pragma once
+#include "common.h"
+#include "ntt16_core.h"
+
+#define KS_THREADS 256
+
+__device__ __forceinline__ int ks_ext_prime(int e, int l1, int L) { return e < l1 ? e : L + (e - l1); }
+__device__ __forceinline__ double as_f64(u64 x) { return __longlong_as_double((long long)x); }
+__device__ __forceinline__ u64 as_u64(double x) { return (u64)__double_as_longlong(x); }
+
+__device__ __forceinline__ RotDesc load_desc(const RotDesc *desc, int i) {
+    static_assert(sizeof(RotDesc) == 6 * sizeof(u64), "six words");
+    auto w = as_const((const u64 *)(desc + i));
+    RotDesc d;
+    d.c0 = (const u64 *)w[0];
+    d.digits = (const u64 *)w[1];
+    d.key = (const u64 *)w[2];
+    d.out = (u64 *)w[3];
+    d.g = (u32)w[4];
+    d.g_inv = (u32)(w[4] >> 32);
+    d.accumulate = (u32)w[5];
+    return d;
+}
+
+// ------------------------------------------------------------------ ModUp + forward column pass
+// Basis conversion of values h .. h+7 of a column: sum_a y_a h_a over the 25-bit halves of y against split h and
+// h 2^25 is a1 2^b + a0 (b = 25 or 30: where the halves of h meet); four multiply-adds per source, one reduction
+// per word afterwards (a modular product per source in fp64 took twice the instructions).
+__device__ __forceinline__ void modup_sums(int64_t *a0, int64_t *a1, const u64 *hat, u64 (*y)[16], int ns, int h) {
+#pragma unroll
+    for (int a = 0; a < ENSI_MAX_ALPHA; a++) {
+        if (a == 0 || a < ns) {  // (ns >= 1)
+            const u64 w = as_const(hat)[2 * a], w25 = as_const(hat)[2 * a + 1];
+#pragma unroll
+            for (int i = 0; i < 8; i++) {
+                const int yl = (int)(u32)y[a][h + i], yh = (int)(y[a][h + i] >> 32);
+                a0[i] = mad_i(yh, (int)(u32)w25, a ? mad_i(yl, (int)(u32)w, a0[i]) : mul_i(yl, (int)(u32)w));
+                a1[i] = mad_i(yh, (int)(w25 >> 32), a ? mad_i(yl, (int)(w >> 32), a1[i]) : mul_i(yl, (int)(w >> 32)));
+            }
+        }
+    }
+}
+
+__device__ __forceinline__ void modup_to(const ArithFp &ar, double *v, const u64 *hat, const u64 *, u64 (*y)[16], int ns, const PrimeConst &) {
+#pragma unroll
+    for (int h = 0; h < 16; h += 8) {
+        int64_t a0[8], a1[8];
+        modup_sums(a0, a1, hat, y, ns, h);
+#pragma unroll
+        for (int i = 0; i < 8; i++) v[h + i] = ar.reduce25(a1[i], a0[i]);
+    }
+}
+// |a0|, |a1| <= 2^57 leave the value within 1.14 q, as a forward step may start
+__device__ __forceinline__ void modup_to(const ArithWide &ar, int64_t *v, const u64 *hat, const u64 *, u64 (*y)[16], int ns, const PrimeConst &) {
+#pragma unroll
+    for (int h = 0; h < 16; h += 8) {
+        int64_t a0[8], a1[8];
+        modup_sums(a0, a1, hat, y, ns, h);
+#pragma unroll
+        for (int i = 0; i < 8; i++)
+            v[h + i] = mad_pow2<30>((u32)a1[i] & 0x3fffffffu, mad_i((int)(a1[i] >> 30), ar.d, a0[i]));
+    }
+}
+__device__ __forceinline__ void modup_to(const ArithInt &, u64 *v, const u64 *, const u64 *hat_mont, u64 (*y)[16], int ns, const PrimeConst &pc) {
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        acc128 acc = {0, 0};
+#pragma unroll
+        for (int a = 0; a < ENSI_MAX_ALPHA; a++)
+            if (a < ns) mac128(acc, (y[a][i] >> 32 << 25) | (u32)y[a][i], as_const(hat_mont)[a]);
+        v[i] = mont_reduce(acc, pc.q, pc.qneg_inv);
+    }
+}
+
+// LDS of a block that walks limbs, one barrier per pass.  A thread past the barrier of pass t may write the tile of pass
+// t + 1 while another still reads the tile of pass t: two tiles in turn.  The table of pass t + 1 is written before the
+// barrier of pass t, when another thread may still be reading the table of pass t - 1: three tables in turn.
+struct ColLds {
+    ulonglong2 tab[3][COL_TAB];
+    u64 tile[2][4096];
+};
+
+// grid (TILES, beta * ceil(ext / per) + ceil(l1 / per), n_ct): a block takes `per` targets of one digit, or `per` limbs of
+// P * c0.  dig: [n_ct][beta*ext + l1][N], row R < beta*ext is limb R % ext of raised digit R / ext.
+// W: the arithmetic of the special primes (one kind for all of them).
+template <int S, class W>
+__global__ __launch_bounds__(KS_THREADS, 2) void k_ks16_fcols(Ks16Const kc, const PrimeConst *pcs, const u64 *tw_all, const u64 *ct_base,
+                                                              size_t ct_stride, int limb_stride, u64 *dig, int per) {
+    typedef Ring<S> R;
+    constexpr size_t N = R::N;
+    __shared__ ColLds sh;
+    const int tid = threadIdx.x, c = R::col(tid), jj = R::grp(tid);
+    const int l1 = kc.l1, ext = l1 + kc.K, chunks = (ext + per - 1) / per;
+    const u64 *c0 = ct_base + (size_t)blockIdx.z * ct_stride + (size_t)blockIdx.x * R::COLS;
+    u64 *out_ct = dig + (size_t)blockIdx.z * (kc.beta * ext + l1) * N + (size_t)blockIdx.x * R::COLS;
+    const u32 off_in = (R::row(jj, 0) * 256 + c) * 8, off_out = (16 * jj * 256 + c) * 8;  // of value 0; value i adds the same for all threads
+    u32 tidx = 0;
+    const int tplace = col_tab_index<S>(tid, &tidx);
+    ulonglong2 tnext;
+    auto fetch_tab = [&](int prime) {
+        const u64 *tw = tw_all + (size_t)prime * 4 * N;
+        tnext = make_ulonglong2(tw[tidx], tw[N + tidx]);
+    };
+    auto put_tab = [&](int buf) {
+        if (tplace >= 0) sh.tab[buf][tplace] = tnext;
+    };
+    if ((int)blockIdx.y < kc.beta * chunks) {
+        const u64 *c1 = c0 + (size_t)limb_stride * N;
+        const int j = blockIdx.y / chunks, e0 = (blockIdx.y - j * chunks) * per, e1 = min(ext, e0 + per);
+        const int first = j * kc.alpha, ns = kc.n_src[j];
+        fetch_tab(ks_ext_prime(e0, l1, kc.L));
+        u64 y[ENSI_MAX_ALPHA][16] = {};
+#pragma unroll
+        for (int a = 0; a < ENSI_MAX_ALPHA; a++) {
+            if (a < ns) {
+                const u64 q = load_prime(pcs, first + a).q, inv = as_const(kc.inv)[first + a], inv_s = as_const(kc.inv_s)[first + a];
+                const u64 *src = c1 + (size_t)(first + a) * N;
+#pragma unroll
+                for (int i = 0; i < 16; i++) y[a][i] = ld_off(src + R::row(0, i) * 256, off_in);
+#pragma unroll
+                for (int i = 0; i < 16; i++) {
+                    const u64 t = mul_shoup(y[a][i], inv, inv_s, q);
+                    y[a][i] = (t >> 25) << 32 | (t & 0x1ffffffu);
+                }
+            }
+        }
+        put_tab(0);
+        __syncthreads();
+        int tcur = 0;
+#pragma unroll 1
+        for (int e = e0; e < e1; e++) {
+#pragma unroll
+            for (int a = 0; a < ENSI_MAX_ALPHA; a++)
+#pragma unroll
+                for (int i = 0; i < 16; i++) keep_narrow(y[a][i]);
+            const int prime = ks_ext_prime(e, l1, kc.L);
+            const PrimeConst pc = load_prime(pcs, prime);
+            const u64 *hat = kc.hat_sp + ((size_t)j * ext + e) * kc.alpha * 2;
+            u64 *out = out_ct + ((size_t)j * ext + e) * N, *l = sh.tile[e & 1];
+            const int tnxt = tcur == 2 ? 0 : tcur + 1;
+            const ulonglong2 *tb = sh.tab[tcur];
+            tcur = tnxt;
+            if (e + 1 < e1) fetch_tab(ks_ext_prime(e + 1, l1, kc.L));
+            if (e < l1) {
+                ArithFp ar;
+                ar.init(pc);
+                double v[16];
+                if (e >= first && e < first + ns) {
+#pragma unroll
+                    for (int i = 0; i < 16; i++) v[i] = (double)ld_off(c1 + (size_t)e * N + R::row(0, i) * 256, off_in);
+                } else {
+                    modup_to(ar, v, hat, nullptr, y, ns, pc);
+                }
+                put_tab(tnxt);
+                cols_fwd_tab<S>(ar, v, tb, l, c, jj);
+#pragma unroll
+                for (int i = 0; i < 16; i++) st_off(out + i * 256, off_out, ar.store_ws_cols(v[i]));
+            } else {
+                W ar;
+                ar.init(pc);
+                typename W::T v[16];
+                modup_to(ar, v, hat, kc.hat_mont + ((size_t)j * ext + e) * kc.alpha, y, ns, pc);
+                put_tab(tnxt);
+                cols_fwd_tab<S>(ar, v, tb, l, c, jj);
+#pragma unroll
+                for (int i = 0; i < 16; i++) st_off(out + i * 256, off_out, ar.store_ws_cols(v[i]));
+            }
+        }
+    } else {
+        const int i0 = (blockIdx.y - kc.beta * chunks) * per, i1 = min(l1, i0 + per);
+        fetch_tab(i0);
+        u64 nv[16];
+#pragma unroll
+        for (int i = 0; i < 16; i++) nv[i] = ld_off(c0 + (size_t)i0 * N + R::row(0, i) * 256, off_in);
+        put_tab(0);
+        __syncthreads();
+        int tcur = 0;
+#pragma unroll 1
+        for (int limb = i0; limb < i1; limb++) {
+            ArithFp ar;
+            ar.init(load_prime(pcs, limb));
+            const double pm = as_const(kc.pmod_fp)[2 * limb], pm_p = as_const(kc.pmod_fp)[2 * limb + 1];
+            double v[16];
+#pragma unroll
+            for (int i = 0; i < 16; i++) v[i] = ar.mid(ar.mulmod((double)nv[i], pm, pm_p));
+            if (limb + 1 < i1) {
+                fetch_tab(limb + 1);
+#pragma unroll
+                for (int i = 0; i < 16; i++) nv[i] = ld_off(c0 + (size_t)(limb + 1) * N + R::row(0, i) * 256, off_in);
+            }
+            const int tnxt = tcur == 2 ? 0 : tcur + 1;
+            put_tab(tnxt);
+            cols_fwd_tab<S>(ar, v, sh.tab[tcur], sh.tile[limb & 1], c, jj);
+            tcur = tnxt;
+            u64 *out = out_ct + (size_t)(kc.beta * ext + limb) * N;
+#pragma unroll
+            for (int i = 0; i < 16; i++) st_off(out + i * 256, off_out, ar.store_ws_cols(v[i]));
+        }
+    }
+}
+
+// ------------------------------------------------------------------ forward row pass (in place)
+// A wave runs its four rows of one limb for up to KS_FROWS_GROUP ciphertexts: the twiddles of the rows -- more bytes than
+// the rows themselves -- are fetched once (first step: LDS, second step: registers), and the next ciphertext's rows are
+// requested before the current ones are transformed.  grid (4 TILES * (beta*ext + l1) * ceil(n_ct / KS_FROWS_GROUP)).
+#define KS_FROWS_GROUP 8
+template <int S, class A>
+__device__ __forceinline__ void frows_body(u64 *g, size_t ct_stride, int n_here, const u64 *tw, const PrimeConst &pc, u64 *lds, ulonglong2 *tw1,
+                                           int r0) {
+    A ar;
+    ar.init(pc);
+    const int lane = threadIdx.x, rho = lane >> 4, j = lane & 15;
+    const u32 base = Ring<S>::ROWS + r0 + rho;
+    const u64 *tws = tw + Ring<S>::N;
+    row_table_to_lds(tw1, tw, tws, base, rho, j);
+    TwRegs tw2;
+    tw2.load(tw, tws, base * 16u + j);
+    const ulonglong2 *tab = tw1 + rho * 16;
+    typename A::T v[16], nv[16];
+    {
+        const typename A::T *gt = (const typename A::T *)g;
+#pragma unroll
+        for (int i = 0; i < 16; i++) nv[i] = gt[rho * 256 + j + 16 * i];
+    }
+    wave_lds_fence();
+#pragma unroll 1
+    for (int c = 0; c < n_here; c++) {
+        tw2.keep();
+#pragma unroll
+        for (int i = 0; i < 16; i++) v[i] = nv[i];
+        if (c + 1 < n_here) {
+            const typename A::T *gt = (const typename A::T *)(g + (size_t)(c + 1) * ct_stride);
+#pragma unroll
+            for (int i = 0; i < 16; i++) nv[i] = gt[rho * 256 + j + 16 * i];
+        }
+        row_fwd(ar, v, tab, tw2, lds, rho, j);
+        u64 *go = g + (size_t)c * ct_stride + lane;
+#pragma unroll
+        for (int i = 0; i < 16; i++) go[64 * i] = ar.store_ws_fwd(v[i]);
+    }
+}
+
+template <int S, class W>
+__global__ __launch_bounds__(64, 2) void k_ks16_frows(Ks16Const kc, const PrimeConst *pcs, const u64 *tw_all, u64 *dig, int n_ct) {
+    typedef Ring<S> R;
+    __shared__ u64 lds[ROW_LDS];
+    __shared__ ulonglong2 tw1[4 * 16];
+    // The ciphertext group runs fastest: blocks that share a part of the twiddle table (same limb, same rows) are
+    // launched together and fetch it from memory once per XCD.
+    const int n_grp = (n_ct + KS_FROWS_GROUP - 1) / KS_FROWS_GROUP;
+    const int grp = blockIdx.x % n_grp, tile = (blockIdx.x / n_grp) % (4 * R::TILES), row = blockIdx.x / (n_grp * 4 * R::TILES);
+    const int l1 = kc.l1, ext = l1 + kc.K, n_rows = kc.beta * ext + l1;
+    const int prime = row < kc.beta * ext ? ks_ext_prime(row % ext, l1, kc.L) : row - kc.beta * ext;
+    const PrimeConst pc = load_prime(pcs, prime);
+    const u64 *tw = tw_all + (size_t)prime * 4 * R::N;
+    const int r0 = tile * 4, ct0 = grp * KS_FROWS_GROUP;
+    const int n_here = min(KS_FROWS_GROUP, n_ct - ct0);
+    const size_t ct_stride = (size_t)n_rows * R::N;
+    u64 *g = dig + ((size_t)ct0 * n_rows + row) * R::N + (size_t)r0 * 256;
+    if (prime < kc.L) frows_body<S, ArithFp>(g, ct_stride, n_here, tw, pc, lds, tw1, r0);
+    else frows_body<S, W>(g, ct_stride, n_here, tw, pc, lds, tw1, r0);
+}
+
+// ---------------------------------------- automorphism + key inner product + inverse row pass
+// Sums of products of transformed digit words x with key words k, both as 64-bit words in their stored formats.
+template <class A>
+struct Inner;
+template <>
+struct Inner<ArithFp> {
+    struct Acc {
+        double s;
+    };
+    static __device__ __forceinline__ void zero(Acc &a) { a.s = 0.0; }
+    static __device__ __forceinline__ void mac(const ArithFp &ar, Acc &a, u64 x, u64 k) { a.s += ar.mulmod_np(as_f64(x), as_f64(k)); }
+    static __device__ __forceinline__ void add(Acc &a, u64 x) { a.s += as_f64(x); }
+    // a rotation adds up to nine terms below 0.7 p: reduced after each, the sums stay exact integers
+    static __device__ __forceinline__ void fold(const ArithFp &ar, Acc &a) { a.s = ar.mid(a.s); }
+    static __device__ __forceinline__ double value(const Acc &a) { return a.s; }
+};
+// x = xh 2^30 + xl, k = kh 2^30 + kl: xh kh 2^60 is taken apart into dwords and folded by 2^60 = d, 2^62 = 4 d, like the
+// middle sum m 2^30.  Every half is at most 2^29 (a little more for the high ones): within 6 q before the last fold.
+template <>
+struct Inner<ArithWide> {
+    struct Acc {
+        int64_t s;
+    };
+    static __device__ __forceinline__ void zero(Acc &a) { a.s = 0; }
+    static __device__ __forceinline__ void mac(const ArithWide &ar, Acc &a, u64 x, u64 k) {
+        const int xl = (int)(u32)x, xh = (int)(x >> 32), kl = (int)(u32)k, kh = (int)(k >> 32);
+        const int64_t h = mul_i(xh, kh);
+        const int64_t m = mad_i((int)(h >> 32), ar.d4, mad_i(xh, kl, mul_i(xl, kh)));
+        const int64_t l = mad_uu((u32)h, (u32)ar.d, mad_i(xl, kl, a.s));
+        a.s = ar.mid(mad_pow2<30>((u32)m, mad_i((int)(m >> 32), ar.d4, l)));
+    }
+    static __device__ __forceinline__ void add(Acc &, u64) {}
+    static __device__ __forceinline__ void fold(const ArithWide &, Acc &) {}
+    static __device__ __forceinline__ int64_t value(const Acc &a) { return a.s; }
+};
+template <>
+struct Inner<ArithInt> {
+    struct Acc {
+        u64 s;
+    };
+    static __device__ __forceinline__ void zero(Acc &a) { a.s = 0; }
+    static __device__ __forceinline__ void mac(const ArithInt &ar, Acc &a, u64 x, u64 k) { a.s = add_mod(a.s, mont_mul(x, k, ar.q, ar.qneg_inv), ar.q); }
+    static __device__ __forceinline__ void add(Acc &, u64) {}
+    static __device__ __forceinline__ void fold(const ArithInt &, Acc &) {}
+    static __device__ __forceinline__ u64 value(const Acc &a) { return a.s; }
+};
+
+__device__ __forceinline__ u32 brev8(u32 x) { return __brev(x) >> 24; }
+
+// Four output rows of one limb of both accumulators, by one wave.  Transform-domain position k holds the evaluation at
+// psi^(2 brev(k) + 1) and phi_g(d)(psi^x) = d(psi^(x g)): output row r reads one source row, within which position p
+// reads brev8(g brev8(p) + carry mod 256), where the carry comes from the row's part of the exponent.
+// RAW: the digits have only been through their column pass; their row passes are run here.
+template <int S, bool RAW, class A>
+__device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *desc, const PrimeConst &pc, const u64 *tw_all, u64 *u, int prime, int e,
+                                           int members, u64 *lds, ulonglong2 *tw1) {
+    typedef Ring<S> R;
+    typedef Inner<A> I;
+    constexpr size_t N = R::N;
+    constexpr int LOGR = 4 + S;
+    const int lane = threadIdx.x, rho = lane >> 4, j = lane & 15;
+    const int l1 = kc.l1, ext = l1 + kc.K, beta = kc.beta;
+    const u32 r = blockIdx.x * 4 + rho;
+    const size_t kstride = (size_t)(kc.L + kc.K) * N;  // words between b_j and a_j, and half the distance between digits
+    const u64 *tw = tw_all + (size_t)prime * 4 * N;
+    const ulonglong2 *tab = tw1 + rho * 16;
+    A ar;
+    ar.init(pc);
+    typename I::Acc a0[16], a1[16];
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        I::zero(a0[i]);
+        I::zero(a1[i]);
+    }
+#pragma unroll 1
+    for (int mem = 0; mem < members; mem++) {
+        const RotDesc d = load_desc(desc, blockIdx.y * members + mem);
+        const u32 er = d.g * (2 * (__brev(r) >> (32 - LOGR)) + 1) & (2 * R::N - 1);
+        const u32 rs = __brev((er & (2 * R::ROWS - 1)) >> 1) >> (32 - LOGR), carry = er >> (LOGR + 1);
+        auto src = as_global(d.digits) + (size_t)e * N;
+        src += RAW ? rs * 256 + j : (rs >> 2) * 1024 + (rs & 3) * 16 + j;
+        constexpr int step = RAW ? 16 : 64;
+        auto key = as_global(d.key) + (size_t)prime * N + (size_t)blockIdx.x * 1024 + lane;
+        TwRegs tw2;
+        if (RAW) {
+            row_table_to_lds(tw1, tw, tw + N, R::ROWS + rs, rho, j);
+            tw2.load(tw, tw + N, (R::ROWS + rs) * 16u + j);
+        }
+        u32 at[16];
+#pragma unroll
+        for (int i = 0; i < 16; i++) at[i] = rpad(rho * 256 + brev8((d.g * brev8(16 * j + i) + carry) & 255));
+        const int nd = e < l1 ? beta + 1 : beta;  // the digits, then P * c0
+        u64 nv[16];
+#pragma unroll
+        for (int i = 0; i < 16; i++) nv[i] = src[step * i];
+        if (RAW) wave_lds_fence();
+#pragma unroll 1
+        for (int jd = 0; jd < nd; jd++) {
+            if (RAW) {
+                tw2.keep();
+                typename A::T v[16];
+#pragma unroll
+                for (int i = 0; i < 16; i++) v[i] = A::from_bits(nv[i]);
+                if (jd + 1 < nd) {
+#pragma unroll
+                    for (int i = 0; i < 16; i++) nv[i] = src[(size_t)(jd + 1) * ext * N + step * i];
+                }
+                row_fwd(ar, v, tab, tw2, lds, rho, j);
+#pragma unroll
+                for (int i = 0; i < 16; i++) lds[rpad(rho * 256 + 16 * j + i)] = ar.store_ws_fwd(v[i]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 16; i++) lds[rpad(rho * 256 + 16 * j + i)] = nv[i];
+                if (jd + 1 < nd) {
+#pragma unroll
+                    for (int i = 0; i < 16; i++) nv[i] = src[(size_t)(jd + 1) * ext * N + step * i];
+                }
+            }
+            wave_lds_fence();
+            if (jd < beta) {
+                auto kj = key + (size_t)jd * 2 * kstride;
+#pragma unroll
+                for (int h = 0; h < 16; h += 8) {
+                    u64 k0[8], k1[8];
+#pragma unroll
+                    for (int i = 0; i < 8; i++) {
+                        k0[i] = kj[64 * (h + i)];
+                        k1[i] = kj[kstride + 64 * (h + i)];
+                    }
+#pragma unroll
+                    for (int i = 0; i < 8; i++) {
+                        const u64 x = lds[at[h + i]];
+                        I::mac(ar, a0[h + i], x, k0[i]);
+                        I::mac(ar, a1[h + i], x, k1[i]);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 16; i++) I::add(a0[i], lds[at[i]]);
+            }
+            wave_lds_fence();
+        }
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            I::fold(ar, a0[i]);
+            I::fold(ar, a1[i]);
+        }
+    }
+    // inverse row pass of both sums: its twiddles are fetched once
+    tw += 2 * N;
+    row_table_to_lds(tw1, tw, tw + N, R::ROWS + r, rho, j);
+    TwRegs twi;
+    twi.load(tw, tw + N, (R::ROWS + r) * 16u + j);
+    wave_lds_fence();
+    u64 *uo = u + ((size_t)blockIdx.y * 2 * ext + e) * N + (size_t)r * 256 + j;
+#pragma unroll
+    for (int poly = 0; poly < 2; poly++) {
+        typename A::T v[16];
+#pragma unroll
+        for (int i = 0; i < 16; i++) v[i] = I::value(poly ? a1[i] : a0[i]);
+        row_inv(ar, v, tab, twi, lds, rho, j);
+        u64 *o = uo + (size_t)poly * ext * N;
+#pragma unroll
+        for (int i = 0; i < 16; i++) o[16 * i] = ar.store_ws_inv(v[i]);
+    }
+}
+
+// grid (4 TILES, n_rot / members, ext): limb slowest, so that the blocks in flight share one limb of the digits and keys.
+// members > 1: the block adds the inner products of `members` consecutive descriptors (rotations of one ciphertext:
+// same digits, their own Galois element and key) before the inverse pass, so that the group is brought back to
+// the ciphertext basis by one inverse transform and one ModDown; grid y then counts groups.
+template <int S, bool RAW, class W>
+__global__ __launch_bounds__(64, 2) void k_ks16_inner(Ks16Const kc, const RotDesc *desc, const PrimeConst *pcs, const u64 *tw_all, u64 *u, int members) {
+    __shared__ u64 lds[ROW_LDS];
+    __shared__ ulonglong2 tw1[4 * 16];
+    const int e = kc.l1 + kc.K - 1 - blockIdx.z, prime = ks_ext_prime(e, kc.l1, kc.L);  // the special limbs, which take longer, first
+    const PrimeConst pc = load_prime(pcs, prime);
+    if (e < kc.l1) inner_body<S, RAW, ArithFp>(kc, desc, pc, tw_all, u, prime, e, members, lds, tw1);
+    else inner_body<S, RAW, W>(kc, desc, pc, tw_all, u, prime, e, members, lds, tw1);
+}
+
+// ------------------------------------------------------ inverse column pass + ModDown
+// Special limb k of one column tile: inverse column pass and the centred residue of u (P/p_k)^-1, as hi * 2^30 + lo (lo in
+// [0, 2^30), hi signed).
+__device__ __forceinline__ int64_t special_centred(const ArithWide &ar, int64_t v, const Ks16Const &kc, int k) {
+    return ar.centred(ar.mul(v, as_const(kc.down_p)[2 * k], as_const(kc.down_p)[2 * k + 1]));
+}
+__device__ __forceinline__ int64_t special_centred(const ArithFp &ar, double v, const Ks16Const &kc, int k) {
+    return (int64_t)ar.mid(ar.mulmod(ar.mid(v), as_const(kc.down_p_fp)[2 * k], as_const(kc.down_p_fp)[2 * k + 1]));
+}
+__device__ __forceinline__ int64_t special_centred(const ArithInt &ar, u64 v, const Ks16Const &kc, int k) {
+    const u64 y = mul_shoup(v, as_const(kc.down_p)[2 * k], as_const(kc.down_p)[2 * k + 1], ar.q);
+    return y > ar.q / 2 ? (int64_t)y - (int64_t)ar.q : (int64_t)y;
+}
+// grid (TILES, 2 * parts, n_rot / members): a block brings the special limbs of one column tile of one accumulator back
+// and then `per` ciphertext limbs.  K: the number of special primes.
+template <int S, class W, int K>
+__global__ __launch_bounds__(KS_THREADS, 2) void k_ks16_icols(Ks16Const kc, const RotDesc *desc, const PrimeConst *pcs, const u64 *tw_all, const u64 *u,
+                                                              int limb_stride_out, int members, int per) {
+    typedef Ring<S> R;
+    constexpr size_t N = R::N;
+    __shared__ ColLds sh;
+    const int tid = threadIdx.x, c = R::col(tid), jj = R::grp(tid);
+    const int l1 = kc.l1, ext = l1 + K;
+    const int parts = (l1 + per - 1) / per, poly = blockIdx.y / parts, i0 = (blockIdx.y - poly * parts) * per, i1 = min(l1, i0 + per);
+    const u64 *src = u + ((size_t)blockIdx.z * 2 + poly) * ext * N + (size_t)blockIdx.x * R::COLS;
+    const u32 off_in = (16 * jj * 256 + c) * 8, off_out = (R::row(jj, 0) * 256 + c) * 8;
+    u32 tidx = 0;
+    const int tplace = col_tab_index<S>(tid, &tidx);
+    ulonglong2 tnext;
+    u64 nv[16];
+    // step t of the walk: special limb t for t < K, then ciphertext limb i0 + t - K
+    const int n_steps = K + i1 - i0;
+    auto fetch = [&](int t) {
+        const int limb = t < K ? l1 + t : i0 + t - K;
+        const u64 *tw = tw_all + (size_t)ks_ext_prime(limb, l1, kc.L) * 4 * N + 2 * N;
+        tnext = make_ulonglong2(tw[tidx], tw[N + tidx]);
+#pragma unroll
+        for (int i = 0; i < 16; i++) nv[i] = ld_off(src + (size_t)limb * N + i * 256, off_in);
+    };
+    auto put_tab = [&](int buf) {
+        if (tplace >= 0) sh.tab[buf][tplace] = tnext;
+    };
+    fetch(0);
+    put_tab(0);
+    __syncthreads();
+    u64 y[K][16];
+    auto special = [&](u64 *yk, int k) {
+        W ar;
+        ar.init(load_prime(pcs, kc.L + k));
+        typename W::T v[16];
+#pragma unroll
+        for (int i = 0; i < 16; i++) v[i] = W::from_bits(nv[i]);
+        fetch(k + 1);
+        put_tab((k + 1) % 3);
+        cols_inv_tab<S>(ar, v, sh.tab[k % 3], sh.tile[k & 1], c, jj);
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int64_t z = special_centred(ar, v[i], kc, k);
+            yk[i] = ((u64)(u32)(int32_t)(z >> 30) << 32) | (u32)(z & 0x3fffffff);
+        }
+    };
+    special(y[0], 0);
+    if constexpr (K > 1) special(y[1], 1);
+    if constexpr (K > 2) special(y[2], 2);
+    if constexpr (K > 3) special(y[3], 3);
+    const RotDesc dl = load_desc(desc, blockIdx.z * members);  // the group's first descriptor carries the destination
+    auto out_at = [&](u64 *out, int i) { return as_global((u64 *)((char *)(out + R::row(0, i) * 256) + off_out)); };
+    int tcur = K % 3;
+#pragma unroll 1
+    for (int t = K; t < n_steps; t++) {
+        const int limb = i0 + t - K;
+#pragma unroll
+        for (int k = 0; k < K; k++)
+#pragma unroll
+            for (int i = 0; i < 16; i++) keep_narrow(y[k][i]);
+        const PrimeConst pc = load_prime(pcs, limb);
+        ArithFp ar;
+        ar.init(pc);
+        double v[16];
+#pragma unroll
+        for (int i = 0; i < 16; i++) v[i] = as_f64(nv[i]);
+        if (t + 1 < n_steps) fetch(t + 1);
+        const int tnxt = tcur == 2 ? 0 : tcur + 1;
+        put_tab(tnxt);
+        cols_inv_tab<S>(ar, v, sh.tab[tcur], sh.tile[t & 1], c, jj);
+        tcur = tnxt;
+        const double sc = as_const(kc.down_q)[2 * limb], sc_p = as_const(kc.down_q)[2 * limb + 1];
+        u64 *out = dl.out + ((size_t)poly * limb_stride_out + limb) * N + (size_t)blockIdx.x * R::COLS;
+        // sum_k lo_k p_k^-1 + hi_k 2^30 p_k^-1 over split constants: four multiply-adds per special limb, one reduction
+        // (two modular products per special limb in fp64 took 2.5 times the instructions); |sums| < 2^59
+#pragma unroll
+        for (int h = 0; h < 16; h += 4) {
+            int64_t a0[4], a1[4];
+#pragma unroll
+            for (int k = 0; k < K; k++) {
+                const u64 hl = as_const(kc.down_h)[(limb * K + k) * 2], hh = as_const(kc.down_h)[(limb * K + k) * 2 + 1];
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const int lo = (int)(u32)y[k][h + i], hi = (int)(y[k][h + i] >> 32);
+                    a0[i] = mad_i(hi, (int)(u32)hh, k ? mad_i(lo, (int)(u32)hl, a0[i]) : mul_i(lo, (int)(u32)hl));
+                    a1[i] = mad_i(hi, (int)(hh >> 32), k ? mad_i(lo, (int)(hl >> 32), a1[i]) : mul_i(lo, (int)(hl >> 32)));
+                }
+            }
+            u64 w[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) w[i] = ar.canon(ar.mulmod(ar.mid(v[h + i]), sc, sc_p) - ar.reduce25_long(a1[i], a0[i]));
+            if (dl.accumulate) {
+                // out <- out + result.  `out` may be the rotation's own source (every read of the source happened in the
+                // raise kernels, which have finished), which turns t <- t + Rot(t; r) into one pass
+#pragma unroll
+                for (int i = 0; i < 4; i++) w[i] = add_mod(*out_at(out, h + i), w[i], pc.q);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; i++) *out_at(out, h + i) = w[i];
+        }
+    }
+}
+
+// ---------------------------------------------------------------- launchers of one ring
+// Limbs per block of the two column kernels: all of them where that still gives every CU four blocks (y is then formed
+// once), otherwise as few as it takes to get there.  blocks: blocks at one limb-walk each; limbs: length of the walk.
+static int limbs_per_block(long blocks, int limbs) {
+    const long want = 1024;
+    if (blocks >= want) return limbs;
+    const long parts = (want + blocks - 1) / blocks;
+    return (int)((limbs + parts - 1) / parts);
+}
+
+// Calls f with the arithmetic of the special primes.
+template <class F>
+static void special_dispatch(const ensi_ctx *ctx, F f) {
+    if (ctx->special_kind == PRIME_WIDE) f(ArithWide{});
+    else if (ctx->special_kind == PRIME_FP) f(ArithFp{});
+    else f(ArithInt{});
+}
+
+template <int S>
+void ks16_raise(ensi_ctx *ctx, const Ks16Const &kc, const u64 *ct_base, size_t ct_stride_words, int limb_stride, int n_ct, u64 *dig, bool rows,
+                       hipStream_t st) {
+    const int ext = kc.l1 + kc.K, n_rows = kc.beta * ext + kc.l1;
+    special_dispatch(ctx, [&](auto w) {
+        constexpr int TILES = Ring<S>::TILES;
+        typedef decltype(w) W;
+        {
+            ScopedTimer t(ctx, "ks_modup_fcols", st);
+            const int per = limbs_per_block((long)TILES * (kc.beta + 1) * n_ct, ext);
+            hipLaunchKernelGGL((k_ks16_fcols<S, W>), dim3(TILES, kc.beta * ((ext + per - 1) / per) + (kc.l1 + per - 1) / per, n_ct), dim3(KS_THREADS), 0, st, kc,
+                               ctx->d_pc, ctx->d_tw, ct_base, ct_stride_words, limb_stride, dig, per);
+        }
+        if (rows) {
+            ScopedTimer t(ctx, "ks_frows", st);
+            hipLaunchKernelGGL((k_ks16_frows<S, W>), dim3(4 * TILES * n_rows * ((n_ct + KS_FROWS_GROUP - 1) / KS_FROWS_GROUP)), dim3(64), 0, st, kc, ctx->d_pc,
+                               ctx->d_tw, dig, n_ct);
+        }
+    });
+}
+
+template <int S>
+void ks16_switch(ensi_ctx *ctx, const Ks16Const &kc, const RotDesc *d_desc, int n_rot, u64 *u, int limb_stride_out, bool raw, hipStream_t st,
+                        int members) {
+    // n_rot descriptors in groups of `members` (1: every rotation on its own); u is indexed by group
+    const int n_grp = n_rot / members, ext = kc.l1 + kc.K;
+    special_dispatch(ctx, [&](auto w) {
+        constexpr int TILES = Ring<S>::TILES;
+        typedef decltype(w) W;
+        {
+            ScopedTimer t(ctx, "ks_inner", st);
+            if (raw)
+                hipLaunchKernelGGL((k_ks16_inner<S, true, W>), dim3(4 * TILES, n_grp, ext), dim3(64), 0, st, kc, d_desc, ctx->d_pc, ctx->d_tw, u, members);
+            else
+                hipLaunchKernelGGL((k_ks16_inner<S, false, W>), dim3(4 * TILES, n_grp, ext), dim3(64), 0, st, kc, d_desc, ctx->d_pc, ctx->d_tw, u, members);
+        }
+        ScopedTimer t(ctx, "ks_icols_moddown", st);
+        const int per = limbs_per_block((long)TILES * 2 * n_grp, kc.l1);
+        auto icols = [&](auto k) {
+            hipLaunchKernelGGL((k_ks16_icols<S, W, decltype(k)::value>), dim3(TILES, 2 * ((kc.l1 + per - 1) / per), n_grp), dim3(KS_THREADS), 0, st, kc, d_desc,
+                               ctx->d_pc, ctx->d_tw, u, limb_stride_out, members, per);
+        };
+        if (kc.K == 1) icols(std::integral_constant<int, 1>{});
+        else if (kc.K == 2) icols(std::integral_constant<int, 2>{});
+        else if (kc.K == 3) icols(std::integral_constant<int, 3>{});
+        else icols(std::integral_constant<int, 4>{});
+    });
+}

@@ -183,7 +183,7 @@ static void launch_ntt_chunk(ensi_ctx *ctx, u64 *data, int n_inst, const LimbMap
 // Rows beyond the grid's y limit are transformed in several launches, each a whole
 // number of periods of the prime map.
 void launch_ntt(ensi_ctx *ctx, u64 *data, int n_inst, const LimbMap &map, bool inverse, hipStream_t st) {
-    if (ctx->log_n == 16) {
+    if (ctx->log_n >= 12) {
         launch_ntt16(ctx, data, n_inst, map, inverse, st);
         return;
     }

@@ -9,7 +9,7 @@
 //
 //   generic  any ring size and prime: gather the sources, the library's transform, a Montgomery
 //            multiply-add kernel, the inverse transform, the integer or fp64 rescale kernel, a strided copy.
-//   pm16     N = 2^16 with ciphertext primes below 2^50, four kernels that keep every intermediate in the
+//   pm16     N = 2^12 .. 2^16 with ciphertext primes below 2^50, four kernels that keep every intermediate in the
 //            layout and number format (exact integers in doubles) of the transform passes around it:
 //              k_pm16_fcols            forward column pass of every source limb, read straight from the
 //                                      source ciphertexts
@@ -26,7 +26,6 @@
 #include "ntt16_core.h"
 
 #define PM_THREADS 256
-#define PM_N 65536
 #ifndef PM_MAC_BLOCKS
 #define PM_MAC_BLOCKS 2
 #endif
@@ -97,27 +96,29 @@ void launch_pm_generic(ensi_ctx *ctx, const PmGroup &g, const u64 *d_consts, con
     }
 }
 
-// ===================================================================== N = 2^16, fp64 arithmetic
+// ===================================================================== N = 2^12 .. 2^16, fp64 arithmetic
 // Plaintext in the order the row pass holds it: within the 16-row tile b, thread (rho, j) = tid owns, as its
 // i-th value, position 16 j + i of row rho; that value is stored at b*4096 + i*256 + tid, as a double.
-// grid (16, n_rows)
-__global__ __launch_bounds__(PM_THREADS) void k_pm16_pt_format(const u64 *in, u64 *out) {
+// grid (N / 4096, n_rows)
+__global__ __launch_bounds__(PM_THREADS) void k_pm16_pt_format(const u64 *in, u64 *out, int N) {
     const int tid = threadIdx.x, rho = tid >> 4, j = tid & 15;
-    const size_t base = (size_t)blockIdx.y * PM_N + (size_t)blockIdx.x * 4096;
+    const size_t base = (size_t)blockIdx.y * N + (size_t)blockIdx.x * 4096;
 #pragma unroll
     for (int i = 0; i < 16; i++) out[base + i * 256 + tid] = pm_u64((double)in[base + rho * 256 + 16 * j + i]);
 }
 void launch_pm16_pt_format(ensi_ctx *ctx, const u64 *ntt_form, int n_rows, u64 *out, hipStream_t st) {
-    (void)ctx;
-    hipLaunchKernelGGL(k_pm16_pt_format, dim3(16, n_rows), dim3(PM_THREADS), 0, st, ntt_form, out);
+    hipLaunchKernelGGL(k_pm16_pt_format, dim3(ctx->N / 4096, n_rows), dim3(PM_THREADS), 0, st, ntt_form, out, ctx->N);
 }
 
-// grid (16, 2*l1, n_src)
+// grid (TILES, 2*l1, n_src)
+template <int S>
 __global__ __launch_bounds__(PM_THREADS) void k_pm16_fcols(PmGroup g, const PrimeConst *pcs, const u64 *tw_all) {
+    typedef Ring<S> R;
+    constexpr size_t PM_N = R::N;
     __shared__ u64 lds[4096];
-    const int tid = threadIdx.x, c16 = tid & 15, jj = tid >> 4;
+    const int tid = threadIdx.x, c16 = R::col(tid), jj = R::grp(tid);
     const int y = blockIdx.y, c = y / g.l1, i = y - c * g.l1, t = blockIdx.z;
-    const size_t col = (size_t)blockIdx.x * 16 + c16;
+    const size_t col = (size_t)blockIdx.x * R::COLS + c16;
     const u64 *src = g.terms[g.owner[t]].src + ((size_t)c * g.limb_stride_in + i) * PM_N + col;
     u64 *out = g.ws_a + ((size_t)t * 2 * g.l1 + y) * PM_N + col;
     ArithFp ar;
@@ -125,34 +126,19 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm16_fcols(PmGroup g, const Prim
     const u64 *tw = tw_all + (size_t)i * 4 * PM_N;
     double v[16];
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = (double)src[(size_t)(jj + 16 * k) * 256];
-    cols_fwd_regs(ar, v, tw, tw + PM_N, lds, c16, jj);
+    for (int k = 0; k < 16; k++) v[k] = (double)src[(size_t)R::row(jj, k) * 256];
+    cols_fwd_regs<S>(ar, v, tw, tw + PM_N, lds, c16, jj);
 #pragma unroll
     for (int k = 0; k < 16; k++) out[(size_t)(16 * jj + k) * 256] = pm_u64(ar.mid(v[k]));
 }
 
-// Four Cooley-Tukey stages like ct4, with the 15 twiddles (value, companion) of the step read from a table in LDS:
-// entry (1 << k) - 1 + g serves stage k, butterfly group g.
-__device__ __forceinline__ void pm_ct4_tab(const ArithFp &ar, double *v, const ulonglong2 *tab) {
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-        const int d = 8 >> k;
-#pragma unroll
-        for (int gq = 0; gq < (1 << k); gq++) {
-            const ulonglong2 w = tab[(1 << k) - 1 + gq];
-#pragma unroll
-            for (int o = 0; o < d; o++) {
-                const int i0 = gq * 2 * d + o;
-                ar.ct(v[i0], v[i0 + d], w.x, w.y);
-            }
-        }
-    }
-}
-
-// grid (16 * 2*l1 * n_out).  The operand of the next term is fetched while the current forward pass runs.  The
+// grid (TILES * 2*l1 * n_out).  The operand of the next term is fetched while the current forward pass runs.  The
 // twiddles of a pass's first step depend on the row only and sit in LDS (the 16 threads of a row read the same
 // word); those of the second step differ per thread and stay in registers across all terms.
+template <int S>
 __global__ __launch_bounds__(PM_THREADS, PM_MAC_BLOCKS) void k_pm16_frows_mac_irows(PmGroup g, const PrimeConst *pcs, const u64 *tw_all) {
+    typedef Ring<S> R;
+    constexpr size_t PM_N = R::N;
     __shared__ u64 lds[4096 + 256];
     __shared__ ulonglong2 tw1[16 * 16];
     const int tid = threadIdx.x, rho = tid >> 4, j = tid & 15;
@@ -160,7 +146,8 @@ __global__ __launch_bounds__(PM_THREADS, PM_MAC_BLOCKS) void k_pm16_frows_mac_ir
     // plaintext tile, so their blocks are made consecutive on one XCD (ids n and n + 8) and the second read of
     // the tile is served by that XCD's L2.
     const u32 id = blockIdx.x, q = (id >> 4) * 8 + (id & 7);
-    const int cpoly = (id >> 3) & 1, tile = q & 15, i = (q >> 4) % g.l1, o = (q >> 4) / g.l1;
+    const int cpoly = (id >> 3) & 1, tile = q % R::TILES, i = q / R::TILES % g.l1, o = q / R::TILES / g.l1;
+    if (o >= g.n_out) return;  // the last group of eight tiles may be incomplete
     const int y = cpoly * g.l1 + i;
     const int r0 = tile * 16;
     ArithFp ar;
@@ -169,7 +156,7 @@ __global__ __launch_bounds__(PM_THREADS, PM_MAC_BLOCKS) void k_pm16_frows_mac_ir
     const u32 r = (u32)(r0 + rho);
     if (j < 15) {
         const int k = 31 - __clz(j + 1), gq = j + 1 - (1 << k);
-        const u32 idx = ((256u + r) << k) + gq;
+        const u32 idx = ((R::ROWS + r) << k) + gq;
         tw1[rho * 16 + j] = make_ulonglong2(twf[idx], twf[PM_N + idx]);
     }
     const ulonglong2 *tab = tw1 + rho * 16;
@@ -201,13 +188,13 @@ __global__ __launch_bounds__(PM_THREADS, PM_MAC_BLOCKS) void k_pm16_frows_mac_ir
             for (int k = 0; k < 16; k++) nv[k] = pm_f64(a[16 * k]);
         }
         // forward row pass (the steps of rows_fwd_regs)
-        pm_ct4_tab(ar, v, tab);
+        ct4_tab(ar, v, tab);
 #pragma unroll
         for (int k = 0; k < 16; k++) l[rpad(rho * 256 + j + 16 * k)] = ar.mid(v[k]);
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 16; k++) v[k] = l[rpad(rho * 256 + 16 * j + k)];
-        ct4(ar, v, twf, twf + PM_N, (256u + r) * 16u + j);
+        ct4(ar, v, twf, twf + PM_N, (R::ROWS + r) * 16u + j);
 #pragma unroll
         for (int k = 0; k < 16; k++) acc[k] += ar.mulmod_np(ar.mid(v[k]), w[k]);
         // a product is below 0.7 q in magnitude: eight of them stay exact in a double
@@ -220,18 +207,28 @@ __global__ __launch_bounds__(PM_THREADS, PM_MAC_BLOCKS) void k_pm16_frows_mac_ir
     double v[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) v[k] = ar.mid(acc[k]);
-    rows_inv_regs(ar, v, twi, twi + PM_N, lds, rho, j, r);
+    // inverse row pass of the sum
+    gs4(ar, v, twi, twi + PM_N, (R::ROWS + r) * 16u + j);
+#pragma unroll
+    for (int k = 0; k < 16; k++) l[rpad(rho * 256 + 16 * j + k)] = ar.mid(v[k]);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 16; k++) v[k] = l[rpad(rho * 256 + j + 16 * k)];
+    gs4(ar, v, twi, twi + PM_N, R::ROWS + r);
     u64 *out = g.ws_b + (size_t)o * term + a_off;
 #pragma unroll
     for (int k = 0; k < 16; k++) out[16 * k] = pm_u64(ar.mid(v[k]));
 }
 
-// grid (16, 2, n_out): ws_last[o][c][N] <- centred residue of limb l1-1 (coefficient form)
+// grid (TILES, 2, n_out): ws_last[o][c][N] <- centred residue of limb l1-1 (coefficient form)
+template <int S>
 __global__ __launch_bounds__(PM_THREADS) void k_pm16_icols_last(PmGroup g, const PrimeConst *pcs, const u64 *tw_all) {
+    typedef Ring<S> R;
+    constexpr size_t PM_N = R::N;
     __shared__ u64 lds[4096];
-    const int tid = threadIdx.x, c16 = tid & 15, jj = tid >> 4;
+    const int tid = threadIdx.x, c16 = R::col(tid), jj = R::grp(tid);
     const int c = blockIdx.y, o = blockIdx.z, i = g.l1 - 1;
-    const size_t col = (size_t)blockIdx.x * 16 + c16;
+    const size_t col = (size_t)blockIdx.x * R::COLS + c16;
     const u64 *src = g.ws_b + ((size_t)o * 2 * g.l1 + c * g.l1 + i) * PM_N + col;
     u64 *dst = g.ws_last + ((size_t)o * 2 + c) * PM_N + col;
     ArithFp ar;
@@ -240,18 +237,21 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm16_icols_last(PmGroup g, const
     double v[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) v[k] = pm_f64(src[(size_t)(16 * jj + k) * 256]);
-    cols_inv_regs(ar, v, tw, tw + PM_N, lds, c16, jj);
+    cols_inv_regs<S>(ar, v, tw, tw + PM_N, lds, c16, jj);
 #pragma unroll
-    for (int k = 0; k < 16; k++) dst[(size_t)(jj + 16 * k) * 256] = pm_u64(ar.mid(ar.mulmod(ar.mid(v[k]), ar.ninv, ar.ninv_p)));
+    for (int k = 0; k < 16; k++) dst[(size_t)R::row(jj, k) * 256] = pm_u64(ar.mid(ar.mulmod(ar.mid(v[k]), ar.ninv, ar.ninv_p)));
 }
 
-// grid (16, 2*(l1-1), n_out)
+// grid (TILES, 2*(l1-1), n_out)
+template <int S>
 __global__ __launch_bounds__(PM_THREADS) void k_pm16_icols_rescale(PmGroup g, PmRescale rs, const PrimeConst *pcs, const u64 *tw_all) {
+    typedef Ring<S> R;
+    constexpr size_t PM_N = R::N;
     __shared__ u64 lds[4096];
-    const int tid = threadIdx.x, c16 = tid & 15, jj = tid >> 4;
+    const int tid = threadIdx.x, c16 = R::col(tid), jj = R::grp(tid);
     const int lo = g.l1 - 1;
     const int y = blockIdx.y, c = y / lo, i = y - c * lo, o = blockIdx.z;
-    const size_t col = (size_t)blockIdx.x * 16 + c16;
+    const size_t col = (size_t)blockIdx.x * R::COLS + c16;
     const u64 *src = g.ws_b + ((size_t)o * 2 * g.l1 + c * g.l1 + i) * PM_N + col;
     const u64 *last = g.ws_last + ((size_t)o * 2 + c) * PM_N + col;
     u64 *dst = g.out + (size_t)o * g.out_stride + ((size_t)c * g.limb_stride_out + i) * PM_N + col;
@@ -263,31 +263,35 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm16_icols_rescale(PmGroup g, Pm
 #pragma unroll
     for (int k = 0; k < 16; k++) v[k] = pm_f64(src[(size_t)(16 * jj + k) * 256]);
 #pragma unroll
-    for (int k = 0; k < 16; k++) tl[k] = pm_f64(last[(size_t)(jj + 16 * k) * 256]);
-    cols_inv_regs(ar, v, tw, tw + PM_N, lds, c16, jj);
+    for (int k = 0; k < 16; k++) tl[k] = pm_f64(last[(size_t)R::row(jj, k) * 256]);
+    cols_inv_regs<S>(ar, v, tw, tw + PM_N, lds, c16, jj);
 #pragma unroll
     for (int k = 0; k < 16; k++) {
         const double x = ar.mid(ar.mulmod(ar.mid(v[k]), ar.ninv, ar.ninv_p));
         const double z = ar.mid(x - ar.mid(tl[k]));
-        dst[(size_t)(jj + 16 * k) * 256] = ar.canon(ar.mulmod(z, w, wp));
+        dst[(size_t)R::row(jj, k) * 256] = ar.canon(ar.mulmod(z, w, wp));
     }
 }
 
 void launch_pm16(ensi_ctx *ctx, const PmGroup &g, const PmRescale &rs, hipStream_t st) {
-    if (g.n_src > 0) {
-        ScopedTimer t(ctx, "pm_fcols", st);
-        hipLaunchKernelGGL(k_pm16_fcols, dim3(16, 2 * g.l1, g.n_src), dim3(PM_THREADS), 0, st, g, ctx->d_pc, ctx->d_tw);
-    }
-    {
-        ScopedTimer t(ctx, "pm_frows_mac_irows", st);
-        hipLaunchKernelGGL(k_pm16_frows_mac_irows, dim3(16 * 2 * g.l1 * g.n_out), dim3(PM_THREADS), 0, st, g, ctx->d_pc, ctx->d_tw);
-    }
-    {
-        ScopedTimer t(ctx, "pm_icols_last", st);
-        hipLaunchKernelGGL(k_pm16_icols_last, dim3(16, 2, g.n_out), dim3(PM_THREADS), 0, st, g, ctx->d_pc, ctx->d_tw);
-    }
-    {
-        ScopedTimer t(ctx, "pm_icols_rescale", st);
-        hipLaunchKernelGGL(k_pm16_icols_rescale, dim3(16, 2 * (g.l1 - 1), g.n_out), dim3(PM_THREADS), 0, st, g, rs, ctx->d_pc, ctx->d_tw);
-    }
+    ring_dispatch(ctx->log_n, [&](auto s) {
+        constexpr int S = decltype(s)::value, TILES = Ring<S>::TILES;
+        if (g.n_src > 0) {
+            ScopedTimer t(ctx, "pm_fcols", st);
+            hipLaunchKernelGGL((k_pm16_fcols<S>), dim3(TILES, 2 * g.l1, g.n_src), dim3(PM_THREADS), 0, st, g, ctx->d_pc, ctx->d_tw);
+        }
+        {
+            ScopedTimer t(ctx, "pm_frows_mac_irows", st);
+            const unsigned tiles = (unsigned)TILES * g.l1 * g.n_out;  // per polynomial, in groups of eight (one per XCD)
+            hipLaunchKernelGGL((k_pm16_frows_mac_irows<S>), dim3((tiles + 7) / 8 * 16), dim3(PM_THREADS), 0, st, g, ctx->d_pc, ctx->d_tw);
+        }
+        {
+            ScopedTimer t(ctx, "pm_icols_last", st);
+            hipLaunchKernelGGL((k_pm16_icols_last<S>), dim3(TILES, 2, g.n_out), dim3(PM_THREADS), 0, st, g, ctx->d_pc, ctx->d_tw);
+        }
+        {
+            ScopedTimer t(ctx, "pm_icols_rescale", st);
+            hipLaunchKernelGGL((k_pm16_icols_rescale<S>), dim3(TILES, 2 * (g.l1 - 1), g.n_out), dim3(PM_THREADS), 0, st, g, rs, ctx->d_pc, ctx->d_tw);
+        }
+    });
 }

@@ -477,6 +477,43 @@ def test_full_ring_rotate_other_prime_sizes(params, why):
     p.close()
 
 
+@pytest.mark.parametrize("params", [
+    (12, 50, 5, 60, 4, 4, 40), (13, 50, 5, 60, 3, 2, 40), (14, 50, 6, 60, 2, 2, 40), (15, 50, 4, 60, 1, 1, 36),  # special primes just below 2^60
+    (12, 45, 4, 48, 3, 3, 36),  # every prime in fp64
+    (13, 50, 3, 61, 2, 2, 40), (12, 50, 3, 55, 4, 1, 36),  # special primes in neither of the two fast arithmetics
+], ids=["4K-wide4", "8K-wide3", "16K-wide2", "32K-wide1", "4K-fp3", "8K-61bit", "4K-55bit"])
+def test_register_transform_rings_bit_exact(params):
+    """Every ring of the register transform and every kind and number of special primes: rotations that have their raised
+    ciphertext to themselves, and rotations (of a product) that share one."""
+    p = Pair(params)
+    s = p.n // 4
+    steps = [s, 2 * s, 3 * s, -1]
+    o_gks, g_gk = p.galois_keys(steps)
+    z = p.rng.uniform(-1, 1, (3, p.n))
+    for limbs in (p.pr.L, 2):
+        o_cts, g_ct = p.encrypt_both(z, limbs)
+        assert np.array_equal(g_ct.export(), stack_cts(o_cts))
+        for n in (1, 3):
+            one = p.ctx.ct_import(stack_cts(o_cts[:n]), g_ct.scale)
+            out = p.ctx.rotate(g_gk, one, [-1, s, s][:n])
+            want = [p.o.rotate(c, o_gks[st]) for c, st in zip(o_cts, [-1, s, s][:n])]
+            assert np.array_equal(out.export(), stack_cts(want)), (limbs, n)
+            out.free()
+            one.free()
+        g_ct.free()
+    rng = np.random.default_rng(3)
+    d, m = 6, 5
+    W = wl.ternary_weights(rng, d, m)
+    o_cts, g_ct = p.encrypt_both(wl.pack_columns(rng.uniform(-1, 1, (s, d)), p.n), p.pr.L)
+    out = p.ctx.ternary_matmul(g_gk, g_ct, s, d, W, "diagonal")
+    want = p.o.ternary_matmul(o_cts, s, d, W, "diagonal", {r: o_gks[r * s] for r in range(1, 4)})
+    assert np.array_equal(out.export(), stack_cts(want))
+    out.free()
+    g_ct.free()
+    g_gk.free()
+    p.close()
+
+
 def test_full_ring_rotate_batch_longer_than_one_group(full):
     """More ciphertexts than the library raises at once (groups of 64), at a low level to keep the oracle quick."""
     p = full
