@@ -9,7 +9,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libensi_hip.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["api.hip", "api_keys.hip", "api_static.hip", "api_matmul.hip", "api_pmult.hip", "api_ccmm.hip", "ntt.hip", "ntt16.hip", "keyswitch16.hip", "pmult.hip", "ccmm.hip", "kernels.hip",
-           "accumulate_mfma.hip"] + ["keyswitch16_ring.hip:%d" % s for s in range(5)]  # file:s -- compiled with -DKS_RING=s
+           "accumulate_mfma.hip", "client16.hip"] + ["keyswitch16_ring.hip:%d" % s for s in range(5)]  # file:s -- compiled with -DKS_RING=s
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",

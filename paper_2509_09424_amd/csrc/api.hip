@@ -52,6 +52,52 @@ int stage_prealloc(ensi_ctx *ctx) {
     return ENSI_OK;
 }
 
+// ------------------------------------------------------------- memory of handles
+hipError_t DevPool::take(void **p, size_t bytes, size_t *got) {
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        auto it = blocks.lower_bound(bytes);
+        if (it != blocks.end() && it->first <= bytes + bytes / 8) {
+            *p = it->second;
+            *got = it->first;
+            held -= it->first;
+            blocks.erase(it);
+        } else {
+            *p = nullptr;
+        }
+    }
+    if (*p) return hipDeviceSynchronize();
+    *got = bytes;
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        std::lock_guard<std::mutex> lock(mu);
+        for (auto &b : blocks) (void)hipFree(b.second);
+        blocks.clear();
+        held = 0;
+        e = hipMalloc(p, bytes);
+    }
+    return e;
+}
+void DevPool::give(void *p, size_t bytes) {
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        if (!closed && bytes <= KEEP_EACH && held + bytes <= KEEP_ALL) {
+            blocks.emplace(bytes, p);
+            held += bytes;
+            return;
+        }
+    }
+    (void)hipFree(p);
+}
+void DevPool::close() {
+    std::lock_guard<std::mutex> lock(mu);
+    closed = true;
+    for (auto &b : blocks) (void)hipFree(b.second);
+    blocks.clear();
+    held = 0;
+}
+
 // ---------------------------------------------------------------------- timers
 int timer_id(ensi_ctx *ctx, const char *name) {
     for (size_t i = 0; i < ctx->timers.size(); i++)
@@ -242,7 +288,9 @@ extern "C" int ensi_ctx_create(const ensi_params *prm, ensi_ctx **out) {
         ctx->rot_exp[j] = (u32)x;
         x = x * 5 % two_n;
     }
-    if (upload(&ctx->d_pc, pcs) != hipSuccess || upload(&ctx->d_tw, tw) != hipSuccess || upload(&ctx->d_cos, cs) != hipSuccess ||
+    std::vector<u32> slot_of_k(N / 2);
+    for (int j = 0; j < N / 2; j++) slot_of_k[(ctx->rot_exp[j] - 1) / 4] = (u32)j;
+    if (upload(&ctx->d_slot_of_k, slot_of_k) != hipSuccess || upload(&ctx->d_pc, pcs) != hipSuccess || upload(&ctx->d_tw, tw) != hipSuccess || upload(&ctx->d_cos, cs) != hipSuccess ||
         upload(&ctx->d_rot_exp, ctx->rot_exp) != hipSuccess) {
         ensi_ctx_free(ctx);
         return ENSI_E_HIP;
@@ -302,6 +350,10 @@ extern "C" void ensi_ctx_free(ensi_ctx *ctx) {
     if (ctx->d_tw) (void)hipFree(ctx->d_tw);
     if (ctx->d_cos) (void)hipFree(ctx->d_cos);
     if (ctx->d_rot_exp) (void)hipFree(ctx->d_rot_exp);
+    if (ctx->d_slot_of_k) (void)hipFree(ctx->d_slot_of_k);
+    ctx->pool->close();
+    if (ctx->ws_cl) (void)hipFree(ctx->ws_cl);
+    if (ctx->pinned_out) (void)hipHostFree(ctx->pinned_out);
     if (ctx->ws_digits) (void)hipFree(ctx->ws_digits);
     if (ctx->ws_u) (void)hipFree(ctx->ws_u);
     if (ctx->ws_y) (void)hipFree(ctx->ws_y);
@@ -511,17 +563,25 @@ int get_ks16(ensi_ctx *ctx, int l1, const Ks16Const **out) {
 }
 
 // ------------------------------------------------------------------ plaintexts
-static int pt_from_coeffs(ensi_ctx *ctx, const int64_t *d_coeffs, int n_pt, int limbs, double scale, ensi_pt **out) {
+static int pt_alloc(ensi_ctx *ctx, int n_pt, int limbs, double scale, ensi_pt **out) {
     ensi_pt *pt = new ensi_pt();
     pt->ctx = ctx;
     pt->n = n_pt;
     pt->limbs = limbs;
     pt->scale = scale;
     pt->d = nullptr;
-    if (hipMalloc((void **)&pt->d, (size_t)n_pt * limbs * ctx->N * 8) != hipSuccess) {
+    pt->pool = ctx->pool;
+    if (ctx->pool->take((void **)&pt->d, (size_t)n_pt * limbs * ctx->N * 8, &pt->d_bytes) != hipSuccess) {
         delete pt;
         ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed for plaintext");
     }
+    *out = pt;
+    return ENSI_OK;
+}
+static int pt_from_coeffs(ensi_ctx *ctx, const int64_t *d_coeffs, int n_pt, int limbs, double scale, ensi_pt **out) {
+    ensi_pt *pt;
+    int rc = pt_alloc(ctx, n_pt, limbs, scale, &pt);
+    if (rc) return rc;
     launch_i64_to_rns(ctx, d_coeffs, n_pt, make_map(ctx, limbs, false), pt->d, nullptr);
     if (hipStreamSynchronize(nullptr) != hipSuccess) {
         ensi_pt_free(pt);
@@ -531,9 +591,40 @@ static int pt_from_coeffs(ensi_ctx *ctx, const int64_t *d_coeffs, int n_pt, int 
     return ENSI_OK;
 }
 
+// Bytes of 64-bit words per polynomial that one chunk of a client-side batch takes (its host copies and workspaces are bounded by
+// that, and the copy of one chunk overlaps the kernels of the one before).
+static constexpr size_t CLIENT_CHUNK = (size_t)8 << 20;
+// Above this scale the encoding takes the 2N-point transform: with less than ten bits of a double left below the unit, another
+// order of summation rounds some coefficients to a neighbour, and the plaintexts encoded at a prime (masks, rotary
+// constants: once per program) should not change with the kernel.
+static constexpr double CLIENT_MAX_SCALE = 0x1p43;
+
 // slots: host [n_pt][n_slots]; plaintext y holds its values in slots [slot0 + y*slot_step, ...+n_slots)
 int encode_window(ensi_ctx *ctx, const double *slots, int n_pt, int n_slots, int slot0, int slot_step, int limbs, double scale,
                          ensi_pt **out) {
+    if (ctx->ks16 && scale <= CLIENT_MAX_SCALE) {
+        ensi_pt *pt;
+        int rc = pt_alloc(ctx, n_pt, limbs, scale, &pt);
+        if (rc) return rc;
+        const int per = std::max(1, (int)(CLIENT_CHUNK / ((size_t)ctx->N * 8)));
+        const size_t f_words = (size_t)std::min(n_pt, per) * ctx->N;
+        hipError_t e = hipSuccess;
+        rc = grow(ctx, &ctx->ws_cl, &ctx->ws_cl_words, f_words + (size_t)std::min(n_pt, per) * n_slots);
+        double *d_slots = (double *)(ctx->ws_cl + f_words);
+        for (int y0 = 0; y0 < n_pt && !rc && e == hipSuccess; y0 += per) {
+            const int cnt = std::min(per, n_pt - y0);
+            e = host_to_device(ctx, d_slots, slots + (size_t)y0 * n_slots, (size_t)cnt * n_slots * 8, nullptr);
+            if (e == hipSuccess)
+                launch_cl_encode(ctx, d_slots, cnt, n_slots, slot0, slot_step, y0, scale, limbs, (double2 *)ctx->ws_cl, pt->d + (size_t)y0 * limbs * ctx->N, nullptr);
+        }
+        if (rc || e != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess || hipGetLastError() != hipSuccess) {
+            ensi_pt_free(pt);
+            if (rc) return rc;
+            ENSI_FAIL(ctx, ENSI_E_HIP, "encode failed: %s", hipGetErrorString(e));
+        }
+        *out = pt;
+        return ENSI_OK;
+    }
     DevBuf d_slots, d_coeffs;
     if (d_slots.alloc((size_t)n_pt * n_slots * 8) != hipSuccess || d_coeffs.alloc((size_t)n_pt * ctx->N * 8) != hipSuccess)
         ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in encode");
@@ -572,7 +663,7 @@ extern "C" int ensi_pt_export(ensi_ctx *ctx, const ensi_pt *pt, int64_t *coeffs)
 }
 extern "C" void ensi_pt_free(ensi_pt *pt) {
     if (!pt) return;
-    if (pt->d) (void)hipFree(pt->d);
+    if (pt->d) pt->pool->give(pt->d, pt->d_bytes);
     if (pt->d_mont) (void)hipFree(pt->d_mont);
     if (pt->d_fp) (void)hipFree(pt->d_fp);
     delete pt;
@@ -588,7 +679,8 @@ extern "C" int ensi_ct_alloc(ensi_ctx *ctx, int32_t n, int32_t limbs, ensi_ct **
     ct->scale = ctx->scale;
     ct->owns = true;
     ct->d = nullptr;
-    hipError_t e = hipMalloc((void **)&ct->d, (size_t)n * 2 * limbs * ctx->N * 8);
+    ct->pool = ctx->pool;
+    hipError_t e = ctx->pool->take((void **)&ct->d, (size_t)n * 2 * limbs * ctx->N * 8, &ct->d_bytes);
     if (e != hipSuccess) {
         delete ct;
         ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation of %zu bytes failed: %s", (size_t)n * 2 * limbs * ctx->N * 8, hipGetErrorString(e));
@@ -610,7 +702,7 @@ extern "C" int ensi_ct_wrap(ensi_ctx *ctx, void *device_words, int32_t n, int32_
 }
 extern "C" void ensi_ct_free(ensi_ct *ct) {
     if (!ct) return;
-    if (ct->owns && ct->d) (void)hipFree(ct->d);
+    if (ct->owns && ct->d) ct->pool->give(ct->d, ct->d_bytes);
     delete ct;
 }
 extern "C" int ensi_ct_info(const ensi_ct *ct, int32_t *n, int32_t *limbs, double *scale, void **device_words) {
@@ -672,19 +764,42 @@ extern "C" int ensi_encrypt(ensi_ctx *ctx, const ensi_pk *pk, const ensi_pt *pt,
     if (!((v && e0 && e1) || (!v && !e0 && !e1))) ENSI_FAIL(ctx, ENSI_E_BADARG, "v, e0, e1 must be all given or all NULL");
     const int N = ctx->N, L = ctx->L, l1 = pt->limbs, n = pt->n;
     const size_t pn = (size_t)n * N;
-    std::vector<int8_t> small(3 * pn);
-    if (v) {
-        memcpy(small.data(), v, pn);
-        memcpy(small.data() + pn, e0, pn);
-        memcpy(small.data() + 2 * pn, e1, pn);
-    } else {
+    std::vector<int8_t> small;
+    if (!v) {
         int rs;
+        small.resize(3 * pn);
         if ((rs = sample_ternary(ctx, small.data(), pn)) || (rs = sample_error(ctx, small.data() + pn, 2 * pn))) return rs;
+        v = small.data();
+        e0 = v + pn;
+        e1 = e0 + pn;
     }
     int rc = ensi_ct_alloc(ctx, n, l1, out);
     if (rc) return rc;
     ensi_ct *ct = *out;
     hipStream_t st = nullptr;
+    if (ctx->ks16) {
+        // three kernels per chunk of ciphertexts (client16.hip)
+        const int per = std::max(1, (int)(CLIENT_CHUNK / ((size_t)N * 8)));
+        const size_t chunk_rows = (size_t)std::min(n, per), ws_words = chunk_rows * l1 * N;
+        rc = grow(ctx, &ctx->ws_cl, &ctx->ws_cl_words, ws_words + (3 * chunk_rows * N + 7) / 8);
+        int8_t *d_small = (int8_t *)(ctx->ws_cl + ws_words);
+        hipError_t e = hipSuccess;
+        for (int c0 = 0; c0 < n && !rc && e == hipSuccess; c0 += per) {
+            const size_t cn = (size_t)std::min(per, n - c0) * N, at = (size_t)c0 * N;
+            e = host_to_device(ctx, d_small, v + at, cn, st);
+            if (e == hipSuccess) e = host_to_device(ctx, d_small + cn, e0 + at, cn, st);
+            if (e == hipSuccess) e = host_to_device(ctx, d_small + 2 * cn, e1 + at, cn, st);
+            if (e == hipSuccess)
+                launch_cl_encrypt(ctx, pk->d_pk, d_small, pt->d + (size_t)c0 * l1 * N, (int)(cn / N), l1, ctx->ws_cl, ct->d + (size_t)c0 * 2 * l1 * N, st);
+        }
+        if (rc || e != hipSuccess || hipStreamSynchronize(st) != hipSuccess || hipGetLastError() != hipSuccess) {
+            ensi_ct_free(ct);
+            *out = nullptr;
+            if (rc) return rc;
+            ENSI_FAIL(ctx, ENSI_E_HIP, "kernel failure in encrypt");
+        }
+        return ENSI_OK;
+    }
     LimbMap mq = make_map(ctx, l1, false);
     DevBuf d_small, d_v, d_t, d_e;
     const size_t rows = (size_t)n * l1;
@@ -694,7 +809,9 @@ extern "C" int ensi_encrypt(ensi_ctx *ctx, const ensi_pk *pk, const ensi_pt *pt,
         *out = nullptr;
         ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in encrypt");
     }
-    (void)hipMemcpy(d_small.p, small.data(), 3 * pn, hipMemcpyHostToDevice);
+    (void)hipMemcpy(d_small.p, v, pn, hipMemcpyHostToDevice);
+    (void)hipMemcpy(d_small.as<int8_t>() + pn, e0, pn, hipMemcpyHostToDevice);
+    (void)hipMemcpy(d_small.as<int8_t>() + 2 * pn, e1, pn, hipMemcpyHostToDevice);
     // v: residues -> transform domain
     launch_small_to_rns(ctx, d_small.as<int8_t>(), n, mq, d_v.as<u64>(), st);
     launch_ntt(ctx, d_v.as<u64>(), (int)rows, mq, false, st);
@@ -726,6 +843,35 @@ extern "C" int ensi_decrypt(ensi_ctx *ctx, const ensi_sk *sk, const ensi_ct *ct,
     const int N = ctx->N, n = ct->n;
     const int use = std::min(ct->limbs, 2);
     hipStream_t st = nullptr;
+    if (ctx->ks16) {
+        // four kernels per chunk of ciphertexts (client16.hip); the slots of a chunk leave through pinned memory
+        const CrtPair crt = crt_pair(ctx, use);
+        const int per = std::max(1, (int)(CLIENT_CHUNK / ((size_t)N * 8)));
+        const size_t rows = (size_t)std::min(n, per), ws_words = rows * use * N, f_words = rows * N, out_bytes = rows * n_slots * 8;
+        int rc = grow(ctx, &ctx->ws_cl, &ctx->ws_cl_words, ws_words + f_words + rows * n_slots);
+        if (rc) return rc;
+        if (ctx->pinned_out_bytes < out_bytes) {
+            if (ctx->pinned_out) (void)hipHostFree(ctx->pinned_out);
+            ctx->pinned_out = nullptr;
+            ctx->pinned_out_bytes = 0;
+            if (hipHostMalloc(&ctx->pinned_out, out_bytes, hipHostMallocDefault) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "pinned buffer allocation failed in decrypt");
+            ctx->pinned_out_bytes = out_bytes;
+        }
+        double2 *f = (double2 *)(ctx->ws_cl + ws_words);
+        double *d_out = (double *)(ctx->ws_cl + ws_words + f_words);
+        ENSI_HIP(ctx, hipDeviceSynchronize());
+        for (int c0 = 0; c0 < n; c0 += per) {
+            const int cnt = std::min(per, n - c0);
+            const size_t bytes = (size_t)cnt * n_slots * 8;
+            launch_cl_decrypt(ctx, sk->d_s_hat, ct->d + (size_t)c0 * 2 * ct->limbs_alloc * N, cnt, ct->limbs_alloc, use, crt, slot_begin, n_slots, 1.0 / ct->scale,
+                              ctx->ws_cl, f, d_out, st);
+            ENSI_HIP(ctx, hipMemcpyAsync(ctx->pinned_out, d_out, bytes, hipMemcpyDeviceToHost, st));
+            ENSI_HIP(ctx, hipStreamSynchronize(st));
+            ENSI_HIP(ctx, hipGetLastError());
+            memcpy(slots_out + (size_t)c0 * n_slots, ctx->pinned_out, bytes);
+        }
+        return ENSI_OK;
+    }
     LimbMap mq = make_map(ctx, use, false);
     DevBuf d_m, d_coef, d_out;
     if (d_m.alloc((size_t)n * use * N * 8) != hipSuccess || d_coef.alloc((size_t)n * N * 8) != hipSuccess ||

@@ -1,0 +1,319 @@
+// The client's side on the rings N = 2^12 .. 2^16 with ciphertext primes below 2^50: encode, encrypt, decrypt and decode on
+// the passes of the register transform (ntt16_core.h), so that a batch is a handful of launches.
+//
+// Encoding (paper, Preliminaries: SIMD Encoding).  Slot j is the value of m(X) at exp(i pi 5^j / N), and the exponents
+// 5^j mod 2N, j < n = N/2, are exactly those congruent to 1 modulo 4.  With 5^j = 4k + 1, w = exp(i pi / N) and
+// u_t = (m_t + i m_(t+n)) w^t,
+//   slot(k) = sum_(t<n) u_t exp(2 pi i t k / n)                                           (decode)
+//   m_t + i m_(t+n) = w^-t (scale / n) sum_k slot(k) exp(-2 pi i t k / n), rounded          (encode)
+// a complex transform of n points -- a quarter of the 2N-point one that the defining sums are a special case of.  It is
+// cut as t = 256 r + c, k = k1 + R2 k2 (R2 = N / 512 rows): a transform over 256 elements of a row and one over the R2
+// rows of a column, with the twiddle exp(+-2 pi i c k1 / n) between them, each on 2048 values in LDS.
+//
+// These kernels are small against the copies from and to host memory beside them; what counts is their number.
+#include "common.h"
+#include "ntt16_core.h"
+
+#define CL_THREADS 256
+
+// ------------------------------------------------------------------ complex transforms in LDS
+__device__ __forceinline__ double2 cmul(double2 a, double2 b) { return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
+// exp(+-i pi e / N), 0 <= e < 2N, from the table of cosines
+template <int N, bool INV>
+__device__ __forceinline__ double2 unit(const double *cos_tab, u32 e) {
+    const double s = cos_tab[(e - N / 2) & (2 * N - 1)];
+    return make_double2(cos_tab[e & (2 * N - 1)], INV ? -s : s);
+}
+// LEN-point transforms of 2048 / LEN sequences at once (element t of sequence b at x[t * B + b], B = 2048 / LEN): radix-2
+// self-sorting passes between two buffers.  Returns the buffer that holds the result; every thread may read it.
+template <int N, int LEN, bool INV>
+__device__ __forceinline__ double2 *lds_dft(double2 *x, double2 *y, const double *cos_tab, int tid) {
+    constexpr int B = 2048 / LEN;
+    __syncthreads();
+#pragma unroll 1
+    for (int s = 1; s < LEN; s *= 2) {
+#pragma unroll
+        for (int m = 0; m < 4; m++) {
+            const int w = tid + CL_THREADS * m, b = w % B, t = w / B;
+            const int q = t & (s - 1), idx = t - q;
+            const double2 p0 = x[t * B + b], p1 = x[(t + LEN / 2) * B + b];
+            const double2 tw = unit<N, INV>(cos_tab, (u32)idx * (2 * N / LEN));
+            y[(q + 2 * idx) * B + b] = make_double2(p0.x + p1.x, p0.y + p1.y);
+            y[(q + 2 * idx + s) * B + b] = cmul(make_double2(p0.x - p1.x, p0.y - p1.y), tw);
+        }
+        __syncthreads();
+        double2 *h = x;
+        x = y;
+        y = h;
+    }
+    return x;
+}
+
+// ------------------------------------------------------------------ encode
+// grid (R2 / 8, n_pt): eight rows k1.  ws: [n_pt][R2][256]
+template <int S>
+__global__ __launch_bounds__(CL_THREADS) void k_cl_enc_rows(const double *slots, int n_slots, int slot0, int slot_step, int y0, const u32 *slot_of_k,
+                                                            const double *cos_tab, double2 *ws) {
+    constexpr int N = Ring<S>::N, R2 = N / 512;
+    __shared__ double2 buf[2][2048];
+    const int tid = threadIdx.x, y = y0 + blockIdx.y, first = slot0 + y * slot_step;
+    const double *z = slots + (size_t)blockIdx.y * n_slots;
+#pragma unroll
+    for (int m = 0; m < 8; m++) {
+        const int w = tid + CL_THREADS * m, row = w & 7, k2 = w >> 3;
+        const int j = (int)slot_of_k[blockIdx.x * 8 + row + R2 * k2] - first;
+        buf[0][w] = make_double2(j >= 0 && j < n_slots ? z[j] : 0.0, 0.0);
+    }
+    const double2 *f = lds_dft<N, 256, true>(buf[0], buf[1], cos_tab, tid);
+#pragma unroll
+    for (int row = 0; row < 8; row++) {
+        const int k1 = blockIdx.x * 8 + row;
+        ws[((size_t)blockIdx.y * R2 + k1) * 256 + tid] = cmul(f[tid * 8 + row], unit<N, true>(cos_tab, (u32)tid * k1 * 4));
+    }
+}
+// grid (TILES, n_pt): one tile of columns.  out: [n_pt][limbs][N] canonical residues
+template <int S>
+__global__ __launch_bounds__(CL_THREADS) void k_cl_enc_cols(const double2 *ws, double factor, int limbs, const PrimeConst *pcs, const double *cos_tab,
+                                                            u64 *out) {
+    typedef Ring<S> R;
+    constexpr int N = R::N, R2 = N / 512;
+    __shared__ double2 buf[2][2048];
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int m = 0; m < 8; m++) {
+        const int w = tid + CL_THREADS * m, c = w % R::COLS, k1 = w / R::COLS;
+        buf[0][w] = ws[((size_t)blockIdx.y * R2 + k1) * 256 + blockIdx.x * R::COLS + c];
+    }
+    const double2 *f = lds_dft<N, R2, true>(buf[0], buf[1], cos_tab, tid);
+    double v[16];
+#pragma unroll
+    for (int m = 0; m < 8; m++) {
+        const int w = tid + CL_THREADS * m, t = w / R::COLS * 256 + blockIdx.x * R::COLS + w % R::COLS;
+        const double2 x = cmul(f[w], unit<N, true>(cos_tab, t));
+        v[2 * m] = x.x * factor;
+        v[2 * m + 1] = x.y * factor;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; i++) {  // round half away from zero
+        const double r = floor(fabs(v[i]) + 0.5);
+        v[i] = v[i] < 0 ? -r : r;
+    }
+    for (int l = 0; l < limbs; l++) {
+        ArithFp ar;
+        ar.init(load_prime(pcs, l));
+        u64 *o = out + ((size_t)blockIdx.y * limbs + l) * N;
+#pragma unroll
+        for (int m = 0; m < 8; m++) {
+            const int w = tid + CL_THREADS * m, t = w / R::COLS * 256 + blockIdx.x * R::COLS + w % R::COLS;
+            o[t] = ar.canon(v[2 * m]);
+            o[t + N / 2] = ar.canon(v[2 * m + 1]);
+        }
+    }
+}
+
+// ------------------------------------------------------------------ encrypt
+// Forward column pass of n polynomials of small integers at every limb.  grid (TILES, limbs, n); ws: [n][limbs][N] doubles
+template <int S>
+__global__ __launch_bounds__(CL_THREADS) void k_cl_fcols_small(const int8_t *small, const PrimeConst *pcs, const u64 *tw_all, u64 *ws) {
+    typedef Ring<S> R;
+    constexpr size_t N = R::N;
+    __shared__ u64 lds[4096];
+    const int c = R::col(threadIdx.x), jj = R::grp(threadIdx.x), limb = blockIdx.y;
+    ArithFp ar;
+    ar.init(load_prime(pcs, limb));
+    const u64 *tw = tw_all + (size_t)limb * 4 * N;
+    const int8_t *in = small + (size_t)blockIdx.z * N + blockIdx.x * R::COLS + c;
+    double v[16];
+#pragma unroll
+    for (int i = 0; i < 16; i++) v[i] = (double)in[R::row(jj, i) * 256];
+    cols_fwd_regs<S>(ar, v, tw, tw + N, lds, c, jj);
+    u64 *o = ws + ((size_t)blockIdx.z * gridDim.y + limb) * N + (size_t)blockIdx.x * R::COLS + c;
+#pragma unroll
+    for (int i = 0; i < 16; i++) o[(size_t)(16 * jj + i) * 256] = ar.store_ws_cols(v[i]);
+}
+// Forward row pass, product with POLYS key polynomials (key: limb `limb` of polynomial p at (p * key_limbs + limb) * N, in
+// position order, Montgomery residues) and inverse row pass of each product.  A wave runs four rows.
+// grid (4 TILES, limbs, n); in: [n][limbs][N], out: [n][POLYS][limbs][N] doubles (may be the same array if POLYS is 1)
+template <int S, int POLYS>
+__global__ __launch_bounds__(64, 2) void k_cl_rows_key(const u64 *in, const u64 *key, int key_limbs, const PrimeConst *pcs, const u64 *tw_all, u64 *out) {
+    typedef Ring<S> R;
+    constexpr size_t N = R::N;
+    __shared__ u64 lds[ROW_LDS];
+    __shared__ ulonglong2 tw1[2][4 * 16];
+    const int lane = threadIdx.x, rho = lane >> 4, j = lane & 15, limb = blockIdx.y, limbs = gridDim.y;
+    const u32 r = blockIdx.x * 4 + rho;
+    const PrimeConst pc = load_prime(pcs, limb);
+    ArithFp ar;
+    ar.init(pc);
+    const u64 *twf = tw_all + (size_t)limb * 4 * N, *twi = twf + 2 * N;
+    row_table_to_lds(tw1[0], twf, twf + N, R::ROWS + r, rho, j);
+    row_table_to_lds(tw1[1], twi, twi + N, R::ROWS + r, rho, j);
+    TwRegs tw2;
+    tw2.load(twf, twf + N, (R::ROWS + r) * 16u + j);
+    double v[16];
+    const u64 *src = in + ((size_t)blockIdx.z * limbs + limb) * N + (size_t)r * 256 + j;
+#pragma unroll
+    for (int i = 0; i < 16; i++) v[i] = __longlong_as_double((long long)src[16 * i]);
+    wave_lds_fence();
+    row_fwd(ar, v, tw1[0] + rho * 16, tw2, lds, rho, j);
+#pragma unroll
+    for (int i = 0; i < 16; i++) v[i] = ar.mid(v[i]);
+    tw2.load(twi, twi + N, (R::ROWS + r) * 16u + j);
+#pragma unroll
+    for (int p = 0; p < POLYS; p++) {
+        const u64 *k = key + ((size_t)p * key_limbs + limb) * N + (size_t)r * 256 + 16 * j;
+        double x[16];
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            acc128 m = {k[i], 0};
+            x[i] = ar.mid(ar.mulmod_np(v[i], (double)mont_reduce(m, pc.q, pc.qneg_inv)));
+        }
+        row_inv(ar, x, tw1[1] + rho * 16, tw2, lds, rho, j);
+        u64 *o = out + (((size_t)blockIdx.z * POLYS + p) * limbs + limb) * N + (size_t)r * 256 + j;
+#pragma unroll
+        for (int i = 0; i < 16; i++) o[16 * i] = ar.store_ws_inv(x[i]);
+    }
+}
+// Inverse column pass in place, plus the error polynomial and, on the first polynomial, the message: the ciphertext.
+// grid (TILES, 2 * limbs, n); errors: e0 of all ciphertexts, then (err_stride further) e1
+template <int S>
+__global__ __launch_bounds__(CL_THREADS) void k_cl_icols_add(u64 *ct, const int8_t *errors, size_t err_stride, const u64 *pt, int limbs,
+                                                             const PrimeConst *pcs, const u64 *tw_all) {
+    typedef Ring<S> R;
+    constexpr size_t N = R::N;
+    __shared__ u64 lds[4096];
+    const int c = R::col(threadIdx.x), jj = R::grp(threadIdx.x), poly = blockIdx.y / limbs, limb = blockIdx.y - poly * limbs;
+    const size_t col = (size_t)blockIdx.x * R::COLS + c;
+    ArithFp ar;
+    ar.init(load_prime(pcs, limb));
+    const u64 *tw = tw_all + (size_t)limb * 4 * N + 2 * N;
+    u64 *g = ct + ((size_t)blockIdx.z * 2 * limbs + blockIdx.y) * N + col;
+    const int8_t *e = errors + poly * err_stride + blockIdx.z * N + col;
+    const u64 *m = pt + ((size_t)blockIdx.z * limbs + limb) * N + col;
+    double v[16], a[16];
+#pragma unroll
+    for (int i = 0; i < 16; i++) v[i] = __longlong_as_double((long long)g[(size_t)(16 * jj + i) * 256]);
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const size_t at = (size_t)R::row(jj, i) * 256;
+        a[i] = (double)e[at];
+        if (poly == 0) a[i] += (double)m[at];
+    }
+    cols_inv_regs<S>(ar, v, tw, tw + N, lds, c, jj);
+#pragma unroll
+    for (int i = 0; i < 16; i++) g[(size_t)R::row(jj, i) * 256] = ar.canon(ar.mulmod(ar.mid(v[i]), ar.ninv, ar.ninv_p) + a[i]);
+}
+
+// ------------------------------------------------------------------ decrypt
+// Forward column pass of c1.  grid (TILES, use, n); ws: [n][use][N]
+template <int S>
+__global__ __launch_bounds__(CL_THREADS) void k_cl_fcols_c1(const u64 *ct, int limbs_alloc, const PrimeConst *pcs, const u64 *tw_all, u64 *ws) {
+    typedef Ring<S> R;
+    constexpr size_t N = R::N;
+    __shared__ u64 lds[4096];
+    const int c = R::col(threadIdx.x), jj = R::grp(threadIdx.x), limb = blockIdx.y;
+    const size_t col = (size_t)blockIdx.x * R::COLS + c;
+    ArithFp ar;
+    ar.init(load_prime(pcs, limb));
+    const u64 *tw = tw_all + (size_t)limb * 4 * N, *in = ct + (((size_t)blockIdx.z * 2 + 1) * limbs_alloc + limb) * N + col;
+    double v[16];
+#pragma unroll
+    for (int i = 0; i < 16; i++) v[i] = (double)in[(size_t)R::row(jj, i) * 256];
+    cols_fwd_regs<S>(ar, v, tw, tw + N, lds, c, jj);
+    u64 *o = ws + ((size_t)blockIdx.z * gridDim.y + limb) * N + col;
+#pragma unroll
+    for (int i = 0; i < 16; i++) o[(size_t)(16 * jj + i) * 256] = ar.store_ws_cols(v[i]);
+}
+// Inverse column pass of c1 s on both limbs, + c0, the centred coefficient, and the column part of the decoding transform.
+// grid (TILES, n); f: [n][R2][256]
+template <int S>
+__global__ __launch_bounds__(CL_THREADS) void k_cl_dec_cols(const u64 *ws, int use, const u64 *ct, int limbs_alloc, CrtPair crt, const PrimeConst *pcs,
+                                                            const u64 *tw_all, const double *cos_tab, double2 *f) {
+    typedef Ring<S> R;
+    constexpr int NI = R::N, R2 = NI / 512;
+    constexpr size_t N = R::N;
+    __shared__ double2 buf[2][2048];  // the column passes use it as a tile of words
+    const int tid = threadIdx.x, c = R::col(tid), jj = R::grp(tid);
+    const size_t col = (size_t)blockIdx.x * R::COLS + c;
+    u64 r[2][16];
+#pragma unroll
+    for (int limb = 0; limb < 2; limb++) {
+        if (limb < use) {
+            ArithFp ar;
+            ar.init(load_prime(pcs, limb));
+            const u64 *tw = tw_all + (size_t)limb * 4 * N + 2 * N;
+            const u64 *in = ws + ((size_t)blockIdx.y * use + limb) * N + col, *c0 = ct + ((size_t)blockIdx.y * 2 * limbs_alloc + limb) * N + col;
+            double v[16];
+#pragma unroll
+            for (int i = 0; i < 16; i++) v[i] = __longlong_as_double((long long)in[(size_t)(16 * jj + i) * 256]);
+            cols_inv_regs<S>(ar, v, tw, tw + N, buf[limb], c, jj);
+#pragma unroll
+            for (int i = 0; i < 16; i++) r[limb][i] = ar.canon(ar.mulmod(ar.mid(v[i]), ar.ninv, ar.ninv_p) + (double)c0[(size_t)R::row(jj, i) * 256]);
+        }
+    }
+    double m[16];
+#pragma unroll
+    for (int i = 0; i < 16; i++) m[i] = use > 1 ? crt_centred(r[0][i], r[1][i], crt) : r[0][i] > crt.q0 / 2 ? -(double)(crt.q0 - r[0][i]) : (double)r[0][i];
+    __syncthreads();  // the tiles have been read
+    // values i and i + 8 are the coefficients t and t + N/2
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+        const int row = R::row(jj, i);
+        buf[0][row * R::COLS + c] = cmul(make_double2(m[i], m[i + 8]), unit<NI, false>(cos_tab, row * 256 + (u32)col));
+    }
+    const double2 *x = lds_dft<NI, R2, false>(buf[0], buf[1], cos_tab, tid);
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        const int w = tid + CL_THREADS * k, cc = blockIdx.x * R::COLS + w % R::COLS, k1 = w / R::COLS;
+        f[((size_t)blockIdx.y * R2 + k1) * 256 + cc] = cmul(x[w], unit<NI, false>(cos_tab, (u32)cc * k1 * 4));
+    }
+}
+// grid (R2 / 8, n): eight rows k1; out: [n][n_slots], slots slot_begin .. slot_begin + n_slots - 1
+template <int S>
+__global__ __launch_bounds__(CL_THREADS) void k_cl_dec_rows(const double2 *f, const u32 *slot_of_k, int slot_begin, int n_slots, double inv_scale,
+                                                            const double *cos_tab, double *out) {
+    constexpr int N = Ring<S>::N, R2 = N / 512;
+    __shared__ double2 buf[2][2048];
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int row = 0; row < 8; row++) buf[0][tid * 8 + row] = f[((size_t)blockIdx.y * R2 + blockIdx.x * 8 + row) * 256 + tid];
+    const double2 *x = lds_dft<N, 256, false>(buf[0], buf[1], cos_tab, tid);
+#pragma unroll
+    for (int m = 0; m < 8; m++) {
+        const int w = tid + CL_THREADS * m, row = w & 7, k2 = w >> 3;
+        const int j = (int)slot_of_k[blockIdx.x * 8 + row + R2 * k2] - slot_begin;
+        if (j >= 0 && j < n_slots) out[(size_t)blockIdx.y * n_slots + j] = x[w].x * inv_scale;
+    }
+}
+
+// ------------------------------------------------------------------ launchers
+void launch_cl_encode(ensi_ctx *ctx, const double *d_slots, int n_pt, int n_slots, int slot0, int slot_step, int y0, double scale, int limbs, double2 *ws,
+                      u64 *out, hipStream_t st) {
+    ring_dispatch(ctx->log_n, [&](auto s) {
+        constexpr int S = decltype(s)::value;
+        hipLaunchKernelGGL((k_cl_enc_rows<S>), dim3(ctx->N / 4096, n_pt), dim3(CL_THREADS), 0, st, d_slots, n_slots, slot0, slot_step, y0, ctx->d_slot_of_k,
+                           ctx->d_cos, ws);
+        hipLaunchKernelGGL((k_cl_enc_cols<S>), dim3(Ring<S>::TILES, n_pt), dim3(CL_THREADS), 0, st, ws, 2.0 * scale / ctx->N, limbs, ctx->d_pc, ctx->d_cos, out);
+    });
+}
+
+void launch_cl_encrypt(ensi_ctx *ctx, const u64 *d_pk, const int8_t *d_small, const u64 *pt, int n, int limbs, u64 *ws, u64 *ct, hipStream_t st) {
+    const size_t pn = (size_t)n * ctx->N;
+    ring_dispatch(ctx->log_n, [&](auto s) {
+        constexpr int S = decltype(s)::value, TILES = Ring<S>::TILES;
+        hipLaunchKernelGGL((k_cl_fcols_small<S>), dim3(TILES, limbs, n), dim3(CL_THREADS), 0, st, d_small, ctx->d_pc, ctx->d_tw, ws);
+        hipLaunchKernelGGL((k_cl_rows_key<S, 2>), dim3(4 * TILES, limbs, n), dim3(64), 0, st, ws, d_pk, ctx->L, ctx->d_pc, ctx->d_tw, ct);
+        hipLaunchKernelGGL((k_cl_icols_add<S>), dim3(TILES, 2 * limbs, n), dim3(CL_THREADS), 0, st, ct, d_small + pn, pn, pt, limbs, ctx->d_pc, ctx->d_tw);
+    });
+}
+
+void launch_cl_decrypt(ensi_ctx *ctx, const u64 *d_s_hat, const u64 *ct, int n, int limbs_alloc, int use, const CrtPair &crt, int slot_begin, int n_slots,
+                       double inv_scale, u64 *ws, double2 *f, double *out, hipStream_t st) {
+    ring_dispatch(ctx->log_n, [&](auto s) {
+        constexpr int S = decltype(s)::value, TILES = Ring<S>::TILES;
+        hipLaunchKernelGGL((k_cl_fcols_c1<S>), dim3(TILES, use, n), dim3(CL_THREADS), 0, st, ct, limbs_alloc, ctx->d_pc, ctx->d_tw, ws);
+        hipLaunchKernelGGL((k_cl_rows_key<S, 1>), dim3(4 * TILES, use, n), dim3(64), 0, st, ws, d_s_hat, ctx->L + ctx->K, ctx->d_pc, ctx->d_tw, ws);
+        hipLaunchKernelGGL((k_cl_dec_cols<S>), dim3(TILES, n), dim3(CL_THREADS), 0, st, ws, use, ct, limbs_alloc, crt, ctx->d_pc, ctx->d_tw, ctx->d_cos, f);
+        hipLaunchKernelGGL((k_cl_dec_rows<S>), dim3(ctx->N / 4096, n), dim3(CL_THREADS), 0, st, f, ctx->d_slot_of_k, slot_begin, n_slots, inv_scale, ctx->d_cos, out);
+    });
+}

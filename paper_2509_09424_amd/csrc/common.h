@@ -5,6 +5,8 @@
 #include <stdio.h>
 
 #include <map>
+#include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -178,6 +180,47 @@ struct StageSlot {
 };
 #define ENSI_STAGE_SLOTS 8
 
+// Device memory of freed plaintext and ciphertext handles, kept for the next handle of about the same size: freeing a large
+// block costs a quarter of a millisecond.  Bounded (KEEP_EACH, KEEP_ALL); emptied when the context is freed, or when an
+// allocation fails.  Shared by the context and its handles, which may outlive it, and safe with several threads.  The
+// release of a block waits for nothing; taking one waits for the device, as hipFree did when the block was freed.
+struct DevPool {
+    static constexpr size_t KEEP_EACH = (size_t)256 << 20, KEEP_ALL = (size_t)1 << 30;
+    std::mutex mu;
+    std::multimap<size_t, void *> blocks;  // by size
+    size_t held = 0;
+    bool closed = false;
+    hipError_t take(void **p, size_t bytes, size_t *got);
+    void give(void *p, size_t bytes);
+    void close();
+    ~DevPool() { close(); }
+};
+
+// Constants of the combination of limbs 0 and 1 into one centred coefficient (crt_centred).
+struct CrtPair {
+    u64 q0, q1, q0_inv_mont, q1_neg_inv, big_hi, big_lo;
+};
+CrtPair crt_pair(const ensi_ctx *ctx, int n_limbs_used);
+// The representative of (r0 mod q0, r1 mod q1) nearest to zero, as a double.
+ENSI_HD double crt_centred(u64 r0, u64 r1, const CrtPair &c) {
+    const u64 d = sub_mod(r1, r0 % c.q1, c.q1);
+    const u64 t = mont_mul(d, c.q0_inv_mont, c.q1, c.q1_neg_inv);  // (r1-r0) * q0^{-1} mod q1
+    // val = r0 + q0*t  (< q0*q1 < 2^124)
+    u64 lo = c.q0 * t, hi = mulhi64(c.q0, t);
+    lo += r0;
+    hi += lo < r0 ? 1 : 0;
+    // half = floor(big/2); negative branch when val > half
+    const u64 half_hi = c.big_hi >> 1, half_lo = (c.big_lo >> 1) | (c.big_hi << 63);
+    const bool neg = hi > half_hi || (hi == half_hi && lo > half_lo);
+    if (neg) {  // val = big - val
+        const u64 nlo = c.big_lo - lo;
+        hi = c.big_hi - hi - (c.big_lo < lo ? 1 : 0);
+        lo = nlo;
+    }
+    const double v = (double)hi * 18446744073709551616.0 + (double)lo;
+    return neg ? -v : v;
+}
+
 struct ensi_ctx {
     ensi_params prm;
     int log_n, N, L, K, alpha;
@@ -191,6 +234,10 @@ struct ensi_ctx {
     u64 *d_tw = nullptr;            // [L+K][4][N]: fwd, fwd Shoup, inv, inv Shoup
     double *d_cos = nullptr;        // [2N] cos(pi e / N)
     u32 *d_rot_exp = nullptr;       // [N/2] 5^j mod 2N
+    u32 *d_slot_of_k = nullptr;     // [N/2] the j with 5^j = 4k + 1 mod 2N
+    std::shared_ptr<DevPool> pool = std::make_shared<DevPool>();
+    u64 *ws_cl = nullptr; size_t ws_cl_words = 0;       // client side: one chunk's intermediates
+    void *pinned_out = nullptr; size_t pinned_out_bytes = 0;  // decoded slots on their way to the caller
     std::vector<u32> rot_exp;
     std::map<int, ModUpConst> modup;      // by l1
     std::map<int, ModDownConst> moddown;  // by l1
@@ -257,6 +304,8 @@ struct ensi_pt {
     int n, limbs;
     double scale;
     u64 *d;  // [n][limbs][N] coefficient form
+    size_t d_bytes = 0;
+    std::shared_ptr<DevPool> pool;
     // multiplier forms, built on first use by a plaintext multiplication
     mutable u64 *d_mont = nullptr;  // transform domain, Montgomery form
     mutable u64 *d_fp = nullptr;    // transform domain, doubles in [0,q), register order of the row pass (N >= 2^12)
@@ -266,6 +315,8 @@ struct ensi_ct {
     int n, limbs, limbs_alloc;
     double scale;
     u64 *d;
+    size_t d_bytes = 0;
+    std::shared_ptr<DevPool> pool;  // of the context, where the handle owns its memory
     bool owns;
     bool prepared = false;  // holds transform-domain data that only ensi_ccmm_av reads (ensi_diagonalise_weights)
 };
@@ -347,6 +398,15 @@ int launch_matrix_rate(ensi_ctx *ctx, double seconds, double *ops_per_second, hi
 void launch_pm_generic(ensi_ctx *ctx, const PmGroup &g, const u64 *d_consts, const double *d_fconsts, hipStream_t st);
 void launch_pm16(ensi_ctx *ctx, const PmGroup &g, const PmRescale &rs, hipStream_t st);
 void launch_pm16_pt_format(ensi_ctx *ctx, const u64 *ntt_form, int n_rows, u64 *out, hipStream_t st);
+
+// the client's side on the register transform (client16.hip): N >= 2^12, ciphertext primes below 2^50
+void launch_cl_encode(ensi_ctx *ctx, const double *d_slots, int n_pt, int n_slots, int slot0, int slot_step, int y0, double scale, int limbs, double2 *ws,
+                      u64 *out, hipStream_t st);  // ws: n_pt * N / 2 values
+// d_small: int8 [3][n][N] (mask, two error polynomials); pt: [n][limbs][N]; ws: n * limbs * N words
+void launch_cl_encrypt(ensi_ctx *ctx, const u64 *d_pk, const int8_t *d_small, const u64 *pt, int n, int limbs, u64 *ws, u64 *ct, hipStream_t st);
+// ws: n * use * N words; f: n * N / 2 values
+void launch_cl_decrypt(ensi_ctx *ctx, const u64 *d_s_hat, const u64 *ct, int n, int limbs_alloc, int use, const CrtPair &crt, int slot_begin, int n_slots,
+                       double inv_scale, u64 *ws, double2 *f, double *out, hipStream_t st);
 
 // ciphertext-ciphertext products (ccmm.hip)
 void launch_mm_tensor(ensi_ctx *ctx, const MmGroup &g, hipStream_t st);

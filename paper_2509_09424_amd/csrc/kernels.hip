@@ -596,52 +596,28 @@ hipError_t launch_encode(ensi_ctx *ctx, const double *d_slots, int n_pt, int n_s
 }
 
 // Garner CRT of limbs 0 and 1 (rows 0,1 of each [n_used][N] block), centred, as double.
-// big = q0*q1 is passed as (big_hi, big_lo).
-__global__ __launch_bounds__(EW_THREADS) void k_crt_center(const u64 *m, int n_used, int N, u64 q0, u64 q1, u64 q0_inv_mont,
-                                                           u64 q1_neg_inv, u64 big_hi, u64 big_lo, double *out) {
+__global__ __launch_bounds__(EW_THREADS) void k_crt_center(const u64 *m, int n_used, int N, CrtPair crt, double *out) {
     const int idx = blockIdx.x * EW_THREADS + threadIdx.x;
     if (idx >= N) return;
     const u64 *mm = m + (size_t)blockIdx.y * n_used * N;
     const u64 r0 = mm[idx];
-    double v;
-    if (n_used == 1) {
-        v = r0 > q0 / 2 ? -(double)(q0 - r0) : (double)r0;
-    } else {
-        const u64 r1 = mm[(size_t)N + idx];
-        const u64 d = sub_mod(r1, r0 % q1, q1);
-        const u64 t = mont_mul(d, q0_inv_mont, q1, q1_neg_inv);  // (r1-r0) * q0^{-1} mod q1
-        // val = r0 + q0*t  (< q0*q1 < 2^124)
-        u64 lo = q0 * t, hi = mulhi64(q0, t);
-        lo += r0;
-        hi += lo < r0 ? 1 : 0;
-        // half = floor(big/2); negative branch when val > half
-        const u64 half_hi = big_hi >> 1, half_lo = (big_lo >> 1) | (big_hi << 63);
-        const bool neg = hi > half_hi || (hi == half_hi && lo > half_lo);
-        if (neg) {  // val = big - val
-            const u64 nlo = big_lo - lo;
-            hi = big_hi - hi - (big_lo < lo ? 1 : 0);
-            lo = nlo;
-        }
-        v = (double)hi * 18446744073709551616.0 + (double)lo;
-        if (neg) v = -v;
+    out[(size_t)blockIdx.y * N + idx] = n_used > 1 ? crt_centred(r0, mm[(size_t)N + idx], crt) : r0 > crt.q0 / 2 ? -(double)(crt.q0 - r0) : (double)r0;
+}
+CrtPair crt_pair(const ensi_ctx *ctx, int n_limbs_used) {
+    CrtPair c = {ctx->primes[0], 0, 0, 0, 0, 0};
+    if (n_limbs_used >= 2) {
+        c.q1 = ctx->primes[1];
+        c.q0_inv_mont = (u64)((((u128)hm_invmod(c.q0 % c.q1, c.q1)) << 64) % c.q1);
+        c.q1_neg_inv = hm_neg_inv64(c.q1);
+        const u128 big = (u128)c.q0 * c.q1;
+        c.big_hi = (u64)(big >> 64);
+        c.big_lo = (u64)big;
     }
-    out[(size_t)blockIdx.y * N + idx] = v;
+    return c;
 }
 void launch_crt_center(ensi_ctx *ctx, const u64 *m, int n_ct, int n_limbs_used, double *out, hipStream_t st) {
-    const u64 q0 = ctx->primes[0];
-    u64 q1 = 0, q0_inv_mont = 0, q1_neg_inv = 0, big_hi = 0, big_lo = 0;
-    if (n_limbs_used >= 2) {
-        q1 = ctx->primes[1];
-        u64 q0_inv = hm_invmod(q0 % q1, q1);
-        q0_inv_mont = (u64)((((u128)q0_inv) << 64) % q1);
-        q1_neg_inv = hm_neg_inv64(q1);
-        u128 big = (u128)q0 * q1;
-        big_hi = (u64)(big >> 64);
-        big_lo = (u64)big;
-    }
     dim3 grid((ctx->N + EW_THREADS - 1) / EW_THREADS, n_ct);
-    hipLaunchKernelGGL(k_crt_center, grid, dim3(EW_THREADS), 0, st, m, n_limbs_used, ctx->N, q0, q1, q0_inv_mont, q1_neg_inv,
-                       big_hi, big_lo, out);
+    hipLaunchKernelGGL(k_crt_center, grid, dim3(EW_THREADS), 0, st, m, n_limbs_used, ctx->N, crt_pair(ctx, n_limbs_used), out);
 }
 
 __global__ __launch_bounds__(EW_THREADS) void k_center_i64(const u64 *m, size_t stride, int N, u64 q0, int64_t *out) {

@@ -493,6 +493,10 @@ def test_register_transform_rings_bit_exact(params):
     for limbs in (p.pr.L, 2):
         o_cts, g_ct = p.encrypt_both(z, limbs)
         assert np.array_equal(g_ct.export(), stack_cts(o_cts))
+        dec = p.ctx.decrypt(p.g_sk, g_ct)
+        assert np.abs(dec - z).max() < 1e-3
+        part = p.ctx.decrypt(p.g_sk, g_ct, p.n // 3, 11)  # a window of slots; the values are exact sums in double precision
+        assert np.abs(part - dec[:, p.n // 3:p.n // 3 + 11]).max() <= 1e-13 * np.abs(dec).max()
         for n in (1, 3):
             one = p.ctx.ct_import(stack_cts(o_cts[:n]), g_ct.scale)
             out = p.ctx.rotate(g_gk, one, [-1, s, s][:n])
@@ -501,6 +505,15 @@ def test_register_transform_rings_bit_exact(params):
             out.free()
             one.free()
         g_ct.free()
+    # encode: slots that do not fill the ring
+    pt = p.ctx.encode(z[:, :p.n - 3], p.pr.L)
+    want = np.stack([p.o.encode_coeffs(np.concatenate([v[:p.n - 3], np.zeros(3)])) for v in z])
+    got = p.ctx.pt_export(pt)
+    assert np.abs(got - want).max() <= 1 and (got != want).mean() < 0.01
+    pt.free()
+    one = p.ctx.encrypt(p.g_pk, p.ctx.pt_import(want, 1))  # a single limb: decrypted without the combination of two
+    assert np.abs(p.ctx.decrypt(p.g_sk, one)[:, :p.n - 3] - z[:, :p.n - 3]).max() < 1e-3
+    one.free()
     rng = np.random.default_rng(3)
     d, m = 6, 5
     W = wl.ternary_weights(rng, d, m)
