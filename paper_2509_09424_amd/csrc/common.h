@@ -82,6 +82,13 @@ struct PmTerm {
     int32_t slot;  // set by the library: which of its group's distinct sources this is (a source that enters several
                    // products is transformed once)
 };
+// Where sources enter several products each, the fused path also takes the products source by source for PM_MAC_OUT
+// neighbouring outputs at a time: the plaintext of each, -1 for none.
+#define PM_MAC_OUT 4
+struct PmEntry {
+    int32_t slot;
+    int32_t pt[PM_MAC_OUT];
+};
 // q_l^{-1} mod q_i and that divided by q_i, for the rescale that ends the fused plaintext multiplication
 struct PmRescale {
     double w[ENSI_MAX_EXT], wp[ENSI_MAX_EXT];
@@ -94,6 +101,8 @@ struct PmGroup {
     int t_base, n_terms, n_out;
     const int32_t *owner;   // this group's distinct sources: owner[slot] = a term (index into the table) that names it
     int n_src;
+    const PmEntry *entries = nullptr;     // this group's lists by group of outputs (null: products term by term)
+    const int32_t *entry_begin = nullptr;
     int l1, limb_stride_in;
     const u64 *pt;          // d_mont or d_fp of the plaintext batch
     int pt_limbs;

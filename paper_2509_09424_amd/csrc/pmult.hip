@@ -13,10 +13,11 @@
 //            layout and number format (exact integers in doubles) of the transform passes around it:
 //              k_pm16_fcols            forward column pass of every source limb, read straight from the
 //                                      source ciphertexts
-//              k_pm16_frows_mac_irows  per output limb and 16-row tile: forward row pass of each term in
+//              k_pm16_rows_mac         per output limb and four rows: forward row pass of each term in
 //                                      registers, multiply by the plaintext (stored in the register order
 //                                      of that pass, so its loads are contiguous), accumulate, and run the
 //                                      inverse row pass on the sum -- the products never reach memory
+//              (k_pm16_rows, k_pm16_mac  the same in three kernels, where sources enter several products each)
 //              k_pm16_icols_last       inverse column pass of the limb the rescale drops, left as the
 //                                      centred residue [c_l]
 //              k_pm16_icols_rescale    inverse column pass of every other limb fused with
@@ -26,9 +27,6 @@
 #include "ntt16_core.h"
 
 #define PM_THREADS 256
-#ifndef PM_MAC_BLOCKS
-#define PM_MAC_BLOCKS 2
-#endif
 
 __device__ __forceinline__ double pm_f64(u64 x) { return __longlong_as_double((long long)x); }
 __device__ __forceinline__ u64 pm_u64(double x) { return (u64)__double_as_longlong(x); }
@@ -97,17 +95,17 @@ void launch_pm_generic(ensi_ctx *ctx, const PmGroup &g, const u64 *d_consts, con
 }
 
 // ===================================================================== N = 2^12 .. 2^16, fp64 arithmetic
-// Plaintext in the order the row pass holds it: within the 16-row tile b, thread (rho, j) = tid owns, as its
-// i-th value, position 16 j + i of row rho; that value is stored at b*4096 + i*256 + tid, as a double.
-// grid (N / 4096, n_rows)
-__global__ __launch_bounds__(PM_THREADS) void k_pm16_pt_format(const u64 *in, u64 *out, int N) {
+// Plaintext in the order a wave holds it in the row pass: within the four rows b, lane (rho, j) owns, as its i-th
+// value, position 16 j + i of row rho; that value is stored at b*1024 + i*64 + lane, as a double.
+// grid (N / 1024, n_rows)
+__global__ __launch_bounds__(64) void k_pm16_pt_format(const u64 *in, u64 *out, int N) {
     const int tid = threadIdx.x, rho = tid >> 4, j = tid & 15;
-    const size_t base = (size_t)blockIdx.y * N + (size_t)blockIdx.x * 4096;
+    const size_t base = (size_t)blockIdx.y * N + (size_t)blockIdx.x * 1024;
 #pragma unroll
-    for (int i = 0; i < 16; i++) out[base + i * 256 + tid] = pm_u64((double)in[base + rho * 256 + 16 * j + i]);
+    for (int i = 0; i < 16; i++) out[base + i * 64 + tid] = pm_u64((double)in[base + rho * 256 + 16 * j + i]);
 }
 void launch_pm16_pt_format(ensi_ctx *ctx, const u64 *ntt_form, int n_rows, u64 *out, hipStream_t st) {
-    hipLaunchKernelGGL(k_pm16_pt_format, dim3(ctx->N / 4096, n_rows), dim3(PM_THREADS), 0, st, ntt_form, out, ctx->N);
+    hipLaunchKernelGGL(k_pm16_pt_format, dim3(ctx->N / 1024, n_rows), dim3(64), 0, st, ntt_form, out, ctx->N);
 }
 
 // grid (TILES, 2*l1, n_src)
@@ -119,10 +117,10 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm16_fcols(PmGroup g, const Prim
     const int tid = threadIdx.x, c16 = R::col(tid), jj = R::grp(tid);
     const int y = blockIdx.y, c = y / g.l1, i = y - c * g.l1, t = blockIdx.z;
     const size_t col = (size_t)blockIdx.x * R::COLS + c16;
-    const u64 *src = g.terms[g.owner[t]].src + ((size_t)c * g.limb_stride_in + i) * PM_N + col;
+    auto src = as_global(g.terms[g.owner[t]].src) + ((size_t)c * g.limb_stride_in + i) * PM_N + col;
     u64 *out = g.ws_a + ((size_t)t * 2 * g.l1 + y) * PM_N + col;
     ArithFp ar;
-    ar.init(pcs[i]);
+    ar.init(load_prime(pcs, i));
     const u64 *tw = tw_all + (size_t)i * 4 * PM_N;
     double v[16];
 #pragma unroll
@@ -132,92 +130,207 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm16_fcols(PmGroup g, const Prim
     for (int k = 0; k < 16; k++) out[(size_t)(16 * jj + k) * 256] = pm_u64(ar.mid(v[k]));
 }
 
-// grid (TILES * 2*l1 * n_out).  The operand of the next term is fetched while the current forward pass runs.  The
-// twiddles of a pass's first step depend on the row only and sit in LDS (the 16 threads of a row read the same
-// word); those of the second step differ per thread and stay in registers across all terms.
+// Row passes and products where (nearly) every source enters one product.  A wave takes four rows of one limb of one
+// polynomial of one output: per term the forward row pass, times the plaintext, accumulated; then the inverse row pass of
+// the sum.  The next operand is requested while the current one is transformed; waves do not wait for each other (with
+// blocks of 16 rows and two barriers per term this kernel reached 2.2 TB/s of operand reads).  The two polynomials of an
+// output, and then the other outputs, which multiply by the same plaintext tiles, run next to each other on one XCD and
+// share those tiles in its L2.  grid (8 * ceil(4 TILES * l1 / 8) * 2 n_out)
 template <int S>
-__global__ __launch_bounds__(PM_THREADS, PM_MAC_BLOCKS) void k_pm16_frows_mac_irows(PmGroup g, const PrimeConst *pcs, const u64 *tw_all) {
+__global__ __launch_bounds__(64, 2) void k_pm16_rows_mac(PmGroup g, const PrimeConst *pcs, const u64 *tw_all) {
     typedef Ring<S> R;
-    constexpr size_t PM_N = R::N;
-    __shared__ u64 lds[4096 + 256];
-    __shared__ ulonglong2 tw1[16 * 16];
-    const int tid = threadIdx.x, rho = tid >> 4, j = tid & 15;
-    // Workgroups are dealt to the eight XCDs in turn.  The two polynomials of an output tile multiply by the same
-    // plaintext tile, so their blocks are made consecutive on one XCD (ids n and n + 8) and the second read of
-    // the tile is served by that XCD's L2.
-    const u32 id = blockIdx.x, q = (id >> 4) * 8 + (id & 7);
-    const int cpoly = (id >> 3) & 1, tile = q % R::TILES, i = q / R::TILES % g.l1, o = q / R::TILES / g.l1;
-    if (o >= g.n_out) return;  // the last group of eight tiles may be incomplete
-    const int y = cpoly * g.l1 + i;
-    const int r0 = tile * 16;
+    constexpr size_t N = R::N;
+    __shared__ u64 lds[ROW_LDS];
+    __shared__ ulonglong2 tw1[4 * 16];
+    const int lane = threadIdx.x, rho = lane >> 4, j = lane & 15;
+    const u32 k = blockIdx.x >> 3, po = k % (2 * (u32)g.n_out), q = k / (2 * (u32)g.n_out) * 8 + (blockIdx.x & 7);
+    const int tile = q % (4 * R::TILES), limb = q / (4 * R::TILES), p = po & 1, o = po >> 1;
+    if (limb >= g.l1) return;
+    const u32 r = tile * 4 + rho;
     ArithFp ar;
-    ar.init(pcs[i]);
-    const u64 *twf = tw_all + (size_t)i * 4 * PM_N, *twi = twf + 2 * PM_N;
-    const u32 r = (u32)(r0 + rho);
-    if (j < 15) {
-        const int k = 31 - __clz(j + 1), gq = j + 1 - (1 << k);
-        const u32 idx = ((R::ROWS + r) << k) + gq;
-        tw1[rho * 16 + j] = make_ulonglong2(twf[idx], twf[PM_N + idx]);
-    }
+    ar.init(load_prime(pcs, limb));
+    const u64 *twf = tw_all + (size_t)limb * 4 * N, *twi = twf + 2 * N;
+    row_table_to_lds(tw1, twf, twf + N, R::ROWS + r, rho, j);
+    TwRegs tw2;
+    tw2.load(twf, twf + N, (R::ROWS + r) * 16u + j);
     const ulonglong2 *tab = tw1 + rho * 16;
-    const int t0 = g.begin[o], t1 = g.begin[o + 1];
+    const int t0 = as_const(g.begin)[o], t1 = as_const(g.begin)[o + 1];
     double acc[16], nv[16];
 #pragma unroll
-    for (int k = 0; k < 16; k++) acc[k] = 0.0;
-    const size_t term = (size_t)2 * g.l1 * PM_N;  // words per term in ws_a
-    const size_t a_off = (size_t)y * PM_N + (size_t)r0 * 256 + rho * 256 + j;
-    const size_t b_off = (size_t)i * PM_N + (size_t)tile * 4096 + tid;
+    for (int i = 0; i < 16; i++) acc[i] = 0.0;
+    const size_t term = (size_t)2 * g.l1 * N, at = (size_t)(p * g.l1 + limb) * N + (size_t)tile * 1024;  // words per source; place in it
+    const u64 *a = g.ws_a + at, *b = g.pt + (size_t)limb * N + (size_t)tile * 1024;
+    const u32 a_off = (rho * 256 + j) * 8, b_off = lane * 8;
+    auto slot_and_pt = [&](int t) { return as_const((const u64 *)(g.terms + t))[1]; };
     if (t0 < t1) {
-        const u64 *a = g.ws_a + (size_t)g.terms[t0].slot * term + a_off;
+        const u64 *s = a + (slot_and_pt(t0) >> 32) * term;
 #pragma unroll
-        for (int k = 0; k < 16; k++) nv[k] = pm_f64(a[16 * k]);
+        for (int i = 0; i < 16; i++) nv[i] = pm_f64(ld_off(s + 16 * i, a_off));
     }
-    double *l = (double *)lds;
-    __syncthreads();
+    wave_lds_fence();
 #pragma unroll 1
     for (int t = t0; t < t1; t++) {
-        const u64 *b = g.pt + (size_t)g.terms[t].pt * g.pt_limbs * PM_N + b_off;
+        const u64 *w_src = b + (size_t)(u32)slot_and_pt(t) * g.pt_limbs * N;
         double v[16], w[16];
 #pragma unroll
-        for (int k = 0; k < 16; k++) w[k] = pm_f64(b[256 * k]);
+        for (int i = 0; i < 16; i++) w[i] = pm_f64(ld_off(w_src + 64 * i, b_off));
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = nv[k];
+        for (int i = 0; i < 16; i++) v[i] = nv[i];
         if (t + 1 < t1) {
-            const u64 *a = g.ws_a + (size_t)g.terms[t + 1].slot * term + a_off;
+            const u64 *s = a + (slot_and_pt(t + 1) >> 32) * term;
 #pragma unroll
-            for (int k = 0; k < 16; k++) nv[k] = pm_f64(a[16 * k]);
+            for (int i = 0; i < 16; i++) nv[i] = pm_f64(ld_off(s + 16 * i, a_off));
         }
-        // forward row pass (the steps of rows_fwd_regs)
-        ct4_tab(ar, v, tab);
+        row_fwd(ar, v, tab, tw2, lds, rho, j);
 #pragma unroll
-        for (int k = 0; k < 16; k++) l[rpad(rho * 256 + j + 16 * k)] = ar.mid(v[k]);
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = l[rpad(rho * 256 + 16 * j + k)];
-        ct4(ar, v, twf, twf + PM_N, (R::ROWS + r) * 16u + j);
-#pragma unroll
-        for (int k = 0; k < 16; k++) acc[k] += ar.mulmod_np(ar.mid(v[k]), w[k]);
+        for (int i = 0; i < 16; i++) acc[i] += ar.mulmod_np(ar.mid(v[i]), w[i]);
         // a product is below 0.7 q in magnitude: eight of them stay exact in a double
         if (((t - t0) & 7) == 7) {
 #pragma unroll
-            for (int k = 0; k < 16; k++) acc[k] = ar.mid(acc[k]);
+            for (int i = 0; i < 16; i++) acc[i] = ar.mid(acc[i]);
         }
-        __syncthreads();  // the tile is reused by the next exchange
     }
-    double v[16];
+    row_table_to_lds(tw1, twi, twi + N, R::ROWS + r, rho, j);
+    tw2.load(twi, twi + N, (R::ROWS + r) * 16u + j);
+    wave_lds_fence();
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = ar.mid(acc[k]);
-    // inverse row pass of the sum
-    gs4(ar, v, twi, twi + PM_N, (R::ROWS + r) * 16u + j);
+    for (int i = 0; i < 16; i++) acc[i] = ar.mid(acc[i]);
+    row_inv(ar, acc, tab, tw2, lds, rho, j);
+    u64 *out = g.ws_b + (size_t)o * term + at;
 #pragma unroll
-    for (int k = 0; k < 16; k++) l[rpad(rho * 256 + 16 * j + k)] = ar.mid(v[k]);
-    __syncthreads();
+    for (int i = 0; i < 16; i++) st_off(out + 16 * i, a_off, ar.store_ws_inv(acc[i]));
+}
+
+// Where sources enter several products each, their row passes are run once (k_pm16_rows<true>), the products are formed
+// on whole tiles (k_pm16_mac) and the sums brought back (k_pm16_rows<false>).  Between these the words of a wave's four rows
+// are in register order: value i of lane l at 64 i + l.
+// grid (4 TILES, 2 * l1 * ceil(n / PM_ROWS_GROUP)): a wave takes four rows of polynomial-limb y for up to PM_ROWS_GROUP of the n
+// ciphertexts (the twiddles are fetched once), in place.
+#define PM_ROWS_GROUP 8
+template <int S, bool FWD>
+__global__ __launch_bounds__(64, 2) void k_pm16_rows(u64 *data, int n, int l1, const PrimeConst *pcs, const u64 *tw_all) {
+    typedef Ring<S> R;
+    constexpr size_t N = R::N;
+    __shared__ u64 lds[ROW_LDS];
+    __shared__ ulonglong2 tw1[4 * 16];
+    const int lane = threadIdx.x, rho = lane >> 4, j = lane & 15;
+    const int y = blockIdx.y % (2 * l1), c0 = blockIdx.y / (2 * l1) * PM_ROWS_GROUP, limb = y % l1;
+    const u32 r = blockIdx.x * 4 + rho;
+    ArithFp ar;
+    ar.init(load_prime(pcs, limb));
+    const u64 *tw = tw_all + (size_t)limb * 4 * N + (FWD ? 0 : 2 * N);
+    row_table_to_lds(tw1, tw, tw + N, R::ROWS + r, rho, j);
+    TwRegs tw2;
+    tw2.load(tw, tw + N, (R::ROWS + r) * 16u + j);
+    const ulonglong2 *tab = tw1 + rho * 16;
+    const u32 row_off = (rho * 256 + j) * 8, reg_off = lane * 8;
+    constexpr int in_step = FWD ? 16 : 64, out_step = FWD ? 64 : 16;
+    const size_t ct = (size_t)2 * l1 * N;
+    u64 *g = data + c0 * ct + (size_t)y * N + (size_t)blockIdx.x * 1024;
+    const int n_here = min(PM_ROWS_GROUP, n - c0);
+    double v[16], nv[16];
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = l[rpad(rho * 256 + j + 16 * k)];
-    gs4(ar, v, twi, twi + PM_N, R::ROWS + r);
-    u64 *out = g.ws_b + (size_t)o * term + a_off;
+    for (int i = 0; i < 16; i++) nv[i] = pm_f64(ld_off(g + in_step * i, FWD ? row_off : reg_off));
+    wave_lds_fence();
+#pragma unroll 1
+    for (int c = 0; c < n_here; c++) {
 #pragma unroll
-    for (int k = 0; k < 16; k++) out[16 * k] = pm_u64(ar.mid(v[k]));
+        for (int i = 0; i < 16; i++) v[i] = nv[i];
+        if (c + 1 < n_here) {
+#pragma unroll
+            for (int i = 0; i < 16; i++) nv[i] = pm_f64(ld_off(g + ct + in_step * i, FWD ? row_off : reg_off));
+        }
+        if (FWD) row_fwd(ar, v, tab, tw2, lds, rho, j);
+        else row_inv(ar, v, tab, tw2, lds, rho, j);
+#pragma unroll
+        for (int i = 0; i < 16; i++) st_off(g + out_step * i, FWD ? reg_off : row_off, pm_u64(ar.mid(v[i])));
+        g += ct;
+    }
+}
+
+// Sums of products of transformed sources for PM_MAC_OUT outputs at a time: an operand word is read once for them.  All groups
+// of outputs of a tile of 1024 words run together on one XCD, whose L2 then serves their sources and plaintexts
+// (127 sources and 192 plaintexts are 0.9 MiB a tile).  entries: per group a list of (source, plaintext per output or
+// -1); entry_begin: [n_groups + 1].  grid (8 * ceil(N / 1024 * l1 / 8) * n_groups)
+template <int S>
+__global__ __launch_bounds__(PM_THREADS) void k_pm16_mac(PmGroup g, const PmEntry *entries, const int32_t *entry_begin, int n_groups, const PrimeConst *pcs) {
+    typedef Ring<S> R;
+    constexpr size_t N = R::N;
+    const u32 k = blockIdx.x >> 3, grp = k % (u32)n_groups, q = k / (u32)n_groups * 8 + (blockIdx.x & 7);
+    const int tile = q % (4 * R::TILES), limb = q / (4 * R::TILES);
+    if (limb >= g.l1) return;
+    ArithFp ar;
+    ar.init(load_prime(pcs, limb));
+    const size_t poly = (size_t)g.l1 * N;
+    const u64 *a = g.ws_a + (size_t)limb * N + (size_t)tile * 1024, *b = g.pt + (size_t)limb * N + (size_t)tile * 1024;
+    const u32 off = threadIdx.x * 8;
+    double acc[PM_MAC_OUT][2][4];
+#pragma unroll
+    for (int o = 0; o < PM_MAC_OUT; o++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) acc[o][0][i] = acc[o][1][i] = 0.0;
+    const int e0 = as_const(entry_begin)[grp], e1 = as_const(entry_begin)[grp + 1];
+    double x[2][4];
+    auto fetch = [&](int slot) {
+        const u64 *s = a + (size_t)slot * 2 * poly;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            x[0][i] = pm_f64(ld_off(s + 256 * i, off));
+            x[1][i] = pm_f64(ld_off(s + poly + 256 * i, off));
+        }
+    };
+    auto entry = [&](int e, int w) { return as_const((const int32_t *)(entries + e))[w]; };
+    if (e0 < e1) fetch(entry(e0, 0));
+#pragma unroll 1
+    for (int e = e0; e < e1; e++) {
+        double v[2][4], w[PM_MAC_OUT][4];
+#pragma unroll
+        for (int o = 0; o < PM_MAC_OUT; o++) {
+            const int pt = entry(e, 1 + o);
+            if (pt >= 0) {
+#pragma unroll
+                for (int i = 0; i < 4; i++) w[o][i] = pm_f64(ld_off(b + (size_t)pt * g.pt_limbs * N + 256 * i, off));
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            v[0][i] = x[0][i];
+            v[1][i] = x[1][i];
+        }
+        if (e + 1 < e1) fetch(entry(e + 1, 0));
+#pragma unroll
+        for (int o = 0; o < PM_MAC_OUT; o++) {
+            if (entry(e, 1 + o) >= 0) {
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    acc[o][0][i] += ar.mulmod_np(v[0][i], w[o][i]);
+                    acc[o][1][i] += ar.mulmod_np(v[1][i], w[o][i]);
+                }
+            }
+        }
+        // a product is below 0.7 q in magnitude: eight of them stay exact in a double
+        if (((e - e0) & 7) == 7) {
+#pragma unroll
+            for (int o = 0; o < PM_MAC_OUT; o++)
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    acc[o][0][i] = ar.mid(acc[o][0][i]);
+                    acc[o][1][i] = ar.mid(acc[o][1][i]);
+                }
+        }
+    }
+#pragma unroll
+    for (int o = 0; o < PM_MAC_OUT; o++) {
+        const u32 out_idx = grp * PM_MAC_OUT + o;
+        if (out_idx < (u32)g.n_out) {
+            u64 *d = g.ws_b + (size_t)out_idx * 2 * poly + (size_t)limb * N + (size_t)tile * 1024;
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                st_off(d + 256 * i, off, pm_u64(ar.mid(acc[o][0][i])));
+                st_off(d + poly + 256 * i, off, pm_u64(ar.mid(acc[o][1][i])));
+            }
+        }
+    }
 }
 
 // grid (TILES, 2, n_out): ws_last[o][c][N] <- centred residue of limb l1-1 (coefficient form)
@@ -232,7 +345,7 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm16_icols_last(PmGroup g, const
     const u64 *src = g.ws_b + ((size_t)o * 2 * g.l1 + c * g.l1 + i) * PM_N + col;
     u64 *dst = g.ws_last + ((size_t)o * 2 + c) * PM_N + col;
     ArithFp ar;
-    ar.init(pcs[i]);
+    ar.init(load_prime(pcs, i));
     const u64 *tw = tw_all + (size_t)i * 4 * PM_N + 2 * PM_N;
     double v[16];
 #pragma unroll
@@ -256,7 +369,7 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm16_icols_rescale(PmGroup g, Pm
     const u64 *last = g.ws_last + ((size_t)o * 2 + c) * PM_N + col;
     u64 *dst = g.out + (size_t)o * g.out_stride + ((size_t)c * g.limb_stride_out + i) * PM_N + col;
     ArithFp ar;
-    ar.init(pcs[i]);
+    ar.init(load_prime(pcs, i));
     const u64 *tw = tw_all + (size_t)i * 4 * PM_N + 2 * PM_N;
     const double w = rs.w[i], wp = rs.wp[i];
     double v[16], tl[16];
@@ -280,10 +393,26 @@ void launch_pm16(ensi_ctx *ctx, const PmGroup &g, const PmRescale &rs, hipStream
             ScopedTimer t(ctx, "pm_fcols", st);
             hipLaunchKernelGGL((k_pm16_fcols<S>), dim3(TILES, 2 * g.l1, g.n_src), dim3(PM_THREADS), 0, st, g, ctx->d_pc, ctx->d_tw);
         }
-        {
-            ScopedTimer t(ctx, "pm_frows_mac_irows", st);
-            const unsigned tiles = (unsigned)TILES * g.l1 * g.n_out;  // per polynomial, in groups of eight (one per XCD)
-            hipLaunchKernelGGL((k_pm16_frows_mac_irows<S>), dim3((tiles + 7) / 8 * 16), dim3(PM_THREADS), 0, st, g, ctx->d_pc, ctx->d_tw);
+        const unsigned tiles = (4u * TILES * g.l1 + 7) / 8 * 8;  // tiles of four rows, in groups of eight (one per XCD)
+        if (g.entries) {
+            const int n_groups = (g.n_out + PM_MAC_OUT - 1) / PM_MAC_OUT;
+            {
+                ScopedTimer t(ctx, "pm_frows", st);
+                hipLaunchKernelGGL((k_pm16_rows<S, true>), dim3(4 * TILES, 2 * g.l1 * ((g.n_src + PM_ROWS_GROUP - 1) / PM_ROWS_GROUP)), dim3(64), 0, st, g.ws_a,
+                                   g.n_src, g.l1, ctx->d_pc, ctx->d_tw);
+            }
+            {
+                ScopedTimer t(ctx, "pm_mac", st);
+                hipLaunchKernelGGL((k_pm16_mac<S>), dim3(tiles * n_groups), dim3(PM_THREADS), 0, st, g, g.entries, g.entry_begin, n_groups, ctx->d_pc);
+            }
+            {
+                ScopedTimer t(ctx, "pm_irows", st);
+                hipLaunchKernelGGL((k_pm16_rows<S, false>), dim3(4 * TILES, 2 * g.l1 * ((g.n_out + PM_ROWS_GROUP - 1) / PM_ROWS_GROUP)), dim3(64), 0, st, g.ws_b,
+                                   g.n_out, g.l1, ctx->d_pc, ctx->d_tw);
+            }
+        } else {
+            ScopedTimer t(ctx, "pm_rows_mac", st);
+            hipLaunchKernelGGL((k_pm16_rows_mac<S>), dim3(tiles * 2 * g.n_out), dim3(64), 0, st, g, ctx->d_pc, ctx->d_tw);
         }
         {
             ScopedTimer t(ctx, "pm_icols_last", st);
