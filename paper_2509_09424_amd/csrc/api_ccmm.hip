@@ -23,7 +23,7 @@ extern "C" int ensi_ct_drop_limbs(ensi_ct *ct, int32_t limbs) {
 // a_pre: the a operands already hold their transform (limb stride l1): they are read in place.  rescale = false stops
 // after the relinearisation: the outputs keep l1 limbs and the product's scale.
 // grid_x, grid_y > 0: the caller states that output x * grid_y + y sums a_(j,x) (x) b_(j,y) over j, with every output's terms
-// in the same order of j; where the fp64 kernels apply and the outputs make one group, the tiled multiply-add is used.
+// in the same order of j; where the outputs make one group, the multiply-add then takes tiles of both.
 static int mult_core(ensi_ctx *ctx, const u64 *rkey, const std::vector<MmTerm> &terms, const std::vector<int32_t> &begin, int l1,
                      int limb_stride_a, int limb_stride_b, ensi_ct *out, hipStream_t st, bool a_pre = false, bool rescale = true,
                      int grid_x = 0, int grid_y = 0) {
@@ -101,8 +101,56 @@ static int mult_core(ensi_ctx *ctx, const u64 *rkey, const std::vector<MmTerm> &
     for (size_t k = 0; k + 1 < op_base.size(); k++)
         for (size_t u = op_base[k]; u < op_base[k + 1]; u++)
             ops[u].t = ops[u].pre ? ops[u].p : ctx->ws_ma + (u - op_base[k]) * 2 * l1 * N;
+    // The products by tiles of outputs: 4 x 2 of a grid, else four neighbouring outputs that name the same right operand.
+    std::vector<MmEntry> entries;
+    std::vector<int32_t> entry_begin, entry_out;
+    std::vector<size_t> tile_at(1, 0);  // per group of outputs: its first tile
+    bool even = grid_x > 0 && grid_y > 0 && cut.size() == 2 && grid_x * grid_y == n_out;
+    for (int o = 1; o < n_out && even; o++) even = begin[o + 1] - begin[o] == begin[1] - begin[0];
+    const int tile_y = even ? 2 : 1;
+    for (size_t k = 0; k + 1 < cut.size() && ctx->ks16; k++) {
+        const int o0 = cut[k], o1 = cut[k + 1];
+        if (even) {
+            for (int x0 = 0; x0 < grid_x; x0 += 4)
+                for (int y0 = 0; y0 < grid_y; y0 += 2) {
+                    entry_begin.push_back((int32_t)entries.size());
+                    for (int j = 0; j < begin[1] - begin[0]; j++) {
+                        MmEntry e;
+                        for (int x = 0; x < 4; x++) e.a[x] = x0 + x < grid_x ? pairs[begin[(x0 + x) * grid_y + y0] + j].a : -1;
+                        for (int y = 0; y < 2; y++) e.b[y] = y0 + y < grid_y ? pairs[begin[x0 * grid_y + y0 + y] + j].b : -1;
+                        entries.push_back(e);
+                    }
+                    for (int x = 0; x < 4; x++)
+                        for (int y = 0; y < 2; y++) entry_out.push_back(x0 + x < grid_x && y0 + y < grid_y ? (x0 + x) * grid_y + y0 + y : -1);
+                }
+        } else {
+            for (int o = o0; o < o1; o += 4) {
+                entry_begin.push_back((int32_t)entries.size());
+                std::map<int, size_t> last;  // per right operand its latest entry
+                for (int x = 0; x < 4; x++) {
+                    entry_out.push_back(o + x < o1 ? o + x - o0 : -1);
+                    for (int t = o + x < o1 ? begin[o + x] : 0; t < (o + x < o1 ? begin[o + x + 1] : 0); t++) {
+                        auto it = last.find(pairs[t].b);
+                        if (it == last.end() || entries[it->second].a[x] >= 0) {
+                            it = last.insert_or_assign(pairs[t].b, entries.size()).first;
+                            entries.push_back({{-1, -1, -1, -1}, {pairs[t].b, -1}});
+                        }
+                        entries[it->second].a[x] = pairs[t].a;
+                    }
+                }
+            }
+        }
+        entry_begin.push_back((int32_t)entries.size());
+        tile_at.push_back(entry_out.size() / (4 * tile_y));
+    }
     const size_t ow = ops.size() * (sizeof(MmOperand) / 8), pw = pairs.size() * (sizeof(MmPair) / 8), bw = (begin.size() + 1) / 2;
-    if ((rc = grow(ctx, &ctx->ws_mt, &ctx->ws_mt_words, ow + pw + bw + 2))) return rc;
+    const size_t ew = entries.size() * (sizeof(MmEntry) / 8), ebw = (entry_begin.size() + 1) / 2, eow = (entry_out.size() + 1) / 2;
+    if ((rc = grow(ctx, &ctx->ws_mt, &ctx->ws_mt_words, ow + pw + bw + ew + ebw + eow + 2))) return rc;
+    if (!entries.empty()) ENSI_HIP(ctx, host_to_device(ctx, ctx->ws_mt + ow + pw + bw, entries.data(), entries.size() * sizeof(MmEntry), st));
+    if (!entry_out.empty()) {
+        ENSI_HIP(ctx, host_to_device(ctx, ctx->ws_mt + ow + pw + bw + ew, entry_begin.data(), entry_begin.size() * 4, st));
+        ENSI_HIP(ctx, host_to_device(ctx, ctx->ws_mt + ow + pw + bw + ew + ebw, entry_out.data(), entry_out.size() * 4, st));
+    }
     if (!ops.empty()) ENSI_HIP(ctx, host_to_device(ctx, ctx->ws_mt, ops.data(), ops.size() * sizeof(MmOperand), st));
     if (!pairs.empty()) ENSI_HIP(ctx, host_to_device(ctx, ctx->ws_mt + ow, pairs.data(), pairs.size() * sizeof(MmPair), st));
     ENSI_HIP(ctx, host_to_device(ctx, ctx->ws_mt + ow + pw, begin.data(), begin.size() * 4, st));
@@ -122,13 +170,11 @@ static int mult_core(ensi_ctx *ctx, const u64 *rkey, const std::vector<MmTerm> &
         g.n_out = cnt;
         g.l1 = l1;
         g.limbs_out = rescale ? l1 - 1 : l1;
-        g.grid_x = g.grid_y = 0;
-        bool even = grid_x > 0 && grid_y > 0 && cut.size() == 2 && grid_x * grid_y == n_out && ctx->ks16 && n_out > 0;
-        for (int o = 1; o < n_out && even; o++) even = begin[o + 1] - begin[o] == begin[1] - begin[0];
-        if (even && begin[1] > begin[0]) {
-            g.grid_x = grid_x;
-            g.grid_y = grid_y;
-        }
+        g.n_groups = ctx->ks16 ? (int)(tile_at[k + 1] - tile_at[k]) : 0;
+        g.tile_y = tile_y;
+        g.entries = (const MmEntry *)(ctx->ws_mt + ow + pw + bw);
+        g.entry_begin = (const int32_t *)(ctx->ws_mt + ow + pw + bw + ew) + (ctx->ks16 ? tile_at[k] + k : 0);  // (a group's offsets have one more entry than it has tiles)
+        g.entry_out = (const int32_t *)(ctx->ws_mt + ow + pw + bw + ew + ebw) + (ctx->ks16 ? tile_at[k] * 4 * tile_y : 0);
         g.ws_a = ctx->ws_ma;
         g.ws_d = ctx->ws_md;
         g.ws_e = ctx->ws_me;

@@ -53,77 +53,125 @@ __global__ __launch_bounds__(MM_THREADS) void k_mm_tensor_mac(MmGroup g, int N, 
     out[2 * poly] = mont_mul(d1, pc.r2, q, qn);
 }
 
-// The same sums for outputs that form a grid (MmGroup.grid_x, grid_y), primes below 2^50: a block forms a tile of 4 x 2
-// outputs for 256 words of one limb, so that every operand word it reads enters 2 or 4 products (the plain kernel reads
-// four operand words per product, most of them again and again for other outputs), and multiplies in fp64 on exact
-// integers.  grid (ceil(N/256), l1, tiles_x * tiles_y).
-#define MM_TX 4
-#define MM_TY 2
-__global__ __launch_bounds__(MM_THREADS) void k_mm_grid_mac_fp(MmGroup g, int N, const PrimeConst *pcs) {
-    const int idx = blockIdx.x * MM_THREADS + threadIdx.x;
-    if (idx >= N) return;
-    const int i = blockIdx.y;
-    const int tiles_y = (g.grid_y + MM_TY - 1) / MM_TY;
-    const int x0 = (blockIdx.z / tiles_y) * MM_TX, y0 = (blockIdx.z % tiles_y) * MM_TY;
+// The same sums for TX x TY outputs at a time, primes below 2^50: output (x, y) of a group adds a_x (x) b_y over the group's
+// entries.  Every operand word a block reads enters TY or TX products, and all groups of a range of words run together on one
+// XCD, so that operands shared by groups come from its L2: memory is read about once, which is what bounds this kernel (the
+// plain kernel reads four operand words per product).
+// Arithmetic: words are taken as two 25-bit halves, products of halves added up in 64-bit integers -- four multiply-adds per
+// product, against six instructions for a reduced product in fp64 -- and reduced every MM_FOLD entries and at the end.
+// The middle polynomial is formed from (a0 + a1)(b0 + b1): twelve multiply-adds instead of sixteen per pair.
+// grid (8 * ceil(N / 256 * l1 / 8) * n_groups)
+#define MM_FOLD 512  // a sum of 512 middle terms of twice 2^52 stays below 2^62.1
+template <int TX, int TY>
+__global__ __launch_bounds__(MM_THREADS, TX * TY > 4 ? 2 : 3) void k_mm_mac(MmGroup g, int N, const PrimeConst *pcs) {
+    const u32 k = blockIdx.x >> 3, grp = k % (u32)g.n_groups, q = k / (u32)g.n_groups * 8 + (blockIdx.x & 7);
+    const int per_limb = N / MM_THREADS, limb = q / per_limb;
+    if (limb >= g.l1) return;
+    const u32 off = ((q - limb * per_limb) * MM_THREADS + threadIdx.x) * 8;
+    const size_t poly = (size_t)g.l1 * N, at = (size_t)limb * N;
     ArithFp ar;
-    ar.init(pcs[i]);
-    const double half = 0.5 * ar.p;
-    const size_t poly = (size_t)g.l1 * N, off = (size_t)i * N + idx;
-    const int J = g.begin[1] - g.begin[0];
-    // term j of output (x, y0) names the left operand of row x, term j of output (x0, y) the right operand of column y
-    const MmPair *pa[MM_TX], *pb[MM_TY];
+    ar.init(load_prime(pcs, limb));
+    // sums of products of halves: [0] low * low, [1] the two mixed ones, [2] high * high; of a0 b0, (a0+a1)(b0+b1), a1 b1
+    int64_t s[TX][TY][3][3];
 #pragma unroll
-    for (int x = 0; x < MM_TX; x++) pa[x] = g.pairs + (g.begin[(x0 + x < g.grid_x ? x0 + x : x0) * g.grid_y + y0] - g.t_base);
+    for (int x = 0; x < TX; x++)
 #pragma unroll
-    for (int y = 0; y < MM_TY; y++) pb[y] = g.pairs + (g.begin[x0 * g.grid_y + (y0 + y < g.grid_y ? y0 + y : y0)] - g.t_base);
-    double d0[MM_TX][MM_TY], d1[MM_TX][MM_TY], d2[MM_TX][MM_TY];
+        for (int y = 0; y < TY; y++)
 #pragma unroll
-    for (int x = 0; x < MM_TX; x++)
+            for (int d = 0; d < 9; d++) s[x][y][d / 3][d % 3] = 0;
+    const double c25r = ar.mid(33554432.0), c25 = c25r < 0.0 ? c25r + ar.p : c25r;
+    const double c50r = ar.mid(ar.mulmod_np(ar.mid(c25), c25)), c50 = c50r < 0.0 ? c50r + ar.p : c50r;
+    auto residue = [&](int64_t v) {  // centred
+        const double h = (double)(int)(v >> 32) * 4294967296.0;
+        return ar.mid(fma(-rint(h * ar.pinv), ar.p, h) + (double)(u32)v);
+    };
+    auto reduce = [&](const int64_t *v) { return ar.mid(ar.mulmod_np(residue(v[2]), c50) + ar.mulmod_np(residue(v[1]), c25) + residue(v[0])); };
+    const int e0 = as_const(g.entry_begin)[grp], e1 = as_const(g.entry_begin)[grp + 1];
+    auto index = [&](int e, int w) { return as_const((const int32_t *)(g.entries + e))[w]; };
+    auto operand = [&](int i) { return as_const((const u64 *)(g.ops + i))[1]; };  // MmOperand.t
+    u64 na[TX][2], nb[TY][2];
+    auto fetch = [&](int e) {
 #pragma unroll
-        for (int y = 0; y < MM_TY; y++) d0[x][y] = d1[x][y] = d2[x][y] = 0.0;
-    for (int j = 0; j < J; j++) {
-        double a0[MM_TX], a1[MM_TX], b0[MM_TY], b1[MM_TY];
-#pragma unroll
-        for (int x = 0; x < MM_TX; x++) {
-            const u64 *p = g.ops[pa[x][j].a].t + off;
-            const double v0 = (double)p[0], v1 = (double)p[poly];
-            a0[x] = v0 > half ? v0 - ar.p : v0;  // the left factor centred: |a| <= p/2
-            a1[x] = v1 > half ? v1 - ar.p : v1;
-        }
-#pragma unroll
-        for (int y = 0; y < MM_TY; y++) {
-            const u64 *p = g.ops[pb[y][j].b].t + off;
-            b0[y] = (double)p[0];
-            b1[y] = (double)p[poly];
-        }
-#pragma unroll
-        for (int x = 0; x < MM_TX; x++)
-#pragma unroll
-            for (int y = 0; y < MM_TY; y++) {
-                d0[x][y] += ar.mulmod_np(a0[x], b0[y]);
-                d1[x][y] += ar.mulmod_np(a0[x], b1[y]) + ar.mulmod_np(a1[x], b0[y]);
-                d2[x][y] += ar.mulmod_np(a1[x], b1[y]);
+        for (int x = 0; x < TX; x++) {
+            const int i = index(e, x);
+            if (i >= 0) {
+                const u64 *p = (const u64 *)operand(i) + at;
+                na[x][0] = *as_global((const u64 *)((const char *)p + off));
+                na[x][1] = *as_global((const u64 *)((const char *)(p + poly) + off));
+            } else {
+                na[x][0] = na[x][1] = 0;
             }
-        if ((j & 3) == 3) {
+        }
 #pragma unroll
-            for (int x = 0; x < MM_TX; x++)
+        for (int y = 0; y < TY; y++) {
+            const int i = index(e, 4 + y);
+            if (i >= 0) {
+                const u64 *p = (const u64 *)operand(i) + at;
+                nb[y][0] = *as_global((const u64 *)((const char *)p + off));
+                nb[y][1] = *as_global((const u64 *)((const char *)(p + poly) + off));
+            } else {
+                nb[y][0] = nb[y][1] = 0;
+            }
+        }
+    };
+    if (e0 < e1) fetch(e0);
+#pragma unroll 1
+    for (int e = e0; e < e1; e++) {
+        // halves of a0, a0 + a1, a1 (and b alike): at most 26 bits
+        int al[TX][3], ah[TX][3], bl[TY][3], bh[TY][3];
 #pragma unroll
-                for (int y = 0; y < MM_TY; y++) {
-                    d0[x][y] = ar.mid(d0[x][y]);
-                    d1[x][y] = ar.mid(d1[x][y]);
-                    d2[x][y] = ar.mid(d2[x][y]);
+        for (int x = 0; x < TX; x++) {
+            al[x][0] = (int)((u32)na[x][0] & 0x1ffffffu);
+            ah[x][0] = (int)(u32)(na[x][0] >> 25);
+            al[x][2] = (int)((u32)na[x][1] & 0x1ffffffu);
+            ah[x][2] = (int)(u32)(na[x][1] >> 25);
+            al[x][1] = al[x][0] + al[x][2];
+            ah[x][1] = ah[x][0] + ah[x][2];
+        }
+#pragma unroll
+        for (int y = 0; y < TY; y++) {
+            bl[y][0] = (int)((u32)nb[y][0] & 0x1ffffffu);
+            bh[y][0] = (int)(u32)(nb[y][0] >> 25);
+            bl[y][2] = (int)((u32)nb[y][1] & 0x1ffffffu);
+            bh[y][2] = (int)(u32)(nb[y][1] >> 25);
+            bl[y][1] = bl[y][0] + bl[y][2];
+            bh[y][1] = bh[y][0] + bh[y][2];
+        }
+        if (e + 1 < e1) fetch(e + 1);
+#pragma unroll
+        for (int x = 0; x < TX; x++)
+#pragma unroll
+            for (int y = 0; y < TY; y++)
+#pragma unroll
+                for (int d = 0; d < 3; d++) {
+                    s[x][y][d][0] = mad_i(al[x][d], bl[y][d], s[x][y][d][0]);
+                    s[x][y][d][1] = mad_i(al[x][d], bh[y][d], s[x][y][d][1]);
+                    s[x][y][d][1] = mad_i(ah[x][d], bl[y][d], s[x][y][d][1]);
+                    s[x][y][d][2] = mad_i(ah[x][d], bh[y][d], s[x][y][d][2]);
                 }
+        if ((e - e0) % MM_FOLD == MM_FOLD - 1) {
+#pragma unroll
+            for (int x = 0; x < TX; x++)
+#pragma unroll
+                for (int y = 0; y < TY; y++)
+#pragma unroll
+                    for (int d = 0; d < 3; d++) {
+                        s[x][y][d][0] = (int64_t)reduce(s[x][y][d]);
+                        s[x][y][d][1] = s[x][y][d][2] = 0;
+                    }
         }
     }
 #pragma unroll
-    for (int x = 0; x < MM_TX; x++)
+    for (int x = 0; x < TX; x++)
 #pragma unroll
-        for (int y = 0; y < MM_TY; y++) {
-            if (x0 + x >= g.grid_x || y0 + y >= g.grid_y) continue;
-            u64 *out = g.ws_d + ((size_t)((x0 + x) * g.grid_y + y0 + y) * 3 * g.l1 + i) * N + idx;
-            out[0] = ar.canon(d0[x][y]);
-            out[poly] = ar.canon(d2[x][y]);
-            out[2 * poly] = ar.canon(d1[x][y]);
+        for (int y = 0; y < TY; y++) {
+            const int o = as_const(g.entry_out)[(grp * TX + x) * TY + y];
+            if (o < 0) continue;
+            const double d0 = reduce(s[x][y][0]), d2 = reduce(s[x][y][2]), d1 = reduce(s[x][y][1]) - d0 - d2;
+            u64 *out = g.ws_d + (size_t)o * 3 * poly + at;
+            st_off(out, off, ar.canon(d0));
+            st_off(out + poly, off, ar.canon(d2));
+            st_off(out + 2 * poly, off, ar.canon(d1));
         }
 }
 
@@ -180,12 +228,13 @@ void launch_mm_tensor(ensi_ctx *ctx, const MmGroup &g, hipStream_t st) {
     }
     {
         ScopedTimer t(ctx, "mm_tensor_mac", st);
-        if (g.grid_x > 0) {
-            const int tiles = ((g.grid_x + MM_TX - 1) / MM_TX) * ((g.grid_y + MM_TY - 1) / MM_TY);
-            hipLaunchKernelGGL(k_mm_grid_mac_fp, dim3(nb, g.l1, tiles), dim3(MM_THREADS), 0, st, g, N, ctx->d_pc);
-        } else {
+        const unsigned blocks = ((unsigned)nb * g.l1 + 7) / 8 * 8 * g.n_groups;
+        if (g.n_groups > 0 && g.tile_y == 2)
+            hipLaunchKernelGGL((k_mm_mac<4, 2>), dim3(blocks), dim3(MM_THREADS), 0, st, g, N, ctx->d_pc);
+        else if (g.n_groups > 0)
+            hipLaunchKernelGGL((k_mm_mac<4, 1>), dim3(blocks), dim3(MM_THREADS), 0, st, g, N, ctx->d_pc);
+        else
             hipLaunchKernelGGL(k_mm_tensor_mac, dim3(nb, g.l1, g.n_out), dim3(MM_THREADS), 0, st, g, N, ctx->d_pc);
-        }
     }
     launch_ntt(ctx, g.ws_d, g.n_out * 3 * g.l1, map, true, st);
 }

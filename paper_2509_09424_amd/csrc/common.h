@@ -129,6 +129,12 @@ struct MmOperand {
 struct MmPair {
     int32_t a, b;
 };
+// The products of a group by tile of outputs (primes below 2^50): up to four left and two right operands whose products enter
+// the outputs of a tile; -1 for none.
+struct MmEntry {
+    int32_t a[4];
+    int32_t b[2];
+};
 // One group of outputs of out_o = Rescale(Relin(sum_t a_t (x) b_t)); same conventions as PmGroup.
 struct MmGroup {
     const MmOperand *ops;  // the group's operands; the first n_ops are gathered and transformed, prepared ones follow
@@ -137,8 +143,11 @@ struct MmGroup {
     int t_base, n_terms, n_ops, n_out;
     int l1;
     int limbs_out;  // limbs copied to the output: l1 - 1 after the rescale, l1 without it
-    int grid_x, grid_y;  // > 0: output x * grid_y + y sums, over j, a_(j,x) (x) b_(j,y): every output has the same number of
-                         // terms in the same order, and outputs of a row share their left, of a column their right operands
+    int n_groups;               // > 0: the products by tiles of 4 x tile_y outputs
+    int tile_y;
+    const MmEntry *entries;
+    const int32_t *entry_begin; // [n_groups + 1]
+    const int32_t *entry_out;   // [n_groups][4][tile_y] output of the group, -1 for none
     u64 *ws_a;   // [n_ops][2][l1][N] operand polynomials (transformed in place)
     u64 *ws_d;   // [n_out][3][l1][N]   d0, d2, d1: (d0, d2) is laid out like a ciphertext for the key switch
     u64 *ws_e;   // [n_out][2][l1][N]   relinearised product

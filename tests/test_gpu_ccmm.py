@@ -57,6 +57,26 @@ def test_mult_sum_relin_rescale_small_ring(params, l1):
     p.close()
 
 
+@pytest.mark.parametrize("params,l1", [((12, 50, 4, 60, 2, 2, 40), 4), ((13, 45, 3, 48, 3, 3, 36), 2)], ids=["4K", "8K"])
+def test_mult_tiles_of_outputs(params, l1):
+    """Products by tiles of four outputs: right operands that outputs share and that one output names twice, a ragged last
+    tile, an output without terms, and one with more terms than are added between two reductions."""
+    p = Pair(params)
+    o_rk, g_rk = relin_keys(p)
+    _, o_cts, g_ct = mult_case(p, l1)
+    lists = [[(0, 7), (1, 7), (2, 6)], [(3, 7)], [], [(4, 6), (5, 5)], [(i % 5, 7 - i % 3) for i in range(520)], [(6, 6)]]
+    terms = [t for terms in lists for t in terms]
+    begin = [sum(len(t) for t in lists[:o]) for o in range(len(lists) + 1)]
+    out = p.ctx.mult_sum_relin_rescale(g_rk, g_ct, g_ct, begin, [t[0] for t in terms], [t[1] for t in terms])
+    got = out.export()
+    for o, ts in enumerate(lists):
+        want = p.o.mult_sum_relin_rescale([(o_cts[a], o_cts[b]) for a, b in ts], o_rk).limbs() if ts else np.zeros((2, l1 - 1, p.N), dtype=np.uint64)
+        assert np.array_equal(got[o], want), o
+    for h in (g_ct, out, g_rk):
+        h.free()
+    p.close()
+
+
 def test_mult_full_ring():
     """N = 2^16: the transform and key-switch kernels of the fused path carry the product; a low level keeps the
     oracle quick; operands whose limb stride is wider than their level."""

@@ -67,6 +67,24 @@ def test_pmult_sum_rescale_small_ring(params, l1):
     p.close()
 
 
+@pytest.mark.parametrize("params,l1", [((12, 50, 4, 60, 2, 2, 40), 4), ((14, 50, 3, 60, 2, 2, 40), 2)], ids=["4K", "16K"])
+def test_pmult_register_transform_rings(params, l1):
+    """Products term by term, and source by source where sources are shared: tiles of four outputs of which the last is
+    ragged, a source that enters one output twice, an output without terms, an output alone."""
+    p = Pair(params)
+    _, o_cts, g_ct = random_cts(p, 6, l1, 51)
+    rns, g_pt, ql = random_plaintexts(p, 3, l1, 52)
+    shared = [[0, 1, 1], [], [2, 0, 2, 2], [1], [0, 1, 2, 3], [3, 3]]
+    alone = [[4, 2], [0], [], [1, 5, 3]]
+    for lists, what in ((shared, "shared"), (alone, "alone"), ([[1] * 9], "one output")):
+        term_ct = [c for terms in lists for c in terms]
+        begin = [sum(len(t) for t in lists[:o]) for o in range(len(lists) + 1)]
+        check_terms(p, o_cts, g_ct, rns, g_pt, ql, begin, term_ct, [t % 3 for t in range(len(term_ct))], l1, what)
+    g_ct.free()
+    g_pt.free()
+    p.close()
+
+
 def test_pmult_sum_rescale_full_ring_both_kernel_sets(full):
     """N = 2^16, primes below 2^50: the fused kernels (a 19-term output crosses two of the accumulator's
     reductions, one output has no term) and the generic kernels, each against the oracle."""
