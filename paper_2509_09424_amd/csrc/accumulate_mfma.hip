@@ -17,8 +17,8 @@
 //
 // Two kernels.  k_byte_planes runs once per operand array: it splits every 32 x 32 tile
 // (32 operands x 32 consecutive words) into its byte planes, already in the register
-// layout of the matrix instruction's second operand (lane = 32*(operand/16) + word, 16
-// operand bytes per lane), so that the tile of one plane is 1 KiB that a single
+// layout of the matrix instruction's first operand (lane = 32*(operand/16) + row, 16
+// operand bytes per lane; plane_row says which word a row is), so that the tile of one plane is 1 KiB that a single
 // asynchronous global->LDS copy drops in place.  Tiles are stored [word tile][step]
 // [plane]: a work item of the contraction streams one contiguous run.  The split is done
 // once instead of once per output tile (10 to 27 times at the benchmark shapes), which
@@ -38,6 +38,11 @@
 //   * the fragments of step k+1 are read from LDS while the matrix instructions of
 //     step k run from registers;
 //   * one barrier.
+// The words are the first operand of the matrix instruction and the weights the second: under this load the chip is bound by
+// power, and a register-only loop on random bytes and ternary weights takes 41.1 cycles (of 2.4 GHz) per instruction this way
+// round against 46.3 the other.
+// An item's own cost, beside the 448 matrix-pipe cycles of each step, is its recombination: 12300 cycles, one wave to a SIMD
+// (15500 before decoding items by multiplication, adding the first step to a constant zero and no longer waiting for stores).
 // The step loop holds no vector-ALU instruction besides the matrix instructions: the running source addresses of the
 // copies are wave-uniform and live in scalar registers (a lane adds 16 * lane through the instruction's offset
 // operand).  Vector instructions issued between matrix instructions slow the matrix pipe down measurably -- four 64-bit
@@ -47,8 +52,10 @@
 // workers of that XCD take the list round-robin, so they read the same plane tiles
 // at nearly the same time and all but the first read are served by that XCD's L2.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
+#include "ntt16_core.h"
 
 #include <ensi_dma.h>
 
@@ -63,6 +70,9 @@ typedef int v16i __attribute__((vector_size(64)));
 #define AM_RING (AM_DEPTH + 1)  // power of two; the step loop is unrolled by it so every LDS offset is a constant
 #define AM_BSLOT 8192           // plane tiles of one step (1 KiB each, PLANES of 8 used)
 #define AM_ASLOT 2048           // one wave's two weight fragments of one step
+
+#define AM_STORES 16            // stores of one item by one wave: 64 outputs x 32 words, 1 KiB each
+#define AM_OROW 144             // 16 words of an output, padded
 
 // Byte b of four dwords gathered into one dword (4x4 byte transpose, two stages).
 __device__ __forceinline__ void transpose4(u32 a0, u32 a1, u32 a2, u32 a3, u32 *p) {
@@ -121,6 +131,10 @@ __device__ __forceinline__ u64 recombine_fp(const int (&S)[PLANES], double B, do
 // words give one dword (4 operand bytes) of every plane.  A plane tile is staged in LDS and written out as
 // whole 16-byte lane entries.  Bytes are stored as u - 128 (u xor 0x80); operands beyond n_v are zero
 // words (their weights are zero).
+// Row of the plane tile that holds word ln: accumulator register r of a lane is row 8*(r/4) + 4*(lane/32) + r%4 and holds
+// word 16*(r/8) + 8*(lane/32) + r%8, so that the two lanes of an output hold 16 consecutive words in eight registers.
+__device__ __forceinline__ int plane_row(int ln) { return ((ln >> 4) * 2 + ((ln >> 2) & 1)) * 8 + ((ln >> 3) & 1) * 4 + (ln & 3); }
+
 struct AmFp {  // fp64 arithmetic on exact integers modulo a prime below 2^50 (as in the rescale kernel)
     double q, qinv;
     __device__ __forceinline__ double mid(double x) const { return fma(-rint(x * qinv), q, x); }
@@ -157,7 +171,7 @@ __global__ __launch_bounds__(AM_THREADS) void k_byte_planes(const u64 *xbase, u3
     const int pl = blockIdx.z, poly = pl / l1, limb = pl - poly * l1;
     const u64 *xw = xbase + ((size_t)poly * limb_stride_in + limb) * N + (size_t)(c0 + blockIdx.x) * AM_TILE_N + ln;
     // destination dword of this thread inside a plane tile: lane (k4/4)*32 + ln, dword k4 % 4
-    const int dst = ((k4 >> 2) * 32 + ln) * 4 + (k4 & 3);
+    const int dst = ((k4 >> 2) * 32 + plane_row(ln)) * 4 + (k4 & 3);
     v4i *out = (v4i *)(xp + (((size_t)pl * cw + blockIdx.x) * nk + (size_t)blockIdx.y * 8) * PLANES * 1024);
     // all 32 words of the block's 8 steps are requested before the first is used
     u64 w[8][4];
@@ -186,7 +200,7 @@ __global__ __launch_bounds__(AM_THREADS) void k_byte_planes_rescale(const u64 *x
     const int tid = threadIdx.x, k4 = tid >> 5, ln = tid & 31;
     const int poly = blockIdx.z, lin = l1 + 1;
     const u64 *xw = xbase + (size_t)poly * limb_stride_in * N + (size_t)(c0 + blockIdx.x) * AM_TILE_N + ln;
-    const int dst = ((k4 >> 2) * 32 + ln) * 4 + (k4 & 3);
+    const int dst = ((k4 >> 2) * 32 + plane_row(ln)) * 4 + (k4 & 3);
     u64 w[AM_RS_STEPS][4];
     double xl[AM_RS_STEPS][4];
     // operand rows of this thread: row[s8] + j * xstride for j < n_live[s8] (a multiple of four operands except in
@@ -245,7 +259,8 @@ struct AmLayout {
     static constexpr int bring_off = 0;                                  // [AM_RING][AM_BSLOT]
     static constexpr int aring_off = bring_off + AM_RING * AM_BSLOT;     // [4 waves][AM_RING][AM_ASLOT]
     static constexpr int bias_off = aring_off + 4 * AM_RING * AM_ASLOT;  // [2][256] offset terms of an item's outputs (int32 or double)
-    static constexpr int total = bias_off + 2 * AM_TILE_M * 8;
+    static constexpr int out_off = bias_off + 2 * AM_TILE_M * 8;         // [4 waves][32 outputs][AM_OROW] results on their way out
+    static constexpr int total = out_off + 4 * 32 * AM_OROW;
 };
 
 // xp: plane tiles of the slice, [word tile][nk][PLANES][1024]; the slice covers coefficient tiles c0 .. c0+cw-1
@@ -271,27 +286,35 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
     const u32 a_lds = (u32)__builtin_amdgcn_readfirstlane((int)(smem0 + LY::aring_off + wv * AM_RING * AM_ASLOT));
     const char *a_rd = smem + LY::aring_off + wv * AM_RING * AM_ASLOT + lane * 16;
     const char *b_rd = smem + LY::bring_off + lane * 16;
+    char *o_lds = smem + LY::out_off + wv * 32 * AM_OROW;
     const size_t ct_words_out = (size_t)2 * limb_stride_out * N;
     const int xcd = blockIdx.x & 7, worker = blockIdx.x >> 3;
     const int n_nt = (n_tiles_n + 7) / 8;  // word tiles of this XCD
-    const int items = n_nt * n_tiles_m;
-    const int per_group = n_nt * m_group, last_group = (n_tiles_m - 1) / m_group;
+    const int per_group = n_nt * m_group, last_group = (n_tiles_m - 1) / m_group, last_size = n_tiles_m - last_group * m_group;
 
-    // item index -> (output tile, word tile of the slice); false for the padding slots of the last group of 8 word tiles.
     // Items are ordered: group of m_group output tiles, word tile, output tile inside the group; the workers of an
-    // XCD therefore share both plane tiles and weight fragments through its L2.
-    auto decode = [&](int item, int &m_tile, int &nt_local) {
-        const int mg = item / per_group < last_group ? item / per_group : last_group;
-        const int j = item - mg * per_group;
-        const int gsize = n_tiles_m - mg * m_group < m_group ? n_tiles_m - mg * m_group : m_group;
-        m_tile = mg * m_group + j % gsize;
-        nt_local = (j / gsize) * 8 + xcd;
-        return nt_local < n_tiles_n;
+    // XCD therefore share both plane tiles and weight fragments through its L2.  A workgroup steps through its items with
+    // (group, place in the group); dividing by the group's size takes one multiplication by a rounded-up reciprocal, exact
+    // for places below 2^29 / 8 (an item's address arithmetic sits between its matrix instructions and the next item's).
+    const u32 recip_full = 0xffffffffu / (u32)m_group + 1, recip_last = 0xffffffffu / (u32)last_size + 1;  // (unused for a size of one)
+    struct Item {
+        int mg, j;            // group of output tiles, place in it
+        int m_tile, nt_local;  // output tile, word tile of the slice
     };
-    auto next_valid = [&](int item) {
-        int mt, nt;
-        while (item < items && !decode(item, mt, nt)) item += workers_per_xcd;
-        return item;
+    // item at or after place (mg, j) that is not one of the padding slots of the last group of 8 word tiles
+    auto settle = [&](Item &t) {
+        for (;; t.j += workers_per_xcd) {
+            while (t.mg < last_group && t.j >= per_group) {
+                t.j -= per_group;
+                t.mg++;
+            }
+            const int size = t.mg < last_group ? m_group : last_size;
+            if (t.mg >= last_group && t.j >= n_nt * size) return false;
+            const int col = size == 1 ? t.j : (int)__umulhi((u32)t.j, t.mg < last_group ? recip_full : recip_last);
+            t.m_tile = t.mg * m_group + t.j - col * size;
+            t.nt_local = col * 8 + xcd;
+            if (t.nt_local < n_tiles_n) return true;
+        }
     };
 
     // The copies of all items of this workgroup form one stream of steps: the ring never drains between items.
@@ -299,13 +322,11 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
     // pb/pa are wave-uniform (scalar registers, advanced by the scalar unit); a lane adds its own 16 * lane bytes.
     const char *pb[2], *pa;
     const u32 lane_off = (u32)lane * 16;
-    auto seek = [&](int item) {
-        int mt, nt;
-        decode(item, mt, nt);
-        const char *pbase = xp + (size_t)nt * nk * PLANES * 1024;
+    auto seek = [&](const Item &t) {
+        const char *pbase = xp + (size_t)t.nt_local * nk * PLANES * 1024;
         pb[0] = pbase + pb0 * 1024;
         pb[1] = pbase + pb1 * 1024;
-        pa = (const char *)(wfrag + ((size_t)mt * nk * 4 + wv) * 128);
+        pa = (const char *)(wfrag + ((size_t)t.m_tile * nk * 4 + wv) * 128);
     };
     // one of the wave's two plane tiles of the stream's next step -> ring slot
     auto issue_b = [&](int slot, int c) {
@@ -321,22 +342,22 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
     // offset terms of an item's 256 outputs -> one of two LDS buffers (64 per wave); issued one item ahead
     constexpr int BIAS_BYTES = FP_EPI ? 8 : 4;
     const u32 bias_lds = (u32)__builtin_amdgcn_readfirstlane((int)(smem0 + LY::bias_off + wv * 64 * BIAS_BYTES));
-    auto issue_bias = [&](int item, int buf) {
-        int mt, nt;
-        decode(item, mt, nt);
+    const u32 recip_cw = 0xffffffffu / (u32)cw + 1;  // limb row of a word tile: exact for 2^16 tiles and cw up to 2^15
+    auto limb_row = [&](const Item &t) { return cw == 1 ? t.nt_local : (int)__umulhi((u32)t.nt_local, recip_cw); };
+    auto issue_bias = [&](const Item &t, int buf) {
         if (FP_EPI) {
             // the wave's 64 doubles of the item's limb, as two copies of 4 bytes per lane (256 contiguous bytes each)
-            const int pl = nt / cw, limb = pl - (pl / l1) * l1;
-            const char *src = (const char *)((const double *)bias + (size_t)limb * n_tiles_m * AM_TILE_M + mt * AM_TILE_M + wv * 64) + lane * 4;
+            const int pl = limb_row(t), limb = pl < l1 ? pl : pl - l1;
+            const char *src = (const char *)((const double *)bias + (size_t)limb * n_tiles_m * AM_TILE_M + t.m_tile * AM_TILE_M + wv * 64) + lane * 4;
             dma_load4(src, bias_lds + (u32)buf * (AM_TILE_M * 8));
             dma_load4(src + 256, bias_lds + (u32)buf * (AM_TILE_M * 8) + 256);
         } else {
-            dma_load4((const int32_t *)bias + mt * AM_TILE_M + wv * 64 + lane, bias_lds + (u32)buf * (AM_TILE_M * 4));
+            dma_load4((const int32_t *)bias + t.m_tile * AM_TILE_M + wv * 64 + lane, bias_lds + (u32)buf * (AM_TILE_M * 4));
         }
     };
 
-    int item = next_valid(worker);
-    if (item >= items) return;
+    Item item = {0, worker, 0, 0};
+    if (!settle(item)) return;
     issue_bias(item, 0);
     // Copies are issued in one fixed order, "iteration j issues B(j+8) then A(j+8) into slot j % 8" (j counts the
     // steps of the stream), from j = -8 on, so that waiting until at most 24 copies are outstanding always means:
@@ -362,35 +383,30 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
     af[0][1] = *(const v4i *)(a_rd + 1024);
     __syncthreads();  // slot 0 has been read by every wave before step 0 refills it
 
-    for (int it = 0; item < items; it++) {
-        int m_tile, nt_local;
-        decode(item, m_tile, nt_local);
-        const int next = next_valid(item + workers_per_xcd);
-        const int pl = nt_local / cw, poly = pl / l1, limb = pl - poly * l1;
-        const size_t off_out = ((size_t)poly * limb_stride_out + limb) * N + (size_t)(c0 + nt_local - pl * cw) * AM_TILE_N;
-        const int i0 = m_tile * AM_TILE_M + wv * 64;
+    bool stores_pending = false;  // the previous item's AM_STORES stores of this wave may still be on their way
+    bool more = true;
+    for (int it = 0; more; it++) {
+        Item next = {item.mg, item.j + workers_per_xcd, 0, 0};
+        more = settle(next);
+        const int pl = limb_row(item), poly = pl >= l1, limb = poly ? pl - l1 : pl;
+        const size_t off_out = ((size_t)poly * limb_stride_out + limb) * N + (size_t)(c0 + item.nt_local - pl * cw) * AM_TILE_N;
+        const int i0 = item.m_tile * AM_TILE_M + wv * 64;
         // offset terms of this item's outputs: copied one item ahead into two buffers used alternately (the
         // other one may still be read by a wave that has not finished the previous item's recombination)
         const char *bl = smem + LY::bias_off + (it & 1) * AM_TILE_M * BIAS_BYTES;
 
         v16i acc[PLANES][2];
-#pragma unroll
-        for (int p = 0; p < PLANES; p++)
-#pragma unroll
-            for (int mb = 0; mb < 2; mb++)
-#pragma unroll
-                for (int r = 0; r < 16; r++) acc[p][mb][r] = 0;
-
         // Step ks multiplies from registers filled during step ks-1; meanwhile it reads the fragments of step
         // ks+1 from slot (ks+1) % RING and issues the copies of the stream's step ks+8 into slot ks % RING (read
         // during step ks-1, before the barrier that ended it).  During the last 8 steps of an item the stream
         // has moved on to the first 8 steps of the next item (after the last item: of the same item again,
         // which nobody reads).  Scheduling fences keep the LDS reads and the copies spread between the matrix
         // instructions.
-        for (int ks0 = 0; ks0 < nk; ks0 += AM_RING) {
+        auto steps = [&](int ks0, auto first_group) {
+            constexpr bool FIRST = decltype(first_group)::value;
             if (ks0 + AM_RING == nk) {
-                seek(next < items ? next : item);
-                if (next < items) issue_bias(next, (it + 1) & 1);
+                seek(more ? next : item);
+                if (more) issue_bias(next, (it + 1) & 1);
             }
 #pragma unroll
             for (int s = 0; s < AM_RING; s++) {
@@ -404,8 +420,10 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
                 for (int p = 0; p < PLANES; p++) {
                     bf[nxt][p] = *(const v4i *)(brn + p * 1024);
                     __builtin_amdgcn_sched_barrier(0);
-                    acc[p][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[cur][0], bf[cur][p], acc[p][0], 0, 0, 0);
-                    acc[p][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[cur][1], bf[cur][p], acc[p][1], 0, 0, 0);
+                    // (the first step adds to the constant zero: clearing 32 registers a plane by hand is not hidden)
+                    const v16i zero = {};
+                    acc[p][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[cur][p], af[cur][0], FIRST && s == 0 ? zero : acc[p][0], 0, 0, 0);
+                    acc[p][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[cur][p], af[cur][1], FIRST && s == 0 ? zero : acc[p][1], 0, 0, 0);
                     if (p == 0) issue_b(s, 0);
                     if (p == 1) issue_b(s, 1);
                     if (p == 2) issue_a(s, 0);
@@ -417,19 +435,23 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
 #pragma unroll
                 for (int p = 0; p < PLANES; p++) asm volatile("" ::"v"(bf[cur][p]));
                 asm volatile("" ::"v"(af[cur][0]), "v"(af[cur][1]));
-                // The stores of the previous item's recombination are younger than the copies this step needs
-                // but older than the ones it issued; the first step of an item therefore waits for everything
-                // except its own copies, which drains those stores whatever order stores and loads complete in.
-                if (ks0 == 0 && s == 0) wait_vmcnt<4>();
-                else wait_vmcnt<4 * (AM_DEPTH - 1)>();  // step ks+2 has landed
+                // Step ks+2 has landed once at most six iterations' copies are outstanding.  The counter goes down in the order
+                // of issue, and the AM_STORES stores of the previous item's recombination lie between its last copies and
+                // this item's first: for six steps they may be outstanding as well, so that no step waits for memory to
+                // take them (waiting at the first step cost 3 % of a 1536 x 4096 product on 2^21 words, 149 -> 145 ms for two).
+                if (FIRST && s < AM_DEPTH - 1 && stores_pending) wait_vmcnt<4 * (AM_DEPTH - 1) + AM_STORES>();
+                else wait_vmcnt<4 * (AM_DEPTH - 1)>();
                 __syncthreads();
             }
-        }
+        };
+        steps(0, std::true_type());
+        for (int ks0 = AM_RING; ks0 < nk; ks0 += AM_RING) steps(ks0, std::false_type());
         // here bf[0]/af[0] already hold step 0 of the next item
 
         // Recombine planes, add the offset term 128 * sum_v W'[v][i] * sum_p 256^p, reduce mod q, store.
-        // Accumulator register r of a lane holds output row 8*(r/4) + 4*(lane/32) + r%4 of the 32x32
-        // block, column lane%32.
+        // Accumulator register r of a lane holds output lane%32 of the block, word 16*(r/8) + 8*(lane/32) + r%8 (plane_row).
+        // 32 outputs x 16 words at a time pass through LDS so that a store writes whole lines: outputs lie a power of two
+        // apart, and stores of 16 bytes to each of 32 of them at once all went to one L2 channel.
         const u64 q = pr.q[limb];
         const double q_inv = pr.q_inv[limb], qd = (double)q;
         u64 ones = 0;
@@ -438,40 +460,45 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
         const bool whole = i0 + 64 <= m;  // all 64 outputs of this wave exist (wave-uniform): stores need no bounds check
 #pragma unroll
         for (int mb = 0; mb < 2; mb++) {
+            const int ib = i0 + mb * 32;
+            const double b_fp = FP_EPI ? ((const double *)bl)[wv * 64 + mb * 32 + nl] : 0.0;
+            const int64_t b_int = FP_EPI ? 0 : (int64_t)((u64)(int64_t)((const int *)bl)[wv * 64 + mb * 32 + nl] * ones);
 #pragma unroll
-            for (int c = 0; c < 4; c++) {
-                const int ib = i0 + mb * 32 + 8 * c + 4 * g;  // rows ib .. ib+3
-                u64 res[4];
-                if (FP_EPI) {
-                    const double *b4 = (const double *)bl + (ib - m_tile * AM_TILE_M);
+            for (int h = 0; h < 2; h++) {
 #pragma unroll
-                    for (int e = 0; e < 4; e++) {
-                        int S[PLANES];
+                for (int c = 0; c < 4; c++) {
+                    u64 res[2];
 #pragma unroll
-                        for (int p = 0; p < PLANES; p++) S[p] = acc[p][mb][4 * c + e];
-                        res[e] = recombine_fp<PLANES>(S, b4[e], qd, q_inv);
+                    for (int e = 0; e < 2; e++) {
+                        const int r = 8 * h + 2 * c + e;
+                        if (FP_EPI) {
+                            int S[PLANES];
+#pragma unroll
+                            for (int p = 0; p < PLANES; p++) S[p] = acc[p][mb][r];
+                            res[e] = recombine_fp<PLANES>(S, b_fp, qd, q_inv);
+                        } else {
+                            int64_t t = b_int;
+#pragma unroll
+                            for (int p = 0; p < PLANES; p++) t += (int64_t)((u64)(int64_t)acc[p][mb][r] << (8 * p));
+                            res[e] = reduce_signed(t, q, q_inv);
+                        }
                     }
-                } else {
-                    const v4i b4 = *(const v4i *)((const int *)bl + (ib - m_tile * AM_TILE_M));
-#pragma unroll
-                    for (int e = 0; e < 4; e++) {
-                        int64_t t = (int64_t)((u64)(int64_t)b4[e] * ones);
-#pragma unroll
-                        for (int p = 0; p < PLANES; p++) t += (int64_t)((u64)(int64_t)acc[p][mb][4 * c + e] << (8 * p));
-                        res[e] = reduce_signed(t, q, q_inv);
-                    }
+                    *(ulonglong2 *)(o_lds + nl * AM_OROW + g * 64 + c * 16) = make_ulonglong2(res[0], res[1]);
                 }
-                u64 *o = out + (size_t)ib * ct_words_out + off_out + nl;
-                if (whole) {
+                wave_lds_fence();
 #pragma unroll
-                    for (int e = 0; e < 4; e++) o[(size_t)e * ct_words_out] = res[e];
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; e++)
-                        if (ib + e < m) o[(size_t)e * ct_words_out] = res[e];
+                for (int k = 0; k < 4; k++) {
+                    const int row = 8 * k + (lane >> 3);
+                    const ulonglong2 v = *(const ulonglong2 *)(o_lds + row * AM_OROW + (lane & 7) * 16);
+                    u64 *o = out + (size_t)(ib + row) * ct_words_out + off_out + 16 * h + (lane & 7) * 2;
+                    if (whole) *(ulonglong2 *)o = v;
+                    else if (ib + row < m) *(ulonglong2 *)o = v;
                 }
+                wave_lds_fence();
             }
         }
+        stores_pending = whole;
+        if (!whole) wait_vmcnt<0>();  // some stores were left out: start the next item from a known count
         item = next;
     }
     wait_vmcnt<0>();  // no copy may still be in flight into LDS when the workgroup ends
