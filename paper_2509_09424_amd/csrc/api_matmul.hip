@@ -273,20 +273,23 @@ static int matmul_run(ensi_ctx *ctx, const ensi_gk *gk, const ensi_ct *in, Matmu
     }
     // ---- workspaces.  With rotations, operand v is written to slot v of ws_virt (inputs used
     // unrotated are copied there); without, the operands are the input batch itself.
-    const int chunk = 128;
+    // Rotations per launch and packed inputs raised together, for equal bytes on every ring: the same counts on a ring of 2^14
+    // left the chip a quarter full (1536 x 1536 there: 24 rounds of launches, 9.0 ms; 6 rounds, 7.4 ms).
+    const int more = ctx->log_n < 12 ? 4 : 16 - ctx->log_n, chunk = 128 << more;
     const u64 *xbase = in->d;
     if (n_rot) {
-        const int GS = std::min(n_in, 16);  // packed inputs raised together (about 48 MiB of digits each at 16 limbs)
+        const int GS = std::min(n_in, 16 << more);  // (about 48 MiB of digits each at 16 limbs of the largest ring)
         const size_t rw = raised_words(ctx, l1);
         if ((rc = grow(ctx, &ctx->ws_digits, &ctx->ws_digits_words, (size_t)GS * rw))) return rc;
         if ((rc = grow(ctx, &ctx->ws_u, &ctx->ws_u_words, (size_t)std::min(chunk, n_rot) * 2 * ext * N))) return rc;
         if ((rc = grow(ctx, &ctx->ws_virt, &ctx->ws_virt_words, (size_t)n_v * in_ct))) return rc;
-        if ((rc = ensure_desc(ctx, n_rot))) return rc;
+        if ((rc = ensure_desc(ctx, n_rot + n_in))) return rc;
         xbase = ctx->ws_virt;
         // Packed inputs are raised GS at a time and their rotations ordered by amount, so that the GS
         // rotations that use one key sit next to each other in a launch: the blocks that read a key tile then
         // run at nearly the same time on one XCD and all but the first read are served by its L2.
         std::vector<RotDesc> desc;
+        std::vector<RotDesc> copies;              // inputs used unrotated
         std::vector<std::pair<int, int>> groups;  // (first descriptor, count) per group of GS packed inputs
         for (int G0 = 0; G0 < n_in; G0 += GS) {
             const int first = (int)desc.size();
@@ -295,12 +298,13 @@ static int matmul_run(ensi_ctx *ctx, const ensi_gk *gk, const ensi_ct *in, Matmu
                     const int v = vid[(size_t)G * c_tot + rho];
                     if (v < 0) continue;
                     u64 *slot = ctx->ws_virt + (size_t)v * in_ct;
-                    if (rho == 0) {
-                        ENSI_HIP(ctx, hipMemcpyAsync(slot, in->d + (size_t)G * in_ct, in_ct * sizeof(u64), hipMemcpyDeviceToDevice, st));
-                        continue;
-                    }
                     RotDesc ds = {};
                     ds.c0 = in->d + (size_t)G * in_ct;
+                    if (rho == 0) {
+                        ds.out = slot;
+                        copies.push_back(ds);
+                        continue;
+                    }
                     ds.digits = ctx->ws_digits + (size_t)(G - G0) * rw;
                     ds.key = key_of[rho];
                     ds.out = slot;
@@ -311,7 +315,10 @@ static int matmul_run(ensi_ctx *ctx, const ensi_gk *gk, const ensi_ct *in, Matmu
             }
             groups.push_back({first, (int)desc.size() - first});
         }
+        const size_t n_desc = desc.size();
+        desc.insert(desc.end(), copies.begin(), copies.end());
         ENSI_HIP(ctx, host_to_device(ctx, ctx->ws_desc, desc.data(), desc.size() * sizeof(RotDesc), st));
+        if (!copies.empty()) launch_copy_cts(ctx, ctx->ws_desc + n_desc, (int)copies.size(), in_ct, st);
         // ---- unpack: one ModUp per packed input, shared by all its rotations
         for (size_t gi = 0; gi < groups.size(); gi++) {
             if (!groups[gi].second) continue;

@@ -439,6 +439,7 @@ void launch_uniform(ensi_ctx *ctx, u64 *out, const LimbMap &map, u64 seed, u64 s
 // out = a (.) b_mont  (+ add) per limb row; rows cycle through map
 void launch_mul_mont(ensi_ctx *ctx, u64 *out, const u64 *a, const u64 *b_mont, int n_rows, const LimbMap &map,
                      hipStream_t st);
+void launch_copy_cts(ensi_ctx *ctx, const RotDesc *d_desc, int n, size_t words, hipStream_t st);
 void launch_add(ensi_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int n_rows, const LimbMap &map, hipStream_t st);
 void launch_to_mont(ensi_ctx *ctx, u64 *data, int n_rows, const LimbMap &map, hipStream_t st);
 void launch_from_mont(ensi_ctx *ctx, u64 *data, int n_rows, const LimbMap &map, hipStream_t st);

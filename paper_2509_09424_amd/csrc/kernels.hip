@@ -397,6 +397,18 @@ __global__ __launch_bounds__(EW_THREADS) void k_add(u64 *out, const u64 *a, cons
     const size_t o = (size_t)row * N + idx;
     out[o] = add_mod(a[o], b[o], q);
 }
+// Whole ciphertexts from c0 to out of their descriptors.  grid (chunks, n)
+__global__ __launch_bounds__(256) void k_copy_cts(const RotDesc *desc, u32 words) {
+    const u64 *src = desc[blockIdx.y].c0;
+    u64 *dst = desc[blockIdx.y].out;
+    for (u32 i = (blockIdx.x * 256 + threadIdx.x) * 2; i < words; i += gridDim.x * 512)  // two words at a time: rings have an even size
+        *(ulonglong2 *)(dst + i) = *(const ulonglong2 *)(src + i);
+}
+void launch_copy_cts(ensi_ctx *ctx, const RotDesc *d_desc, int n, size_t words, hipStream_t st) {
+    ScopedTimer t(ctx, "copy_cts", st);
+    const unsigned chunks = (unsigned)std::min<size_t>((words + 511) / 512, 64);
+    for (int o = 0; o < n; o += 65535) hipLaunchKernelGGL(k_copy_cts, dim3(chunks, std::min(n - o, 65535)), dim3(256), 0, st, d_desc + o, (u32)words);
+}
 void launch_add(ensi_ctx *ctx, u64 *out, const u64 *a, const u64 *b, int n_rows, const LimbMap &map, hipStream_t st) {
     dim3 grid((ctx->N + EW_THREADS - 1) / EW_THREADS, n_rows);
     hipLaunchKernelGGL(k_add, grid, dim3(EW_THREADS), 0, st, out, a, b, map, ctx->d_pc, ctx->N);
