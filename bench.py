@@ -516,11 +516,13 @@ def roofline_for(w, prof):
     hbm = {
         # fused path (N = 2^16, ciphertext primes below 2^50)
         "ks_pre": ks_sum(lambda l, b, e, rot, ra, sw, key: ra * 2 * l),
-        "ks_modup_fcols": ks_sum(lambda l, b, e, rot, ra, sw, key: ra * (3 * l + b * e + l)),        # y, c1, c0 in; raised digits and P*c0 out
+        "ks_modup_fcols": ks_sum(lambda l, b, e, rot, ra, sw, key: ra * (2 * l + b * e + l)),        # c1, c0 in; raised digits and P*c0 out
         "ks_frows": ks_sum(lambda l, b, e, rot, ra, sw, key: ra * 2 * (b * e + l)),
-        # ciphertext limbs: digits, P*c0, key in; accumulators out
+        # all limbs: digits, P*c0, key in; accumulators out
+        "ks_inner": ks_sum(lambda l, b, e, rot, ra, sw, key: rot * (b * e + l) + sw * 2 * e + key * 2 * b * e),
+        # its ciphertext limbs alone: digits, P*c0, key in; accumulators out
         "ks_inner_irows": ks_sum(lambda l, b, e, rot, ra, sw, key: rot * (b * l + l) + sw * 2 * l + key * 2 * b * l),
-        # special limbs (integer arithmetic)
+        # its special limbs alone
         "ks_inner_irows_wide": ks_sum(lambda l, b, e, rot, ra, sw, key: rot * b * K + sw * 2 * K + key * 2 * b * K),
         "ks_icols_special": ks_sum(lambda l, b, e, rot, ra, sw, key: sw * 4 * K),                    # special limbs in, split residues out
         "ks_icols_moddown": ks_sum(lambda l, b, e, rot, ra, sw, key: sw * (2 * l + 2 * K + 2 * l)),  # accumulators and residues in, ciphertext out
@@ -538,7 +540,12 @@ def roofline_for(w, prof):
         "rescale_byte_planes": (w.d_mid or 0) * (2 * L + 2 * (L - 1) * 7 / 8.0),
         # plaintext multiplication, summed and rescaled (the few plaintext limbs are not counted)
         "pm_fcols": pm_sum(lambda l, t, o, src: src * 4 * l),                    # source limbs in, column-transformed limbs out
-        "pm_frows_mac_irows": pm_sum(lambda l, t, o, src: (t + o) * 2 * l),      # those in, one sum per output limb out
+        "pm_frows_mac_irows": pm_sum(lambda l, t, o, src: (t + o) * 2 * l),      # those in per product, one sum per output limb out
+        # the same by the rule of the library: term by term, or, where sources enter at least two products each, in three kernels
+        "pm_rows_mac": pm_sum(lambda l, t, o, src: (t + o) * 2 * l if t < 2 * src else 0),
+        "pm_frows": pm_sum(lambda l, t, o, src: src * 4 * l if t >= 2 * src else 0),
+        "pm_mac": pm_sum(lambda l, t, o, src: (src + o) * 2 * l if t >= 2 * src else 0),
+        "pm_irows": pm_sum(lambda l, t, o, src: o * 4 * l if t >= 2 * src else 0),
         "pm_icols_last": pm_sum(lambda l, t, o, src: o * 4),
         "pm_icols_rescale": pm_sum(lambda l, t, o, src: o * (2 * (l - 1) + 2 + 2 * (l - 1))),
     }
