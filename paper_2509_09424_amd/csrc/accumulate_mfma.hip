@@ -569,7 +569,7 @@ int launch_accumulate_mfma(ensi_ctx *ctx, const u64 *xbase, size_t xstride, int 
         if (ctx->ws_xp) (void)hipFree(ctx->ws_xp);
         ctx->ws_xp = nullptr;
         ctx->ws_xp_words = 0;
-        if (hipMalloc((void **)&ctx->ws_xp, xp_words * 8) != hipSuccess) {
+        if (ctx->pool->alloc((void **)&ctx->ws_xp, xp_words * 8) != hipSuccess) {
             ctx->err = "device allocation of the byte-plane workspace failed";
             return ENSI_E_NOMEM;
         }
@@ -632,7 +632,7 @@ int launch_matrix_rate(ensi_ctx *ctx, double seconds, double *ops_per_second, hi
     }
     int *d_seed = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
-    hipError_t e = hipMalloc((void **)&d_seed, (h.size() + 1) * sizeof(int));
+    hipError_t e = ctx->pool->alloc((void **)&d_seed, (h.size() + 1) * sizeof(int));
     if (e == hipSuccess) e = hipMemcpy(d_seed, h.data(), h.size() * sizeof(int), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);

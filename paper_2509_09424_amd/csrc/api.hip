@@ -53,6 +53,19 @@ int stage_prealloc(ensi_ctx *ctx) {
 }
 
 // ------------------------------------------------------------- memory of handles
+hipError_t DevPool::alloc(void **p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipErrorOutOfMemory) return e;
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        if (blocks.empty()) return e;
+        for (auto &b : blocks) (void)hipFree(b.second);
+        blocks.clear();
+        held = 0;
+    }
+    (void)hipGetLastError();
+    return hipMalloc(p, bytes);
+}
 hipError_t DevPool::take(void **p, size_t bytes, size_t *got) {
     {
         std::lock_guard<std::mutex> lock(mu);
@@ -68,16 +81,7 @@ hipError_t DevPool::take(void **p, size_t bytes, size_t *got) {
     }
     if (*p) return hipDeviceSynchronize();
     *got = bytes;
-    hipError_t e = hipMalloc(p, bytes);
-    if (e == hipErrorOutOfMemory) {
-        (void)hipGetLastError();
-        std::lock_guard<std::mutex> lock(mu);
-        for (auto &b : blocks) (void)hipFree(b.second);
-        blocks.clear();
-        held = 0;
-        e = hipMalloc(p, bytes);
-    }
-    return e;
+    return alloc(p, bytes);
 }
 void DevPool::give(void *p, size_t bytes) {
     {
@@ -626,7 +630,7 @@ int encode_window(ensi_ctx *ctx, const double *slots, int n_pt, int n_slots, int
         return ENSI_OK;
     }
     DevBuf d_slots, d_coeffs;
-    if (d_slots.alloc((size_t)n_pt * n_slots * 8) != hipSuccess || d_coeffs.alloc((size_t)n_pt * ctx->N * 8) != hipSuccess)
+    if (d_slots.alloc(ctx, (size_t)n_pt * n_slots * 8) != hipSuccess || d_coeffs.alloc(ctx, (size_t)n_pt * ctx->N * 8) != hipSuccess)
         ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in encode");
     ENSI_HIP(ctx, hipMemcpy(d_slots.p, slots, (size_t)n_pt * n_slots * 8, hipMemcpyHostToDevice));
     ENSI_HIP(ctx, launch_encode(ctx, d_slots.as<double>(), n_pt, n_slots, slot0, slot_step, scale, d_coeffs.as<int64_t>(), nullptr));
@@ -649,14 +653,14 @@ extern "C" int ensi_pt_set_scale(ensi_pt *pt, double scale) {
 extern "C" int ensi_pt_import(ensi_ctx *ctx, const int64_t *coeffs, int32_t n_pt, int32_t limbs, ensi_pt **out) {
     if (!ctx || !coeffs || !out || n_pt < 1 || limbs < 1 || limbs > ctx->L) return ENSI_E_BADARG;
     DevBuf d_coeffs;
-    if (d_coeffs.alloc((size_t)n_pt * ctx->N * 8) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in pt_import");
+    if (d_coeffs.alloc(ctx, (size_t)n_pt * ctx->N * 8) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in pt_import");
     ENSI_HIP(ctx, hipMemcpy(d_coeffs.p, coeffs, (size_t)n_pt * ctx->N * 8, hipMemcpyHostToDevice));
     return pt_from_coeffs(ctx, d_coeffs.as<int64_t>(), n_pt, limbs, ctx->scale, out);
 }
 extern "C" int ensi_pt_export(ensi_ctx *ctx, const ensi_pt *pt, int64_t *coeffs) {
     if (!ctx || !pt || !coeffs) return ENSI_E_BADARG;
     DevBuf d_out;
-    if (d_out.alloc((size_t)pt->n * ctx->N * 8) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in pt_export");
+    if (d_out.alloc(ctx, (size_t)pt->n * ctx->N * 8) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in pt_export");
     launch_center_i64(ctx, pt->d, (size_t)pt->limbs * ctx->N, pt->n, d_out.as<int64_t>(), nullptr);
     ENSI_HIP(ctx, hipMemcpy(coeffs, d_out.p, (size_t)pt->n * ctx->N * 8, hipMemcpyDeviceToHost));
     return ENSI_OK;
@@ -750,7 +754,7 @@ extern "C" int ensi_ct_checksum(ensi_ctx *ctx, const ensi_ct *ct, uint64_t *sums
     if (ct->prepared) ENSI_FAIL(ctx, ENSI_E_BADARG, "the batch holds prepared weights, which only ensi_ccmm_av reads");
     hipStream_t st = (hipStream_t)stream;
     DevBuf d_sums;
-    if (d_sums.alloc((size_t)ct->n * 8) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in ct_checksum");
+    if (d_sums.alloc(ctx, (size_t)ct->n * 8) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in ct_checksum");
     ENSI_HIP(ctx, hipMemsetAsync(d_sums.p, 0, (size_t)ct->n * 8, st));
     launch_ct_checksum(ctx, ct->d, ct->n, ct->limbs, ct->limbs_alloc, d_sums.as<u64>(), st);
     ENSI_HIP(ctx, hipMemcpyAsync(sums, d_sums.p, (size_t)ct->n * 8, hipMemcpyDeviceToHost, st));
@@ -803,8 +807,8 @@ extern "C" int ensi_encrypt(ensi_ctx *ctx, const ensi_pk *pk, const ensi_pt *pt,
     LimbMap mq = make_map(ctx, l1, false);
     DevBuf d_small, d_v, d_t, d_e;
     const size_t rows = (size_t)n * l1;
-    if (d_small.alloc(3 * pn) != hipSuccess || d_v.alloc(rows * N * 8) != hipSuccess || d_t.alloc(rows * N * 8) != hipSuccess ||
-        d_e.alloc(rows * N * 8) != hipSuccess) {
+    if (d_small.alloc(ctx, 3 * pn) != hipSuccess || d_v.alloc(ctx, rows * N * 8) != hipSuccess || d_t.alloc(ctx, rows * N * 8) != hipSuccess ||
+        d_e.alloc(ctx, rows * N * 8) != hipSuccess) {
         ensi_ct_free(ct);
         *out = nullptr;
         ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in encrypt");
@@ -874,8 +878,8 @@ extern "C" int ensi_decrypt(ensi_ctx *ctx, const ensi_sk *sk, const ensi_ct *ct,
     }
     LimbMap mq = make_map(ctx, use, false);
     DevBuf d_m, d_coef, d_out;
-    if (d_m.alloc((size_t)n * use * N * 8) != hipSuccess || d_coef.alloc((size_t)n * N * 8) != hipSuccess ||
-        d_out.alloc((size_t)n * n_slots * 8) != hipSuccess)
+    if (d_m.alloc(ctx, (size_t)n * use * N * 8) != hipSuccess || d_coef.alloc(ctx, (size_t)n * N * 8) != hipSuccess ||
+        d_out.alloc(ctx, (size_t)n * n_slots * 8) != hipSuccess)
         ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in decrypt");
     ENSI_HIP(ctx, hipDeviceSynchronize());
     const size_t poly_words = (size_t)ct->limbs_alloc * N;
@@ -982,7 +986,7 @@ int ensure_desc(ensi_ctx *ctx, size_t n) {
     if (ctx->ws_desc) ENSI_HIP(ctx, hipFree(ctx->ws_desc));
     ctx->ws_desc = nullptr;
     ctx->ws_desc_n = 0;
-    if (hipMalloc((void **)&ctx->ws_desc, n * sizeof(RotDesc)) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "descriptor allocation failed");
+    if (ctx->pool->alloc((void **)&ctx->ws_desc, n * sizeof(RotDesc)) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "descriptor allocation failed");
     ctx->ws_desc_n = n;
     return ENSI_OK;
 }

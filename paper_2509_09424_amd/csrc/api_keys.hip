@@ -87,7 +87,7 @@ static int make_sk(ensi_ctx *ctx, const std::vector<int8_t> &sv, ensi_sk **out) 
     sk->ctx = ctx;
     sk->s = sv;
     sk->d_s_hat = nullptr;
-    if (d_small.alloc((size_t)N) != hipSuccess || hipMalloc((void **)&sk->d_s_hat, (size_t)ext * N * 8) != hipSuccess) {
+    if (d_small.alloc(ctx, (size_t)N) != hipSuccess || ctx->pool->alloc((void **)&sk->d_s_hat, (size_t)ext * N * 8) != hipSuccess) {
         ensi_sk_free(sk);
         ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed for the secret key");
     }
@@ -126,8 +126,8 @@ extern "C" int ensi_keygen(ensi_ctx *ctx, const int8_t *s, const int8_t *e, uint
         ensi_pk_free(pk);
         return code;
     };
-    if (d_small.alloc((size_t)N) != hipSuccess || d_e.alloc((size_t)L * N * 8) != hipSuccess || d_a.alloc((size_t)L * N * 8) != hipSuccess ||
-        hipMalloc((void **)&pk->d_pk, (size_t)2 * L * N * 8) != hipSuccess) {
+    if (d_small.alloc(ctx, (size_t)N) != hipSuccess || d_e.alloc(ctx, (size_t)L * N * 8) != hipSuccess || d_a.alloc(ctx, (size_t)L * N * 8) != hipSuccess ||
+        ctx->pool->alloc((void **)&pk->d_pk, (size_t)2 * L * N * 8) != hipSuccess) {
         ctx->err = "device allocation failed in keygen";
         return fail(ENSI_E_NOMEM);
     }
@@ -166,8 +166,8 @@ struct KeygenScratch {
 };
 static int keygen_scratch(ensi_ctx *ctx, const ensi_sk *sk, KeygenScratch &k, hipStream_t st) {
     const int N = ctx->N, ext = ctx->L + ctx->K;
-    if (k.d_s.alloc((size_t)ext * N * 8) != hipSuccess || k.d_target.alloc((size_t)ext * N * 8) != hipSuccess || k.d_e8.alloc(N) != hipSuccess ||
-        k.d_e.alloc((size_t)ext * N * 8) != hipSuccess || k.d_fac.alloc((size_t)ext * 8) != hipSuccess || k.d_s8.alloc(N) != hipSuccess)
+    if (k.d_s.alloc(ctx, (size_t)ext * N * 8) != hipSuccess || k.d_target.alloc(ctx, (size_t)ext * N * 8) != hipSuccess || k.d_e8.alloc(ctx, N) != hipSuccess ||
+        k.d_e.alloc(ctx, (size_t)ext * N * 8) != hipSuccess || k.d_fac.alloc(ctx, (size_t)ext * 8) != hipSuccess || k.d_s8.alloc(ctx, N) != hipSuccess)
         ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in key generation");
     (void)hipMemcpy(k.d_s8.p, sk->s.data(), N, hipMemcpyHostToDevice);
     launch_small_to_rns(ctx, k.d_s8.as<int8_t>(), 1, make_map(ctx, ctx->L, true), k.d_s.as<u64>(), st);  // coefficient form of s
@@ -227,7 +227,7 @@ extern "C" int ensi_galois_keygen(ensi_ctx *ctx, const ensi_sk *sk, const int32_
         const u32 g = galois_element(ctx, steps[t]);
         if (gk->keys.count(g)) continue;
         u64 *key = nullptr;
-        if (hipMalloc((void **)&key, (size_t)beta * 2 * ext * N * 8) != hipSuccess) {
+        if (ctx->pool->alloc((void **)&key, (size_t)beta * 2 * ext * N * 8) != hipSuccess) {
             ensi_gk_free(gk);
             ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation of a Galois key failed");
         }
@@ -265,7 +265,7 @@ extern "C" int ensi_relin_keygen(ensi_ctx *ctx, const ensi_sk *sk, const int8_t 
         return rc;
     }
     u64 *key = nullptr;
-    if (hipMalloc((void **)&key, (size_t)beta * 2 * ext * N * 8) != hipSuccess) {
+    if (ctx->pool->alloc((void **)&key, (size_t)beta * 2 * ext * N * 8) != hipSuccess) {
         ensi_gk_free(gk);
         ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation of the evaluation key failed");
     }
@@ -300,7 +300,7 @@ extern "C" void ensi_gk_free(ensi_gk *gk) {
 static int upload_residues(ensi_ctx *ctx, u64 *dst, const uint64_t *words, int n_rows, const LimbMap &map, const char *what) {
     const size_t bytes = (size_t)n_rows * ctx->N * 8;
     DevBuf d_bad;
-    if (d_bad.alloc(4) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in %s", what);
+    if (d_bad.alloc(ctx, 4) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in %s", what);
     ENSI_HIP(ctx, hipMemset(d_bad.p, 0, 4));
     ENSI_HIP(ctx, hipMemcpy(dst, words, bytes, hipMemcpyHostToDevice));
     launch_count_noncanonical(ctx, dst, n_rows, map, d_bad.as<unsigned int>(), nullptr);
@@ -328,7 +328,7 @@ extern "C" int ensi_pk_export(ensi_ctx *ctx, const ensi_pk *pk, uint64_t *words)
     const size_t bytes = (size_t)2 * L * N * 8;
     LimbMap mq = make_map(ctx, L, false);
     DevBuf d_t;
-    if (d_t.alloc(bytes) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in pk_export");
+    if (d_t.alloc(ctx, bytes) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in pk_export");
     ENSI_HIP(ctx, hipDeviceSynchronize());
     ENSI_HIP(ctx, hipMemcpy(d_t.p, pk->d_pk, bytes, hipMemcpyDeviceToDevice));
     launch_from_mont(ctx, d_t.as<u64>(), 2 * L, mq, nullptr);
@@ -344,7 +344,7 @@ extern "C" int ensi_pk_import(ensi_ctx *ctx, const uint64_t *words, ensi_pk **ou
     ensi_pk *pk = new ensi_pk();
     pk->ctx = ctx;
     pk->d_pk = nullptr;
-    if (hipMalloc((void **)&pk->d_pk, (size_t)2 * L * N * 8) != hipSuccess) {
+    if (ctx->pool->alloc((void **)&pk->d_pk, (size_t)2 * L * N * 8) != hipSuccess) {
         ensi_pk_free(pk);
         ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in pk_import");
     }
@@ -381,7 +381,7 @@ extern "C" int ensi_gk_export(ensi_ctx *ctx, const ensi_gk *gk, int32_t step, ui
     const size_t bytes = (size_t)beta * 2 * ext * N * 8;
     LimbMap mext = make_map(ctx, ctx->L, true);
     DevBuf d_t;
-    if (d_t.alloc(bytes) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in gk_export");
+    if (d_t.alloc(ctx, bytes) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in gk_export");
     ENSI_HIP(ctx, hipDeviceSynchronize());
     ENSI_HIP(ctx, hipMemcpy(d_t.p, it->second, bytes, hipMemcpyDeviceToDevice));
     if (ctx->ks16) launch_ks16_key_plain(ctx, d_t.as<u64>(), beta * 2 * ext, nullptr);
@@ -398,7 +398,7 @@ extern "C" int ensi_gk_import(ensi_ctx *ctx, ensi_gk **gk_io, int32_t step, cons
     const u32 g = galois_element(ctx, step);
     LimbMap mext = make_map(ctx, ctx->L, true);
     u64 *key = nullptr;
-    if (hipMalloc((void **)&key, (size_t)beta * 2 * ext * N * 8) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation of a key failed");
+    if (ctx->pool->alloc((void **)&key, (size_t)beta * 2 * ext * N * 8) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation of a key failed");
     int rc = upload_residues(ctx, key, words, beta * 2 * ext, mext, "gk_import");
     if (rc) {
         (void)hipFree(key);

@@ -25,14 +25,14 @@ static int pt_prepare(ensi_ctx *ctx, const ensi_pt *pt, bool fused, hipStream_t 
     const int rows = pt->n * pt->limbs;
     const size_t bytes = (size_t)rows * ctx->N * 8;
     u64 *buf = nullptr;
-    if (hipMalloc((void **)&buf, bytes) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed for the transformed plaintext");
+    if (ctx->pool->alloc((void **)&buf, bytes) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed for the transformed plaintext");
     const LimbMap map = make_map(ctx, pt->limbs, false);
     hipError_t e = hipMemcpyAsync(buf, pt->d, bytes, hipMemcpyDeviceToDevice, st);
     if (e == hipSuccess) {
         launch_ntt(ctx, buf, rows, map, false, st);
         if (fused) {
             u64 *f = nullptr;
-            if (hipMalloc((void **)&f, bytes) != hipSuccess) {
+            if (ctx->pool->alloc((void **)&f, bytes) != hipSuccess) {
                 (void)hipFree(buf);
                 ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed for the transformed plaintext");
             }

@@ -13,7 +13,7 @@ struct DevBuf {
     ~DevBuf() {
         if (p) (void)hipFree(p);
     }
-    hipError_t alloc(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 8); }
+    hipError_t alloc(ensi_ctx *ctx, size_t bytes) { return ctx->pool->alloc(&p, bytes ? bytes : 8); }
     template <class T>
     T *as() { return (T *)p; }
 };
@@ -51,7 +51,7 @@ inline int grow(ensi_ctx *ctx, u64 **p, size_t *have, size_t need) {
     if (*p) ENSI_HIP(ctx, hipFree(*p));
     *p = nullptr;
     *have = 0;
-    hipError_t e = hipMalloc((void **)p, need * sizeof(u64));
+    hipError_t e = ctx->pool->alloc((void **)p, need * sizeof(u64));
     if (e != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation of %zu bytes failed: %s", need * sizeof(u64), hipGetErrorString(e));
     *have = need;
     return ENSI_OK;

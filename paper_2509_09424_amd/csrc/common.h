@@ -200,7 +200,7 @@ struct StageSlot {
 
 // Device memory of freed plaintext and ciphertext handles, kept for the next handle of about the same size: freeing a large
 // block costs a quarter of a millisecond.  Bounded (KEEP_EACH, KEEP_ALL); emptied when the context is freed, or when an
-// allocation fails.  Shared by the context and its handles, which may outlive it, and safe with several threads.  The
+// allocation of the library fails.  Shared by the context and its handles, which may outlive it, and safe with several threads.  The
 // release of a block waits for nothing; taking one waits for the device, as hipFree did when the block was freed.
 struct DevPool {
     static constexpr size_t KEEP_EACH = (size_t)256 << 20, KEEP_ALL = (size_t)1 << 30;
@@ -208,6 +208,7 @@ struct DevPool {
     std::multimap<size_t, void *> blocks;  // by size
     size_t held = 0;
     bool closed = false;
+    hipError_t alloc(void **p, size_t bytes);  // hipMalloc, with the kept blocks given back first if the card is full
     hipError_t take(void **p, size_t bytes, size_t *got);
     void give(void *p, size_t bytes);
     void close();

@@ -578,8 +578,8 @@ static double2 *fft_passes(ensi_ctx *ctx, double2 *a, double2 *b, int count, hip
 static hipError_t fft_workspace(ensi_ctx *ctx, int n, double2 **a, double2 **b) {
     const size_t bytes = (size_t)std::min(n, FFT_CHUNK) * 2 * ctx->N * sizeof(double2);
     *a = *b = nullptr;
-    hipError_t e = hipMalloc((void **)a, bytes);
-    if (e == hipSuccess) e = hipMalloc((void **)b, bytes);
+    hipError_t e = ctx->pool->alloc((void **)a, bytes);
+    if (e == hipSuccess) e = ctx->pool->alloc((void **)b, bytes);
     if (e != hipSuccess && *a) {
         (void)hipFree(*a);
         *a = nullptr;
