@@ -58,13 +58,12 @@ hipError_t DevPool::alloc(void **p, size_t bytes) {
     if (e != hipErrorOutOfMemory) return e;
     {
         std::lock_guard<std::mutex> lock(mu);
-        if (blocks.empty()) return e;
         for (auto &b : blocks) (void)hipFree(b.second);
         blocks.clear();
         held = 0;
     }
     (void)hipGetLastError();
-    return hipMalloc(p, bytes);
+    return hipMalloc(p, bytes);  // also where nothing was kept: another thread may just have given it back
 }
 hipError_t DevPool::take(void **p, size_t bytes, size_t *got) {
     {
