@@ -597,15 +597,11 @@ static int pt_from_coeffs(ensi_ctx *ctx, const int64_t *d_coeffs, int n_pt, int 
 // Bytes of 64-bit words per polynomial that one chunk of a client-side batch takes (its host copies and workspaces are bounded by
 // that, and the copy of one chunk overlaps the kernels of the one before).
 static constexpr size_t CLIENT_CHUNK = (size_t)8 << 20;
-// Above this scale the encoding takes the 2N-point transform: with less than ten bits of a double left below the unit, another
-// order of summation rounds some coefficients to a neighbour, and the plaintexts encoded at a prime (masks, rotary
-// constants: once per program) should not change with the kernel.
-static constexpr double CLIENT_MAX_SCALE = 0x1p43;
 
 // slots: host [n_pt][n_slots]; plaintext y holds its values in slots [slot0 + y*slot_step, ...+n_slots)
 int encode_window(ensi_ctx *ctx, const double *slots, int n_pt, int n_slots, int slot0, int slot_step, int limbs, double scale,
                          ensi_pt **out) {
-    if (ctx->ks16 && scale <= CLIENT_MAX_SCALE) {
+    if (ctx->ks16) {
         ensi_pt *pt;
         int rc = pt_alloc(ctx, n_pt, limbs, scale, &pt);
         if (rc) return rc;

@@ -1,14 +1,16 @@
 // The client's side on the rings N = 2^12 .. 2^16 with ciphertext primes below 2^50: encode, encrypt, decrypt and decode on
 // the passes of the register transform (ntt16_core.h), so that a batch is a handful of launches.
 //
-// Encoding (paper, Preliminaries: SIMD Encoding).  Slot j is the value of m(X) at exp(i pi 5^j / N), and the exponents
-// 5^j mod 2N, j < n = N/2, are exactly those congruent to 1 modulo 4.  With 5^j = 4k + 1, w = exp(i pi / N) and
-// u_t = (m_t + i m_(t+n)) w^t,
-//   slot(k) = sum_(t<n) u_t exp(2 pi i t k / n)                                           (decode)
-//   m_t + i m_(t+n) = w^-t (scale / n) sum_k slot(k) exp(-2 pi i t k / n), rounded          (encode)
-// a complex transform of n points -- a quarter of the 2N-point one that the defining sums are a special case of.  It is
-// cut as t = 256 r + c, k = k1 + R2 k2 (R2 = N / 512 rows): a transform over 256 elements of a row and one over the R2
-// rows of a column, with the twiddle exp(+-2 pi i c k1 / n) between them, each on 2048 values in LDS.
+// Encoding (paper, Preliminaries: SIMD Encoding).  Slot j is the value of m(X) at exp(i pi 5^j / N), and both directions are
+// the length-2N transform of kernels.hip -- with the same butterflies on the same numbers in the same order, so that
+// coefficients and slots are those of that transform to the last bit, on every ring and at every scale.  What is left
+// out are butterflies on zeros and on outputs that nobody reads.  The exponents 5^j mod 2N, j < n = N/2, are exactly those
+// congruent to 1 modulo 4; with 5^j = 4k + 1 and the pass of stride s pairing the elements p and p + N/s:
+//   encode  Every pass keeps an element's p modulo 4, so that only the n elements with p = 4 p' + 1 ever differ from zero until
+//           the last two passes, which take x = (re, im) of those to the coefficients t and t + n.
+//   decode  The first pass has one input per butterfly, the second is read at its even outputs alone; the others are n points.
+// The n points are cut as t = 256 r + c, k = k1 + R2 k2 (R2 = N / 512 rows): the passes over 256 elements of a row and those
+// over the R2 rows of a column, each on 2048 values in LDS.
 //
 // These kernels are small against the copies from and to host memory beside them; what counts is their number.
 #include "common.h"
@@ -17,17 +19,14 @@
 #define CL_THREADS 256
 
 // ------------------------------------------------------------------ complex transforms in LDS
-__device__ __forceinline__ double2 cmul(double2 a, double2 b) { return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
-// exp(+-i pi e / N), 0 <= e < 2N, from the table of cosines
-template <int N, bool INV>
-__device__ __forceinline__ double2 unit(const double *cos_tab, u32 e) {
-    const double s = cos_tab[(e - N / 2) & (2 * N - 1)];
-    return make_double2(cos_tab[e & (2 * N - 1)], INV ? -s : s);
-}
-// LEN-point transforms of 2048 / LEN sequences at once (element t of sequence b at x[t * B + b], B = 2048 / LEN): radix-2
-// self-sorting passes between two buffers.  Returns the buffer that holds the result; every thread may read it.
-template <int N, int LEN, bool INV>
-__device__ __forceinline__ double2 *lds_dft(double2 *x, double2 *y, const double *cos_tab, int tid) {
+// sine of exponent e of the table of cosines, as the transform's passes read it
+template <int N>
+__device__ __forceinline__ double sine(const double *cos_tab, u32 e) { return cos_tab[(e - N / 2) & (2 * N - 1)]; }
+// Consecutive passes of the transform on 2048 / LEN sequences of LEN points at once (element t of sequence b at x[t * B + b],
+// B = 2048 / LEN).  The butterfly of element p in the pass of local stride s has the exponent base(b) s + STEP p s.
+// Returns the buffer that holds the result; every thread may read it.
+template <int N, int LEN, int STEP, class F>
+__device__ __forceinline__ double2 *lds_passes(double2 *x, double2 *y, const double *cos_tab, int tid, F base) {
     constexpr int B = 2048 / LEN;
     __syncthreads();
 #pragma unroll 1
@@ -36,10 +35,8 @@ __device__ __forceinline__ double2 *lds_dft(double2 *x, double2 *y, const double
         for (int m = 0; m < 4; m++) {
             const int w = tid + CL_THREADS * m, b = w % B, t = w / B;
             const int q = t & (s - 1), idx = t - q;
-            const double2 p0 = x[t * B + b], p1 = x[(t + LEN / 2) * B + b];
-            const double2 tw = unit<N, INV>(cos_tab, (u32)idx * (2 * N / LEN));
-            y[(q + 2 * idx) * B + b] = make_double2(p0.x + p1.x, p0.y + p1.y);
-            y[(q + 2 * idx + s) * B + b] = cmul(make_double2(p0.x - p1.x, p0.y - p1.y), tw);
+            const u32 e = (u32)base(b) * s + (u32)idx * STEP;
+            fft_butterfly(x[t * B + b], x[(t + LEN / 2) * B + b], cos_tab[e], sine<N>(cos_tab, e), y[(q + 2 * idx) * B + b], y[(q + 2 * idx + s) * B + b]);
         }
         __syncthreads();
         double2 *h = x;
@@ -56,20 +53,17 @@ __global__ __launch_bounds__(CL_THREADS) void k_cl_enc_rows(const double *slots,
                                                             const double *cos_tab, double2 *ws) {
     constexpr int N = Ring<S>::N, R2 = N / 512;
     __shared__ double2 buf[2][2048];
-    const int tid = threadIdx.x, y = y0 + blockIdx.y, first = slot0 + y * slot_step;
+    const int tid = threadIdx.x, y = y0 + blockIdx.y, first = slot0 + y * slot_step, k1 = blockIdx.x * 8;
     const double *z = slots + (size_t)blockIdx.y * n_slots;
 #pragma unroll
     for (int m = 0; m < 8; m++) {
         const int w = tid + CL_THREADS * m, row = w & 7, k2 = w >> 3;
-        const int j = (int)slot_of_k[blockIdx.x * 8 + row + R2 * k2] - first;
+        const int j = (int)slot_of_k[k1 + row + R2 * k2] - first;
         buf[0][w] = make_double2(j >= 0 && j < n_slots ? z[j] : 0.0, 0.0);
     }
-    const double2 *f = lds_dft<N, 256, true>(buf[0], buf[1], cos_tab, tid);
+    const double2 *f = lds_passes<N, 256, 4 * R2>(buf[0], buf[1], cos_tab, tid, [&](int row) { return 4 * (k1 + row) + 1; });
 #pragma unroll
-    for (int row = 0; row < 8; row++) {
-        const int k1 = blockIdx.x * 8 + row;
-        ws[((size_t)blockIdx.y * R2 + k1) * 256 + tid] = cmul(f[tid * 8 + row], unit<N, true>(cos_tab, (u32)tid * k1 * 4));
-    }
+    for (int row = 0; row < 8; row++) ws[((size_t)blockIdx.y * R2 + k1 + row) * 256 + tid] = f[tid * 8 + row];
 }
 // grid (TILES, n_pt): one tile of columns.  out: [n_pt][limbs][N] canonical residues
 template <int S>
@@ -84,29 +78,26 @@ __global__ __launch_bounds__(CL_THREADS) void k_cl_enc_cols(const double2 *ws, d
         const int w = tid + CL_THREADS * m, c = w % R::COLS, k1 = w / R::COLS;
         buf[0][w] = ws[((size_t)blockIdx.y * R2 + k1) * 256 + blockIdx.x * R::COLS + c];
     }
-    const double2 *f = lds_dft<N, R2, true>(buf[0], buf[1], cos_tab, tid);
-    double v[16];
+    const double2 *f = lds_passes<N, R2, 1024>(buf[0], buf[1], cos_tab, tid, [](int) { return 256; });
+    int64_t v[16];
 #pragma unroll
     for (int m = 0; m < 8; m++) {
-        const int w = tid + CL_THREADS * m, t = w / R::COLS * 256 + blockIdx.x * R::COLS + w % R::COLS;
-        const double2 x = cmul(f[w], unit<N, true>(cos_tab, t));
-        v[2 * m] = x.x * factor;
-        v[2 * m + 1] = x.y * factor;
-    }
-#pragma unroll
-    for (int i = 0; i < 16; i++) {  // round half away from zero
-        const double r = floor(fabs(v[i]) + 0.5);
-        v[i] = v[i] < 0 ? -r : r;
+        // the last two passes: one input of each butterfly is zero
+        double2 even, odd;
+        fft_butterfly(f[tid + CL_THREADS * m], make_double2(0.0, 0.0), cos_tab[N / 2], cos_tab[0], even, odd);
+        v[2 * m] = round_coeff(even.x * factor);
+        v[2 * m + 1] = round_coeff(odd.x * factor);
     }
     for (int l = 0; l < limbs; l++) {
         ArithFp ar;
         ar.init(load_prime(pcs, l));
+        auto residue = [&](int64_t x) { return ar.canon(ar.mid((double)(int)(x >> 32) * 4294967296.0) + (double)(u32)x); };
         u64 *o = out + ((size_t)blockIdx.y * limbs + l) * N;
 #pragma unroll
         for (int m = 0; m < 8; m++) {
             const int w = tid + CL_THREADS * m, t = w / R::COLS * 256 + blockIdx.x * R::COLS + w % R::COLS;
-            o[t] = ar.canon(v[2 * m]);
-            o[t + N / 2] = ar.canon(v[2 * m + 1]);
+            o[t] = residue(v[2 * m]);
+            o[t + N / 2] = residue(v[2 * m + 1]);
         }
     }
 }
@@ -255,17 +246,23 @@ __global__ __launch_bounds__(CL_THREADS) void k_cl_dec_cols(const u64 *ws, int u
 #pragma unroll
     for (int i = 0; i < 16; i++) m[i] = use > 1 ? crt_centred(r[0][i], r[1][i], crt) : r[0][i] > crt.q0 / 2 ? -(double)(crt.q0 - r[0][i]) : (double)r[0][i];
     __syncthreads();  // the tiles have been read
-    // values i and i + 8 are the coefficients t and t + N/2
+    // values i and i + 8 are the coefficients t and t + N/2: the first pass multiplies each by its power, the second adds them
 #pragma unroll
     for (int i = 0; i < 8; i++) {
         const int row = R::row(jj, i);
-        buf[0][row * R::COLS + c] = cmul(make_double2(m[i], m[i + 8]), unit<NI, false>(cos_tab, row * 256 + (u32)col));
+        const u32 t = row * 256 + (u32)col;
+        const double2 zero = make_double2(0.0, 0.0);
+        double2 unread, p0, p1, sum;
+        fft_butterfly(make_double2(m[i], 0.0), zero, cos_tab[t], sine<NI>(cos_tab, t), unread, p0);
+        fft_butterfly(make_double2(m[i + 8], 0.0), zero, cos_tab[t + NI / 2], sine<NI>(cos_tab, t + NI / 2), unread, p1);
+        fft_butterfly(p0, p1, 0.0, 0.0, sum, unread);
+        buf[0][row * R::COLS + c] = sum;
     }
-    const double2 *x = lds_dft<NI, R2, false>(buf[0], buf[1], cos_tab, tid);
+    const double2 *x = lds_passes<NI, R2, 1024>(buf[0], buf[1], cos_tab, tid, [&](int cc) { return 4 * (blockIdx.x * R::COLS + cc); });
 #pragma unroll
     for (int k = 0; k < 8; k++) {
         const int w = tid + CL_THREADS * k, cc = blockIdx.x * R::COLS + w % R::COLS, k1 = w / R::COLS;
-        f[((size_t)blockIdx.y * R2 + k1) * 256 + cc] = cmul(x[w], unit<NI, false>(cos_tab, (u32)cc * k1 * 4));
+        f[((size_t)blockIdx.y * R2 + k1) * 256 + cc] = x[w];
     }
 }
 // grid (R2 / 8, n): eight rows k1; out: [n][n_slots], slots slot_begin .. slot_begin + n_slots - 1
@@ -277,7 +274,7 @@ __global__ __launch_bounds__(CL_THREADS) void k_cl_dec_rows(const double2 *f, co
     const int tid = threadIdx.x;
 #pragma unroll
     for (int row = 0; row < 8; row++) buf[0][tid * 8 + row] = f[((size_t)blockIdx.y * R2 + blockIdx.x * 8 + row) * 256 + tid];
-    const double2 *x = lds_dft<N, 256, false>(buf[0], buf[1], cos_tab, tid);
+    const double2 *x = lds_passes<N, 256, 4 * R2>(buf[0], buf[1], cos_tab, tid, [](int) { return 0; });
 #pragma unroll
     for (int m = 0; m < 8; m++) {
         const int w = tid + CL_THREADS * m, row = w & 7, k2 = w >> 3;

@@ -240,6 +240,19 @@ ENSI_HD double crt_centred(u64 r0, u64 r1, const CrtPair &c) {
     return neg ? -v : v;
 }
 
+// A butterfly of the encoding transform (exponential exp(-i x), c = cos x, s = sin x), and the rounding of a coefficient: half
+// away from zero.  Shared by all kernels that encode or decode, with the roundings written out: which of two
+// neighbouring integers a coefficient becomes hangs on the last bit.
+__device__ __forceinline__ void fft_butterfly(double2 a, double2 b, double c, double s, double2 &even, double2 &odd) {
+    const double dr = a.x - b.x, di = a.y - b.y;
+    even = make_double2(a.x + b.x, a.y + b.y);
+    odd = make_double2(__builtin_fma(dr, c, di * s), __builtin_fma(di, c, -(dr * s)));
+}
+__device__ __forceinline__ int64_t round_coeff(double m) {
+    const double r = floor(fabs(m) + 0.5);
+    return (int64_t)(m < 0 ? -r : r);
+}
+
 struct ensi_ctx {
     ensi_params prm;
     int log_n, N, L, K, alpha;

@@ -532,12 +532,8 @@ __global__ __launch_bounds__(EW_THREADS) void k_fft_pass(const double2 *x, doubl
     x += (size_t)blockIdx.y * n2;
     y += (size_t)blockIdx.y * n2;
     const int q = t & (s - 1), idx = t - q;  // idx = p * s with p = t / s: the twiddle is exp(-2 pi i idx / n2)
-    const double2 a = x[t], b = x[t + n2 / 2];
-    const double c = cos_tab[idx], sn = cos_tab[(idx - n2 / 4) & (n2 - 1)];
-    const double dr = a.x - b.x, di = a.y - b.y;
     const size_t o = (size_t)q + 2 * (size_t)idx;
-    y[o] = make_double2(a.x + b.x, a.y + b.y);
-    y[o + s] = make_double2(dr * c + di * sn, di * c - dr * sn);
+    fft_butterfly(x[t], x[t + n2 / 2], cos_tab[idx], cos_tab[(idx - n2 / 4) & (n2 - 1)], y[o], y[o + s]);
 }
 // Plaintext y of the chunk holds its n_slots values in slots [slot0 + (y0 + y)*slot_step, ... + n_slots); x is zero beforehand.
 __global__ __launch_bounds__(EW_THREADS) void k_fft_scatter_slots(const double *slots, int n_slots, int slot0, int slot_step, int y0,
@@ -550,9 +546,7 @@ __global__ __launch_bounds__(EW_THREADS) void k_fft_scatter_slots(const double *
 __global__ __launch_bounds__(EW_THREADS) void k_fft_round_coeffs(const double2 *f, int N, double factor, int64_t *coeffs) {
     const int k = blockIdx.x * EW_THREADS + threadIdx.x;
     if (k >= N) return;
-    const double m = f[(size_t)blockIdx.y * 2 * N + k].x * factor;
-    const double r = floor(fabs(m) + 0.5);
-    coeffs[(size_t)blockIdx.y * N + k] = (int64_t)(m < 0 ? -r : r);
+    coeffs[(size_t)blockIdx.y * N + k] = round_coeff(f[(size_t)blockIdx.y * 2 * N + k].x * factor);
 }
 __global__ __launch_bounds__(EW_THREADS) void k_fft_load_coeffs(const double *coeffs, int N, double2 *x) {
     const int k = blockIdx.x * EW_THREADS + threadIdx.x;

@@ -527,6 +527,55 @@ def test_register_transform_rings_bit_exact(params):
     p.close()
 
 
+@pytest.mark.parametrize("log_n,n", [(12, 300), (13, 5), (14, 70), (15, 3), (16, 37)])
+def test_client_transforms_equal_the_length_2n_transform(log_n, n):
+    """Encoding and decoding by the kernels of the register transform against the length-2N transform, which a context with
+    55-bit ciphertext primes runs: the same coefficients and the same slots to the last bit (neither depends on the
+    primes), at batches of several chunks with a ragged last one, and at scales where a coefficient hangs on the last bit."""
+    from paper_2509_09424_amd import binding
+    ctx = {bits: binding.Context(log_n, bits, 2, 60, 1, 1, 43, seed=1) for bits in (50, 55)}
+    N, rng = 1 << log_n, np.random.default_rng(log_n)
+    z = rng.uniform(-1, 1, (n, N // 2 - 3))
+    for slots, scale in ((z, None), (z[:2, :11], None), (z * 2.0 ** -8, 2.0 ** 55)):
+        got = {}
+        for bits, c in ctx.items():
+            pt = c.encode(slots, 2) if scale is None else c.encode_at(slots, 2, scale)
+            got[bits] = c.pt_export(pt)
+            pt.free()
+        assert np.array_equal(got[50], got[55]), scale
+    # coefficients up to the end of the 64-bit range, beyond what a double or one prime holds: from their residues modulo two
+    # primes (an encryption with no randomness is the plaintext itself)
+    big = {}
+    for bits, c in ctx.items():
+        _, pk = c.keygen(None, None, 5)
+        pt = c.encode_at(0.9 + 0.1 * z[:1], 2, 2.0 ** 62)
+        none = np.zeros((1, N), dtype=np.int8)
+        ct = c.encrypt(pk, pt, none, none, none)
+        q, r = c.primes()[0], ct.export()[0, 0].astype(object)
+        m = (r[0] + q[0] * ((r[1] - r[0]) * pow(q[0], -1, q[1]) % q[1])) % (q[0] * q[1])
+        big[bits] = np.where(m > q[0] * q[1] // 2, m - q[0] * q[1], m)
+        for h in (pt, ct, pk):
+            h.free()
+    assert max(abs(x) for x in big[50]) > 1 << 61 and np.array_equal(big[50], big[55])
+    # decoding: ciphertexts that are plaintexts
+    m = rng.integers(-2 ** 44, 2 ** 44, (min(n, 19 if log_n == 16 else n), N))
+    for limbs in (1, 2):
+        out = {}
+        for bits, c in ctx.items():
+            sk, pk = c.keygen(None, None, 5)
+            words = np.zeros((len(m), 2, limbs, N), dtype=np.uint64)
+            for i in range(limbs):
+                words[:, 0, i] = m % c.primes()[0][i]
+            ct = c.ct_import(words, 2.0 ** 43)
+            out[bits] = c.decrypt(sk, ct), c.decrypt(sk, ct, N // 6, 17)
+            for h in (ct, sk, pk):
+                h.free()
+        assert np.array_equal(out[50][0], out[55][0]) and np.array_equal(out[50][1], out[55][1]), limbs
+        assert np.array_equal(out[50][1], out[50][0][:, N // 6:N // 6 + 17]), limbs
+    for c in ctx.values():
+        c.close()
+
+
 def test_full_ring_rotate_batch_longer_than_one_group(full):
     """More ciphertexts than the library raises at once (groups of 64), at a low level to keep the oracle quick."""
     p = full
