@@ -46,13 +46,14 @@ extern "C" int ensi_rotate_static(ensi_ctx *ctx, const ensi_gk *gk, const ensi_c
     if (ctx->profiling) ENSI_FAIL(ctx, ENSI_E_BADARG, "the per-kernel timers create events: switch them off for the allocation-free call");
     hipStream_t st = (hipStream_t)stream;
     const int N = ctx->N, l1 = in->limbs, ext = l1 + ctx->K, n = in->n;
-    // workspace layout inside the static array: descriptors, then the four arrays of the key switch
+    // workspace layout inside the static array: descriptors, raised digits, accumulators
     const size_t rw = raised_words(ctx, l1);
     const size_t desc_bytes = (((size_t)n * sizeof(RotDesc)) + 255) & ~(size_t)255;
-    const size_t w_digits = (size_t)n * rw, w_u = (size_t)n * 2 * ext * N;
-    // (the documented limit also counts inner factors and special residues, which the kernels of every ring now keep in registers)
-    const size_t w_more = (size_t)n * (l1 + 2 * ctx->K) * N;
-    const size_t need = desc_bytes + (w_digits + w_u + w_more) * sizeof(u64);
+    const size_t w_digits = (size_t)n * rw;
+    // What a call is charged is the bound the header states, whatever the kernels of a ring keep in registers.  It covers what
+    // they use, beta ext limbs of digits, 2 ext of accumulators and on the fused rings l1 of P*c0.
+    const size_t beta = (l1 + ctx->alpha - 1) / ctx->alpha, more = ctx->ks16 && ctx->log_n == 16 ? l1 : 0;
+    const size_t need = desc_bytes + (size_t)n * (beta * ext + 3 * l1 + 4 * ctx->K + more) * N * sizeof(u64);
     if (n > ENSI_STATIC_MAX_BATCH || need > ctx->static_scratch_bytes)
         ENSI_FAIL(ctx, ENSI_E_SHAPE, "rotate_static: %d ciphertexts at %d limbs need %zu bytes of workspace; the static workspace holds %zu (at most %d per call)",
                   n, l1, need, ctx->static_scratch_bytes, ENSI_STATIC_MAX_BATCH);

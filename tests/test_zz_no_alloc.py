@@ -74,3 +74,32 @@ def test_rotate_static_full_ring_and_size_limit():
             h.free()
     finally:
         p.close()
+
+
+@pytest.mark.parametrize("params,limbs", [
+    ((14, 50, 6, 60, 2, 2, 40), 6), ((14, 50, 6, 60, 2, 2, 40), 3), ((15, 50, 4, 60, 2, 2, 40), 4), ((13, 50, 8, 60, 4, 4, 40), 8), (KEYSWITCH, 4),
+    ((13, 55, 8, 60, 4, 4, 40), 8), ((12, 36, 3, 37, 1, 1, 30), 3),
+], ids=["16K", "16K-low", "32K", "8K", "64K", "8K-55bit", "4K"])
+def test_rotate_static_takes_the_documented_batch_and_no_more(params, limbs):
+    """The largest batch that the stated bound admits runs and equals ensi_rotate; one more is refused."""
+    from paper_2509_09424_amd import binding
+    ctx = binding.Context(*params, seed=1)
+    N, l, K = ctx.N, limbs, ctx.K
+    rows = -(-l // ctx.alpha) * (l + K) + 3 * l + 4 * K + (l if params[0] == 16 and params[1] <= 50 else 0)
+    fits = max(n for n in range(1, 65) if n * rows * 8 * N + 4096 <= 96 << 20)  # (descriptors take up to 3 KiB more)
+    assert fits < 64 or params[0] == 12
+    sk, pk = ctx.keygen(None, None, 3)
+    gk = ctx.galois_keygen(sk, [1, -3], None, 4)
+    rng = np.random.default_rng(5)
+    words = np.stack([rng.integers(0, q, (fits + 1, 2, N), dtype=np.uint64) for q in ctx.primes()[0][:l]], axis=2)
+    steps = [(1, -3)[c % 2] for c in range(fits + 1)]
+    ct = ctx.ct_import(words[:fits], 1.0)
+    want, got = ctx.rotate(gk, ct, steps[:fits]), ctx.ct_alloc(fits, l)
+    ctx.rotate_static(gk, ct, steps[:fits], got)
+    assert np.array_equal(got.export(), want.export())
+    more, out = ctx.ct_import(words, 1.0), ctx.ct_alloc(fits + 1, l)
+    with pytest.raises(binding.EnsiError, match="static workspace holds"):
+        ctx.rotate_static(gk, more, steps, out)
+    for h in (ct, want, got, more, out, gk, pk, sk):
+        h.free()
+    ctx.close()
