@@ -293,8 +293,8 @@ extern "C" int ensi_ctx_create(const ensi_params *prm, ensi_ctx **out) {
     }
     std::vector<u32> slot_of_k(N / 2);
     for (int j = 0; j < N / 2; j++) slot_of_k[(ctx->rot_exp[j] - 1) / 4] = (u32)j;
-    if (upload(&ctx->d_slot_of_k, slot_of_k) != hipSuccess || upload(&ctx->d_pc, pcs) != hipSuccess || upload(&ctx->d_tw, tw) != hipSuccess || upload(&ctx->d_cos, cs) != hipSuccess ||
-        upload(&ctx->d_rot_exp, ctx->rot_exp) != hipSuccess) {
+    if (upload(ctx, &ctx->d_slot_of_k, slot_of_k) != hipSuccess || upload(ctx, &ctx->d_pc, pcs) != hipSuccess || upload(ctx, &ctx->d_tw, tw) != hipSuccess || upload(ctx, &ctx->d_cos, cs) != hipSuccess ||
+        upload(ctx, &ctx->d_rot_exp, ctx->rot_exp) != hipSuccess) {
         ensi_ctx_free(ctx);
         return ENSI_E_HIP;
     }
@@ -429,7 +429,7 @@ int get_modup(ensi_ctx *ctx, int l1, const ModUpConst **out) {
                 }
             }
         }
-        if (upload(&mc.inv, inv) != hipSuccess || upload(&mc.inv_s, inv_s) != hipSuccess || upload(&mc.hat, hat) != hipSuccess)
+        if (upload(ctx, &mc.inv, inv) != hipSuccess || upload(ctx, &mc.inv_s, inv_s) != hipSuccess || upload(ctx, &mc.hat, hat) != hipSuccess)
             ENSI_FAIL(ctx, ENSI_E_HIP, "uploading ModUp constants failed");
         it = ctx->modup.insert({l1, mc}).first;
     }
@@ -468,8 +468,8 @@ int get_moddown(ensi_ctx *ctx, int l1, const ModDownConst **out) {
                 hat[(size_t)i * K + k] = hm_to_mont(h, q);
             }
         }
-        if (upload(&mc.inv, inv) != hipSuccess || upload(&mc.inv_s, inv_s) != hipSuccess || upload(&mc.hat, hat) != hipSuccess ||
-            upload(&mc.pinv, pinv) != hipSuccess || upload(&mc.pinv_s, pinv_s) != hipSuccess || upload(&mc.negtab, negtab) != hipSuccess)
+        if (upload(ctx, &mc.inv, inv) != hipSuccess || upload(ctx, &mc.inv_s, inv_s) != hipSuccess || upload(ctx, &mc.hat, hat) != hipSuccess ||
+            upload(ctx, &mc.pinv, pinv) != hipSuccess || upload(ctx, &mc.pinv_s, pinv_s) != hipSuccess || upload(ctx, &mc.negtab, negtab) != hipSuccess)
             ENSI_FAIL(ctx, ENSI_E_HIP, "uploading ModDown constants failed");
         it = ctx->moddown.insert({l1, mc}).first;
     }
@@ -550,8 +550,8 @@ int get_ks16(ensi_ctx *ctx, int l1, const Ks16Const **out) {
         }
         double *d_pmod = nullptr, *d_dpf = nullptr, *d_dq = nullptr;
         u64 *d_dp = nullptr, *d_hat = nullptr, *d_dh = nullptr;
-        if (upload(&d_hat, hat_sp) != hipSuccess || upload(&d_dh, down_h) != hipSuccess || upload(&d_pmod, pmod) != hipSuccess || upload(&d_dp, down_p) != hipSuccess ||
-            upload(&d_dpf, down_p_fp) != hipSuccess || upload(&d_dq, down_q) != hipSuccess)
+        if (upload(ctx, &d_hat, hat_sp) != hipSuccess || upload(ctx, &d_dh, down_h) != hipSuccess || upload(ctx, &d_pmod, pmod) != hipSuccess || upload(ctx, &d_dp, down_p) != hipSuccess ||
+            upload(ctx, &d_dpf, down_p_fp) != hipSuccess || upload(ctx, &d_dq, down_q) != hipSuccess)
             ENSI_FAIL(ctx, ENSI_E_HIP, "uploading key-switch constants failed");
         kc.hat_sp = d_hat;
         kc.down_h = d_dh;

@@ -113,10 +113,10 @@ static int build_plan(ensi_ctx *ctx, const int8_t *W, int s, int d, int m, int p
     }
     if (mfma_ok)
         for (int i = 0; i < m; i++) bias[i] *= 128;  // every byte is fed to the matrix pipe as u - 128
-    hipError_t e1 = upload(&p->d_masks, masks), e2 = hipSuccess, e3 = hipSuccess, e4 = hipSuccess;
+    hipError_t e1 = upload(ctx, &p->d_masks, masks), e2 = hipSuccess, e3 = hipSuccess, e4 = hipSuccess;
     if (mfma_ok) {
-        e2 = upload(&p->d_wt, wt);
-        e3 = upload(&p->d_bias, bias);
+        e2 = upload(ctx, &p->d_wt, wt);
+        e3 = upload(ctx, &p->d_bias, bias);
         if (qbits <= 50) {
             // the recombination in double precision adds the offset term already reduced: b * sum_p 256^p mod q_limb
             std::vector<double> bias_fp((size_t)l1 * p->m_pad, 0.0);
@@ -130,7 +130,7 @@ static int build_plan(ensi_ctx *ctx, const int8_t *W, int s, int d, int m, int p
                     bias_fp[(size_t)limb * p->m_pad + i] = (double)(u64)r;
                 }
             }
-            e4 = upload(&p->d_bias_fp, bias_fp);
+            e4 = upload(ctx, &p->d_bias_fp, bias_fp);
         }
     }
     if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess || e4 != hipSuccess) {

@@ -19,8 +19,8 @@ struct DevBuf {
 };
 
 template <class T>
-inline hipError_t upload(T **d, const std::vector<T> &h) {
-    hipError_t e = hipMalloc((void **)d, std::max<size_t>(h.size() * sizeof(T), 8));
+inline hipError_t upload(ensi_ctx *ctx, T **d, const std::vector<T> &h) {
+    hipError_t e = ctx->pool->alloc((void **)d, std::max<size_t>(h.size() * sizeof(T), 8));
     if (e != hipSuccess) return e;
     return hipMemcpy(*d, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice);
 }
