@@ -52,55 +52,6 @@ int stage_prealloc(ensi_ctx *ctx) {
     return ENSI_OK;
 }
 
-// ------------------------------------------------------------- memory of handles
-hipError_t DevPool::alloc(void **p, size_t bytes) {
-    hipError_t e = hipMalloc(p, bytes);
-    if (e != hipErrorOutOfMemory) return e;
-    {
-        std::lock_guard<std::mutex> lock(mu);
-        for (auto &b : blocks) (void)hipFree(b.second);
-        blocks.clear();
-        held = 0;
-    }
-    (void)hipGetLastError();
-    return hipMalloc(p, bytes);  // also where nothing was kept: another thread may just have given it back
-}
-hipError_t DevPool::take(void **p, size_t bytes, size_t *got) {
-    {
-        std::lock_guard<std::mutex> lock(mu);
-        auto it = blocks.lower_bound(bytes);
-        if (it != blocks.end() && it->first <= bytes + bytes / 8) {
-            *p = it->second;
-            *got = it->first;
-            held -= it->first;
-            blocks.erase(it);
-        } else {
-            *p = nullptr;
-        }
-    }
-    if (*p) return hipDeviceSynchronize();
-    *got = bytes;
-    return alloc(p, bytes);
-}
-void DevPool::give(void *p, size_t bytes) {
-    {
-        std::lock_guard<std::mutex> lock(mu);
-        if (!closed && bytes <= KEEP_EACH && held + bytes <= KEEP_ALL) {
-            blocks.emplace(bytes, p);
-            held += bytes;
-            return;
-        }
-    }
-    (void)hipFree(p);
-}
-void DevPool::close() {
-    std::lock_guard<std::mutex> lock(mu);
-    closed = true;
-    for (auto &b : blocks) (void)hipFree(b.second);
-    blocks.clear();
-    held = 0;
-}
-
 // ---------------------------------------------------------------------- timers
 int timer_id(ensi_ctx *ctx, const char *name) {
     for (size_t i = 0; i < ctx->timers.size(); i++)
@@ -616,7 +567,9 @@ int encode_window(ensi_ctx *ctx, const double *slots, int n_pt, int n_slots, int
             if (e == hipSuccess)
                 launch_cl_encode(ctx, d_slots, cnt, n_slots, slot0, slot_step, y0, scale, limbs, (double2 *)ctx->ws_cl, pt->d + (size_t)y0 * limbs * ctx->N, nullptr);
         }
-        if (rc || e != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess || hipGetLastError() != hipSuccess) {
+        if (!rc && e == hipSuccess) e = hipStreamSynchronize(nullptr);
+        if (!rc && e == hipSuccess) e = hipGetLastError();
+        if (rc || e != hipSuccess) {
             ensi_pt_free(pt);
             if (rc) return rc;
             ENSI_FAIL(ctx, ENSI_E_HIP, "encode failed: %s", hipGetErrorString(e));
@@ -791,11 +744,13 @@ extern "C" int ensi_encrypt(ensi_ctx *ctx, const ensi_pk *pk, const ensi_pt *pt,
             if (e == hipSuccess)
                 launch_cl_encrypt(ctx, pk->d_pk, d_small, pt->d + (size_t)c0 * l1 * N, (int)(cn / N), l1, ctx->ws_cl, ct->d + (size_t)c0 * 2 * l1 * N, st);
         }
-        if (rc || e != hipSuccess || hipStreamSynchronize(st) != hipSuccess || hipGetLastError() != hipSuccess) {
+        if (!rc && e == hipSuccess) e = hipStreamSynchronize(st);
+        if (!rc && e == hipSuccess) e = hipGetLastError();
+        if (rc || e != hipSuccess) {
             ensi_ct_free(ct);
             *out = nullptr;
             if (rc) return rc;
-            ENSI_FAIL(ctx, ENSI_E_HIP, "kernel failure in encrypt");
+            ENSI_FAIL(ctx, ENSI_E_HIP, "encrypt failed: %s", hipGetErrorString(e));
         }
         return ENSI_OK;
     }

@@ -6,11 +6,11 @@
 
 #include <map>
 #include <memory>
-#include <mutex>
 #include <string>
 #include <vector>
 
 #include "../../include/ensi.h"
+#include "devpool.h"
 #include "modarith.h"
 
 #define ENSI_MAX_EXT 32   // max limbs of an extended basis (L + K)
@@ -197,23 +197,6 @@ struct StageSlot {
     bool pending = false;
 };
 #define ENSI_STAGE_SLOTS 8
-
-// Device memory of freed plaintext and ciphertext handles, kept for the next handle of about the same size: freeing a large
-// block costs a quarter of a millisecond.  Bounded (KEEP_EACH, KEEP_ALL); emptied when the context is freed, or when an
-// allocation of the library fails.  Shared by the context and its handles, which may outlive it, and safe with several threads.  The
-// release of a block waits for nothing; taking one waits for the device, as hipFree did when the block was freed.
-struct DevPool {
-    static constexpr size_t KEEP_EACH = (size_t)256 << 20, KEEP_ALL = (size_t)1 << 30;
-    std::mutex mu;
-    std::multimap<size_t, void *> blocks;  // by size
-    size_t held = 0;
-    bool closed = false;
-    hipError_t alloc(void **p, size_t bytes);  // hipMalloc, with the kept blocks given back first if the card is full
-    hipError_t take(void **p, size_t bytes, size_t *got);
-    void give(void *p, size_t bytes);
-    void close();
-    ~DevPool() { close(); }
-};
 
 // Constants of the combination of limbs 0 and 1 into one centred coefficient (crt_centred).
 struct CrtPair {

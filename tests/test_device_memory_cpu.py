@@ -2,6 +2,7 @@
 import glob
 import os
 import re
+import subprocess
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2509_09424_amd", "csrc")
 
@@ -18,3 +19,67 @@ def test_every_allocation_goes_through_the_pool():
             if re.search(r"\bhipMalloc\(", line.split("//")[0]):
                 calls.append((os.path.basename(path), where))
     assert calls and all(where == "alloc" for _, where in calls), calls
+
+
+# DevPool on a simulated card: the runtime's calls it makes are defined here, so no GPU and no HIP library are needed.
+CARD = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "devpool.h"
+static size_t card_free = (size_t)4096 << 20, n_freed;
+static hipError_t last = hipSuccess, sync_result = hipSuccess;
+static std::map<void *, size_t> live;
+extern "C" {
+hipError_t hipMalloc(void **p, size_t bytes) {
+    if (bytes > card_free) return last = hipErrorOutOfMemory;
+    card_free -= bytes;
+    live[*p = malloc(1)] = bytes;
+    return hipSuccess;
+}
+hipError_t hipFree(void *p) {
+    card_free += live.at(p);
+    live.erase(p);
+    free(p);
+    n_freed++;
+    return hipSuccess;
+}
+hipError_t hipDeviceSynchronize() { return sync_result == hipSuccess ? hipSuccess : last = sync_result; }
+hipError_t hipGetLastError() { hipError_t e = last; last = hipSuccess; return e; }
+}
+#define CHECK(x) do { if (!(x)) { printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
+static const size_t MB = 1 << 20;
+int main() {
+    @BODY@
+    return 0;
+}
+"""
+
+
+def run_on_simulated_card(tmp_path, body):
+    src, exe = tmp_path / "card.cpp", tmp_path / "card"
+    src.write_text(CARD.replace("@BODY@", body))
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + CSRC, str(src), "-o", str(exe), "-pthread"], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_pool_gives_back_before_an_allocation_fails(tmp_path):
+    run_on_simulated_card(tmp_path, """
+        DevPool pool; void *a, *b, *c; size_t got;
+        CHECK(pool.take(&a, 200 * MB, &got) == hipSuccess && got == 200 * MB);
+        pool.give(a, got);
+        CHECK(n_freed == 0 && pool.held == 200 * MB);
+        CHECK(pool.take(&b, 190 * MB, &got) == hipSuccess && b == a && got == 200 * MB && pool.held == 0);  // the kept block serves it
+        pool.give(b, got);
+        CHECK(pool.take(&c, 4000 * MB, &got) == hipSuccess && n_freed == 1 && pool.held == 0);  // only fits once the kept block is back
+        CHECK(last == hipSuccess);
+    """)
+
+
+def test_failed_allocation_leaves_no_error_behind(tmp_path):
+    """The caller is told; the launch check of the next call must not find the same error again."""
+    run_on_simulated_card(tmp_path, """
+        DevPool pool; void *a; size_t got;
+        CHECK(pool.take(&a, 5000 * MB, &got) == hipErrorOutOfMemory && a == nullptr);
+        CHECK(hipGetLastError() == hipSuccess);
+    """)

@@ -576,6 +576,28 @@ def test_client_transforms_equal_the_length_2n_transform(log_n, n):
         c.close()
 
 
+def test_encode_after_an_allocation_that_failed(small4):
+    """A batch larger than any card is refused, and the next calls work."""
+    from paper_2509_09424_amd import binding
+    ctx = binding.Context(12, 50, 4, 60, 2, 2, 40, seed=1)
+    for c in (small4.ctx, ctx):
+        z = np.ones((1, c.n_slots))
+        with pytest.raises(binding.EnsiError, match="code -5"):
+            c.ct_alloc(1 << 30, c.L)
+        c.encode(z, c.L).free()
+        sk, pk = c.keygen(None, None, 3)
+        pt = c.encode(z, c.L)
+        with pytest.raises(binding.EnsiError, match="code -5"):
+            c.ct_alloc(1 << 30, c.L)
+        ct = c.encrypt(pk, pt)
+        with pytest.raises(binding.EnsiError, match="code -5"):
+            c.ct_alloc(1 << 30, c.L)
+        assert np.abs(c.decrypt(sk, ct) - z).max() < 1e-3
+        for h in (ct, pt, pk, sk):
+            h.free()
+    ctx.close()
+
+
 def test_full_ring_rotate_batch_longer_than_one_group(full):
     """More ciphertexts than the library raises at once (groups of 64), at a low level to keep the oracle quick."""
     p = full
