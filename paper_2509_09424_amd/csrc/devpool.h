@@ -31,19 +31,26 @@ struct DevPool {
     }
     // A kept block, or a new one; *got: its size.
     hipError_t take(void **p, size_t bytes, size_t *got) {
+        void *block = nullptr;
         {
             std::lock_guard<std::mutex> lock(mu);
             auto it = blocks.lower_bound(bytes);
             if (it != blocks.end() && it->first <= bytes + bytes / 8) {
-                *p = it->second;
+                block = it->second;
                 *got = it->first;
                 held -= it->first;
                 blocks.erase(it);
-            } else {
-                *p = nullptr;
             }
         }
-        if (*p) return hipDeviceSynchronize();
+        if (block) {
+            if (hipDeviceSynchronize() == hipSuccess) {
+                *p = block;
+                return hipSuccess;
+            }
+            // the device cannot be waited for now (a stream of this thread is being captured): the block stays, a new one serves
+            (void)hipGetLastError();
+            give(block, *got);
+        }
         *got = bytes;
         return alloc(p, bytes);
     }

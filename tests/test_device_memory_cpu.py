@@ -83,3 +83,17 @@ def test_failed_allocation_leaves_no_error_behind(tmp_path):
         CHECK(pool.take(&a, 5000 * MB, &got) == hipErrorOutOfMemory && a == nullptr);
         CHECK(hipGetLastError() == hipSuccess);
     """)
+
+
+def test_pool_where_the_device_cannot_be_waited_for(tmp_path):
+    """A kept block may still be in use, so it is not handed out then: it stays in the pool, and a new one serves the call."""
+    run_on_simulated_card(tmp_path, """
+        DevPool pool; void *a, *b; size_t got;
+        CHECK(pool.take(&a, 200 * MB, &got) == hipSuccess);
+        pool.give(a, got);
+        sync_result = hipErrorStreamCaptureUnsupported;
+        CHECK(pool.take(&b, 190 * MB, &got) == hipSuccess && b != a && got == 190 * MB && pool.held == 200 * MB);
+        CHECK(hipGetLastError() == hipSuccess);
+        sync_result = hipSuccess;
+        CHECK(pool.take(&b, 200 * MB, &got) == hipSuccess && b == a && pool.held == 0);
+    """)
