@@ -8,6 +8,7 @@
 
 #include <map>
 #include <mutex>
+#include <new>
 
 struct DevPool {
     static constexpr size_t KEEP_EACH = (size_t)256 << 20, KEEP_ALL = (size_t)1 << 30;
@@ -55,13 +56,14 @@ struct DevPool {
         return alloc(p, bytes);
     }
     void give(void *p, size_t bytes) {
-        {
+        try {
             std::lock_guard<std::mutex> lock(mu);
             if (!closed && bytes <= KEEP_EACH && held + bytes <= KEEP_ALL) {
                 blocks.emplace(bytes, p);
                 held += bytes;
                 return;
             }
+        } catch (const std::bad_alloc &) {  // no host memory to note the block down: handles are freed from C, where nothing may throw
         }
         (void)hipFree(p);
     }

@@ -26,6 +26,14 @@ CARD = r"""
 #include <cstdio>
 #include <cstdlib>
 #include "devpool.h"
+static bool host_full = false;
+void *operator new(size_t bytes) {
+    void *p = host_full ? nullptr : malloc(bytes);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
 static size_t card_free = (size_t)4096 << 20, n_freed;
 static hipError_t last = hipSuccess, sync_result = hipSuccess;
 static std::map<void *, size_t> live;
@@ -96,4 +104,16 @@ def test_pool_where_the_device_cannot_be_waited_for(tmp_path):
         CHECK(hipGetLastError() == hipSuccess);
         sync_result = hipSuccess;
         CHECK(pool.take(&b, 200 * MB, &got) == hipSuccess && b == a && pool.held == 0);
+    """)
+
+
+def test_freeing_a_handle_does_not_throw(tmp_path):
+    """Without host memory to note a block down, it goes back to the card."""
+    run_on_simulated_card(tmp_path, """
+        DevPool pool; void *a; size_t got;
+        CHECK(pool.take(&a, 200 * MB, &got) == hipSuccess);
+        host_full = true;
+        pool.give(a, got);
+        host_full = false;
+        CHECK(n_freed == 1 && pool.held == 0 && card_free == 4096 * MB);
     """)
