@@ -87,6 +87,10 @@ typedef struct ensi_params {
  * uploads them to the current HIP device. */
 int ensi_ctx_create(const ensi_params *params, ensi_ctx **out);
 void ensi_ctx_free(ensi_ctx *ctx);
+/* A context keeps up to 1 GiB of the device memory of freed plaintext and ciphertext handles (blocks of up to 256 MiB)
+ * for the next ones.  An allocation of the library that finds the card full gives it back by itself; for other users of
+ * the card, this call does. */
+int ensi_ctx_trim(ensi_ctx *ctx);
 const char *ensi_last_error(const ensi_ctx *ctx); /* string owned by ctx; "" if none */
 /* q: host[L], p: host[K] */
 int ensi_get_primes(const ensi_ctx *ctx, uint64_t *q, uint64_t *p);

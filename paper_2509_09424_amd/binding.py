@@ -17,7 +17,7 @@ PLACE_ZERO, PLACE_DIAGONAL = 0, 1
 _PLACEMENTS = {"zero": PLACE_ZERO, "diagonal": PLACE_DIAGONAL}
 
 EXPORTED = [
-    "ensi_ctx_create", "ensi_ctx_free", "ensi_last_error", "ensi_get_primes", "ensi_keygen", "ensi_sk_free",
+    "ensi_ctx_create", "ensi_ctx_free", "ensi_ctx_trim", "ensi_last_error", "ensi_get_primes", "ensi_keygen", "ensi_sk_free",
     "ensi_pk_free", "ensi_galois_keygen", "ensi_gk_free", "ensi_encode", "ensi_pt_import", "ensi_pt_export",
     "ensi_pt_free", "ensi_ct_alloc", "ensi_ct_wrap", "ensi_ct_free", "ensi_ct_info", "ensi_ct_export",
     "ensi_ct_import", "ensi_encrypt", "ensi_decrypt", "ensi_rotate", "ensi_ternary_matmul",
@@ -95,6 +95,10 @@ class Context:
         if self.h:
             self.lib.ensi_ctx_free(self.h)
             self.h = ctypes.c_void_p()
+
+    def trim(self):
+        """Gives the kept memory of freed handles back to the card."""
+        self._check(self.lib.ensi_ctx_trim(self.h))
 
     def primes(self):
         q = np.zeros(self.L, dtype=np.uint64)

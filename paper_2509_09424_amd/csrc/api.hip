@@ -338,6 +338,11 @@ extern "C" void ensi_ctx_free(ensi_ctx *ctx) {
     delete ctx;
 }
 
+extern "C" int ensi_ctx_trim(ensi_ctx *ctx) {
+    if (!ctx) return ENSI_E_BADARG;
+    ctx->pool->release();
+    return ENSI_OK;
+}
 extern "C" const char *ensi_last_error(const ensi_ctx *ctx) { return ctx ? ctx->err.c_str() : "null context"; }
 
 extern "C" int ensi_get_primes(const ensi_ctx *ctx, uint64_t *q, uint64_t *p) {

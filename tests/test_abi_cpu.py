@@ -43,6 +43,7 @@ def test_null_arguments_of_the_later_entry_points_without_gpu():
     lib = binding.load()
     n = None
     d = ctypes.c_double
+    assert lib.ensi_ctx_trim(n) == -1
     assert lib.ensi_pt_set_scale(n, d(1.0)) == -1
     assert lib.ensi_ct_drop_limbs(n, 1) == -1
     assert lib.ensi_encode_at(n, n, 1, 1, 1, d(2.0), n) == -1

@@ -598,6 +598,16 @@ def test_encode_after_an_allocation_that_failed(small4):
     ctx.close()
 
 
+def test_trim_gives_kept_memory_back_to_the_card(tiny):
+    import torch
+    ct = tiny.ctx.ct_alloc((200 << 20) // (2 * tiny.pr.L * 8 * tiny.N), tiny.pr.L)
+    ct.free()
+    before = torch.cuda.mem_get_info()[0]
+    tiny.ctx.trim()
+    assert torch.cuda.mem_get_info()[0] - before > 190 << 20
+    tiny.ctx.trim()  # nothing left to give
+
+
 def test_full_ring_rotate_batch_longer_than_one_group(full):
     """More ciphertexts than the library raises at once (groups of 64), at a low level to keep the oracle quick."""
     p = full
