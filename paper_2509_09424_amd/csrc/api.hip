@@ -153,10 +153,7 @@ extern "C" int ensi_ctx_create(const ensi_params *prm, ensi_ctx **out) {
     ctx->primes.insert(ctx->primes.end(), ps.begin(), ps.end());
     const int np = ctx->L + ctx->K;
     for (u64 q : ctx->primes)
-        ctx->kind.push_back(ctx->log_n < 12              ? PRIME_INT
-                            : q < ((u64)1 << 50)         ? PRIME_FP
-                            : q < ((u64)1 << 60) && q > ((u64)1 << 60) - ((u64)1 << 26) ? PRIME_WIDE
-                                                         : PRIME_INT);
+        ctx->kind.push_back(ctx->log_n < 12 ? PRIME_INT : q < ((u64)1 << 50) ? PRIME_FP : hm_is_wide(q) ? PRIME_WIDE : PRIME_INT);
     // the key-switch kernels take one arithmetic for all special primes
     ctx->special_kind = ctx->kind[ctx->L];
     for (int k = 1; k < ctx->K; k++)

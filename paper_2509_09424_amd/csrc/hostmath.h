@@ -36,6 +36,9 @@ static inline u64 hm_split(int64_t v, int bits) {
     return ((u64)(u32)(int32_t)hi << 32) | (u32)(int32_t)lo;
 }
 static inline int64_t hm_centred(u64 w, u64 q) { return w > q / 2 ? (int64_t)w - (int64_t)q : (int64_t)w; }
+// Primes of the PRIME_WIDE arithmetic (ArithWide, whose bounds need this d).
+static constexpr u64 HM_WIDE_D = (u64)1 << 26;
+static inline bool hm_is_wide(u64 q) { return q < ((u64)1 << 60) && q > ((u64)1 << 60) - HM_WIDE_D; }
 // multiplier of the PRIME_WIDE arithmetic: the centred residue, split at 28 bits
 static inline u64 hm_wide_pack(u64 w, u64 q) { return hm_split(hm_centred(w, q), 28); }
 static inline bool hm_is_prime(u64 n) {

@@ -19,9 +19,12 @@
 //             32 x 32 + 64 bit multiply-add issues at the rate of an fp64 FMA on this chip (5.4 and 5.2 cycles of 2.4 GHz
 //             per wave measured, held clock about 1.9 GHz), so what counts is the number of instructions -- eleven per
 //             butterfly, against eight for ArithFp and about twenty-six for ArithInt.
-//             Bounds: |x| < 8q gives x w in (-0.52 q, 1.52 q).  A forward step starts within 1.14 q and adds 1.52 q per
-//             stage: below 7.3 q < 2^63 after its four stages without any reduction.  An inverse step starts within
-//             0.51 q; sums double, a product restarts at 1.52 q, so only the elements that are sums of three or four
+//             Bounds, in units of 2^60 (the reduction takes |x| < 7.5): with |xl|, |wh| <= 2^31 and |wl| <= 2^27, A is
+//             within (1 + |x| / 8) / 4, B's upper dword times d within (1 + |x| / 8) / 16, B's lower one times 2^28 in [0, 1): a
+//             product of |x| < 7.5 is in (-0.61, 1.61).  (No power of a 2N-th root of unity, times 1 or 2^32, of an admitted
+//             prime is one of the 2^27 multipliers below 2^59 whose lower half is longer.)  A forward step starts within
+//             1.14 and grows to 2.49, 3.90, 5.37 and 6.89: no reduction in its four stages.  An inverse step starts within
+//             0.51; sums double, a product restarts, so only the elements that are sums of three or four
 //             stages would leave the range: they are folded before the last stage (gs_fix).
 //   ArithInt  every other prime: 64-bit Shoup/Harvey lazy butterflies.
 #pragma once
@@ -123,7 +126,7 @@ struct ArithWide {
         const int64_t a = mad_i(xh, (int)(u32)ws, mul_i(xl, (int)(u32)w));
         return mad_pow2<28>((u32)b, mad_i((int)(b >> 32), d, a));
     }
-    // |x| < 2^63 -> |result| <= 2^59 + 8 d
+    // |x| < 7.5 2^60 -> |result| <= 2^59 + 8 d
     __device__ __forceinline__ T mid(T x) const {
         const int hi = (int)(x >> 32), k = (hi + (1 << 27)) >> 28;
         const int h = __builtin_amdgcn_sbfe(hi, 0, 28);

@@ -329,6 +329,40 @@ def test_full_ring_ntt_roundtrip_and_evaluation_set(full):
     ct.free()
 
 
+@pytest.mark.parametrize("params", [(16, 60, 28, 61, 4, 4, 40), (12, 60, 6, 60, 2, 2, 40)], ids=["64K", "4K"])
+def test_ntt_of_ciphertext_primes_below_2_60(params):
+    """Primes from next to 2^60 down to the far end of the range of the signed arithmetic for them (the 28th of the
+    2^16 ring is 0.79 2^26 below), at extreme residues: all q - 1, all (q - 1) / 2, alternating, random."""
+    import torch
+    from paper_2509_09424_amd import binding
+    from oracle import Oracle, Params
+    ctx, o = binding.Context(*params, seed=1), Oracle(Params(*params))
+    N, primes = ctx.N, [q for q in ctx.primes()[0]]
+    rng = np.random.default_rng(14)
+    rows, idx = [], []
+    for i in sorted({0, len(primes) // 2, len(primes) - 1}):
+        q = np.uint64(primes[i])
+        alternating = np.zeros(N, dtype=np.uint64)
+        alternating[::2] = q - np.uint64(1)
+        rows += [np.full(N, q - np.uint64(1)), np.full(N, (q - np.uint64(1)) // np.uint64(2)), alternating, rng.integers(0, q, size=N, dtype=np.uint64)]
+        idx += [i] * 4
+    x = np.stack(rows)
+    for inverse in (False, True):
+        buf = torch.from_numpy(x.view(np.int64)).cuda()
+        for r in range(0, len(idx), 4):  # (the primes of a call repeat with a period: one call per prime)
+            ctx.ntt(buf[r].data_ptr(), idx[r:r + 4], inverse=inverse)
+        torch.cuda.synchronize()
+        got = buf.cpu().numpy().view(np.uint64)
+        if not inverse:
+            want = o.ntt(x, [primes[i] for i in idx])
+            assert np.array_equal(np.sort(got, axis=1), np.sort(want, axis=1))
+        for r in range(0, len(idx), 4):
+            ctx.ntt(buf[r].data_ptr(), idx[r:r + 4], inverse=not inverse)
+        torch.cuda.synchronize()
+        assert np.array_equal(buf.cpu().numpy().view(np.uint64), x), inverse
+    ctx.close()
+
+
 def test_full_ring_ntt_batch_with_ragged_groups(full):
     """A batch whose limbs cycle through three primes (two below 2^50, one above) and whose count leaves the last
     group of every prime incomplete: the row pass runs a tile for up to eight limbs of one prime per block."""
