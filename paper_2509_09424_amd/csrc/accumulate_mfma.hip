@@ -489,10 +489,11 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
 #pragma unroll
                 for (int k = 0; k < 4; k++) {
                     const int row = 8 * k + (lane >> 3);
-                    const ulonglong2 v = *(const ulonglong2 *)(o_lds + row * AM_OROW + (lane & 7) * 16);
+                    const ulonglong2 w = *(const ulonglong2 *)(o_lds + row * AM_OROW + (lane & 7) * 16);
+                    const ct_pair v = {w.x, w.y};
                     u64 *o = out + (size_t)(ib + row) * ct_words_out + off_out + 16 * h + (lane & 7) * 2;
-                    if (whole) *(ulonglong2 *)o = v;
-                    else if (ib + row < m) *(ulonglong2 *)o = v;
+                    if (whole) *(ct_pair *)o = v;
+                    else if (ib + row < m) *(ct_pair *)o = v;
                 }
                 wave_lds_fence();
             }

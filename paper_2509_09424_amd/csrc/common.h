@@ -198,6 +198,10 @@ struct StageSlot {
 };
 #define ENSI_STAGE_SLOTS 8
 
+// Two words of a ciphertext at a time.  Wrapped batches are u64 arrays of the caller, aligned to a word and no more: these
+// may be read and written in one access all the same, but not by a type that claims 16 bytes.
+typedef u64 ct_pair __attribute__((ext_vector_type(2), aligned(8)));
+
 // Constants of the combination of limbs 0 and 1 into one centred coefficient (crt_centred).
 struct CrtPair {
     u64 q0, q1, q0_inv_mont, q1_neg_inv, big_hi, big_lo;

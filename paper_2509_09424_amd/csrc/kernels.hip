@@ -402,7 +402,7 @@ __global__ __launch_bounds__(256) void k_copy_cts(const RotDesc *desc, u32 words
     const u64 *src = desc[blockIdx.y].c0;
     u64 *dst = desc[blockIdx.y].out;
     for (u32 i = (blockIdx.x * 256 + threadIdx.x) * 2; i < words; i += gridDim.x * 512)  // two words at a time: rings have an even size
-        *(ulonglong2 *)(dst + i) = *(const ulonglong2 *)(src + i);
+        *(ct_pair *)(dst + i) = *(const ct_pair *)(src + i);
 }
 void launch_copy_cts(ensi_ctx *ctx, const RotDesc *d_desc, int n, size_t words, hipStream_t st) {
     ScopedTimer t(ctx, "copy_cts", st);

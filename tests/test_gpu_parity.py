@@ -632,6 +632,29 @@ def test_encode_after_an_allocation_that_failed(small4):
     ctx.close()
 
 
+@pytest.mark.parametrize("params", [SMALL4, (12, 50, 4, 60, 2, 2, 40)], ids=["1K", "4K"])
+def test_matmul_of_wrapped_batches_at_odd_words(params):
+    """Wrapped memory is aligned to a word and no more: input and output one word off a 16-byte boundary."""
+    import torch
+    p = Pair(params)
+    s, d, m = p.n // 4, 6, 70
+    _, g_gk = p.galois_keys([s, 2 * s, 3 * s])
+    W = wl.ternary_weights(np.random.default_rng(8), d, m)
+    _, g_ct = p.encrypt_both(wl.pack_columns(p.rng.uniform(-1, 1, (s, d)), p.n), p.pr.L)
+    want = p.ctx.ternary_matmul(g_gk, g_ct, s, d, W, "diagonal")
+    words = 2 * p.pr.L * p.N
+    bufs = [torch.zeros(n * words + 2, dtype=torch.int64, device="cuda") for n in (g_ct.n, m)]
+    bufs[0][1:-1] = torch.from_numpy(g_ct.export().reshape(-1).view(np.int64)).cuda()
+    torch.cuda.synchronize()
+    ct_in, ct_out = (p.ctx.ct_wrap(b[1:].data_ptr(), n, p.pr.L, g_ct.scale) for b, n in zip(bufs, (g_ct.n, m)))
+    p.ctx.ternary_matmul(g_gk, ct_in, s, d, W, "diagonal", ct_out)
+    assert np.array_equal(ct_out.export(), want.export())
+    assert [int(bufs[1][i]) for i in (0, -1)] == [0, 0]
+    for h in (g_ct, want, ct_in, ct_out, g_gk):
+        h.free()
+    p.close()
+
+
 def test_trim_gives_kept_memory_back_to_the_card(tiny):
     import torch
     ct = tiny.ctx.ct_alloc((200 << 20) // (2 * tiny.pr.L * 8 * tiny.N), tiny.pr.L)
