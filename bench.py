@@ -13,8 +13,11 @@ kernel class of the timed step; `cpu_baseline` is the CPU oracle timed on a
 bounded sample of the same workload on this host.
 """
 import argparse
+import glob
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -384,19 +387,31 @@ def kernel_profile(runner):
     return prof
 
 
+def code_id(folder=os.path.join(ROOT, "paper_2509_09424_amd")):
+    """Identifies the library's code: a hash over its sources without comments and blanks, and over its build flags."""
+    h = hashlib.sha256()
+    for path in sorted(glob.glob(os.path.join(folder, "csrc", "**", "*.h*"), recursive=True)) + [os.path.join(folder, "build.py")]:
+        text = open(path).read()
+        if not path.endswith(".py"):
+            text = re.sub(r"//[^\n]*|/\*.*?\*/", "", text, flags=re.S)
+        h.update((os.path.basename(path) + "".join(text.split())).encode())
+    return h.hexdigest()[:12]
+
+
 def profile_facts(workload, kernel):
     """Figures that come from rocprofv3 counter runs rather than from this process, read from the tracked summary
     profiles/bench_<workload>_kernels_and_hbm_counters.txt: lines of the form
-        @facts <kernel> key=value key=value ...
-    (fetch_GiB_per_step, write_GiB_per_step, launches_per_step, mfma_busy, valu_util, sclk_GHz).  Returns {} when the
-    summary or the line is missing, so a stale constant can never be reported."""
+        @facts <kernel> code=<code_id> key=value key=value ...
+    (fetch_GiB_per_step, write_GiB_per_step, launches_per_step, mfma_busy, valu_util, sclk_GHz).  A line counts only where it
+    was taken from the code that is here: kernels keep their names when they are rewritten.  Returns {} otherwise, and
+    when the summary or the line is missing."""
     path = os.path.join(ROOT, "profiles", "bench_%s_kernels_and_hbm_counters.txt" % workload)
     facts = {}
     try:
         for line in open(path):
             t = line.split()
-            if len(t) >= 2 and t[0] == "@facts" and t[1] == kernel:
-                for kv in t[2:]:
+            if len(t) >= 3 and t[0] == "@facts" and t[1] == kernel and t[2] == "code=" + code_id():
+                for kv in t[3:]:
                     k, _, v = kv.partition("=")
                     facts[k] = float(v)
     except OSError:
@@ -421,14 +436,19 @@ def roofline_for(w, prof):
     """Roofline entry of the dominant kernel class of the step (largest total time)."""
     N, L, K, alpha = w.N, w.q_count, w.p_count, w.alpha
     unit = 8.0 * N  # bytes of one limb
+
+    def shared(rot, raises):  # raises of a fill that serve three rotations (the others serve one)
+        return (rot - raises) // 2
+
     # key-switch work as stages at one level each: (limbs, rotations, raises, switch-backs to the ciphertext basis --
-    # grouped rotations share one --, keys streamed); plaintext multiplications as (limbs, products, outputs)
+    # grouped rotations share one --, keys streamed, raises whose digits several rotations may read and which therefore run
+    # their row passes); plaintext multiplications as (limbs, products, outputs)
     ks, pm, mm = [], [], []  # mm: ciphertext products as (limbs, distinct operands transformed, outputs)
     if w.name == "keyswitch":
-        ks.append((L, w.batch, w.batch, w.batch, w.batch))  # every rotation streams its key
+        ks.append((L, w.batch, w.batch, w.batch, w.batch, 0))  # every rotation streams its key
     elif w.op == "rope":
         n_ct = -(-w.d_in // w.c_tot)
-        ks.append((L, 2 * n_ct, n_ct, 2 * n_ct, 2 * -(-n_ct // 32)))  # inputs are rotated 32 at a time, a key is read once per group
+        ks.append((L, 2 * n_ct, n_ct, 2 * n_ct, 2 * -(-n_ct // 32), n_ct))  # inputs are rotated 32 at a time, a key is read once per group
         pm.append((L, 3 * n_ct, n_ct))
     elif w.op == "merge":
         pm.append((L, w.d_in, -(-w.d_in // w.c_tot)))
@@ -438,7 +458,7 @@ def roofline_for(w, prof):
         n_el = w.d_in * w.d_out
         f_rot, f_raise = fill_counts(1, w.tokens)
         ks.append((L - 1, n_el * (1 + f_rot) + w.d_out, w.d_in + n_el * f_raise + w.d_out, n_el * (1 + f_raise) + w.d_out,
-                   -(-w.d_in // 16) * w.d_out + f_rot * -(-n_el // 64) + 1))
+                   -(-w.d_in // 16) * w.d_out + f_rot * -(-n_el // 64) + 1, w.d_in + n_el * shared(f_rot, f_raise)))
         pm.append((L, n_el, n_el))
         mm.append((L - 1, w.d_in + n_el, w.d_out))
     elif w.op == "ccmm":
@@ -449,7 +469,8 @@ def roofline_for(w, prof):
         b_rot, b_raise = fill_counts(1, period)
         g_rot, g_raise = fill_counts(period, w.n_slots)
         n_raise = n_el * b_raise + w.d_out * g_raise + w.d_out
-        ks.append((L - 1, n_el * b_rot + w.d_out * g_rot + w.d_out, n_raise, n_raise, b_rot * -(-n_el // 64) + g_rot + 1))
+        ks.append((L - 1, n_el * b_rot + w.d_out * g_rot + w.d_out, n_raise, n_raise, b_rot * -(-n_el // 64) + g_rot + 1,
+                   n_el * shared(b_rot, b_raise) + w.d_out * shared(g_rot, g_raise)))
         pm.append((L, n_el, n_el))
         mm.append((L - 1, w.d_in + n_el, w.d_out))
     elif w.op in ("ccmm_bsgs", "ccmm_bsgs_av"):
@@ -463,9 +484,10 @@ def roofline_for(w, prof):
             n_el, n_seg, n_src = w.d_in * w.d_out, -(-w.d_in // P) * w.d_out, w.d_out
         g_rot, g_raise = fill_counts(P, w.tokens)
         b_rot, b_raise = fill_counts(1, P)
-        ks.append((L, n_seg, n_src, n_seg, -(-n_src // 16) * max(1, n_seg // max(n_src, 1))))
-        ks.append((L - 1, n_seg * g_rot + n_el, n_seg * (g_raise + 1), n_seg * g_raise + n_el, g_rot * -(-n_seg // 64) + (P - 1) * -(-n_seg // 16)))
-        ks.append((L - 2, n_el * b_rot + w.d_out, n_el * b_raise + w.d_out, n_el * b_raise + w.d_out, b_rot * -(-n_el // 64) + 1))
+        ks.append((L, n_seg, n_src, n_seg, -(-n_src // 16) * max(1, n_seg // max(n_src, 1)), n_src))
+        ks.append((L - 1, n_seg * g_rot + n_el, n_seg * (g_raise + 1), n_seg * g_raise + n_el, g_rot * -(-n_seg // 64) + (P - 1) * -(-n_seg // 16),
+                   n_seg * (shared(g_rot, g_raise) + 1)))
+        ks.append((L - 2, n_el * b_rot + w.d_out, n_el * b_raise + w.d_out, n_el * b_raise + w.d_out, b_rot * -(-n_el // 64) + 1, n_el * shared(b_rot, b_raise)))
         pm.append((L, n_seg, n_seg))
         pm.append((L - 1, n_el, n_el))
         mm.append((L - 2, w.d_in + n_el, w.d_out))
@@ -475,10 +497,10 @@ def roofline_for(w, prof):
         P, n_seg, m, baby = w.period, -(-w.d_in // w.period), w.d_out, w.baby
         g_rot, g_raise = fill_counts(P, w.tokens)
         n_sg, n_t = n_seg * m, 2 * P // baby  # spread operands; giant steps (sums per output)
-        ks.append((L, n_sg, m, n_sg, n_seg))
+        ks.append((L, n_sg, m, n_sg, n_seg, m))
         ks.append((L - 1, n_sg * (g_rot + baby - 1) + n_t * m, n_sg * (g_raise + 1) + n_t * m, n_sg * (g_raise + baby - 1) + n_t * m,
-                   g_rot * -(-n_sg // 64) + (baby - 1) * -(-n_sg // 16) + 1))
-        ks.append((L - 1, (n_t - 1) * m, (n_t - 1) * m, (n_t - 1) * m, (n_t - 1) * m))  # the sums rotated by their giant steps, before the rescale
+                   g_rot * -(-n_sg // 64) + (baby - 1) * -(-n_sg // 16) + 1, n_sg * (shared(g_rot, g_raise) + 1)))
+        ks.append((L - 1, (n_t - 1) * m, (n_t - 1) * m, (n_t - 1) * m, (n_t - 1) * m, (n_t - 1) * m))  # the sums rotated by their giant steps, before the rescale
         pm.append((L, n_sg, n_sg))
         mm.append((L - 1, n_sg * baby, n_t * m))  # the prepared weights are not transformed again
     elif w.op == "ccmm_segment":
@@ -488,25 +510,26 @@ def roofline_for(w, prof):
         P, dd, baby = w.period, w.d_in, w.baby
         g_rot, g_raise = fill_counts(P, w.tokens)
         n_diag, n_t = 2 * P - 1, 2 * P // baby
-        ks.append((L, dd, dd, dd, -(-dd // 16)))
+        ks.append((L, dd, dd, dd, -(-dd // 16), dd))
         # one level down: the fills, the baby steps of the spread operands and the giant steps of the columns of Q on one raise
         # each, the relinearisations, the giant steps of the sums that have one
         n_rs = n_diag - baby
         # (the columns of Q are moved by their giant steps and transformed once for all segments, outside the step)
         ks.append((L - 1, dd * (g_rot + baby - 1) + n_diag + n_rs, dd * (g_raise + 1) + n_diag + n_rs,
-                   dd * (g_raise + baby - 1) + n_diag + n_rs, g_rot * -(-dd // 64) + (baby - 1) * -(-dd // 16) + 1 + n_rs))
+                   dd * (g_raise + baby - 1) + n_diag + n_rs, g_rot * -(-dd // 64) + (baby - 1) * -(-dd // 16) + 1 + n_rs,
+                   dd * (shared(g_rot, g_raise) + 1) + n_rs))
         pm.append((L, dd, dd))
         pm.append((L - 2, P * P + P * (P - 1) // 2, P, n_diag))  # every diagonal enters many sorting products, transformed once
         mm.append((L - 1, dd * baby, n_diag))
     else:
         n_in = -(-w.d_in // w.c_tot)
-        # the packed inputs (up to 16) are rotated together, so a key is read once per rotation amount
-        ks.append((L, w.d_in - n_in, n_in, w.d_in - n_in, -(-n_in // 16) * (min(w.c_tot, w.d_in) - 1)))
+        # the packed inputs (up to 16 of the largest ring) are rotated together, so a key is read once per rotation amount
+        ks.append((L, w.d_in - n_in, n_in, w.d_in - n_in, -(-n_in // (16 << (16 - w.log_n))) * (min(w.c_tot, w.d_in) - 1), n_in))
 
-    fused_ks = w.log_n == 16 and w.q_bits <= 50  # the key switch transforms inside its own kernels
+    fused_ks = w.log_n >= 12 and w.q_bits <= 50  # the key switch transforms inside its own kernels
 
     def ks_sum(f):
-        return sum(f(l, -(-l // alpha), l + K, n_rot, n_raise, n_sw, n_key) for l, n_rot, n_raise, n_sw, n_key in ks)
+        return sum(f(l, -(-l // alpha), l + K, *rest) for l, *rest in ks)
 
     def pm_sum(f):
         # (limbs, products, outputs[, distinct sources: a source that enters several products is column-transformed once])
@@ -514,34 +537,28 @@ def roofline_for(w, prof):
 
     # HBM-bound classes: algorithmic limb-units per step (every operand read once, every result written once)
     hbm = {
-        # fused path (N = 2^16, ciphertext primes below 2^50)
-        "ks_pre": ks_sum(lambda l, b, e, rot, ra, sw, key: ra * 2 * l),
-        "ks_modup_fcols": ks_sum(lambda l, b, e, rot, ra, sw, key: ra * (2 * l + b * e + l)),        # c1, c0 in; raised digits and P*c0 out
-        "ks_frows": ks_sum(lambda l, b, e, rot, ra, sw, key: ra * 2 * (b * e + l)),
+        # fused path (rings from 2^12, ciphertext primes below 2^50)
+        "ks_modup_fcols": ks_sum(lambda l, b, e, rot, ra, sw, key, sh: ra * (2 * l + b * e + l)),        # c1, c0 in; raised digits and P*c0 out
+        "ks_frows": ks_sum(lambda l, b, e, rot, ra, sw, key, sh: sh * 2 * (b * e + l)),                # digits and P*c0 in and out
         # all limbs: digits, P*c0, key in; accumulators out
-        "ks_inner": ks_sum(lambda l, b, e, rot, ra, sw, key: rot * (b * e + l) + sw * 2 * e + key * 2 * b * e),
-        # its ciphertext limbs alone: digits, P*c0, key in; accumulators out
-        "ks_inner_irows": ks_sum(lambda l, b, e, rot, ra, sw, key: rot * (b * l + l) + sw * 2 * l + key * 2 * b * l),
-        # its special limbs alone
-        "ks_inner_irows_wide": ks_sum(lambda l, b, e, rot, ra, sw, key: rot * b * K + sw * 2 * K + key * 2 * b * K),
-        "ks_icols_special": ks_sum(lambda l, b, e, rot, ra, sw, key: sw * 4 * K),                    # special limbs in, split residues out
-        "ks_icols_moddown": ks_sum(lambda l, b, e, rot, ra, sw, key: sw * (2 * l + 2 * K + 2 * l)),  # accumulators and residues in, ciphertext out
+        "ks_inner": ks_sum(lambda l, b, e, rot, ra, sw, key, sh: rot * (b * e + l) + sw * 2 * e + key * 2 * b * e),
+        "ks_icols_moddown": ks_sum(lambda l, b, e, rot, ra, sw, key, sh: sw * (2 * l + 2 * K + 2 * l)),  # accumulators in, ciphertext out
         # unfused path
         # library transforms: of the key switch on the unfused path; of the ciphertext products' operands (two passes, each
         # limb in and out) and of their three sums per output, back
-        "ntt": (0 if fused_ks else ks_sum(lambda l, b, e, rot, ra, sw, key: 2 * (ra * b * e + rot * 2 * e)))
+        "ntt": (0 if fused_ks else ks_sum(lambda l, b, e, rot, ra, sw, key, sh: 2 * (ra * b * e + rot * 2 * e)))
                + sum(4 * (ops * 2 * l + outs * 3 * l) for l, ops, outs in mm),
-        "inner_product": ks_sum(lambda l, b, e, rot, ra, sw, key: rot * (b * e + 2 * e) + key * 2 * b * e),  # digits in, accumulators out; keys
-        "modup": ks_sum(lambda l, b, e, rot, ra, sw, key: ra * (l + b * e)),
-        "moddown": ks_sum(lambda l, b, e, rot, ra, sw, key: rot * (2 * e + 3 * l)),
+        "inner_product": ks_sum(lambda l, b, e, rot, ra, sw, key, sh: rot * (b * e + 2 * e) + key * 2 * b * e),  # digits in, accumulators out; keys
+        "modup": ks_sum(lambda l, b, e, rot, ra, sw, key, sh: ra * (l + b * e)),
+        "moddown": ks_sum(lambda l, b, e, rot, ra, sw, key, sh: rot * (2 * e + 3 * l)),
         "mul_scalar_rescale": (w.d_mid or 0) * (2 * L + 2 * (L - 1)),
         # plane split: 8 bytes read + planes bytes written per operand word (units of 8 bytes per word: /N below)
         "byte_planes": (w.d_in * 2 * L + (0 if "rescale_byte_planes" in prof else (w.d_mid or 0) * 2 * (L - 1))) * (8 + 7) / 8.0,
         "rescale_byte_planes": (w.d_mid or 0) * (2 * L + 2 * (L - 1) * 7 / 8.0),
         # plaintext multiplication, summed and rescaled (the few plaintext limbs are not counted)
         "pm_fcols": pm_sum(lambda l, t, o, src: src * 4 * l),                    # source limbs in, column-transformed limbs out
-        "pm_frows_mac_irows": pm_sum(lambda l, t, o, src: (t + o) * 2 * l),      # those in per product, one sum per output limb out
-        # the same by the rule of the library: term by term, or, where sources enter at least two products each, in three kernels
+        # products by the rule of the library: term by term (sources in per product, one sum per output limb out), or, where
+        # sources enter at least two products each, in three kernels
         "pm_rows_mac": pm_sum(lambda l, t, o, src: (t + o) * 2 * l if t < 2 * src else 0),
         "pm_frows": pm_sum(lambda l, t, o, src: src * 4 * l if t >= 2 * src else 0),
         "pm_mac": pm_sum(lambda l, t, o, src: (src + o) * 2 * l if t >= 2 * src else 0),
