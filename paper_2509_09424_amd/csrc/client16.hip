@@ -23,11 +23,22 @@
 template <int N>
 __device__ __forceinline__ double sine(const double *cos_tab, u32 e) { return cos_tab[(e - N / 2) & (2 * N - 1)]; }
 // Consecutive passes of the transform on 2048 / LEN sequences of LEN points at once (element t of sequence b at x[t * B + b],
-// B = 2048 / LEN).  The butterfly of element p in the pass of local stride s has the exponent base(b) s + STEP p s.
+// B = 2048 / LEN).  The butterfly of element p in the pass of local stride s has the exponent base(b) s + STEP p s; a pass's
+// exponentials, scattered over the table, are requested before the barrier that precedes it.
 // Returns the buffer that holds the result; every thread may read it.
 template <int N, int LEN, int STEP, class F>
 __device__ __forceinline__ double2 *lds_passes(double2 *x, double2 *y, const double *cos_tab, int tid, F base) {
     constexpr int B = 2048 / LEN;
+    double2 tw[4];
+    auto fetch = [&](int s) {
+#pragma unroll
+        for (int m = 0; m < 4; m++) {
+            const int w = tid + CL_THREADS * m, t = w / B;
+            const u32 e = (u32)base(w % B) * s + (u32)(t - (t & (s - 1))) * STEP;
+            tw[m] = make_double2(cos_tab[e], sine<N>(cos_tab, e));
+        }
+    };
+    fetch(1);
     __syncthreads();
 #pragma unroll 1
     for (int s = 1; s < LEN; s *= 2) {
@@ -35,9 +46,9 @@ __device__ __forceinline__ double2 *lds_passes(double2 *x, double2 *y, const dou
         for (int m = 0; m < 4; m++) {
             const int w = tid + CL_THREADS * m, b = w % B, t = w / B;
             const int q = t & (s - 1), idx = t - q;
-            const u32 e = (u32)base(b) * s + (u32)idx * STEP;
-            fft_butterfly(x[t * B + b], x[(t + LEN / 2) * B + b], cos_tab[e], sine<N>(cos_tab, e), y[(q + 2 * idx) * B + b], y[(q + 2 * idx + s) * B + b]);
+            fft_butterfly(x[t * B + b], x[(t + LEN / 2) * B + b], tw[m].x, tw[m].y, y[(q + 2 * idx) * B + b], y[(q + 2 * idx + s) * B + b]);
         }
+        if (2 * s < LEN) fetch(2 * s);
         __syncthreads();
         double2 *h = x;
         x = y;
