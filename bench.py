@@ -728,7 +728,7 @@ def stagewise_rotation_units(w):
 def ntt_leg(ctx, w, n_limbs=1024, reps=5):
     """Stand-alone transform throughput (row (a1) of the scope table): n_limbs limb rows of N words, forward then
     inverse, in place, timed by the library's per-kernel HIP events; once on 50-bit ciphertext primes (the fp64-assisted
-    kernels) and once on the 60-bit special primes (integer kernels).  Algorithmic bytes: a transform reads and
+    kernels) and once on the 60-bit special primes (signed multiply-adds).  Algorithmic bytes: a transform reads and
     writes its limb once (2 limb-units); the two-pass implementation moves each limb twice (4 limb-units)."""
     import torch
     N = w.N

@@ -275,8 +275,8 @@ int ensi_rescale_ternary_matmul_prepared(ensi_ctx *ctx, ensi_ct *in, double kapp
  * use and keeps that form until freed. */
 int ensi_pmult_sum_rescale(ensi_ctx *ctx, const ensi_ct *in, const ensi_pt *pt, const int32_t *begin, const int32_t *term_ct,
                            const int32_t *term_pt, int32_t n_out, ensi_ct *out, void *stream);
-/* Selects the kernels of the plaintext multiplication: 0 = automatic (the fused N = 2^16 kernels whenever the
- * ring is 2^16 and every ciphertext prime is below 2^50, else the generic ones), 1 = always the generic
+/* Selects the kernels of the plaintext multiplication: 0 = automatic (the fused kernels on rings of 2^12 to 2^16
+ * with every ciphertext prime below 2^50, else the generic ones), 1 = always the generic
  * kernels.  Both give identical residues. */
 int ensi_set_pmult_mode(ensi_ctx *ctx, int32_t mode);
 

@@ -430,7 +430,7 @@ int get_moddown(ensi_ctx *ctx, int l1, const ModDownConst **out) {
     return ENSI_OK;
 }
 
-// Constants of the fused N = 2^16 key switch at level l1 (shares the integer ModUp tables).
+// Constants of the fused key switch at level l1 (shares the integer ModUp tables).
 int get_ks16(ensi_ctx *ctx, int l1, const Ks16Const **out) {
     auto it = ctx->ks16c.find(l1);
     if (it == ctx->ks16c.end()) {
@@ -547,8 +547,9 @@ static int pt_from_coeffs(ensi_ctx *ctx, const int64_t *d_coeffs, int n_pt, int 
     return ENSI_OK;
 }
 
-// Bytes of 64-bit words per polynomial that one chunk of a client-side batch takes (its host copies and workspaces are bounded by
-// that, and the copy of one chunk overlaps the kernels of the one before).
+// Bytes of one polynomial of 64-bit words per plaintext or ciphertext that a chunk of a client-side batch takes (16 of them at
+// N = 2^16): bounds the workspaces and the pinned copies.  Encode and encrypt enqueue a chunk's copies and kernels without waiting
+// for the chunk before; decrypt copies a chunk's slots to the caller before it starts the next.
 static constexpr size_t CLIENT_CHUNK = (size_t)8 << 20;
 
 // slots: host [n_pt][n_slots]; plaintext y holds its values in slots [slot0 + y*slot_step, ...+n_slots)

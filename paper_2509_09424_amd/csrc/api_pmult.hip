@@ -19,7 +19,7 @@ extern "C" int ensi_set_pmult_mode(ensi_ctx *ctx, int32_t mode) {
 }
 
 // Builds the multiplier form of a plaintext batch on first use: transform domain, Montgomery residues (generic
-// kernels) or doubles in the register order of the row pass (N = 2^16 kernels).
+// kernels) or doubles in the register order of the row pass (fused kernels).
 static int pt_prepare(ensi_ctx *ctx, const ensi_pt *pt, bool fused, hipStream_t st) {
     if (fused ? pt->d_fp != nullptr : pt->d_mont != nullptr) return ENSI_OK;
     const int rows = pt->n * pt->limbs;

@@ -7,7 +7,7 @@
 #include "api_util.h"
 #include "common.h"
 
-// 96 MiB: one ciphertext of the N = 2^16 ring at up to 16 + 4 limbs in four digits (80 MiB of intermediates), or a
+// 96 MiB: one ciphertext of the N = 2^16 ring at up to 16 + 4 limbs in four digits (80 MiB by the stated bound), or a
 // batch at smaller parameters.
 #define ENSI_STATIC_SCRATCH_BYTES ((size_t)96 << 20)
 #define ENSI_STATIC_MAX_BATCH 64

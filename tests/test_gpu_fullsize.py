@@ -131,7 +131,7 @@ def test_ffn_rescale_and_down_projection_full_size(name):
 def test_projection_full_size(name):
     """Projection workloads at full size -- the 768 x 768 projection (32 tokens, one packed input, 1023 Galois keys),
     the attention projection (128 tokens, 2560 x 2560, 10 packed inputs, 255 Galois keys) and the paper's QKV shape (2048 tokens, 1536 x 1536; 96 packed inputs and 15 keys at N = 2^16,
-    384 packed inputs and 3 keys at the paper's default ring N = 2^14, where the unfused kernels run), diagonal
+    384 packed inputs and 3 keys at the paper's default ring N = 2^14), diagonal
     placement: unpack rotations against the oracle on sampled outputs, then the workload's own weights."""
     w = wl.BY_NAME[name]
     p = Pair(w.param_tuple())

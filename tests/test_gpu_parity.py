@@ -310,7 +310,7 @@ def full():
 
 def test_full_ring_ntt_roundtrip_and_evaluation_set(full):
     """The N = 2^16 transform (register radix-16 steps; fp64 arithmetic on the 50-bit primes,
-    integer arithmetic on the 60-bit ones)."""
+    signed multiply-adds on the 60-bit ones)."""
     rng = np.random.default_rng(10)
     L = full.pr.L
     primes = full.pr.q + full.pr.p
