@@ -610,6 +610,30 @@ def test_client_transforms_equal_the_length_2n_transform(log_n, n):
         c.close()
 
 
+@pytest.mark.parametrize("log_n,n", [(12, 259), (16, 19)])
+def test_encrypt_and_decrypt_batches_of_several_chunks(log_n, n):
+    """A batch longer than one chunk, the last chunk ragged, gives the words and the slots of its ciphertexts one part at a time."""
+    from paper_2509_09424_amd import binding
+    c = binding.Context(log_n, 50, 3, 60, 1, 1, 40, seed=1)
+    rng = np.random.default_rng(9)
+    sk, pk = c.keygen(None, None, 5)
+    z = rng.uniform(-1, 1, (n, c.n_slots))
+    small = [wl.ternary_poly(rng, (n, c.N)), wl.error_poly(rng, (n, c.N)), wl.error_poly(rng, (n, c.N))]
+    pt = c.encode(z, 3)
+    ct = c.encrypt(pk, pt, *small)
+    words, slots = ct.export(), c.decrypt(sk, ct)
+    assert np.abs(slots - z).max() < 1e-3
+    for a, b in ((0, 1), (1, n // 2), (n // 2, n - 1), (n - 1, n)):
+        part = c.encode(z[a:b], 3)
+        part_ct = c.encrypt(pk, part, *[x[a:b] for x in small])
+        assert np.array_equal(part_ct.export(), words[a:b]) and np.array_equal(c.decrypt(sk, part_ct), slots[a:b]), (a, b)
+        for h in (part, part_ct):
+            h.free()
+    for h in (pt, ct, sk, pk):
+        h.free()
+    c.close()
+
+
 def test_encode_after_an_allocation_that_failed(small4):
     """A batch larger than any card is refused, and the next calls work."""
     from paper_2509_09424_amd import binding
