@@ -8,9 +8,17 @@
 // recombined with shifts and reduced mod q once per output word.  The result is
 // bit-identical to the sequence of modular additions and subtractions.
 //
-// Bytes are unsigned; the matrix pipe is signed, so each byte u is fed as u-128
-// (u xor 0x80) and 128 * sum_v W'[v][i] (`bias`) is added back to every plane of
-// output i when the planes are recombined.
+// The chip is bound by power in this kernel, and what an instruction draws hangs on its data: signed bytes times signed
+// weights keep the sign extensions of products and sums flipping.  Where the primes allow it the digits and the weights
+// are therefore made non-negative (AM_POS7: primes below 2^36 and 2^50): planes of 7 bits below a top plane of 8, weights
+// w + 1 in {0, 1, 2}, and the sum of all operands, one per word (`word sums`), taken off again when the planes are
+// recombined.  An LDS-fed loop of the instruction alone: 19.8 ns each on signed bytes and weights, 19.3 with the weights shifted,
+// 17.0 with both (the same digits and signed weights: 19.8).  A step of the kernel: 0.312 us before, 0.276 with them.
+// Primes between (37 to 40 bits: five planes of 8 bits, seven of 7), primes above 2^50, and products of up to AM_POS7_MIN operands,
+// where an item is mostly its recombination, use 8-bit planes and signed weights (AM_FP8, AM_INT8).
+//
+// The matrix pipe is signed: an 8-bit digit u is fed as u-128 (u xor 0x80), and 128 times the sum of the weights of output i
+// (`bias`) is added back to its plane when the planes are recombined.
 //
 // Operand v is the ciphertext at xbase + v*xstride words (the unpack phase writes its
 // rotations straight into that array).
@@ -41,8 +49,10 @@
 // The words are the first operand of the matrix instruction and the weights the second: under this load the chip is bound by
 // power, and a register-only loop on random bytes and ternary weights takes 41.1 cycles (of 2.4 GHz) per instruction this way
 // round against 46.3 the other.
-// An item's own cost, beside the 448 matrix-pipe cycles of each step, is its recombination: 12300 cycles, one wave to a SIMD
-// (15500 before decoding items by multiplication, adding the first step to a constant zero and no longer waiting for stores).
+// An item costs 5.2 us besides its steps, in a fit over 8 to 128 steps; without its stores 2.8, without its recombination 4.5,
+// without both 1.4.  The stores are bound by what the CUs of an XCD, which run in step, can write at once; spread over
+// the next item's steps (from registers) they cost more, 6 us, because a copy is not seen to have landed before the stores
+// issued ahead of it are done.
 // The step loop holds no vector-ALU instruction besides the matrix instructions: the running source addresses of the
 // copies are wave-uniform and live in scalar registers (a lane adds 16 * lane through the instruction's offset
 // operand).  Vector instructions issued between matrix instructions slow the matrix pipe down measurably -- four 64-bit
@@ -104,28 +114,60 @@ __device__ __forceinline__ u64 reduce_signed(int64_t t, u64 q, double q_inv) {
 // in 32-bit integers (S_p + 2^8 S_(p+1) < 2^31) and the pairs combined into lo + 2^32 hi with |lo| < 2^48 and
 // |hi| < 2^38.1 -- every product by a power of two and every sum below 2^53 is exact in a double.  One reduction:
 // k = rint((lo + B + 2^32 hi) / q) from two rounded products (off by far less than one half except within 2^-30 of
-// a tie), then 2^32 hi - k q, an integer below 2^52 in magnitude that the fused multiply-add returns exactly, plus
-// lo + B: a representative within (1/2 + 2^-30) q of zero, shifted into [0, q).
-template <int PLANES>
-__device__ __forceinline__ u64 recombine_fp(const int (&S)[PLANES], double B, double q, double q_inv) {
-    const int c01 = S[0] + (S[1] << 8), c23 = S[2] + (S[3] << 8);
-    const double lb = fma((double)c23, 65536.0, (double)c01) + B;
+// a tie), then 2^32 hi - k q, an integer below 2^52 in magnitude that the fused multiply-add returns exactly (as a multiple
+// of 2^-32: hi - k (q 2^-32)), plus lo + B: a representative within (1/2 + 2^-30) q of zero, shifted into [0, q).
+// AM_POS7: the same with 2^7 for 2^8.  Only the top plane has an offset; B is that offset 128 2^(7 (PLANES - 1)) (sum of the
+// weights) mod q less the word sum mod q, |B| < q.  |S_p| <= 2^23, so a pair stays below 2^31, lo below 2^45, hi below 2^38.
+struct AmModulus {
+    double q, q_inv, q_lo, q_inv_hi;  // q and 1/q; q / P4 and P4 / q
+};
+template <bool POS7>
+struct AmDigits {
+    static constexpr int BITS = POS7 ? 7 : 8;
+    static constexpr double P2 = 1 << 2 * BITS, P4 = (double)((int64_t)1 << 4 * BITS);
+};
+template <int PLANES, bool POS7>
+__device__ __forceinline__ u64 recombine_fp(const int (&S)[PLANES], double B, const AmModulus &m) {
+    constexpr int DB = AmDigits<POS7>::BITS;
+    constexpr double P2 = AmDigits<POS7>::P2, P4 = AmDigits<POS7>::P4;
+    const int c01 = S[0] + (S[1] << DB), c23 = S[2] + (S[3] << DB);
+    const double lb = fma((double)c23, P2, (double)c01) + B;
     double hi;
     if (PLANES == 7) {
-        const int c45 = S[4] + (S[5] << 8);
-        hi = fma((double)S[6], 65536.0, (double)c45);
+        const int c45 = S[4] + (S[5] << DB);
+        hi = fma((double)S[6], P2, (double)c45);
     } else {
         hi = (double)S[4];
     }
-    const double x = hi * 4294967296.0;
-    const double k = rint(fma(lb, q_inv, x * q_inv));
-    double u = fma(-k, q, x) + lb;
-    u = u < 0.0 ? u + q : u;
+    const double k = rint(fma(lb, m.q_inv, hi * m.q_inv_hi));
+    double u = fma(fma(-k, m.q_lo, hi), P4, lb);
+    u = u < 0.0 ? u + m.q : u;
     // an integer in [0, 2^52) plus 2^52 has that integer as its mantissa
     return (u64)__double_as_longlong(u + 4503599627370496.0) & 0xFFFFFFFFFFFFFull;
 }
 
 // ---------------------------------------------------------------- byte planes of the operands
+// Digits of a word, one per byte: planes 0 .. 3 in d[0], the rest in d[1].
+template <int PLANES, bool POS7>
+__device__ __forceinline__ void digits(u64 w, u32 *d) {
+    if (!POS7) {
+        d[0] = (u32)w;
+        d[1] = (u32)(w >> 32);
+        return;
+    }
+    // 28 bits as two halves of 14 sixteen bits apart, each then as two digits of 7 eight bits apart
+    auto bfi = [](u32 m, u32 a, u32 b) { return (a & m) | (b & ~m); };
+    const u32 lo = bfi(0x3fffu, (u32)w, (u32)w << 2);
+    d[0] = bfi(0x007f007fu, lo, lo << 1) & 0x7f7f7f7fu;
+    const u32 h = (u32)(w >> 28);
+    if (PLANES == 5) {
+        d[1] = h;  // the top digit alone
+    } else {
+        const u32 hi = bfi(0x3fffu, h, h << 2);  // bits 16 up: the top digit
+        d[1] = bfi(0x7f00u, hi << 1, hi) & 0x00ff7f7fu;
+    }
+}
+
 // Slice-local word tile: nt_local = pl * cw + ctile, pl = poly * l1 + limb, ctile = coefficient tile - c0.
 // Thread (k4 = tid / 32, ln = tid % 32) handles operands 4*k4 .. 4*k4+3 of a step, word ln: its four
 // words give one dword (4 operand bytes) of every plane.  A plane tile is staged in LDS and written out as
@@ -146,27 +188,58 @@ struct AmFp {  // fp64 arithmetic on exact integers modulo a prime below 2^50 (a
     }
 };
 
-template <int PLANES, int STEPS>
-__device__ __forceinline__ void planes_out(const u64 (&w)[STEPS][4], u32 (*stage)[PLANES * 256], int dst, v4i *out, int tid) {
+// red (POS7): the sum of the thread's operands, complete for the block after the first barrier.
+template <int PLANES, bool POS7, int STEPS>
+__device__ __forceinline__ void planes_out(const u64 (&w)[STEPS][4], u32 (*stage)[PLANES * 256], int dst, v4i *out, int tid, u64 *red) {
+    if (POS7) {
+        u64 t = 0;
+#pragma unroll
+        for (int s8 = 0; s8 < STEPS; s8++) t += (w[s8][0] + w[s8][1]) + (w[s8][2] + w[s8][3]);
+        red[tid] = t;
+    }
 #pragma unroll
     for (int s8 = 0; s8 < STEPS; s8++) {
-        u32 pl[8];
-        transpose4((u32)w[s8][0], (u32)w[s8][1], (u32)w[s8][2], (u32)w[s8][3], pl);
-        transpose4((u32)(w[s8][0] >> 32), (u32)(w[s8][1] >> 32), (u32)(w[s8][2] >> 32), (u32)(w[s8][3] >> 32), pl + 4);
+        u32 pl[8], d[4][2];
+#pragma unroll
+        for (int j = 0; j < 4; j++) digits<PLANES, POS7>(w[s8][j], d[j]);
+        transpose4(d[0][0], d[1][0], d[2][0], d[3][0], pl);
+        transpose4(d[0][1], d[1][1], d[2][1], d[3][1], pl + 4);
         u32 *st = stage[s8 & 1];
 #pragma unroll
-        for (int p = 0; p < PLANES; p++) st[p * 256 + dst] = pl[p] ^ 0x80808080u;
+        for (int p = 0; p < PLANES; p++) st[p * 256 + dst] = POS7 && p < PLANES - 1 ? pl[p] : pl[p] ^ 0x80808080u;
         __syncthreads();  // (the other staging buffer was read before the previous barrier)
         const v4i *sv = (const v4i *)st;
         for (int e = tid; e < PLANES * 64; e += AM_THREADS) out[(size_t)s8 * PLANES * 64 + e] = sv[e];
     }
 }
 
-// grid (cw, nk / 8, 2 * l1); each block converts 8 steps of one word tile.
-template <int PLANES>
+// Sum of a block's operands at each of its 32 words (red: of each thread's operands) -> part[0 .. 32).  Exact: the operands of a
+// product sum to less than 2^63.
+__device__ __forceinline__ void word_sums_out(const u64 *red, u64 *part, int tid) {
+    if (tid < AM_TILE_N) {
+        u64 t = red[tid];
+#pragma unroll
+        for (int k = 1; k < AM_THREADS / AM_TILE_N; k++) t += red[k * AM_TILE_N + tid];
+        part[tid] = t;
+    }
+}
+// part: [word tile][parts][32] -> tsum: [word tile][32] residues modulo the tile's prime, as doubles.  grid (n_tiles * 32 / AM_THREADS)
+__global__ __launch_bounds__(AM_THREADS) void k_word_sums(const u64 *part, int parts, int n_words, int cw, int l1, const PrimeConst *pc, double *tsum) {
+    const int i = blockIdx.x * AM_THREADS + threadIdx.x, tile = i / AM_TILE_N;
+    if (i >= n_words) return;
+    const u64 *p = part + (size_t)tile * parts * AM_TILE_N + i % AM_TILE_N;
+    u64 t = 0;
+    for (int k = 0; k < parts; k++) t += p[k * AM_TILE_N];
+    const u64 q = pc[tile / cw % l1].q;
+    tsum[i] = (double)reduce_signed((int64_t)t, q, 1.0 / (double)q);
+}
+
+// grid (cw, nk / 8, 2 * l1); each block converts 8 steps of one word tile.  POS7: part receives the block's word sums.
+template <int PLANES, bool POS7>
 __global__ __launch_bounds__(AM_THREADS) void k_byte_planes(const u64 *xbase, u32 xstride, int n_v, int nk, int N, int l1, int limb_stride_in,
-                                                            int c0, int cw, char *xp) {
+                                                            int c0, int cw, char *xp, u64 *part) {
     __shared__ u32 stage[2][PLANES * 256];
+    __shared__ u64 red[POS7 ? AM_THREADS : 1];
     const int tid = threadIdx.x, k4 = tid >> 5, ln = tid & 31;
     const int pl = blockIdx.z, poly = pl / l1, limb = pl - poly * l1;
     const u64 *xw = xbase + ((size_t)poly * limb_stride_in + limb) * N + (size_t)(c0 + blockIdx.x) * AM_TILE_N + ln;
@@ -182,7 +255,8 @@ __global__ __launch_bounds__(AM_THREADS) void k_byte_planes(const u64 *xbase, u3
             const int v = (blockIdx.y * 8 + s8) * AM_TILE_K + 4 * k4 + j;
             w[s8][j] = v < n_v ? xw[(size_t)v * xstride] : 0;
         }
-    planes_out<PLANES, 8>(w, stage, dst, out, tid);
+    planes_out<PLANES, POS7, 8>(w, stage, dst, out, tid, red);
+    if (POS7) word_sums_out(red, part + (((size_t)pl * cw + blockIdx.x) * gridDim.y + blockIdx.y) * AM_TILE_N, tid);
 }
 
 // The same with the scalar-multiply + rescale step applied on the way: the operands are read at l1 + 1
@@ -192,11 +266,12 @@ __global__ __launch_bounds__(AM_THREADS) void k_byte_planes(const u64 *xbase, u3
 // the centred last-limb residues of its 32 coefficients x 128 operands in registers and walks the limbs
 // (4 steps per block keep the register count low enough for four blocks per CU).
 #define AM_RS_STEPS 4
-template <int PLANES>
-__global__ __launch_bounds__(AM_THREADS) void k_byte_planes_rescale(const u64 *xbase, u32 xstride, int n_v, int nk, int N, int l1,
+template <int PLANES, bool POS7>
+__global__ __launch_bounds__(AM_THREADS, 4) void k_byte_planes_rescale(const u64 *xbase, u32 xstride, int n_v, int nk, int N, int l1,
                                                                     int limb_stride_in, int c0, int cw, char *xp, const PrimeConst *pc,
-                                                                    const double *fc) {
+                                                                    const double *fc, u64 *part) {
     __shared__ u32 stage[2][PLANES * 256];
+    __shared__ u64 red[POS7 ? AM_THREADS : 1];
     const int tid = threadIdx.x, k4 = tid >> 5, ln = tid & 31;
     const int poly = blockIdx.z, lin = l1 + 1;
     const u64 *xw = xbase + (size_t)poly * limb_stride_in * N + (size_t)(c0 + blockIdx.x) * AM_TILE_N + ln;
@@ -242,8 +317,9 @@ __global__ __launch_bounds__(AM_THREADS) void k_byte_planes_rescale(const u64 *x
                 w[s8][j] = j < n_live[s8] ? (u64)r : 0;
             }
         v4i *out = (v4i *)(xp + ((((size_t)poly * l1 + limb) * cw + blockIdx.x) * nk + (size_t)blockIdx.y * AM_RS_STEPS) * PLANES * 1024);
-        __syncthreads();  // the staging buffers of the previous limb have been written out
-        planes_out<PLANES, AM_RS_STEPS>(w, stage, dst, out, tid);
+        __syncthreads();  // the staging buffers of the previous limb have been written out, its word sums read
+        planes_out<PLANES, POS7, AM_RS_STEPS>(w, stage, dst, out, tid, red);
+        if (POS7) word_sums_out(red, part + ((((size_t)poly * l1 + limb) * cw + blockIdx.x) * gridDim.y + blockIdx.y) * AM_TILE_N, tid);
     }
 }
 
@@ -259,21 +335,24 @@ struct AmLayout {
     static constexpr int bring_off = 0;                                  // [AM_RING][AM_BSLOT]
     static constexpr int aring_off = bring_off + AM_RING * AM_BSLOT;     // [4 waves][AM_RING][AM_ASLOT]
     static constexpr int bias_off = aring_off + 4 * AM_RING * AM_ASLOT;  // [2][256] offset terms of an item's outputs (int32 or double)
-    static constexpr int out_off = bias_off + 2 * AM_TILE_M * 8;         // [4 waves][32 outputs][AM_OROW] results on their way out
+    static constexpr int tsum_off = bias_off + 2 * AM_TILE_M * 8;        // [2][32] word sums of an item (doubles; AM_POS7)
+    static constexpr int out_off = tsum_off + 2 * AM_TILE_N * 8;             // [4 waves][32 outputs][AM_OROW] results on their way out
     static constexpr int total = out_off + 4 * 32 * AM_OROW;
 };
 
 // xp: plane tiles of the slice, [word tile][nk][PLANES][1024]; the slice covers coefficient tiles c0 .. c0+cw-1
 // of all 2*l1 limb rows (n_tiles_n = 2*l1*cw word tiles); nk = n_kpad / 32, a multiple of AM_RING.
-// FP_EPI: every active prime is below 2^50, so the planes are recombined in double precision (recombine_fp) and bias
-// points to doubles [l1][n_tiles_m * 256], the offset term of every output reduced modulo each limb's prime; else the
-// planes are recombined in 64-bit integers and bias points to int32 [n_tiles_m * 256], 128 * column sum of the weights.
-template <int PLANES, bool FP_EPI>
+// MODE AM_POS7, AM_FP8: every active prime is below 2^50, so the planes are recombined in double precision (recombine_fp) and
+// bias points to doubles [l1][n_tiles_m * 256], the offset term of every output reduced modulo each limb's prime; AM_INT8:
+// the planes are recombined in 64-bit integers and bias points to int32 [n_tiles_m * 256], 128 * column sum of the weights.
+// tsum (AM_POS7): the word sums, [word tile][32].
+template <int PLANES, int MODE>
 __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, int c0, int cw, int n_kpad, const v4i *wfrag, const void *bias,
-                                                                int m, AmPrimes pr, int N, int l1, u64 *out, int limb_stride_out,
+                                                                const double *tsum, int m, AmPrimes pr, int N, int l1, u64 *out, int limb_stride_out,
                                                                 int n_tiles_n, int n_tiles_m, int workers_per_xcd, int m_group) {
     HIP_DYNAMIC_SHARED(char, smem)
     typedef AmLayout<PLANES> LY;
+    constexpr bool FP_EPI = MODE != AM_INT8, POS7 = MODE == AM_POS7;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, nl = lane & 31;
     const int nk = n_kpad / AM_TILE_K;
@@ -344,7 +423,11 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
     const u32 bias_lds = (u32)__builtin_amdgcn_readfirstlane((int)(smem0 + LY::bias_off + wv * 64 * BIAS_BYTES));
     const u32 recip_cw = 0xffffffffu / (u32)cw + 1;  // limb row of a word tile: exact for 2^16 tiles and cw up to 2^15
     auto limb_row = [&](const Item &t) { return cw == 1 ? t.nt_local : (int)__umulhi((u32)t.nt_local, recip_cw); };
+    const u32 tsum_lds = (u32)__builtin_amdgcn_readfirstlane((int)(smem0 + LY::tsum_off));
     auto issue_bias = [&](const Item &t, int buf) {
+        // (the word sums: every wave copies the same 256 bytes to the same place, and waits for its own copy only.  An item of more
+        // than one group of steps begins long after every wave has read those of the item before the last.)
+        if (POS7) dma_load4((const char *)(tsum + (size_t)t.nt_local * AM_TILE_N) + lane * 4, tsum_lds + (u32)buf * (AM_TILE_N * 8));
         if (FP_EPI) {
             // the wave's 64 doubles of the item's limb, as two copies of 4 bytes per lane (256 contiguous bytes each)
             const int pl = limb_row(t), limb = pl < l1 ? pl : pl - l1;
@@ -394,6 +477,7 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
         // offset terms of this item's outputs: copied one item ahead into two buffers used alternately (the
         // other one may still be read by a wave that has not finished the previous item's recombination)
         const char *bl = smem + LY::bias_off + (it & 1) * AM_TILE_M * BIAS_BYTES;
+        const double *tl = (const double *)(smem + LY::tsum_off) + (it & 1) * AM_TILE_N;
 
         v16i acc[PLANES][2];
         // Step ks multiplies from registers filled during step ks-1; meanwhile it reads the fragments of step
@@ -448,55 +532,63 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
         for (int ks0 = AM_RING; ks0 < nk; ks0 += AM_RING) steps(ks0, std::false_type());
         // here bf[0]/af[0] already hold step 0 of the next item
 
-        // Recombine planes, add the offset term 128 * sum_v W'[v][i] * sum_p 256^p, reduce mod q, store.
+        // Recombine planes, add the offset term of the output, take off the word sum, reduce mod q, store.
         // Accumulator register r of a lane holds output lane%32 of the block, word 16*(r/8) + 8*(lane/32) + r%8 (plane_row).
         // 32 outputs x 16 words at a time pass through LDS so that a store writes whole lines: outputs lie a power of two
         // apart, and stores of 16 bytes to each of 32 of them at once all went to one L2 channel.
+        // While one piece is on its way through LDS the next one is recombined.
         const u64 q = pr.q[limb];
         const double q_inv = pr.q_inv[limb], qd = (double)q;
+        const AmModulus md = {qd, q_inv, qd / AmDigits<POS7>::P4, q_inv * AmDigits<POS7>::P4};
         u64 ones = 0;
 #pragma unroll
         for (int p = 0; p < PLANES; p++) ones |= (u64)1 << (8 * p);
         const bool whole = i0 + 64 <= m;  // all 64 outputs of this wave exist (wave-uniform): stores need no bounds check
-#pragma unroll
-        for (int mb = 0; mb < 2; mb++) {
-            const int ib = i0 + mb * 32;
+        u64 res[4][2];
+        auto piece = [&](int mb, int h) {
             const double b_fp = FP_EPI ? ((const double *)bl)[wv * 64 + mb * 32 + nl] : 0.0;
             const int64_t b_int = FP_EPI ? 0 : (int64_t)((u64)(int64_t)((const int *)bl)[wv * 64 + mb * 32 + nl] * ones);
 #pragma unroll
-            for (int h = 0; h < 2; h++) {
+            for (int c = 0; c < 4; c++) {
+                double2 ts = make_double2(0.0, 0.0);
+                if (POS7) ts = *(const double2 *)(tl + 16 * h + 8 * g + 2 * c);
 #pragma unroll
-                for (int c = 0; c < 4; c++) {
-                    u64 res[2];
+                for (int e = 0; e < 2; e++) {
+                    const int r = 8 * h + 2 * c + e;
+                    if (FP_EPI) {
+                        int S[PLANES];
 #pragma unroll
-                    for (int e = 0; e < 2; e++) {
-                        const int r = 8 * h + 2 * c + e;
-                        if (FP_EPI) {
-                            int S[PLANES];
+                        for (int p = 0; p < PLANES; p++) S[p] = acc[p][mb][r];
+                        res[c][e] = recombine_fp<PLANES, POS7>(S, POS7 ? b_fp - (e ? ts.y : ts.x) : b_fp, md);
+                    } else {
+                        int64_t t = b_int;
 #pragma unroll
-                            for (int p = 0; p < PLANES; p++) S[p] = acc[p][mb][r];
-                            res[e] = recombine_fp<PLANES>(S, b_fp, qd, q_inv);
-                        } else {
-                            int64_t t = b_int;
-#pragma unroll
-                            for (int p = 0; p < PLANES; p++) t += (int64_t)((u64)(int64_t)acc[p][mb][r] << (8 * p));
-                            res[e] = reduce_signed(t, q, q_inv);
-                        }
+                        for (int p = 0; p < PLANES; p++) t += (int64_t)((u64)(int64_t)acc[p][mb][r] << (8 * p));
+                        res[c][e] = reduce_signed(t, q, q_inv);
                     }
-                    *(ulonglong2 *)(o_lds + nl * AM_OROW + g * 64 + c * 16) = make_ulonglong2(res[0], res[1]);
                 }
-                wave_lds_fence();
-#pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    const int row = 8 * k + (lane >> 3);
-                    const ulonglong2 w = *(const ulonglong2 *)(o_lds + row * AM_OROW + (lane & 7) * 16);
-                    const ct_pair v = {w.x, w.y};
-                    u64 *o = out + (size_t)(ib + row) * ct_words_out + off_out + 16 * h + (lane & 7) * 2;
-                    if (whole) *(ct_pair *)o = v;
-                    else if (ib + row < m) *(ct_pair *)o = v;
-                }
-                wave_lds_fence();
             }
+        };
+        piece(0, 0);
+#pragma unroll
+        for (int mh = 0; mh < 4; mh++) {
+            const int ib = i0 + (mh >> 1) * 32, h = mh & 1;
+#pragma unroll
+            for (int c = 0; c < 4; c++) *(ulonglong2 *)(o_lds + nl * AM_OROW + g * 64 + c * 16) = make_ulonglong2(res[c][0], res[c][1]);
+            wave_lds_fence();
+            ulonglong2 w[4];
+#pragma unroll
+            for (int k = 0; k < 4; k++) w[k] = *(const ulonglong2 *)(o_lds + (8 * k + (lane >> 3)) * AM_OROW + (lane & 7) * 16);
+            if (mh < 3) piece((mh + 1) >> 1, (mh + 1) & 1);
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const int row = 8 * k + (lane >> 3);
+                const ct_pair v = {w[k].x, w[k].y};
+                u64 *o = out + (size_t)(ib + row) * ct_words_out + off_out + 16 * h + (lane & 7) * 2;
+                if (whole) *(ct_pair *)o = v;
+                else if (ib + row < m) *(ct_pair *)o = v;
+            }
+            wave_lds_fence();
         }
         stores_pending = whole;
         if (!whole) wait_vmcnt<0>();  // some stores were left out: start the next item from a known count
@@ -505,13 +597,14 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
     wait_vmcnt<0>();  // no copy may still be in flight into LDS when the workgroup ends
 }
 
-template <int P, bool FP_EPI>
+template <int P, int MODE>
 static void am_launch(ensi_ctx *ctx, unsigned grid, hipStream_t st, const u64 *xbase, u32 xstride, int n_v, int n_kpad, const v4i *wfrag,
                       const void *bias, int m, int l1, int limb_stride_in, u64 *out, int limb_stride_out, int n_tiles_m, int workers,
                       int m_group, char *xp, int slice_ctiles, const double *d_rescale) {
-    bool &attr_set = ctx->am_attr_set[(P == 5 ? 0 : 1) + (FP_EPI ? 0 : 2)];
+    constexpr bool POS7 = MODE == AM_POS7;
+    bool &attr_set = ctx->am_attr_set[2 * MODE + (P == 5 ? 0 : 1)];
     if (!attr_set) {
-        (void)hipFuncSetAttribute((const void *)k_accumulate_mfma<P, FP_EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, AmLayout<P>::total);
+        (void)hipFuncSetAttribute((const void *)k_accumulate_mfma<P, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, AmLayout<P>::total);
         attr_set = true;
     }
     const int nk = n_kpad / AM_TILE_K, ctiles = ctx->N / AM_TILE_N;
@@ -520,21 +613,29 @@ static void am_launch(ensi_ctx *ctx, unsigned grid, hipStream_t st, const u64 *x
         pr.q[i] = i < l1 ? ctx->primes[i] : 1;
         pr.q_inv[i] = 1.0 / (double)pr.q[i];
     }
+    // behind the planes of a slice: its partial word sums, then the word sums
+    const int parts = d_rescale ? nk / AM_RS_STEPS : nk / 8;
+    u64 *part = (u64 *)(xp + (size_t)2 * l1 * slice_ctiles * nk * P * 1024);
+    double *tsum = (double *)(part + (size_t)2 * l1 * slice_ctiles * parts * AM_TILE_N);
     for (int c0 = 0; c0 < ctiles; c0 += slice_ctiles) {
-        const int cw = std::min(slice_ctiles, ctiles - c0);
+        const int cw = std::min(slice_ctiles, ctiles - c0), n_words = 2 * l1 * cw * AM_TILE_N;
         {
             ScopedTimer t(ctx, d_rescale ? "rescale_byte_planes" : "byte_planes", st);
             if (d_rescale)
-                hipLaunchKernelGGL(k_byte_planes_rescale<P>, dim3(cw, nk / AM_RS_STEPS, 2), dim3(AM_THREADS), 0, st, xbase, xstride, n_v, nk, ctx->N, l1,
-                                   limb_stride_in, c0, cw, xp, ctx->d_pc, d_rescale);
+                hipLaunchKernelGGL((k_byte_planes_rescale<P, POS7>), dim3(cw, nk / AM_RS_STEPS, 2), dim3(AM_THREADS), 0, st, xbase, xstride, n_v, nk, ctx->N, l1,
+                                   limb_stride_in, c0, cw, xp, ctx->d_pc, d_rescale, part);
             else
-                hipLaunchKernelGGL(k_byte_planes<P>, dim3(cw, nk / 8, 2 * l1), dim3(AM_THREADS), 0, st, xbase, xstride, n_v, nk, ctx->N, l1,
-                                   limb_stride_in, c0, cw, xp);
+                hipLaunchKernelGGL((k_byte_planes<P, POS7>), dim3(cw, nk / 8, 2 * l1), dim3(AM_THREADS), 0, st, xbase, xstride, n_v, nk, ctx->N, l1,
+                                   limb_stride_in, c0, cw, xp, part);
+        }
+        if (POS7) {
+            ScopedTimer t(ctx, "word_sums", st);
+            hipLaunchKernelGGL(k_word_sums, dim3((n_words + AM_THREADS - 1) / AM_THREADS), dim3(AM_THREADS), 0, st, part, parts, n_words, cw, l1, ctx->d_pc, tsum);
         }
         {
             ScopedTimer t(ctx, "accumulate_mfma", st);
-            hipLaunchKernelGGL((k_accumulate_mfma<P, FP_EPI>), dim3(grid), dim3(AM_THREADS), AmLayout<P>::total, st, (const char *)xp, c0, cw, n_kpad, wfrag,
-                               bias, m, pr, ctx->N, l1, out, limb_stride_out, 2 * l1 * cw, n_tiles_m, workers, m_group);
+            hipLaunchKernelGGL((k_accumulate_mfma<P, MODE>), dim3(grid), dim3(AM_THREADS), AmLayout<P>::total, st, (const char *)xp, c0, cw, n_kpad, wfrag,
+                               bias, tsum, m, pr, ctx->N, l1, out, limb_stride_out, 2 * l1 * cw, n_tiles_m, workers, m_group);
         }
     }
 }
@@ -549,7 +650,7 @@ static int am_slice_ctiles(int ctiles, int l1, int n_kpad, int planes) {
 // d_rescale != nullptr: the operands are read at l1 + 1 limbs and the scalar-multiply + rescale step is applied while
 // their planes are built (constants as for k_rescale_fp at l1 + 1 limbs); out is at l1 limbs.
 int launch_accumulate_mfma(ensi_ctx *ctx, const u64 *xbase, size_t xstride, int n_v, int n_kpad, const int8_t *d_wt, const int32_t *d_bias,
-                           const double *d_bias_fp, int planes, int m, int l1, int limb_stride_in, u64 *out, int limb_stride_out, const double *d_rescale,
+                           const double *d_bias_fp, int planes, int mode, int m, int l1, int limb_stride_in, u64 *out, int limb_stride_out, const double *d_rescale,
                            hipStream_t st) {
     const int ctiles = ctx->N / AM_TILE_N;
     const int n_tiles_m = (m + AM_TILE_M - 1) / AM_TILE_M;
@@ -565,7 +666,8 @@ int launch_accumulate_mfma(ensi_ctx *ctx, const u64 *xbase, size_t xstride, int 
     const int m_group = 8;  // 8 output tiles x 4 word tiles in flight per XCD
     const int P = planes <= 5 ? 5 : 7;
     const int slice_ctiles = am_slice_ctiles(ctiles, l1, n_kpad, P);
-    const size_t xp_words = ((size_t)slice_ctiles * 2 * l1 * (n_kpad / AM_TILE_K) * P * 1024 + 7) / 8;
+    const size_t tiles = (size_t)slice_ctiles * 2 * l1, nk = n_kpad / AM_TILE_K;
+    const size_t xp_words = tiles * nk * P * 128 + (mode == AM_POS7 ? tiles * (nk / AM_RS_STEPS + 1) * AM_TILE_N : 0);
     if (ctx->ws_xp_words < xp_words) {
         if (ctx->ws_xp) (void)hipFree(ctx->ws_xp);
         ctx->ws_xp = nullptr;
@@ -576,17 +678,18 @@ int launch_accumulate_mfma(ensi_ctx *ctx, const u64 *xbase, size_t xstride, int 
         }
         ctx->ws_xp_words = xp_words;
     }
-    bool fp_epi = d_bias_fp != nullptr;  // the double-precision recombination is exact while every active prime is below 2^50
-    for (int i = 0; i < l1; i++) fp_epi = fp_epi && ctx->primes[i] < ((u64)1 << 50);
-#define AM_LAUNCH(PL, FP)                                                                                                              \
-    am_launch<PL, FP>(ctx, grid, st, xbase, (u32)xstride, n_v, n_kpad, wf, (FP) ? (const void *)d_bias_fp : (const void *)d_bias, m, l1, limb_stride_in, out, limb_stride_out, n_tiles_m, \
-                      workers, m_group, (char *)ctx->ws_xp, slice_ctiles, d_rescale)
-    if (P == 5) {
-        if (fp_epi) AM_LAUNCH(5, true);
-        else AM_LAUNCH(5, false);
+    const void *bias = mode == AM_INT8 ? (const void *)d_bias : (const void *)d_bias_fp;
+#define AM_LAUNCH(PL, MODE)                                                                                                              \
+    am_launch<PL, MODE>(ctx, grid, st, xbase, (u32)xstride, n_v, n_kpad, wf, bias, m, l1, limb_stride_in, out, limb_stride_out, n_tiles_m, \
+                        workers, m_group, (char *)ctx->ws_xp, slice_ctiles, d_rescale)
+    if (mode == AM_POS7) {
+        if (P == 5) AM_LAUNCH(5, AM_POS7);
+        else AM_LAUNCH(7, AM_POS7);
+    } else if (mode == AM_FP8) {
+        if (P == 5) AM_LAUNCH(5, AM_FP8);
+        else AM_LAUNCH(7, AM_FP8);
     } else {
-        if (fp_epi) AM_LAUNCH(7, true);
-        else AM_LAUNCH(7, false);
+        AM_LAUNCH(7, AM_INT8);
     }
 #undef AM_LAUNCH
     return ENSI_OK;

@@ -86,11 +86,27 @@ static int build_plan(ensi_ctx *ctx, const int8_t *W, int s, int d, int m, int p
     std::vector<int8_t> wt;
     std::vector<int32_t> bias;
     if (mfma_ok) {
-        const int need = (qbits + 7) / 8;
-        p->planes = need <= 5 ? 5 : 7;  // qbits <= 56: never more than seven byte planes
+        // Non-negative digits and weights cost the matrix cores least power: six planes of 7 bits and one of 8 hold 50 bits,
+        // four and one 36.  A prime of 37 to 40 bits would take seven planes that way and takes five of 8 bits instead; short sums
+        // do not gain.
+        p->planes = qbits <= 40 ? 5 : 7;  // qbits <= 56: never more than seven byte planes
+        const bool pos7 = n_v > AM_POS7_MIN && (qbits <= 36 || (qbits > 40 && qbits <= 50));
+        p->am_mode = qbits > 50 ? AM_INT8 : pos7 ? AM_POS7 : AM_FP8;
         wt.assign((size_t)p->m_pad * p->n_kpad, 0);
         bias.assign(p->m_pad, 0);
     }
+    // the place of weight (v, i) in fragment order: [output tile of 256][step of 32 operands][wave][block of 32][lane][16 bytes],
+    // lane = 32*(operand half of the step) + output within the block
+    auto wt_at = [&](int v, int i) -> int8_t & {
+        const size_t cell = ((((size_t)(i / 256) * (p->n_kpad / 32) + v / 32) * 4 + (i % 256) / 64) * 2 + (i % 64) / 32) * 64 +
+                            ((v % 32) / 16) * 32 + i % 32;
+        return wt[cell * 16 + v % 16];
+    };
+    if (mfma_ok && p->am_mode == AM_POS7)
+        for (int i = 0; i < m; i++) {
+            for (int v = 0; v < n_v; v++) wt_at(v, i) = 1;
+            bias[i] = n_v;
+        }
     for (int j = 0; j < d; j++) {
         const int G = j / c_tot, b = j % c_tot;
         const int8_t *row = W + (size_t)j * m;
@@ -102,26 +118,25 @@ static int build_plan(ensi_ctx *ctx, const int8_t *W, int s, int d, int m, int p
             const int v = p->vid[(size_t)G * c_tot + rho];
             masks[((size_t)(i / 32) * n_v + v) * 2 + (row[i] > 0 ? 0 : 1)] |= 1u << (i % 32);
             if (mfma_ok) {
-                // fragment order: [output tile of 256][step of 32 operands][wave][block of 32][lane][16 bytes],
-                // lane = 32*(operand half of the step) + output within the block
-                const size_t cell = ((((size_t)(i / 256) * (p->n_kpad / 32) + v / 32) * 4 + (i % 256) / 64) * 2 + (i % 64) / 32) * 64 +
-                                    ((v % 32) / 16) * 32 + i % 32;
-                wt[cell * 16 + v % 16] = row[i];
+                wt_at(v, i) += row[i];
                 bias[i] += row[i];
             }
         }
     }
     if (mfma_ok)
-        for (int i = 0; i < m; i++) bias[i] *= 128;  // every byte is fed to the matrix pipe as u - 128
+        for (int i = 0; i < m; i++) bias[i] *= 128;  // a byte is fed to the matrix pipe as u - 128 (AM_POS7: of the top plane)
     hipError_t e1 = upload(ctx, &p->d_masks, masks), e2 = hipSuccess, e3 = hipSuccess, e4 = hipSuccess;
     if (mfma_ok) {
         e2 = upload(ctx, &p->d_wt, wt);
-        e3 = upload(ctx, &p->d_bias, bias);
-        if (qbits <= 50) {
+        if (p->am_mode == AM_INT8) {
+            e3 = upload(ctx, &p->d_bias, bias);
+        } else {
             // the recombination in double precision adds the offset term already reduced: b * sum_p 256^p mod q_limb
+            // (AM_POS7: b * 128^(planes - 1))
             std::vector<double> bias_fp((size_t)l1 * p->m_pad, 0.0);
             __int128 ones = 0;
             for (int pl = 0; pl < p->planes; pl++) ones |= (__int128)1 << (8 * pl);
+            if (p->am_mode == AM_POS7) ones = (__int128)1 << (7 * (p->planes - 1));
             for (int limb = 0; limb < l1; limb++) {
                 const __int128 q = (__int128)ctx->primes[limb];
                 for (int i = 0; i < m; i++) {
@@ -333,7 +348,7 @@ static int matmul_run(ensi_ctx *ctx, const ensi_gk *gk, const ensi_ct *in, Matmu
     // ---- Alg. 1: signed sums
     const bool use_mfma = plan->planes > 0 && ctx->accumulate_mode != 1;
     if (use_mfma) {
-        if ((rc = launch_accumulate_mfma(ctx, xbase, in_ct, n_v, plan->n_kpad, plan->d_wt, plan->d_bias, plan->d_bias_fp, plan->planes, m, l1, in->limbs_alloc,
+        if ((rc = launch_accumulate_mfma(ctx, xbase, in_ct, n_v, plan->n_kpad, plan->d_wt, plan->d_bias, plan->d_bias_fp, plan->planes, plan->am_mode, m, l1, in->limbs_alloc,
                                          out->d, out->limbs_alloc, nullptr, st)))
             return rc;
     } else
@@ -423,7 +438,7 @@ static int rescale_matmul_run(ensi_ctx *ctx, ensi_ct *in, double kappa, MatmulPl
     const double *d_fconsts;
     const double kr = rescale_constant(ctx, l1_in, kappa);
     if ((rc = upload_rescale_consts(ctx, l1_in, kr, kappa < 0, st, &d_consts, &d_fconsts, &fp))) return rc;
-    if ((rc = launch_accumulate_mfma(ctx, in->d, (size_t)2 * in->limbs_alloc * N, d, plan->n_kpad, plan->d_wt, plan->d_bias, plan->d_bias_fp, plan->planes, m, l1,
+    if ((rc = launch_accumulate_mfma(ctx, in->d, (size_t)2 * in->limbs_alloc * N, d, plan->n_kpad, plan->d_wt, plan->d_bias, plan->d_bias_fp, plan->planes, plan->am_mode, m, l1,
                                      in->limbs_alloc, out->d, out->limbs_alloc, d_fconsts, st)))
         return rc;
     in->limbs = l1;

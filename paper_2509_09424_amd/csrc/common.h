@@ -168,6 +168,15 @@ struct RotDesc {
     u32 pad;
 };
 
+// Digits and weights of the signed sums on the matrix cores (accumulate_mfma.hip).  AM_POS7 needs less power and more work per
+// output word: us per item of 256 x 32 words, 1536 to 4096 operands 18.5 to 40.8 against 19.2 to 44.8, 512 operands 9.9 against 9.8.
+#define AM_POS7_MIN 512  // operands up to which the other digits are taken
+enum {
+    AM_POS7 = 0,  // planes of 7 bits and a top one of 8, weights 0, 1, 2; recombined in double precision (primes below 2^36 or 2^50)
+    AM_FP8 = 1,   // planes of 8 bits, weights -1, 0, 1; recombined in double precision
+    AM_INT8 = 2,  // the same, recombined in 64-bit integers (primes of more than 50 bits)
+};
+
 // Everything about one ternary_matmul that depends only on (W, s, d, m, placement).
 struct MatmulPlan {
     u64 hash;
@@ -176,10 +185,11 @@ struct MatmulPlan {
     int n_v, n_rot;
     std::vector<int> vid;        // [n_in][c_tot] -> operand index or -1
     int n_kpad, m_pad, planes;   // matrix-core layout (planes = 0: not built, use the plain-ALU kernel)
+    int am_mode = 0;             // AM_*: digits and weights of that layout
     u32 *d_masks = nullptr;      // [tiles32][n_v][2] (+1 bits, -1 bits)
-    int8_t *d_wt = nullptr;      // [m_pad][n_kpad] weights, operand index fastest
-    int32_t *d_bias = nullptr;   // [m_pad] 128 * column sum of the weights
-    double *d_bias_fp = nullptr; // [l1][m_pad] that offset times sum_p 256^p, reduced modulo each limb's prime (all primes below 2^50), else null
+    int8_t *d_wt = nullptr;      // [m_pad][n_kpad] weights (AM_POS7: plus one), in fragment order
+    int32_t *d_bias = nullptr;   // AM_INT8: [m_pad] 128 * column sum of the weights
+    double *d_bias_fp = nullptr; // else [l1][m_pad] that offset times the planes' powers that carry it, reduced modulo each limb's prime
 };
 
 struct KernelTimer {
@@ -291,7 +301,7 @@ struct ensi_ctx {
     StageSlot stage[ENSI_STAGE_SLOTS];
     int stage_next = 0;
     int n_cu = 0;                // compute units of the context's device (0: not queried yet)
-    bool am_attr_set[4] = {false, false, false, false};  // dynamic LDS limit of the matrix-core accumulate kernels raised
+    bool am_attr_set[6] = {};    // dynamic LDS limit of the matrix-core accumulate kernels raised
     // timers
     bool profiling = false;
     std::vector<KernelTimer> timers;
@@ -403,11 +413,11 @@ void launch_accumulate(ensi_ctx *ctx, const u64 *xbase, size_t xstride, int n_v,
 void launch_rescale(ensi_ctx *ctx, u64 *ct, int n_ct, int l1, int limb_stride, const u64 *d_consts, const double *d_fconsts,
                     hipStream_t st);
 // planes: 5 or 7 byte planes contracted; weights d_wt in fragment order [m_pad/256][n_kpad/32][4][2][64][16], n_kpad a
-// multiple of 256.  Grows ctx->ws_xp (byte planes of a slice of the operand words); returns an ENSI_E_* code.
+// multiple of 256, and their mode AM_*.  Grows ctx->ws_xp (byte planes of a slice of the operand words); returns an ENSI_E_* code.
 // d_rescale != nullptr: operands are read at l1 + 1 limbs and multiplied/rescaled on the fly (fp64 constants [5][l1+1]).
 int launch_accumulate_mfma(ensi_ctx *ctx, const u64 *xbase, size_t xstride, int n_v, int n_kpad, const int8_t *d_wt, const int32_t *d_bias,
                            const double *d_bias_fp,
-                           int planes, int m, int l1, int limb_stride_in, u64 *out, int limb_stride_out, const double *d_rescale,
+                           int planes, int mode, int m, int l1, int limb_stride_in, u64 *out, int limb_stride_out, const double *d_rescale,
                            hipStream_t st);
 // sustained int8 matrix-instruction rate over the whole chip, measured for about `seconds`
 int launch_matrix_rate(ensi_ctx *ctx, double seconds, double *ops_per_second, hipStream_t st);

@@ -215,6 +215,52 @@ def test_matmul_many_operands_and_wide_primes():
             p.close()
 
 
+@pytest.mark.parametrize("bits,operands,outputs", [(36, 513, 33), (36, 768, 257), (38, 769, 64), (50, 512, 33), (50, 513, 97), (50, 1100, 257), (54, 520, 40)])
+def test_signed_sums_by_digits(bits, operands, outputs):
+    """Every way the words of the signed sums are cut into digits (7 bits with shifted weights: more than 512 operands below
+    2^36 and 2^50; 8 bits: the others) on the smallest and largest residues, ragged operand and output counts, and with
+    the rescale between two layers applied on the way: plain integers, and the plain-ALU kernel on every word."""
+    import torch
+
+    from paper_2509_09424_amd import binding
+    ctx = binding.Context(12, bits, 3, bits + 2, 1, 1, 20, seed=1)
+    L, N, q = 3, ctx.N, [int(x) for x in ctx.primes()[0]]
+    W = np.random.default_rng(bits + operands).integers(-1, 2, (operands, outputs)).astype(np.int8)
+    W[:, 0], W[:, 1] = 1, -1  # the largest sums of either sign
+    x = torch.empty((operands, 2, L, N), dtype=torch.int64, device="cuda")
+    for i in range(L):
+        x[:, :, i].random_(0, q[i], generator=torch.Generator(device="cuda").manual_seed(i))
+        x[:, :, i, :40] = q[i] - 1
+    x[:, :, :, 40:80] = 0
+    rows = [0, 1, outputs - 1]
+    words = x[:, 1, :, 30:100].cpu().numpy().astype(object)
+    want = np.stack([sum(int(W[v, r]) * words[v] for v in range(operands)) % np.array(q, dtype=object)[:, None] for r in rows])
+
+    def product(mode, rescale):
+        ctx.set_accumulate_mode(mode)
+        limbs = L - rescale
+        src, out = x.clone(), torch.full((outputs, 2, limbs, N), -1, dtype=torch.int64, device="cuda")
+        h_in, h_out = ctx.ct_wrap(src.data_ptr(), operands, L, 1.0), ctx.ct_wrap(out.data_ptr(), outputs, limbs, 1.0)
+        wt = ctx.weights_prepare(W, ctx.n_slots, operands, "zero", limbs)
+        if rescale:
+            ctx.rescale_ternary_matmul_prepared(h_in, 2.0 ** -5, wt, h_out)
+        else:
+            ctx.ternary_matmul_prepared(None, h_in, wt, h_out)
+        torch.cuda.synchronize()
+        for h in (wt, h_in, h_out):
+            h.free()
+        return out
+
+    try:
+        for rescale in (False, True):
+            plain, matrix = product(1, rescale), product(2, rescale)
+            assert torch.equal(plain, matrix), "rescale %s" % rescale
+            if not rescale:
+                assert np.array_equal(matrix[rows, 1, :, 30:100].cpu().numpy().astype(object), want)
+    finally:
+        ctx.close()
+
+
 def test_mul_scalar_rescale_bit_exact_and_two_layer(small4):
     p = small4
     rng = np.random.default_rng(7)
