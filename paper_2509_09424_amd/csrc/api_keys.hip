@@ -163,11 +163,13 @@ extern "C" void ensi_pk_free(ensi_pk *pk) {
 // Scratch of the switching-key generation (one secret, any number of keys).
 struct KeygenScratch {
     DevBuf d_s, d_target, d_e8, d_e, d_fac, d_s8;
+    DevBuf d_pair;  // one digit of a key on its way into the stored format (fused kernels only)
 };
 static int keygen_scratch(ensi_ctx *ctx, const ensi_sk *sk, KeygenScratch &k, hipStream_t st) {
     const int N = ctx->N, ext = ctx->L + ctx->K;
     if (k.d_s.alloc(ctx, (size_t)ext * N * 8) != hipSuccess || k.d_target.alloc(ctx, (size_t)ext * N * 8) != hipSuccess || k.d_e8.alloc(ctx, N) != hipSuccess ||
-        k.d_e.alloc(ctx, (size_t)ext * N * 8) != hipSuccess || k.d_fac.alloc(ctx, (size_t)ext * 8) != hipSuccess || k.d_s8.alloc(ctx, N) != hipSuccess)
+        k.d_e.alloc(ctx, (size_t)ext * N * 8) != hipSuccess || k.d_fac.alloc(ctx, (size_t)ext * 8) != hipSuccess || k.d_s8.alloc(ctx, N) != hipSuccess ||
+        (ctx->ks16 && k.d_pair.alloc(ctx, (size_t)2 * ext * N * 8) != hipSuccess))
         ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in key generation");
     (void)hipMemcpy(k.d_s8.p, sk->s.data(), N, hipMemcpyHostToDevice);
     launch_small_to_rns(ctx, k.d_s8.as<int8_t>(), 1, make_map(ctx, ctx->L, true), k.d_s.as<u64>(), st);  // coefficient form of s
@@ -175,15 +177,15 @@ static int keygen_scratch(ensi_ctx *ctx, const ensi_sk *sk, KeygenScratch &k, hi
 }
 // key <- hybrid key-switching key from the secret in k.d_target (transform domain, ordinary residues) to s:
 // per digit j, (b_j, a_j) with b_j = -a_j s + e_j + [P]_{q_i} target on the limbs of digit j.  e: host
-// int8[beta][N] or NULL; a_j is the uniform stream stream_base | j.
-static int make_switch_key(ensi_ctx *ctx, const ensi_sk *sk, KeygenScratch &k, const int8_t *e, uint64_t seed_a, u64 stream_base, u64 *key,
+// int8[beta][N] or NULL; a_j is the uniform stream stream_base | j.  g: the element the key is for.
+static int make_switch_key(ensi_ctx *ctx, const ensi_sk *sk, KeygenScratch &k, const int8_t *e, uint64_t seed_a, u64 stream_base, u32 g, u64 *key,
                             hipStream_t st) {
     const int N = ctx->N, L = ctx->L, K = ctx->K, ext = L + K;
     const int beta = (L + ctx->alpha - 1) / ctx->alpha;
     LimbMap mext = make_map(ctx, L, true);
     std::vector<int8_t> ev(N);
     for (int j = 0; j < beta; j++) {
-        u64 *kb = key + (size_t)(j * 2) * ext * N, *ka = kb + (size_t)ext * N;
+        u64 *pair = key + (size_t)(j * 2) * ext * N, *kb = ctx->ks16 ? k.d_pair.as<u64>() : pair, *ka = kb + (size_t)ext * N;
         if (e) memcpy(ev.data(), e + (size_t)j * N, N);
         else if (sample_error(ctx, ev.data(), N)) return ENSI_E_BADARG;
         (void)hipMemcpyAsync(k.d_e8.p, ev.data(), N, hipMemcpyHostToDevice, st);
@@ -203,8 +205,8 @@ static int make_switch_key(ensi_ctx *ctx, const ensi_sk *sk, KeygenScratch &k, c
         (void)hipStreamSynchronize(st);
         launch_key_assemble(ctx, kb, ka, sk->d_s_hat, k.d_e.as<u64>(), k.d_target.as<u64>(), k.d_fac.as<u64>(), mext, st);
         launch_to_mont(ctx, ka, ext, mext, st);
+        if (ctx->ks16) launch_ks16_key_format(ctx, kb, pair, 2 * ext, g, st);
     }
-    if (ctx->ks16) launch_ks16_key_format(ctx, key, beta, st);
     return ENSI_OK;
 }
 
@@ -235,7 +237,7 @@ extern "C" int ensi_galois_keygen(ensi_ctx *ctx, const ensi_sk *sk, const int32_
         // phi_g(s), transform domain
         launch_automorphism_coef(ctx, k.d_target.as<u64>(), k.d_s.as<u64>(), mext, inv_mod_2n(g, N), st);
         launch_ntt(ctx, k.d_target.as<u64>(), ext, mext, false, st);
-        if ((rc = make_switch_key(ctx, sk, k, e ? e + (size_t)t * beta * N : nullptr, seed_a, ((u64)2 << 56) | ((u64)g << 8), key, st))) {
+        if ((rc = make_switch_key(ctx, sk, k, e ? e + (size_t)t * beta * N : nullptr, seed_a, ((u64)2 << 56) | ((u64)g << 8), g, key, st))) {
             ensi_gk_free(gk);
             return rc;
         }
@@ -273,7 +275,7 @@ extern "C" int ensi_relin_keygen(ensi_ctx *ctx, const ensi_sk *sk, const int8_t 
     // s^2, transform domain: NTT(s) (.) NTT(s), the second factor in Montgomery form
     launch_ntt(ctx, k.d_s.as<u64>(), ext, mext, false, st);
     launch_mul_mont(ctx, k.d_target.as<u64>(), k.d_s.as<u64>(), sk->d_s_hat, ext, mext, st);
-    if ((rc = make_switch_key(ctx, sk, k, e, seed_a, (u64)3 << 56, key, st))) {
+    if ((rc = make_switch_key(ctx, sk, k, e, seed_a, (u64)3 << 56, 1u, key, st))) {
         ensi_gk_free(gk);
         return rc;
     }
@@ -383,9 +385,12 @@ extern "C" int ensi_gk_export(ensi_ctx *ctx, const ensi_gk *gk, int32_t step, ui
     DevBuf d_t;
     if (d_t.alloc(ctx, bytes) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in gk_export");
     ENSI_HIP(ctx, hipDeviceSynchronize());
-    ENSI_HIP(ctx, hipMemcpy(d_t.p, it->second, bytes, hipMemcpyDeviceToDevice));
-    if (ctx->ks16) launch_ks16_key_plain(ctx, d_t.as<u64>(), beta * 2 * ext, nullptr);
-    else launch_from_mont(ctx, d_t.as<u64>(), beta * 2 * ext, mext, nullptr);
+    if (ctx->ks16) {
+        launch_ks16_key_plain(ctx, it->second, d_t.as<u64>(), beta * 2 * ext, it->first, nullptr);
+    } else {
+        ENSI_HIP(ctx, hipMemcpy(d_t.p, it->second, bytes, hipMemcpyDeviceToDevice));
+        launch_from_mont(ctx, d_t.as<u64>(), beta * 2 * ext, mext, nullptr);
+    }
     launch_ntt(ctx, d_t.as<u64>(), beta * 2 * ext, mext, true, nullptr);
     ENSI_HIP(ctx, hipMemcpy(words, d_t.p, bytes, hipMemcpyDeviceToHost));
     return ENSI_OK;
@@ -398,15 +403,22 @@ extern "C" int ensi_gk_import(ensi_ctx *ctx, ensi_gk **gk_io, int32_t step, cons
     const u32 g = galois_element(ctx, step);
     LimbMap mext = make_map(ctx, ctx->L, true);
     u64 *key = nullptr;
-    if (ctx->pool->alloc((void **)&key, (size_t)beta * 2 * ext * N * 8) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation of a key failed");
-    int rc = upload_residues(ctx, key, words, beta * 2 * ext, mext, "gk_import");
+    DevBuf d_t;  // the key in position order (fused kernels only)
+    const size_t bytes = (size_t)beta * 2 * ext * N * 8;
+    if (ctx->pool->alloc((void **)&key, bytes) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation of a key failed");
+    if (ctx->ks16 && d_t.alloc(ctx, bytes) != hipSuccess) {
+        (void)hipFree(key);
+        ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in gk_import");
+    }
+    u64 *plain = ctx->ks16 ? d_t.as<u64>() : key;
+    int rc = upload_residues(ctx, plain, words, beta * 2 * ext, mext, "gk_import");
     if (rc) {
         (void)hipFree(key);
         return rc;
     }
-    launch_ntt(ctx, key, beta * 2 * ext, mext, false, nullptr);
-    launch_to_mont(ctx, key, beta * 2 * ext, mext, nullptr);
-    if (ctx->ks16) launch_ks16_key_format(ctx, key, beta, nullptr);
+    launch_ntt(ctx, plain, beta * 2 * ext, mext, false, nullptr);
+    launch_to_mont(ctx, plain, beta * 2 * ext, mext, nullptr);
+    if (ctx->ks16) launch_ks16_key_format(ctx, plain, key, beta * 2 * ext, g, nullptr);
     if (hipStreamSynchronize(nullptr) != hipSuccess || hipGetLastError() != hipSuccess) {
         (void)hipFree(key);
         ENSI_FAIL(ctx, ENSI_E_HIP, "kernel failure in gk_import");

@@ -388,8 +388,9 @@ void launch_ntt16(ensi_ctx *ctx, u64 *data, int n_inst, const LimbMap &map, bool
 void launch_ntt16_gather(ensi_ctx *ctx, u64 *data, const MmOperand *ops, int n_ops, int l1, hipStream_t st);  // N >= 2^12
 
 // fused key switch (keyswitch16.hip)
-void launch_ks16_key_format(ensi_ctx *ctx, u64 *key, int beta_full, hipStream_t st);
-void launch_ks16_key_plain(ensi_ctx *ctx, u64 *key, int n_rows, hipStream_t st);  // rows of L + K limbs, in place: the stored format -> residues
+// rows (limb r % (L + K)) of the key of element g: Montgomery residues -> the stored format, and that -> residues; not in place
+void launch_ks16_key_format(ensi_ctx *ctx, const u64 *in, u64 *out, int n_rows, u32 g, hipStream_t st);
+void launch_ks16_key_plain(ensi_ctx *ctx, const u64 *in, u64 *out, int n_rows, u32 g, hipStream_t st);
 // raises n_ct ciphertexts: dig [n_ct][beta*ext + l1][N] receives the digits of c1 and P*c0, transformed (rows) or after their
 // column pass only
 void launch_ks16_raise(ensi_ctx *ctx, const Ks16Const &kc, const u64 *ct_base, size_t ct_stride_words, int limb_stride, int n_ct,

@@ -1,4 +1,5 @@
 // Key-switch keys in the format of the fused kernels, and the dispatch to the kernels of a ring (keyswitch16_kernels.h).
+#include "api_util.h"
 #include "common.h"
 #include "ntt16_core.h"
 
@@ -8,64 +9,68 @@ template <int S>
 void ks16_switch(ensi_ctx *ctx, const Ks16Const &kc, const RotDesc *d_desc, int n_rot, u64 *u, int limb_stride_out, bool raw, hipStream_t st, int members);
 
 // ---------------------------------------------------------------- key format
-// In place on one key [beta][2][L+K][N] that holds Montgomery residues in position order: into register order, limbs of
-// primes below 2^50 as doubles in [0,p), PRIME_WIDE limbs as split centred residues.  A wave owns the 1024 words of four
-// rows.  grid (N/1024, L+K, 2*beta)
-__global__ __launch_bounds__(64) void k_ks16_key_format(u64 *key, const PrimeConst *pcs, int ext_full, int N) {
-    const int lane = threadIdx.x, prime = blockIdx.y;
-    const PrimeConst pc = load_prime(pcs, prime);
-    u64 *t = key + ((size_t)blockIdx.z * ext_full + prime) * N + (size_t)blockIdx.x * 1024;
-    u64 w[16];
-#pragma unroll
-    for (int i = 0; i < 16; i++) w[i] = t[16 * lane + i];
+// Montgomery residues in position order -> register order at the source positions of the element g (RowMap), limbs of primes
+// below 2^50 as doubles in [0,p), PRIME_WIDE limbs as split centred residues.  Row y of the two arrays is limb y % ext_full.
+// A wave writes the 1024 words of four source rows; it reads the four rows they map to.  grid (N/1024, rows)
+template <int S>
+__global__ __launch_bounds__(64) void k_ks16_key_format(const u64 *in, u64 *out, const PrimeConst *pcs, int ext_full, u32 g, u32 g_inv) {
+    typedef RowMap<S> M;
+    const int lane = threadIdx.x, rho = lane >> 4, j = lane & 15;
+    const PrimeConst pc = load_prime(pcs, blockIdx.y % ext_full);
+    const u32 r = M::row(g_inv * M::exponent(blockIdx.x * 4 + rho)), carry = M::carry(r, g);
+    const u64 *src = in + (size_t)blockIdx.y * Ring<S>::N + (size_t)r * 256;
+    u64 *dst = out + (size_t)blockIdx.y * Ring<S>::N + (size_t)blockIdx.x * 1024;
 #pragma unroll
     for (int i = 0; i < 16; i++) {
-        acc128 m = {w[i], 0};
+        u64 w = src[brev8((brev8(16 * j + i) - carry) * g_inv & 255)];
+        acc128 m = {w, 0};
         const u64 k = mont_reduce(m, pc.q, pc.qneg_inv);
         if (pc.kind == PRIME_FP) {
-            w[i] = (u64)__double_as_longlong((double)k);
+            w = (u64)__double_as_longlong((double)k);
         } else if (pc.kind == PRIME_WIDE) {
             const int64_t c = (k > pc.q / 2 ? (int64_t)k - (int64_t)pc.q : (int64_t)k) + (1 << 29);
-            w[i] = ((u64)(u32)(u64)(c >> 30) << 32) | (u32)(((u32)c & 0x3fffffffu) - (1u << 29));
+            w = ((u64)(u32)(u64)(c >> 30) << 32) | (u32)(((u32)c & 0x3fffffffu) - (1u << 29));
         }
+        dst[64 * i + lane] = w;
     }
-    __syncthreads();  // every word of the tile has been read
-#pragma unroll
-    for (int i = 0; i < 16; i++) t[64 * i + lane] = w[i];
 }
-// The way back, to ordinary residues in position order.  grid (N/1024, n_rows): row r is limb r % ext_full
-__global__ __launch_bounds__(64) void k_ks16_key_plain(u64 *key, const PrimeConst *pcs, int ext_full, int N) {
-    const int lane = threadIdx.x;
-    const PrimeConst pc = pcs[blockIdx.y % ext_full];
-    u64 *t = key + (size_t)blockIdx.y * N + (size_t)blockIdx.x * 1024;
-    u64 w[16];
-#pragma unroll
-    for (int i = 0; i < 16; i++) w[i] = t[64 * i + lane];
+// The way back, to ordinary residues in position order.
+template <int S>
+__global__ __launch_bounds__(64) void k_ks16_key_plain(const u64 *in, u64 *out, const PrimeConst *pcs, int ext_full, u32 g, u32 g_inv) {
+    typedef RowMap<S> M;
+    const int lane = threadIdx.x, rho = lane >> 4, j = lane & 15;
+    const PrimeConst pc = load_prime(pcs, blockIdx.y % ext_full);
+    const u32 r = M::row(g_inv * M::exponent(blockIdx.x * 4 + rho)), carry = M::carry(r, g);
+    const u64 *src = in + (size_t)blockIdx.y * Ring<S>::N + (size_t)blockIdx.x * 1024;
+    u64 *dst = out + (size_t)blockIdx.y * Ring<S>::N + (size_t)r * 256;
 #pragma unroll
     for (int i = 0; i < 16; i++) {
+        u64 w = src[64 * i + lane];
         if (pc.kind == PRIME_FP) {
-            w[i] = (u64)__longlong_as_double((long long)w[i]);
+            w = (u64)__longlong_as_double((long long)w);
         } else if (pc.kind == PRIME_WIDE) {
-            const int64_t v = (int64_t)(int32_t)(u32)(w[i] >> 32) * (1 << 30) + (int32_t)(u32)w[i];
-            w[i] = v < 0 ? (u64)(v + (int64_t)pc.q) : (u64)v;
+            const int64_t v = (int64_t)(int32_t)(u32)(w >> 32) * (1 << 30) + (int32_t)(u32)w;
+            w = v < 0 ? (u64)(v + (int64_t)pc.q) : (u64)v;
         } else {
-            acc128 m = {w[i], 0};
-            w[i] = mont_reduce(m, pc.q, pc.qneg_inv);
+            acc128 m = {w, 0};
+            w = mont_reduce(m, pc.q, pc.qneg_inv);
         }
+        dst[brev8((brev8(16 * j + i) - carry) * g_inv & 255)] = w;
     }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 16; i++) t[16 * lane + i] = w[i];
 }
 
-void launch_ks16_key_format(ensi_ctx *ctx, u64 *key, int beta_full, hipStream_t st) {
-    dim3 grid(ctx->N / 1024, ctx->L + ctx->K, 2 * beta_full);
-    hipLaunchKernelGGL(k_ks16_key_format, grid, dim3(64), 0, st, key, ctx->d_pc, ctx->L + ctx->K, ctx->N);
+void launch_ks16_key_format(ensi_ctx *ctx, const u64 *in, u64 *out, int n_rows, u32 g, hipStream_t st) {
+    ring_dispatch(ctx->log_n, [&](auto s) {
+        hipLaunchKernelGGL((k_ks16_key_format<decltype(s)::value>), dim3(ctx->N / 1024, n_rows), dim3(64), 0, st, in, out, ctx->d_pc, ctx->L + ctx->K, g,
+                           inv_mod_2n(g, ctx->N));
+    });
 }
-void launch_ks16_key_plain(ensi_ctx *ctx, u64 *key, int n_rows, hipStream_t st) {
-    hipLaunchKernelGGL(k_ks16_key_plain, dim3(ctx->N / 1024, n_rows), dim3(64), 0, st, key, ctx->d_pc, ctx->L + ctx->K, ctx->N);
+void launch_ks16_key_plain(ensi_ctx *ctx, const u64 *in, u64 *out, int n_rows, u32 g, hipStream_t st) {
+    ring_dispatch(ctx->log_n, [&](auto s) {
+        hipLaunchKernelGGL((k_ks16_key_plain<decltype(s)::value>), dim3(ctx->N / 1024, n_rows), dim3(64), 0, st, in, out, ctx->d_pc, ctx->L + ctx->K, g,
+                           inv_mod_2n(g, ctx->N));
+    });
 }
-
 
 void launch_ks16_raise(ensi_ctx *ctx, const Ks16Const &kc, const u64 *ct_base, size_t ct_stride_words, int limb_stride, int n_ct, u64 *dig, bool rows,
                        hipStream_t st) {

@@ -8,9 +8,8 @@
 //                  own digit), runs the column pass on it and writes it.  Further blocks do the same for P * c0, so
 //                  that phi_g(c0) can be added in the transform domain (ModDown divides it by P again, exactly)
 //   k_ks16_frows   forward row pass of the raised digits and of P * c0, where several rotations read them
-//   k_ks16_inner   automorphism (a permutation of transform-domain positions that maps rows onto rows, applied
-//                  between two registers-to-LDS exchanges) + inner product with the key + P * phi_g(c0) + inverse
-//                  row pass.  A raised ciphertext that only one rotation reads is taken after its column
+//   k_ks16_inner   inner product with the key + P * c0, automorphism (a permutation of transform-domain positions that maps
+//                  rows onto rows) of the two sums, inverse row pass.  A raised ciphertext that only one rotation reads is taken after its column
 //                  pass and the row passes of its digits are run here: the transformed digits never reach memory
 //   k_ks16_icols   inverse column pass fused with ModDown.  A block brings the K special limbs of one column tile
 //                  to centred residues y_k = [u (P/p_k)^-1]_{p_k}, held in registers, and then walks the
@@ -29,7 +28,8 @@
 //   PRIME_INT   canonical 64-bit residues; key: Montgomery residues
 // Transformed digits and the key are stored in the order a wave holds them in the row pass ("register order"): within
 // the four rows of a wave, value i of lane (rho, j) -- position 16 j + i of row rho -- at i * 64 + lane, so that reading
-// them needs no exchange and is contiguous.
+// them needs no exchange and is contiguous.  The key of element g lies at the positions its words meet before the automorphism:
+// phi_g^-1 of it is stored.
 // All results that leave the last kernel are canonical residues and equal, word for word, what the unfused sequence
 // (ModUp, transform, inner product, inverse transform, ModDown, + phi_g(c0)) gives.
 #pragma once
@@ -310,6 +310,7 @@ struct Inner<ArithFp> {
     // a rotation adds up to nine terms below 0.7 p: reduced after each, the sums stay exact integers
     static __device__ __forceinline__ void fold(const ArithFp &ar, Acc &a) { a.s = ar.mid(a.s); }
     static __device__ __forceinline__ double value(const Acc &a) { return a.s; }
+    static __device__ __forceinline__ double join(const ArithFp &ar, double x, double y) { return ar.mid(x + y); }
 };
 // x = xh 2^30 + xl, k = kh 2^30 + kl: xh kh 2^60 is taken apart into dwords and folded by 2^60 = d, 2^62 = 4 d, like the
 // middle sum m 2^30.  Every half is at most 2^29 (a little more for the high ones): within 6 q before the last fold.
@@ -329,6 +330,7 @@ struct Inner<ArithWide> {
     static __device__ __forceinline__ void add(Acc &, u64) {}
     static __device__ __forceinline__ void fold(const ArithWide &, Acc &) {}
     static __device__ __forceinline__ int64_t value(const Acc &a) { return a.s; }
+    static __device__ __forceinline__ int64_t join(const ArithWide &ar, int64_t x, int64_t y) { return ar.mid(x + y); }
 };
 template <>
 struct Inner<ArithInt> {
@@ -340,108 +342,160 @@ struct Inner<ArithInt> {
     static __device__ __forceinline__ void add(Acc &, u64) {}
     static __device__ __forceinline__ void fold(const ArithInt &, Acc &) {}
     static __device__ __forceinline__ u64 value(const Acc &a) { return a.s; }
+    static __device__ __forceinline__ u64 join(const ArithInt &ar, u64 x, u64 y) { return add_mod(x, y, ar.q); }
 };
 
-__device__ __forceinline__ u32 brev8(u32 x) { return __brev(x) >> 24; }
-
-// Four output rows of one limb of both accumulators, by one wave.  Transform-domain position k holds the evaluation at
-// psi^(2 brev(k) + 1) and phi_g(d)(psi^x) = d(psi^(x g)): output row r reads one source row, within which position p
-// reads brev8(g brev8(p) + carry mod 256), where the carry comes from the row's part of the exponent.
-// RAW: the digits have only been through their column pass; their row passes are run here.
-template <int S, bool RAW, class A>
+// Four rows of one limb of both accumulators, by one wave, and their inverse row passes.  Digits and keys are multiplied where they
+// lie -- keys are stored at the source positions of their element (k_ks16_key_format) -- and the automorphism permutes the
+// two sums, not the beta + 1 polynomials they are made of.
+//   GROUP = false: one rotation; the wave takes source rows 4 tile .. 4 tile + 3 and writes the rows they map to.
+//   GROUP = true:  `members` rotations whose sums are added: the wave takes output rows 4 tile .. 4 tile + 3.
+// RAW (one rotation): the digits have only been through their column pass; their row passes are run here.
+template <int S, bool RAW, bool GROUP, class A>
 __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *desc, const PrimeConst &pc, const u64 *tw_all, u64 *u, int prime, int e,
-                                           int members, u64 *lds, ulonglong2 *tw1) {
+                                           int members, u32 grp, u32 tile, u64 *lds, ulonglong2 *tw1) {
     typedef Ring<S> R;
+    typedef RowMap<S> M;
     typedef Inner<A> I;
+    typedef typename A::T T;
     constexpr size_t N = R::N;
-    constexpr int LOGR = 4 + S;
     const int lane = threadIdx.x, rho = lane >> 4, j = lane & 15;
     const int l1 = kc.l1, ext = l1 + kc.K, beta = kc.beta;
-    const u32 r = blockIdx.x * 4 + rho;
     const size_t kstride = (size_t)(kc.L + kc.K) * N;  // words between b_j and a_j, and half the distance between digits
     const u64 *tw = tw_all + (size_t)prime * 4 * N;
     const ulonglong2 *tab = tw1 + rho * 16;
     A ar;
     ar.init(pc);
-    typename I::Acc a0[16], a1[16];
-#pragma unroll
-    for (int i = 0; i < 16; i++) {
-        I::zero(a0[i]);
-        I::zero(a1[i]);
-    }
+    T s0[16], s1[16];  // the sums in the order of the output rows
+    u32 r = tile * 4 + rho;
 #pragma unroll 1
-    for (int mem = 0; mem < members; mem++) {
-        const RotDesc d = load_desc(desc, blockIdx.y * members + mem);
-        const u32 er = d.g * (2 * (__brev(r) >> (32 - LOGR)) + 1) & (2 * R::N - 1);
-        const u32 rs = __brev((er & (2 * R::ROWS - 1)) >> 1) >> (32 - LOGR), carry = er >> (LOGR + 1);
-        auto src = as_global(d.digits) + (size_t)e * N;
-        src += RAW ? rs * 256 + j : (rs >> 2) * 1024 + (rs & 3) * 16 + j;
-        constexpr int step = RAW ? 16 : 64;
-        auto key = as_global(d.key) + (size_t)prime * N + (size_t)blockIdx.x * 1024 + lane;
-        TwRegs tw2;
+    for (int mem = 0; mem < (GROUP ? members : 1); mem++) {
+        const RotDesc d = load_desc(desc, grp * members + mem);
+        const u32 rs = GROUP ? M::source(r, d.g) : r;
+        if (!GROUP) r = M::row(d.g_inv * M::exponent(rs));
+        const u32 carry = M::carry(r, d.g);
+        // byte offsets of value 0 from the wave's tile of digits and keys
+        const u32 reg_off = ((GROUP ? (rs >> 2) * 1024 + (rs & 3) * 16 : rho * 16) + j) * 8, row_off = (rho * 256 + j) * 8;
+        const u64 *src = d.digits + (size_t)e * N + (GROUP ? 0 : tile * 1024), *key = d.key + (size_t)prime * N + (GROUP ? 0 : tile * 1024);
+        auto ld = [](const u64 *base, u32 off) { return *(decltype(as_global(base)))((decltype(as_global((const char *)base)))as_global(base) + off); };
+        typename I::Acc a0[16], a1[16];
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            I::zero(a0[i]);
+            I::zero(a1[i]);
+        }
+        const bool with_c0 = e < l1;  // P * c0 follows the digits
         if (RAW) {
+            TwRegs tw2;
             row_table_to_lds(tw1, tw, tw + N, R::ROWS + rs, rho, j);
             tw2.load(tw, tw + N, (R::ROWS + rs) * 16u + j);
-        }
-        u32 at[16];
+            u64 nv[16];
 #pragma unroll
-        for (int i = 0; i < 16; i++) at[i] = rpad(rho * 256 + brev8((d.g * brev8(16 * j + i) + carry) & 255));
-        const int nd = e < l1 ? beta + 1 : beta;  // the digits, then P * c0
-        u64 nv[16];
-#pragma unroll
-        for (int i = 0; i < 16; i++) nv[i] = src[step * i];
-        if (RAW) wave_lds_fence();
+            for (int i = 0; i < 16; i++) nv[i] = ld(src + 16 * i, row_off);
+            wave_lds_fence();
+            const int nd = with_c0 ? beta + 1 : beta;
 #pragma unroll 1
-        for (int jd = 0; jd < nd; jd++) {
-            if (RAW) {
+            for (int jd = 0; jd < nd; jd++) {
                 tw2.keep();
-                typename A::T v[16];
+                T v[16];
 #pragma unroll
                 for (int i = 0; i < 16; i++) v[i] = A::from_bits(nv[i]);
                 if (jd + 1 < nd) {
+                    src += (size_t)ext * N;
 #pragma unroll
-                    for (int i = 0; i < 16; i++) nv[i] = src[(size_t)(jd + 1) * ext * N + step * i];
+                    for (int i = 0; i < 16; i++) nv[i] = ld(src + 16 * i, row_off);
                 }
                 row_fwd(ar, v, tab, tw2, lds, rho, j);
+                if (jd < beta) {
 #pragma unroll
-                for (int i = 0; i < 16; i++) lds[rpad(rho * 256 + 16 * j + i)] = ar.store_ws_fwd(v[i]);
-            } else {
+                    for (int h = 0; h < 16; h += 8) {
+                        u64 k0[8], k1[8];
 #pragma unroll
-                for (int i = 0; i < 16; i++) lds[rpad(rho * 256 + 16 * j + i)] = nv[i];
-                if (jd + 1 < nd) {
+                        for (int i = 0; i < 8; i++) {
+                            k0[i] = ld(key + 64 * (h + i), reg_off);
+                            k1[i] = ld(key + kstride + 64 * (h + i), reg_off);
+                        }
 #pragma unroll
-                    for (int i = 0; i < 16; i++) nv[i] = src[(size_t)(jd + 1) * ext * N + step * i];
+                        for (int i = 0; i < 8; i++) {
+                            const u64 x = ar.store_ws_fwd(v[h + i]);
+                            I::mac(ar, a0[h + i], x, k0[i]);
+                            I::mac(ar, a1[h + i], x, k1[i]);
+                        }
+                    }
+                    key += 2 * kstride;
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 16; i++) I::add(a0[i], ar.store_ws_fwd(v[i]));
                 }
             }
-            wave_lds_fence();
-            if (jd < beta) {
-                auto kj = key + (size_t)jd * 2 * kstride;
+        } else {
+            // C values at a time, the next C requested before the current ones are multiplied.
+            constexpr int C = GROUP ? 4 : 8;
+            u64 x[2][C], k0[2][C], k1[2][C];
+            auto fetch = [&](int i0, bool keys) {
+                const int b = i0 / C & 1;
 #pragma unroll
-                for (int h = 0; h < 16; h += 8) {
-                    u64 k0[8], k1[8];
+                for (int i = 0; i < C; i++) x[b][i] = ld(src + 64 * (i0 + i), reg_off);
+                if (keys) {
 #pragma unroll
-                    for (int i = 0; i < 8; i++) {
-                        k0[i] = kj[64 * (h + i)];
-                        k1[i] = kj[kstride + 64 * (h + i)];
-                    }
-#pragma unroll
-                    for (int i = 0; i < 8; i++) {
-                        const u64 x = lds[at[h + i]];
-                        I::mac(ar, a0[h + i], x, k0[i]);
-                        I::mac(ar, a1[h + i], x, k1[i]);
+                    for (int i = 0; i < C; i++) {
+                        k0[b][i] = ld(key + 64 * (i0 + i), reg_off);
+                        k1[b][i] = ld(key + kstride + 64 * (i0 + i), reg_off);
                     }
                 }
-            } else {
+            };
+            fetch(0, true);
+#pragma unroll 1
+            for (int jd = 0; jd < beta; jd++) {
+                const bool more = jd + 1 < beta;
 #pragma unroll
-                for (int i = 0; i < 16; i++) I::add(a0[i], lds[at[i]]);
+                for (int i0 = 0; i0 < 16; i0 += C) {
+                    if (i0 + C < 16) {
+                        fetch(i0 + C, true);
+                    } else {
+                        src += (size_t)ext * N;
+                        key += 2 * kstride;
+                        if (more || with_c0) fetch(0, more);
+                    }
+#pragma unroll
+                    for (int i = 0; i < C; i++) {
+                        const int b = i0 / C & 1;
+                        I::mac(ar, a0[i0 + i], x[b][i], k0[b][i]);
+                        I::mac(ar, a1[i0 + i], x[b][i], k1[b][i]);
+                    }
+                }
             }
-            wave_lds_fence();
+            if (with_c0) {
+#pragma unroll
+                for (int i0 = 0; i0 < 16; i0 += C) {
+                    if (i0 + C < 16) fetch(i0 + C, false);
+#pragma unroll
+                    for (int i = 0; i < C; i++) I::add(a0[i0 + i], x[i0 / C & 1][i]);
+                }
+            }
         }
 #pragma unroll
         for (int i = 0; i < 16; i++) {
             I::fold(ar, a0[i]);
             I::fold(ar, a1[i]);
         }
+        // the automorphism within the rows
+        T *l = (T *)lds;
+        const u32 first = d.g * (__brev((u32)j) >> 28) + carry;  // of value 0: brev8(16 j + i) = brev4(j) + 16 brev4(i)
+        auto permute = [&](const typename I::Acc *a, T *s) {
+#pragma unroll
+            for (int i = 0; i < 16; i++) l[rpad(rho * 256 + 16 * j + i)] = I::value(a[i]);
+            wave_lds_fence();
+#pragma unroll
+            for (int i = 0; i < 16; i++) {
+                const u32 brev4_i = (i & 1) * 8 + (i & 2) * 2 + (i & 4) / 2 + (i & 8) / 8;
+                const T v = l[rpad(rho * 256 + brev8(first + d.g * (16 * brev4_i)))];
+                s[i] = GROUP && mem > 0 ? I::join(ar, s[i], v) : v;
+            }
+            wave_lds_fence();
+        };
+        permute(a0, s0);
+        permute(a1, s1);
     }
     // inverse row pass of both sums: its twiddles are fetched once
     tw += 2 * N;
@@ -449,12 +503,10 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
     TwRegs twi;
     twi.load(tw, tw + N, (R::ROWS + r) * 16u + j);
     wave_lds_fence();
-    u64 *uo = u + ((size_t)blockIdx.y * 2 * ext + e) * N + (size_t)r * 256 + j;
+    u64 *uo = u + ((size_t)grp * 2 * ext + e) * N + (size_t)r * 256 + j;
 #pragma unroll
     for (int poly = 0; poly < 2; poly++) {
-        typename A::T v[16];
-#pragma unroll
-        for (int i = 0; i < 16; i++) v[i] = I::value(poly ? a1[i] : a0[i]);
+        T *v = poly ? s1 : s0;
         row_inv(ar, v, tab, twi, lds, rho, j);
         u64 *o = uo + (size_t)poly * ext * N;
 #pragma unroll
@@ -462,18 +514,25 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
     }
 }
 
-// grid (4 TILES, n_rot / members, ext): limb slowest, so that the blocks in flight share one limb of the digits and keys.
-// members > 1: the block adds the inner products of `members` consecutive descriptors (rotations of one ciphertext:
-// same digits, their own Galois element and key) before the inverse pass, so that the group is brought back to
-// the ciphertext basis by one inverse transform and one ModDown; grid y then counts groups.
-template <int S, bool RAW, class W>
-__global__ __launch_bounds__(64, 2) void k_ks16_inner(Ks16Const kc, const RotDesc *desc, const PrimeConst *pcs, const u64 *tw_all, u64 *u, int members) {
+// grid (8 * ceil(4 TILES * ext / 8) * n_grp): the rotations of a tile of four rows of one limb run next to each other on one XCD
+// (block b runs on XCD b % 8), whose L2 then serves the digits that several rotations of one ciphertext read and the keys
+// that several ciphertexts read.
+// GROUP: the block adds the inner products of `members` consecutive descriptors (rotations of one ciphertext: same digits,
+// their own Galois element and key) before the inverse pass, so that the group is brought back to the ciphertext basis
+// by one inverse transform and one ModDown; n_grp then counts groups.
+template <int S, bool RAW, bool GROUP, class W>
+__global__ __launch_bounds__(64, 2) void k_ks16_inner(Ks16Const kc, const RotDesc *desc, const PrimeConst *pcs, const u64 *tw_all, u64 *u, int members,
+                                                      u32 n_grp) {
     __shared__ u64 lds[ROW_LDS];
     __shared__ ulonglong2 tw1[4 * 16];
-    const int e = kc.l1 + kc.K - 1 - blockIdx.z, prime = ks_ext_prime(e, kc.l1, kc.L);  // the special limbs, which take longer, first
+    constexpr u32 TILES4 = 4 * Ring<S>::TILES;
+    const int ext = kc.l1 + kc.K;
+    const u32 k = blockIdx.x >> 3, q = k / n_grp * 8 + (blockIdx.x & 7), grp = k % n_grp;
+    if (q >= TILES4 * ext) return;
+    const int e = ext - 1 - (int)(q / TILES4), prime = ks_ext_prime(e, kc.l1, kc.L);  // the special limbs, which take longer, first
     const PrimeConst pc = load_prime(pcs, prime);
-    if (e < kc.l1) inner_body<S, RAW, ArithFp>(kc, desc, pc, tw_all, u, prime, e, members, lds, tw1);
-    else inner_body<S, RAW, W>(kc, desc, pc, tw_all, u, prime, e, members, lds, tw1);
+    if (e < kc.l1) inner_body<S, RAW, GROUP, ArithFp>(kc, desc, pc, tw_all, u, prime, e, members, grp, q % TILES4, lds, tw1);
+    else inner_body<S, RAW, GROUP, W>(kc, desc, pc, tw_all, u, prime, e, members, grp, q % TILES4, lds, tw1);
 }
 
 // ------------------------------------------------------ inverse column pass + ModDown
@@ -535,6 +594,7 @@ __global__ __launch_bounds__(KS_THREADS, 2) void k_ks16_icols(Ks16Const kc, cons
         for (int i = 0; i < 16; i++) {
             const int64_t z = special_centred(ar, v[i], kc, k);
             yk[i] = ((u64)(u32)(int32_t)(z >> 30) << 32) | (u32)(z & 0x3fffffff);
+            keep_narrow(yk[i]);
         }
     };
     special(y[0], 0);
@@ -542,7 +602,7 @@ __global__ __launch_bounds__(KS_THREADS, 2) void k_ks16_icols(Ks16Const kc, cons
     if constexpr (K > 2) special(y[2], 2);
     if constexpr (K > 3) special(y[3], 3);
     const RotDesc dl = load_desc(desc, blockIdx.z * members);  // the group's first descriptor carries the destination
-    auto out_at = [&](u64 *out, int i) { return as_global((u64 *)((char *)(out + R::row(0, i) * 256) + off_out)); };
+    auto out_at = [&](u64 *out, int i) { return (decltype(as_global(out)))((decltype(as_global((char *)out)))as_global(out + R::row(0, i) * 256) + off_out); };
     int tcur = K % 3;
 #pragma unroll 1
     for (int t = K; t < n_steps; t++) {
@@ -643,10 +703,14 @@ void ks16_switch(ensi_ctx *ctx, const Ks16Const &kc, const RotDesc *d_desc, int 
         typedef decltype(w) W;
         {
             ScopedTimer t(ctx, "ks_inner", st);
-            if (raw)
-                hipLaunchKernelGGL((k_ks16_inner<S, true, W>), dim3(4 * TILES, n_grp, ext), dim3(64), 0, st, kc, d_desc, ctx->d_pc, ctx->d_tw, u, members);
-            else
-                hipLaunchKernelGGL((k_ks16_inner<S, false, W>), dim3(4 * TILES, n_grp, ext), dim3(64), 0, st, kc, d_desc, ctx->d_pc, ctx->d_tw, u, members);
+            const unsigned blocks = (4u * TILES * ext + 7) / 8 * 8 * n_grp;
+            auto inner = [&](auto raw_, auto group_) {
+                hipLaunchKernelGGL((k_ks16_inner<S, decltype(raw_)::value, decltype(group_)::value, W>), dim3(blocks), dim3(64), 0, st, kc, d_desc, ctx->d_pc,
+                                   ctx->d_tw, u, members, (u32)n_grp);
+            };
+            if (raw) inner(std::true_type(), std::false_type());
+            else if (members > 1) inner(std::false_type(), std::true_type());
+            else inner(std::false_type(), std::false_type());
         }
         ScopedTimer t(ctx, "ks_icols_moddown", st);
         const int per = limbs_per_block((long)TILES * 2 * n_grp, kc.l1);

@@ -518,6 +518,21 @@ __device__ __forceinline__ void row_inv(const A &ar, typename A::T *v, const TAB
     wave_lds_fence();
 }
 
+__device__ __forceinline__ u32 brev8(u32 x) { return __brev(x) >> 24; }
+
+// phi_g on transform-domain positions.  Position k holds the evaluation at psi^(2 brev(k) + 1) and phi_g(d)(psi^x) = d(psi^(x g)):
+// output row r reads one source row, within which position p reads brev8(g brev8(p) + carry mod 256), where the carry
+// comes from the row's part of the exponent.  Four rows 4t .. 4t + 3 read four rows 4t' .. 4t' + 3.
+template <int S>
+struct RowMap {
+    static constexpr int LOGR = 4 + S;
+    static constexpr u32 ROWS = 1u << LOGR;
+    static __device__ __forceinline__ u32 exponent(u32 row) { return 2 * (__brev(row) >> (32 - LOGR)) + 1; }
+    static __device__ __forceinline__ u32 row(u32 exp) { return __brev((exp & (2 * ROWS - 1)) >> 1) >> (32 - LOGR); }
+    static __device__ __forceinline__ u32 source(u32 r, u32 g) { return row(g * exponent(r)); }
+    static __device__ __forceinline__ u32 carry(u32 r, u32 g) { return g * exponent(r) >> (LOGR + 1) & 255; }
+};
+
 // Calls f with the ring's S as a compile-time constant (12 <= log_n <= 16).
 template <class F>
 inline void ring_dispatch(int log_n, F f) {
