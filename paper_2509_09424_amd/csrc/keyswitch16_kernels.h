@@ -181,7 +181,7 @@ __global__ __launch_bounds__(KS_THREADS, 2) void k_ks16_fcols(Ks16Const kc, cons
                 double v[16];
                 if (e >= first && e < first + ns) {
 #pragma unroll
-                    for (int i = 0; i < 16; i++) v[i] = (double)ld_off(c1 + (size_t)e * N + R::row(0, i) * 256, off_in);
+                    for (int i = 0; i < 16; i++) v[i] = ar.load(ld_off(c1 + (size_t)e * N + R::row(0, i) * 256, off_in));
                 } else {
                     modup_to(ar, v, hat, nullptr, y, ns, pc);
                 }
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(KS_THREADS, 2) void k_ks16_fcols(Ks16Const kc, cons
             const double pm = as_const(kc.pmod_fp)[2 * limb], pm_p = as_const(kc.pmod_fp)[2 * limb + 1];
             double v[16];
 #pragma unroll
-            for (int i = 0; i < 16; i++) v[i] = ar.mid(ar.mulmod((double)nv[i], pm, pm_p));
+            for (int i = 0; i < 16; i++) v[i] = ar.mulmod(ar.load(nv[i]), pm, pm_p);
             if (limb + 1 < i1) {
                 fetch_tab(limb + 1);
 #pragma unroll
@@ -542,7 +542,7 @@ __device__ __forceinline__ int64_t special_centred(const ArithWide &ar, int64_t 
     return ar.centred(ar.mul(v, as_const(kc.down_p)[2 * k], as_const(kc.down_p)[2 * k + 1]));
 }
 __device__ __forceinline__ int64_t special_centred(const ArithFp &ar, double v, const Ks16Const &kc, int k) {
-    return (int64_t)ar.mid(ar.mulmod(ar.mid(v), as_const(kc.down_p_fp)[2 * k], as_const(kc.down_p_fp)[2 * k + 1]));
+    return (int64_t)ar.mid(ar.mulmod(v, as_const(kc.down_p_fp)[2 * k], as_const(kc.down_p_fp)[2 * k + 1]));
 }
 __device__ __forceinline__ int64_t special_centred(const ArithInt &ar, u64 v, const Ks16Const &kc, int k) {
     const u64 y = mul_shoup(v, as_const(kc.down_p)[2 * k], as_const(kc.down_p)[2 * k + 1], ar.q);
@@ -641,7 +641,7 @@ __global__ __launch_bounds__(KS_THREADS, 2) void k_ks16_icols(Ks16Const kc, cons
             }
             u64 w[4];
 #pragma unroll
-            for (int i = 0; i < 4; i++) w[i] = ar.canon(ar.mulmod(ar.mid(v[h + i]), sc, sc_p) - ar.reduce25_long(a1[i], a0[i]));
+            for (int i = 0; i < 4; i++) w[i] = ar.canon(ar.mulmod(v[h + i], sc, sc_p) - ar.reduce25_long(a1[i], a0[i]));
             if (dl.accumulate) {
                 // out <- out + result.  `out` may be the rotation's own source (every read of the source happened in the
                 // raise kernels, which have finished), which turns t <- t + Rot(t; r) into one pass

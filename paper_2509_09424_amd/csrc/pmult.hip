@@ -124,7 +124,7 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm16_fcols(PmGroup g, const Prim
     const u64 *tw = tw_all + (size_t)i * 4 * PM_N;
     double v[16];
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = (double)src[(size_t)R::row(jj, k) * 256];
+    for (int k = 0; k < 16; k++) v[k] = ar.load(src[(size_t)R::row(jj, k) * 256]);
     cols_fwd_regs<S>(ar, v, tw, tw + PM_N, lds, c16, jj);
 #pragma unroll
     for (int k = 0; k < 16; k++) out[(size_t)(16 * jj + k) * 256] = pm_u64(ar.mid(v[k]));
@@ -352,7 +352,7 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm16_icols_last(PmGroup g, const
     for (int k = 0; k < 16; k++) v[k] = pm_f64(src[(size_t)(16 * jj + k) * 256]);
     cols_inv_regs<S>(ar, v, tw, tw + PM_N, lds, c16, jj);
 #pragma unroll
-    for (int k = 0; k < 16; k++) dst[(size_t)R::row(jj, k) * 256] = pm_u64(ar.mid(ar.mulmod(ar.mid(v[k]), ar.ninv, ar.ninv_p)));
+    for (int k = 0; k < 16; k++) dst[(size_t)R::row(jj, k) * 256] = pm_u64(ar.mid(ar.mulmod(v[k], ar.ninv, ar.ninv_p)));
 }
 
 // grid (TILES, 2*(l1-1), n_out)
@@ -380,7 +380,7 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm16_icols_rescale(PmGroup g, Pm
     cols_inv_regs<S>(ar, v, tw, tw + PM_N, lds, c16, jj);
 #pragma unroll
     for (int k = 0; k < 16; k++) {
-        const double x = ar.mid(ar.mulmod(ar.mid(v[k]), ar.ninv, ar.ninv_p));
+        const double x = ar.mid(ar.mulmod(v[k], ar.ninv, ar.ninv_p));
         const double z = ar.mid(x - ar.mid(tl[k]));
         dst[(size_t)R::row(jj, k) * 256] = ar.canon(ar.mulmod(z, w, wp));
     }
