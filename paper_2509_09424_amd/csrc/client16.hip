@@ -134,28 +134,36 @@ __global__ __launch_bounds__(CL_THREADS) void k_cl_fcols_small(const int8_t *sma
     for (int i = 0; i < 16; i++) o[(size_t)(16 * jj + i) * 256] = ar.store_ws_cols(v[i]);
 }
 // Forward row pass, product with POLYS key polynomials (key: limb `limb` of polynomial p at (p * key_limbs + limb) * N, in
-// position order, Montgomery residues) and inverse row pass of each product.  A wave runs four rows.
-// grid (4 TILES, limbs, n); in: [n][limbs][N], out: [n][POLYS][limbs][N] doubles (may be the same array if POLYS is 1)
+// position order, Montgomery residues: the factor 2^-64 they owe is part of the constant that the column pass behind this
+// kernel scales by) and inverse row pass of each product.  A wave runs four rows of one limb of one of the n polynomials.  The
+// twiddles of both directions and the key words are five times the bytes of the rows themselves: the waves of the n polynomials
+// that share them run next to each other on one XCD (block b runs on XCD b % 8) and find them in its L2.  (Polynomials launched
+// one after the other fetched 540 MB for 10 x 16 limbs: 116 us, now 94.  Waves that keep the twiddles for five polynomials in registers: 100.)
+// grid (8 * ceil(4 TILES * limbs / 8) * n); in: [n][limbs][N], out: [n][POLYS][limbs][N] doubles (may be the same array if
+// POLYS is 1)
 template <int S, int POLYS>
-__global__ __launch_bounds__(64, 2) void k_cl_rows_key(const u64 *in, const u64 *key, int key_limbs, const PrimeConst *pcs, const u64 *tw_all, u64 *out) {
+__global__ __launch_bounds__(64, 2) void k_cl_rows_key(const u64 *in, const u64 *key, int key_limbs, int limbs, u32 n, const PrimeConst *pcs,
+                                                       const u64 *tw_all, u64 *out) {
     typedef Ring<S> R;
     constexpr size_t N = R::N;
+    constexpr u32 TILES4 = 4 * R::TILES;
     __shared__ u64 lds[ROW_LDS];
     __shared__ ulonglong2 tw1[2][4 * 16];
-    const int lane = threadIdx.x, rho = lane >> 4, j = lane & 15, limb = blockIdx.y, limbs = gridDim.y;
-    const u32 r = blockIdx.x * 4 + rho;
-    const PrimeConst pc = load_prime(pcs, limb);
+    const u32 k = blockIdx.x >> 3, q = k / n * 8 + (blockIdx.x & 7), z = k % n;
+    if (q >= TILES4 * limbs) return;
+    const int lane = threadIdx.x, rho = lane >> 4, j = lane & 15, limb = q / TILES4;
+    const u32 r = q % TILES4 * 4 + rho;
     ArithFp ar;
-    ar.init(pc);
+    ar.init(load_prime(pcs, limb));
     const u64 *twf = tw_all + (size_t)limb * 4 * N, *twi = twf + 2 * N;
+    double v[16];
+    const u64 *src = in + ((size_t)z * limbs + limb) * N + (size_t)r * 256 + j;
+#pragma unroll
+    for (int i = 0; i < 16; i++) v[i] = __longlong_as_double((long long)src[16 * i]);
     row_table_to_lds(tw1[0], twf, twf + N, R::ROWS + r, rho, j);
     row_table_to_lds(tw1[1], twi, twi + N, R::ROWS + r, rho, j);
     TwRegs tw2;
     tw2.load(twf, twf + N, (R::ROWS + r) * 16u + j);
-    double v[16];
-    const u64 *src = in + ((size_t)blockIdx.z * limbs + limb) * N + (size_t)r * 256 + j;
-#pragma unroll
-    for (int i = 0; i < 16; i++) v[i] = __longlong_as_double((long long)src[16 * i]);
     wave_lds_fence();
     row_fwd(ar, v, tw1[0] + rho * 16, tw2, lds, rho, j);
 #pragma unroll
@@ -163,47 +171,63 @@ __global__ __launch_bounds__(64, 2) void k_cl_rows_key(const u64 *in, const u64 
     tw2.load(twi, twi + N, (R::ROWS + r) * 16u + j);
 #pragma unroll
     for (int p = 0; p < POLYS; p++) {
-        const u64 *k = key + ((size_t)p * key_limbs + limb) * N + (size_t)r * 256 + 16 * j;
+        const u64 *kp = key + ((size_t)p * key_limbs + limb) * N + (size_t)r * 256 + 16 * j;
         double x[16];
 #pragma unroll
-        for (int i = 0; i < 16; i++) {
-            acc128 m = {k[i], 0};
-            x[i] = ar.mid(ar.mulmod_np(v[i], (double)mont_reduce(m, pc.q, pc.qneg_inv)));
-        }
+        for (int i = 0; i < 16; i++) x[i] = ar.mid(ar.mulmod_np(v[i], ar.load(kp[i])));
         row_inv(ar, x, tw1[1] + rho * 16, tw2, lds, rho, j);
-        u64 *o = out + (((size_t)blockIdx.z * POLYS + p) * limbs + limb) * N + (size_t)r * 256 + j;
+        u64 *o = out + (((size_t)z * POLYS + p) * limbs + limb) * N + (size_t)r * 256 + j;
 #pragma unroll
         for (int i = 0; i < 16; i++) o[16 * i] = ar.store_ws_inv(x[i]);
     }
 }
+// x / (N 2^64) mod p of a value of the row pass above
+struct ScaleDown {
+    double w, wp;
+    __device__ __forceinline__ void init(const ArithFp &ar, const PrimeConst &pc) {
+        const acc128 m = {pc.n_inv, 0};
+        w = (double)mont_reduce(m, pc.q, pc.qneg_inv);
+        wp = w * ar.pinv;
+    }
+    __device__ __forceinline__ double operator()(const ArithFp &ar, double x) const { return ar.mulmod(ar.mid(x), w, wp); }
+};
 // Inverse column pass in place, plus the error polynomial and, on the first polynomial, the message: the ciphertext.
 // grid (TILES, 2 * limbs, n); errors: e0 of all ciphertexts, then (err_stride further) e1
 template <int S>
-__global__ __launch_bounds__(CL_THREADS) void k_cl_icols_add(u64 *ct, const int8_t *errors, size_t err_stride, const u64 *pt, int limbs,
+__global__ __launch_bounds__(CL_THREADS, 4) void k_cl_icols_add(u64 *ct, const int8_t *errors, size_t err_stride, const u64 *pt, int limbs,
                                                              const PrimeConst *pcs, const u64 *tw_all) {
     typedef Ring<S> R;
     constexpr size_t N = R::N;
     __shared__ u64 lds[4096];
+    __shared__ __attribute__((aligned(16))) int8_t err[4096];
     const int c = R::col(threadIdx.x), jj = R::grp(threadIdx.x), poly = blockIdx.y / limbs, limb = blockIdx.y - poly * limbs;
     const size_t col = (size_t)blockIdx.x * R::COLS + c;
+    const PrimeConst pc = load_prime(pcs, limb);
     ArithFp ar;
-    ar.init(load_prime(pcs, limb));
+    ar.init(pc);
+    ScaleDown down;
+    down.init(ar, pc);
     const u64 *tw = tw_all + (size_t)limb * 4 * N + 2 * N;
     u64 *g = ct + ((size_t)blockIdx.z * 2 * limbs + blockIdx.y) * N + col;
-    const int8_t *e = errors + poly * err_stride + blockIdx.z * N + col;
     const u64 *m = pt + ((size_t)blockIdx.z * limbs + limb) * N + col;
-    double v[16], a[16];
+    // The tile's errors, sixteen bytes a thread, pass through LDS: fetched byte by byte where they are added they were waited for
+    // one after the other (a wave lived 22 us; 10 x 16 limbs 149 us, now 96).
+    double v[16];
+    u64 a[16] = {};
 #pragma unroll
     for (int i = 0; i < 16; i++) v[i] = __longlong_as_double((long long)g[(size_t)(16 * jj + i) * 256]);
+    const int at = threadIdx.x * 16;  // of the tile's 4096 bytes
+    const uint4 mine = *(const uint4 *)(errors + poly * err_stride + blockIdx.z * N + (at >> R::LOGC) * 256 + blockIdx.x * R::COLS + (at & (R::COLS - 1)));
+    if (poly == 0) {
 #pragma unroll
-    for (int i = 0; i < 16; i++) {
-        const size_t at = (size_t)R::row(jj, i) * 256;
-        a[i] = (double)e[at];
-        if (poly == 0) a[i] += (double)m[at];
+        for (int i = 0; i < 16; i++) a[i] = m[(size_t)R::row(jj, i) * 256];
     }
+    *(uint4 *)(err + at) = mine;
+    if (S == 0) __syncthreads();  // (on larger rings the pass has a barrier)
     cols_inv_regs<S>(ar, v, tw, tw + N, lds, c, jj);
 #pragma unroll
-    for (int i = 0; i < 16; i++) g[(size_t)R::row(jj, i) * 256] = ar.canon(ar.mulmod(ar.mid(v[i]), ar.ninv, ar.ninv_p) + a[i]);
+    for (int i = 0; i < 16; i++)
+        g[(size_t)R::row(jj, i) * 256] = ar.canon(down(ar, v[i]) + ((double)err[R::row(jj, i) * R::COLS + c] + ar.load(a[i])));
 }
 
 // ------------------------------------------------------------------ decrypt
@@ -220,7 +244,7 @@ __global__ __launch_bounds__(CL_THREADS) void k_cl_fcols_c1(const u64 *ct, int l
     const u64 *tw = tw_all + (size_t)limb * 4 * N, *in = ct + (((size_t)blockIdx.z * 2 + 1) * limbs_alloc + limb) * N + col;
     double v[16];
 #pragma unroll
-    for (int i = 0; i < 16; i++) v[i] = (double)in[(size_t)R::row(jj, i) * 256];
+    for (int i = 0; i < 16; i++) v[i] = ar.load(in[(size_t)R::row(jj, i) * 256]);
     cols_fwd_regs<S>(ar, v, tw, tw + N, lds, c, jj);
     u64 *o = ws + ((size_t)blockIdx.z * gridDim.y + limb) * N + col;
 #pragma unroll
@@ -241,8 +265,11 @@ __global__ __launch_bounds__(CL_THREADS) void k_cl_dec_cols(const u64 *ws, int u
 #pragma unroll
     for (int limb = 0; limb < 2; limb++) {
         if (limb < use) {
+            const PrimeConst pc = load_prime(pcs, limb);
             ArithFp ar;
-            ar.init(load_prime(pcs, limb));
+            ar.init(pc);
+            ScaleDown down;
+            down.init(ar, pc);
             const u64 *tw = tw_all + (size_t)limb * 4 * N + 2 * N;
             const u64 *in = ws + ((size_t)blockIdx.y * use + limb) * N + col, *c0 = ct + ((size_t)blockIdx.y * 2 * limbs_alloc + limb) * N + col;
             double v[16];
@@ -250,7 +277,7 @@ __global__ __launch_bounds__(CL_THREADS) void k_cl_dec_cols(const u64 *ws, int u
             for (int i = 0; i < 16; i++) v[i] = __longlong_as_double((long long)in[(size_t)(16 * jj + i) * 256]);
             cols_inv_regs<S>(ar, v, tw, tw + N, buf[limb], c, jj);
 #pragma unroll
-            for (int i = 0; i < 16; i++) r[limb][i] = ar.canon(ar.mulmod(ar.mid(v[i]), ar.ninv, ar.ninv_p) + (double)c0[(size_t)R::row(jj, i) * 256]);
+            for (int i = 0; i < 16; i++) r[limb][i] = ar.canon(down(ar, v[i]) + ar.load(c0[(size_t)R::row(jj, i) * 256]));
         }
     }
     double m[16];
@@ -305,12 +332,18 @@ void launch_cl_encode(ensi_ctx *ctx, const double *d_slots, int n_pt, int n_slot
     });
 }
 
+template <int S, int POLYS>
+static void launch_rows_key(ensi_ctx *ctx, const u64 *in, const u64 *key, int key_limbs, int limbs, int n, u64 *out, hipStream_t st) {
+    const unsigned tiles = (4u * Ring<S>::TILES * limbs + 7) / 8 * 8;
+    hipLaunchKernelGGL((k_cl_rows_key<S, POLYS>), dim3(tiles * n), dim3(64), 0, st, in, key, key_limbs, limbs, (u32)n, ctx->d_pc, ctx->d_tw, out);
+}
+
 void launch_cl_encrypt(ensi_ctx *ctx, const u64 *d_pk, const int8_t *d_small, const u64 *pt, int n, int limbs, u64 *ws, u64 *ct, hipStream_t st) {
     const size_t pn = (size_t)n * ctx->N;
     ring_dispatch(ctx->log_n, [&](auto s) {
         constexpr int S = decltype(s)::value, TILES = Ring<S>::TILES;
         hipLaunchKernelGGL((k_cl_fcols_small<S>), dim3(TILES, limbs, n), dim3(CL_THREADS), 0, st, d_small, ctx->d_pc, ctx->d_tw, ws);
-        hipLaunchKernelGGL((k_cl_rows_key<S, 2>), dim3(4 * TILES, limbs, n), dim3(64), 0, st, ws, d_pk, ctx->L, ctx->d_pc, ctx->d_tw, ct);
+        launch_rows_key<S, 2>(ctx, ws, d_pk, ctx->L, limbs, n, ct, st);
         hipLaunchKernelGGL((k_cl_icols_add<S>), dim3(TILES, 2 * limbs, n), dim3(CL_THREADS), 0, st, ct, d_small + pn, pn, pt, limbs, ctx->d_pc, ctx->d_tw);
     });
 }
@@ -320,7 +353,7 @@ void launch_cl_decrypt(ensi_ctx *ctx, const u64 *d_s_hat, const u64 *ct, int n, 
     ring_dispatch(ctx->log_n, [&](auto s) {
         constexpr int S = decltype(s)::value, TILES = Ring<S>::TILES;
         hipLaunchKernelGGL((k_cl_fcols_c1<S>), dim3(TILES, use, n), dim3(CL_THREADS), 0, st, ct, limbs_alloc, ctx->d_pc, ctx->d_tw, ws);
-        hipLaunchKernelGGL((k_cl_rows_key<S, 1>), dim3(4 * TILES, use, n), dim3(64), 0, st, ws, d_s_hat, ctx->L + ctx->K, ctx->d_pc, ctx->d_tw, ws);
+        launch_rows_key<S, 1>(ctx, ws, d_s_hat, ctx->L + ctx->K, use, n, ws, st);
         hipLaunchKernelGGL((k_cl_dec_cols<S>), dim3(TILES, n), dim3(CL_THREADS), 0, st, ws, use, ct, limbs_alloc, crt, ctx->d_pc, ctx->d_tw, ctx->d_cos, f);
         hipLaunchKernelGGL((k_cl_dec_rows<S>), dim3(ctx->N / 4096, n), dim3(CL_THREADS), 0, st, f, ctx->d_slot_of_k, slot_begin, n_slots, inv_scale, ctx->d_cos, out);
     });
