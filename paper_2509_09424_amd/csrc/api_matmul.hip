@@ -104,7 +104,7 @@ static int build_plan(ensi_ctx *ctx, const int8_t *W, int s, int d, int m, int p
     };
     if (mfma_ok && p->am_mode == AM_POS7)
         for (int i = 0; i < m; i++) {
-            for (int v = 0; v < n_v; v++) wt_at(v, i) = 1;
+            for (int v = 0; v < n_v; v += 16) memset(&wt_at(v, i), 1, std::min(16, n_v - v));
             bias[i] = n_v;
         }
     for (int j = 0; j < d; j++) {
