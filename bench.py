@@ -441,14 +441,14 @@ def roofline_for(w, prof):
         return (rot - raises) // 2
 
     # key-switch work as stages at one level each: (limbs, rotations, raises, switch-backs to the ciphertext basis --
-    # grouped rotations share one --, keys streamed, raises whose digits several rotations may read and which therefore run
+    # grouped rotations share one --, keys streamed, raises whose digits more than two rotations read and which therefore run
     # their row passes); plaintext multiplications as (limbs, products, outputs)
     ks, pm, mm = [], [], []  # mm: ciphertext products as (limbs, distinct operands transformed, outputs)
     if w.name == "keyswitch":
         ks.append((L, w.batch, w.batch, w.batch, w.batch, 0))  # every rotation streams its key
     elif w.op == "rope":
         n_ct = -(-w.d_in // w.c_tot)
-        ks.append((L, 2 * n_ct, n_ct, 2 * n_ct, 2 * -(-n_ct // 32), n_ct))  # inputs are rotated 32 at a time, a key is read once per group
+        ks.append((L, 2 * n_ct, n_ct, 2 * n_ct, 2 * -(-n_ct // 32), 0))  # inputs are rotated 32 at a time, a key is read once per group
         pm.append((L, 3 * n_ct, n_ct))
     elif w.op == "merge":
         pm.append((L, w.d_in, -(-w.d_in // w.c_tot)))
@@ -500,7 +500,7 @@ def roofline_for(w, prof):
         ks.append((L, n_sg, m, n_sg, n_seg, m))
         ks.append((L - 1, n_sg * (g_rot + baby - 1) + n_t * m, n_sg * (g_raise + 1) + n_t * m, n_sg * (g_raise + baby - 1) + n_t * m,
                    g_rot * -(-n_sg // 64) + (baby - 1) * -(-n_sg // 16) + 1, n_sg * (shared(g_rot, g_raise) + 1)))
-        ks.append((L - 1, (n_t - 1) * m, (n_t - 1) * m, (n_t - 1) * m, (n_t - 1) * m, (n_t - 1) * m))  # the sums rotated by their giant steps, before the rescale
+        ks.append((L - 1, (n_t - 1) * m, (n_t - 1) * m, (n_t - 1) * m, (n_t - 1) * m, 0))  # the sums rotated by their giant steps, before the rescale
         pm.append((L, n_sg, n_sg))
         mm.append((L - 1, n_sg * baby, n_t * m))  # the prepared weights are not transformed again
     elif w.op == "ccmm_segment":
@@ -510,21 +510,22 @@ def roofline_for(w, prof):
         P, dd, baby = w.period, w.d_in, w.baby
         g_rot, g_raise = fill_counts(P, w.tokens)
         n_diag, n_t = 2 * P - 1, 2 * P // baby
-        ks.append((L, dd, dd, dd, -(-dd // 16), dd))
+        ks.append((L, dd, dd, dd, -(-dd // 16), 0))
         # one level down: the fills, the baby steps of the spread operands and the giant steps of the columns of Q on one raise
         # each, the relinearisations, the giant steps of the sums that have one
         n_rs = n_diag - baby
         # (the columns of Q are moved by their giant steps and transformed once for all segments, outside the step)
         ks.append((L - 1, dd * (g_rot + baby - 1) + n_diag + n_rs, dd * (g_raise + 1) + n_diag + n_rs,
                    dd * (g_raise + baby - 1) + n_diag + n_rs, g_rot * -(-dd // 64) + (baby - 1) * -(-dd // 16) + 1 + n_rs,
-                   dd * (shared(g_rot, g_raise) + 1) + n_rs))
+                   dd * (shared(g_rot, g_raise) + 1)))
         pm.append((L, dd, dd))
         pm.append((L - 2, P * P + P * (P - 1) // 2, P, n_diag))  # every diagonal enters many sorting products, transformed once
         mm.append((L - 1, dd * baby, n_diag))
     else:
         n_in = -(-w.d_in // w.c_tot)
         # the packed inputs (up to 16 of the largest ring) are rotated together, so a key is read once per rotation amount
-        ks.append((L, w.d_in - n_in, n_in, w.d_in - n_in, -(-n_in // (16 << (16 - w.log_n))) * (min(w.c_tot, w.d_in) - 1), n_in))
+        ks.append((L, w.d_in - n_in, n_in, w.d_in - n_in, -(-n_in // (16 << (16 - w.log_n))) * (min(w.c_tot, w.d_in) - 1),
+                   n_in if min(w.c_tot, w.d_in) - 1 > 2 else 0))
 
     fused_ks = w.log_n >= 12 and w.q_bits <= 50  # the key switch transforms inside its own kernels
 

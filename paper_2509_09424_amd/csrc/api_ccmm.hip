@@ -487,6 +487,7 @@ static int rotate_columns(ensi_ctx *ctx, const ensi_gk *gk, const ensi_ct *B, co
         if (it == gk->keys.end()) ENSI_FAIL(ctx, ENSI_E_NOKEY, "no Galois key for step %d", cols[c]);
         key[c] = it->second;
     }
+    const RaiseUse use = raise_use((size_t)(cnt - std::count(cols, cols + cnt, 0)), 1);
     for (int j0 = 0; j0 < d; j0 += GS) {
         const int gs = std::min(GS, d - j0);
         bool raised = false;
@@ -513,11 +514,11 @@ static int rotate_columns(ensi_ctx *ctx, const ensi_gk *gk, const ensi_ct *B, co
                 }
             if (desc.empty()) continue;
             if (!raised) {
-                if ((rc = raise_cts(ctx, l1, B->d + (size_t)j0 * b_ct, b_ct, B->limbs_alloc, gs, RAISE_SHARED, st))) return rc;
+                if ((rc = raise_cts(ctx, l1, B->d + (size_t)j0 * b_ct, b_ct, B->limbs_alloc, gs, use, st))) return rc;
                 raised = true;
             }
             ENSI_HIP(ctx, host_to_device(ctx, ctx->ws_desc, desc.data(), desc.size() * sizeof(RotDesc), st));
-            if ((rc = run_rotations(ctx, ctx->ws_desc, (int)desc.size(), l1, B->limbs_alloc, l1, RAISE_SHARED, st))) return rc;
+            if ((rc = run_rotations(ctx, ctx->ws_desc, (int)desc.size(), l1, B->limbs_alloc, l1, use, st))) return rc;
         }
     }
     return ENSI_OK;
@@ -622,22 +623,23 @@ static int rotate_jobs(ensi_ctx *ctx, const ensi_gk *gk, const u64 *src, size_t 
         const int grp = jobs[k0].src / GS;
         size_t k1 = k0;
         int lo = n_src, hi = -1;
-        bool any = false;
+        size_t n_rot = 0;
         while (k1 < jobs.size() && jobs[k1].src / GS == grp) {
             if (jobs[k1].step) {
                 lo = std::min(lo, jobs[k1].src);
                 hi = std::max(hi, jobs[k1].src);
-                any = true;
+                n_rot++;
             }
             k1++;
         }
-        if (any && (rc = raise_cts(ctx, l1, src + (size_t)lo * src_ct, src_ct, limb_stride_in, hi - lo + 1, RAISE_SHARED, st))) return rc;
+        const RaiseUse use = raise_use(n_rot, std::max(0, hi - lo + 1));
+        if (n_rot && (rc = raise_cts(ctx, l1, src + (size_t)lo * src_ct, src_ct, limb_stride_in, hi - lo + 1, use, st))) return rc;
         std::vector<RotDesc> desc;
         auto flush = [&]() -> int {
             if (desc.empty()) return ENSI_OK;
             if (host_to_device(ctx, ctx->ws_desc, desc.data(), desc.size() * sizeof(RotDesc), st) != hipSuccess)
                 ENSI_FAIL(ctx, ENSI_E_HIP, "descriptor copy failed");
-            const int r = run_rotations(ctx, ctx->ws_desc, (int)desc.size(), l1, limb_stride_in, l1, RAISE_SHARED, st);
+            const int r = run_rotations(ctx, ctx->ws_desc, (int)desc.size(), l1, limb_stride_in, l1, use, st);
             desc.clear();
             return r;
         };

@@ -338,10 +338,11 @@ static int matmul_run(ensi_ctx *ctx, const ensi_gk *gk, const ensi_ct *in, Matmu
         for (size_t gi = 0; gi < groups.size(); gi++) {
             if (!groups[gi].second) continue;
             const int G0 = (int)gi * GS, cnt_in = std::min(GS, n_in - G0);
-            if ((rc = raise_cts(ctx, l1, in->d + (size_t)G0 * in_ct, in_ct, in->limbs_alloc, cnt_in, RAISE_SHARED, st))) return rc;
+            const RaiseUse use = raise_use(groups[gi].second, cnt_in);
+            if ((rc = raise_cts(ctx, l1, in->d + (size_t)G0 * in_ct, in_ct, in->limbs_alloc, cnt_in, use, st))) return rc;
             for (int o = 0; o < groups[gi].second; o += chunk) {
                 const int cnt = std::min(chunk, groups[gi].second - o);
-                if ((rc = run_rotations(ctx, ctx->ws_desc + groups[gi].first + o, cnt, l1, in->limbs_alloc, in->limbs_alloc, RAISE_SHARED, st))) return rc;
+                if ((rc = run_rotations(ctx, ctx->ws_desc + groups[gi].first + o, cnt, l1, in->limbs_alloc, in->limbs_alloc, use, st))) return rc;
             }
         }
     }

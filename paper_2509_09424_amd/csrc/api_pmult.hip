@@ -300,8 +300,8 @@ extern "C" int ensi_rope(ensi_ctx *ctx, const ensi_gk *gk, const ensi_ct *in, co
                 d.g_inv = inv_mod_2n(g[e], N);
             }
         ENSI_HIP(ctx, host_to_device(ctx, ctx->ws_desc, desc.data(), desc.size() * sizeof(RotDesc), st));
-        if ((rc = raise_cts(ctx, l1, in->d + (size_t)c0 * ct_words, ct_words, ls, cnt, RAISE_SHARED, st))) return rc;
-        if ((rc = run_rotations(ctx, ctx->ws_desc, 2 * cnt, l1, ls, ls, RAISE_SHARED, st))) return rc;
+        if ((rc = raise_cts(ctx, l1, in->d + (size_t)c0 * ct_words, ct_words, ls, cnt, raise_use(2, 1), st))) return rc;
+        if ((rc = run_rotations(ctx, ctx->ws_desc, 2 * cnt, l1, ls, ls, raise_use(2, 1), st))) return rc;
         // y = q (x) cos + Rot(q; 1) (x) (neg sin) + Rot(q; -1) (x) (pos sin), rescaled once
         std::vector<PmTerm> terms(3 * cnt);
         std::vector<int32_t> begin(cnt + 1);

@@ -74,9 +74,15 @@ hipError_t host_to_device(ensi_ctx *ctx, void *dst, const void *src, size_t byte
 struct KsWorkspace {
     u64 *digits, *u;
 };
-// Whether each raised ciphertext serves one rotation (the fused path then leaves its digits after their column pass, and the
-// inner product runs their row passes) or several.
+// Whether each raised ciphertext serves few rotations (RAISE_ONE: the fused path leaves its digits after their column pass, and the
+// inner product runs their row passes, once per rotation) or many (their row passes are run once, by a kernel of their own).
 enum RaiseUse { RAISE_ONE, RAISE_SHARED };
+// A row pass of its own takes the digits through memory twice more; one in the inner product costs arithmetic that the reads of keys
+// partly hide, and the digits of neighbouring rotations come from L2.  Two rotations a raise: 96 ciphertexts
+// under Alg. 2 at 16 + 4 limbs 14.0 -> 12.6 ms; one: 64 columns of scores 90.7 -> 86.6; three: nothing in it (86.2, and 1152 rotations
+// of the 2^14 ring in 7.26 against 7.24).
+#define RAISE_ONE_MAX 2  // rotations per raise
+inline RaiseUse raise_use(size_t n_rot, size_t n_raised) { return n_rot <= RAISE_ONE_MAX * n_raised ? RAISE_ONE : RAISE_SHARED; }
 size_t raised_words(const ensi_ctx *ctx, int l1);
 int get_modup(ensi_ctx *ctx, int l1, const ModUpConst **out);
 int get_moddown(ensi_ctx *ctx, int l1, const ModDownConst **out);

@@ -1,5 +1,5 @@
 // Rotation (paper, Preliminaries: Rot) for the rings N = 2^12 .. 2^16 with ciphertext primes below 2^50:
-// automorphism plus hybrid key switching in three kernels (four where several rotations share one raised
+// automorphism plus hybrid key switching in three kernels (four where more than RAISE_ONE_MAX rotations share one raised
 // ciphertext) that keep every intermediate in the layout and number format of the transform passes around it.
 //
 //   k_ks16_fcols   ModUp fused into the forward column pass.  A block holds the inner factors
@@ -7,9 +7,9 @@
 //                  limbs of the extended basis: it forms  sum_a y_a (Q_j/q_a) mod t  (or takes the limb inside its
 //                  own digit), runs the column pass on it and writes it.  Further blocks do the same for P * c0, so
 //                  that phi_g(c0) can be added in the transform domain (ModDown divides it by P again, exactly)
-//   k_ks16_frows   forward row pass of the raised digits and of P * c0, where several rotations read them
+//   k_ks16_frows   forward row pass of the raised digits and of P * c0, where more than RAISE_ONE_MAX rotations read them
 //   k_ks16_inner   inner product with the key + P * c0, automorphism (a permutation of transform-domain positions that maps
-//                  rows onto rows) of the two sums, inverse row pass.  A raised ciphertext that only one rotation reads is taken after its column
+//                  rows onto rows) of the two sums, inverse row pass.  A raised ciphertext that fewer rotations read is taken after its column
 //                  pass and the row passes of its digits are run here: the transformed digits never reach memory
 //   k_ks16_icols   inverse column pass fused with ModDown.  A block brings the K special limbs of one column tile
 //                  to centred residues y_k = [u (P/p_k)^-1]_{p_k}, held in registers, and then walks the
@@ -350,7 +350,7 @@ struct Inner<ArithInt> {
 // two sums, not the beta + 1 polynomials they are made of.
 //   GROUP = false: one rotation; the wave takes source rows 4 tile .. 4 tile + 3 and writes the rows they map to.
 //   GROUP = true:  `members` rotations whose sums are added: the wave takes output rows 4 tile .. 4 tile + 3.
-// RAW (one rotation): the digits have only been through their column pass; their row passes are run here.
+// RAW (not GROUP): the digits have only been through their column pass; their row passes are run here.
 template <int S, bool RAW, bool GROUP, class A>
 __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *desc, const PrimeConst &pc, const u64 *tw_all, u64 *u, int prime, int e,
                                            int members, u32 grp, u32 tile, u64 *lds, ulonglong2 *tw1) {

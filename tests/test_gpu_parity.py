@@ -557,6 +557,26 @@ def test_full_ring_rotate_other_prime_sizes(params, why):
     p.close()
 
 
+@pytest.mark.parametrize("params", [(12, 50, 5, 60, 4, 4, 40), (14, 50, 6, 60, 2, 2, 40)], ids=["4K", "16K"])
+def test_few_and_many_rotations_of_a_raised_input_bit_exact(params):
+    """Around the two rotations per raised ciphertext up to which the inner product runs the digits' row passes itself: one to
+    three on one input, and on two inputs four (still two each) and five."""
+    p = Pair(params)
+    s = p.n // 4
+    o_gks, g_gk = p.galois_keys([s, 2 * s, 3 * s])
+    rng = np.random.default_rng(8)
+    for d in (2, 3, 4, 6, 7):
+        W = wl.ternary_weights(rng, d, 3)
+        o_cts, g_ct = p.encrypt_both(wl.pack_columns(rng.uniform(-1, 1, (s, d)), p.n), p.pr.L)
+        out = p.ctx.ternary_matmul(g_gk, g_ct, s, d, W, "zero")
+        want = p.o.ternary_matmul(o_cts, s, d, W, "zero", {r: o_gks[r * s] for r in range(1, 4)})
+        assert np.array_equal(out.export(), stack_cts(want)), d
+        out.free()
+        g_ct.free()
+    g_gk.free()
+    p.close()
+
+
 @pytest.mark.parametrize("params", [
     (12, 50, 5, 60, 4, 4, 40), (13, 50, 5, 60, 3, 2, 40), (14, 50, 6, 60, 2, 2, 40), (15, 50, 4, 60, 1, 1, 36),  # special primes just below 2^60
     (12, 45, 4, 48, 3, 3, 36),  # every prime in fp64
