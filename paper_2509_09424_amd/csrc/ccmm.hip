@@ -88,12 +88,20 @@ __global__ __launch_bounds__(MM_THREADS, TX * TY > 4 ? 2 : 3) void k_mm_mac(MmGr
     auto reduce = [&](const int64_t *v) { return ar.mid(ar.mulmod_np(residue(v[2]), c50) + ar.mulmod_np(residue(v[1]), c25) + residue(v[0])); };
     const int e0 = as_const(g.entry_begin)[grp], e1 = as_const(g.entry_begin)[grp + 1];
     auto index = [&](int e, int w) { return as_const((const int32_t *)(g.entries + e))[w]; };
+    struct Words {
+        u64 a[TX][2], b[TY][2];
+    };
+    auto place_of = [&](int i) { return as_const((const u64 *)(g.ops + i))[1]; };  // MmOperand.t
+    auto two = [&](u64 p, u64 *d) {
+        const u64 *s0 = (const u64 *)p + at;
+        d[0] = *as_global((const u64 *)((const char *)s0 + off));
+        d[1] = *as_global((const u64 *)((const char *)(s0 + poly) + off));
+    };
     // In a grid of outputs the words of two entries are on their way while one is multiplied, with the places of the next one
     // and the indices of the one after it in scalar registers: there the kernel waited for operand words and for look-ups, not
-    // for multiply-adds or memory (96 x 32 x 4 products at 15 limbs: 17.8 ms with one entry ahead, 14.4 so).  Without a grid every
-    // operand is read about once, at the rate of memory, and one entry ahead is enough (3.1 ms for 16 GB, 3.25 with two).
-    // No load hangs on a branch -- an operand that an entry does not name is read from another place and, where its products
-    // would be added to an output, masked -- so that the compiler can count the loads it does not wait for.
+    // for multiply-adds or memory (96 x 32 x 4 products at 15 limbs: 17.8 ms with one entry ahead, 14.4 so).
+    // No load hangs on a branch, so that the compiler can count the loads it does not wait for: an operand that an entry does not
+    // name -- only products of outputs that do not exist lack one -- is read from another place.
     u64 pa[TX], pb[TY];
     int ia[TX], ib[TY];
     auto look_up = [&](int e) {
@@ -103,60 +111,57 @@ __global__ __launch_bounds__(MM_THREADS, TX * TY > 4 ? 2 : 3) void k_mm_mac(MmGr
 #pragma unroll
         for (int y = 0; y < TY; y++) ib[y] = index(e, 4 + y);
     };
-    struct Words {
-        u64 a[TX][2], b[TY][2];
-        u32 named[TX];  // 25 ones where the entry names operand x
-    };
-    u32 next_named[TX];
     auto place = [&]() {
-        auto of = [&](int i) { return as_const((const u64 *)(g.ops + max(i, 0)))[1]; };  // MmOperand.t
 #pragma unroll
-        for (int x = 0; x < TX; x++) {
-            pa[x] = of(ia[x]);
-            next_named[x] = ia[x] >= 0 ? 0x1ffffffu : 0u;
-        }
+        for (int x = 0; x < TX; x++) pa[x] = place_of(max(ia[x], 0));
 #pragma unroll
-        for (int y = 0; y < TY; y++) pb[y] = of(ib[y]);
+        for (int y = 0; y < TY; y++) pb[y] = place_of(max(ib[y], 0));
     };
-    auto fetch = [&](Words &w, int e) {  // the words of entry e, whose places are at hand
-        auto two = [&](u64 p, u64 *d) {
-            const u64 *s0 = (const u64 *)p + at;
-            d[0] = *as_global((const u64 *)((const char *)s0 + off));
-            d[1] = *as_global((const u64 *)((const char *)(s0 + poly) + off));
-        };
+    auto fetch_placed = [&](Words &w, int e) {  // the words of entry e, whose places are at hand
 #pragma unroll
-        for (int x = 0; x < TX; x++) {
-            two(pa[x], w.a[x]);
-            w.named[x] = next_named[x];
-        }
+        for (int x = 0; x < TX; x++) two(pa[x], w.a[x]);
 #pragma unroll
         for (int y = 0; y < TY; y++) two(pb[y], w.b[y]);
         place();
         look_up(e + 2);
     };
+    // Without a grid every operand is read about once, at the rate of memory, and one entry ahead is enough.  An entry then names one
+    // to four left operands, and those that it does not name are not read: where sums share no right operand that is three of
+    // four (four sums of 96 products at 15 limbs: 2.2 ms, and 2.9 with all four read).  Sums that share every right operand: 3.1 ms
+    // for 16 GB, 3.25 with two entries ahead.
+    auto fetch_named = [&](Words &w, int e) {
+        if (e >= e1) return;
+#pragma unroll
+        for (int x = 0; x < TX; x++) {
+            const int i = index(e, x);
+            if (i >= 0) two(place_of(i), w.a[x]);
+            else w.a[x][0] = w.a[x][1] = 0;
+        }
+#pragma unroll
+        for (int y = 0; y < TY; y++) two(place_of(index(e, 4 + y)), w.b[y]);
+    };
     constexpr int AHEAD = TY > 1 ? 2 : 1;
     auto multiply = [&](Words &w, int e) {
         // halves of a0, a0 + a1, a1 (and b alike): at most 26 bits
         int al[TX][3], ah[TX][3], bl[TY][3], bh[TY][3];
-        auto halves = [](const u64 *d, int *l, int *h, u32 mask, bool mask_high) {
-            l[0] = (int)((u32)d[0] & mask);
+        auto halves = [](const u64 *d, int *l, int *h) {
+            l[0] = (int)((u32)d[0] & 0x1ffffffu);
             h[0] = (int)(u32)(d[0] >> 25);
-            l[2] = (int)((u32)d[1] & mask);
+            l[2] = (int)((u32)d[1] & 0x1ffffffu);
             h[2] = (int)(u32)(d[1] >> 25);
-            if (mask_high) {
-                h[0] &= mask;
-                h[2] &= mask;
-            }
             l[1] = l[0] + l[2];
             h[1] = h[0] + h[2];
         };
-        // (of a grid of outputs, TY > 1, only products of outputs that do not exist lack an operand)
 #pragma unroll
-        for (int x = 0; x < TX; x++) halves(w.a[x], al[x], ah[x], TY > 1 ? 0x1ffffffu : w.named[x], TY == 1);
+        for (int x = 0; x < TX; x++) halves(w.a[x], al[x], ah[x]);
 #pragma unroll
-        for (int y = 0; y < TY; y++) halves(w.b[y], bl[y], bh[y], 0x1ffffffu, false);
-        fetch(w, e + AHEAD);
-        __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the multiply-adds
+        for (int y = 0; y < TY; y++) halves(w.b[y], bl[y], bh[y]);
+        if (TY > 1) {
+            fetch_placed(w, e + AHEAD);
+            __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the multiply-adds
+        } else {
+            fetch_named(w, e + AHEAD);
+        }
 #pragma unroll
         for (int x = 0; x < TX; x++)
 #pragma unroll
@@ -170,12 +175,14 @@ __global__ __launch_bounds__(MM_THREADS, TX * TY > 4 ? 2 : 3) void k_mm_mac(MmGr
                 }
     };
     Words w0, w1;
-    if (e0 < e1) {
+    if (TY == 1) {
+        fetch_named(w0, e0);
+    } else if (e0 < e1) {
         look_up(e0);
         place();
         look_up(e0 + 1);
-        fetch(w0, e0);
-        if (AHEAD > 1) fetch(w1, e0 + 1);
+        fetch_placed(w0, e0);
+        fetch_placed(w1, e0 + 1);
     }
 #pragma unroll 1
     for (int e = e0; e < e1; e += AHEAD) {
