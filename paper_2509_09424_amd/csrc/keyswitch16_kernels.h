@@ -307,10 +307,8 @@ struct Inner<ArithFp> {
     static __device__ __forceinline__ void zero(Acc &a) { a.s = 0.0; }
     static __device__ __forceinline__ void mac(const ArithFp &ar, Acc &a, u64 x, u64 k) { a.s += ar.mulmod_np(as_f64(x), as_f64(k)); }
     static __device__ __forceinline__ void add(Acc &a, u64 x) { a.s += as_f64(x); }
-    // a rotation adds up to nine terms below 0.7 p: reduced after each, the sums stay exact integers
+    // a rotation adds up to nine terms below 0.7 p to what those before it left: reduced after each, the sums stay exact integers
     static __device__ __forceinline__ void fold(const ArithFp &ar, Acc &a) { a.s = ar.mid(a.s); }
-    static __device__ __forceinline__ double value(const Acc &a) { return a.s; }
-    static __device__ __forceinline__ double join(const ArithFp &ar, double x, double y) { return ar.mid(x + y); }
 };
 // x = xh 2^30 + xl, k = kh 2^30 + kl: xh kh 2^60 is taken apart into dwords and folded by 2^60 = d, 2^62 = 4 d, like the
 // middle sum m 2^30.  Every half is at most 2^29 (a little more for the high ones): within 6 q before the last fold.
@@ -329,8 +327,6 @@ struct Inner<ArithWide> {
     }
     static __device__ __forceinline__ void add(Acc &, u64) {}
     static __device__ __forceinline__ void fold(const ArithWide &, Acc &) {}
-    static __device__ __forceinline__ int64_t value(const Acc &a) { return a.s; }
-    static __device__ __forceinline__ int64_t join(const ArithWide &ar, int64_t x, int64_t y) { return ar.mid(x + y); }
 };
 template <>
 struct Inner<ArithInt> {
@@ -341,8 +337,6 @@ struct Inner<ArithInt> {
     static __device__ __forceinline__ void mac(const ArithInt &ar, Acc &a, u64 x, u64 k) { a.s = add_mod(a.s, mont_mul(x, k, ar.q, ar.qneg_inv), ar.q); }
     static __device__ __forceinline__ void add(Acc &, u64) {}
     static __device__ __forceinline__ void fold(const ArithInt &, Acc &) {}
-    static __device__ __forceinline__ u64 value(const Acc &a) { return a.s; }
-    static __device__ __forceinline__ u64 join(const ArithInt &ar, u64 x, u64 y) { return add_mod(x, y, ar.q); }
 };
 
 // Four rows of one limb of both accumulators, by one wave, and their inverse row passes.  Digits and keys are multiplied where they
@@ -366,23 +360,42 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
     const ulonglong2 *tab = tw1 + rho * 16;
     A ar;
     ar.init(pc);
-    T s0[16], s1[16];  // the sums in the order of the output rows
-    u32 r = tile * 4 + rho;
+    typename I::Acc a0[16], a1[16];
+    u32 r = tile * 4 + rho, g = 1, carry = 0;
+    // Moves a sum from the positions that the element g reads (carry: of this row) to those that the next rotation's element reads,
+    // or, with 1 and 0, to the output's own order.  The rotations of a group add to one pair of sums in this way; a
+    // second pair in the output's order took 14 to 58 registers more than there are (fills of 384 and 768 ciphertexts, 15 limbs: 48.7
+    // and 79.1 ms of inner products with it, 46.0 and 75.0 so).
+    auto move = [&](typename I::Acc *a, u32 to_g_inv, u32 to_carry) {
+        T *l = (T *)lds;
+        // value i of lane j, position p = 16 j + i with brev8(p) = brev4(j) + 16 brev4(i), is at brev8(h (brev8(p) - to_carry) + carry)
+        const u32 h = g * to_g_inv, first = h * ((__brev((u32)j) >> 28) - to_carry) + carry;
+#pragma unroll
+        for (int i = 0; i < 16; i++) l[rpad(rho * 256 + 16 * j + i)] = a[i].s;
+        wave_lds_fence();
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const u32 brev4_i = (i & 1) * 8 + (i & 2) * 2 + (i & 4) / 2 + (i & 8) / 8;
+            a[i].s = l[rpad(rho * 256 + brev8(first + h * (16 * brev4_i)))];
+        }
+        wave_lds_fence();
+    };
 #pragma unroll 1
     for (int mem = 0; mem < (GROUP ? members : 1); mem++) {
         const RotDesc d = load_desc(desc, grp * members + mem);
         const u32 rs = GROUP ? M::source(r, d.g) : r;
         if (!GROUP) r = M::row(d.g_inv * M::exponent(rs));
-        const u32 carry = M::carry(r, d.g);
+        const u32 to_carry = M::carry(r, d.g);
         // byte offsets of value 0 from the wave's tile of digits and keys
         const u32 reg_off = ((GROUP ? (rs >> 2) * 1024 + (rs & 3) * 16 : rho * 16) + j) * 8, row_off = (rho * 256 + j) * 8;
         const u64 *src = d.digits + (size_t)e * N + (GROUP ? 0 : tile * 1024), *key = d.key + (size_t)prime * N + (GROUP ? 0 : tile * 1024);
         auto ld = [](const u64 *base, u32 off) { return *(decltype(as_global(base)))((decltype(as_global((const char *)base)))as_global(base) + off); };
-        typename I::Acc a0[16], a1[16];
+        if (!GROUP || mem == 0) {
 #pragma unroll
-        for (int i = 0; i < 16; i++) {
-            I::zero(a0[i]);
-            I::zero(a1[i]);
+            for (int i = 0; i < 16; i++) {
+                I::zero(a0[i]);
+                I::zero(a1[i]);
+            }
         }
         const bool with_c0 = e < l1;  // P * c0 follows the digits
         if (RAW) {
@@ -430,7 +443,7 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
             }
         } else {
             // C values at a time, the next C requested before the current ones are multiplied.
-            constexpr int C = GROUP ? 4 : 8;
+            constexpr int C = 8;
             u64 x[2][C], k0[2][C], k1[2][C];
             auto fetch = [&](int i0, bool keys) {
                 const int b = i0 / C & 1;
@@ -445,6 +458,10 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
                 }
             };
             fetch(0, true);
+            if (GROUP && mem > 0) {
+                move(a0, d.g_inv, to_carry);
+                move(a1, d.g_inv, to_carry);
+            }
 #pragma unroll 1
             for (int jd = 0; jd < beta; jd++) {
                 const bool more = jd + 1 < beta;
@@ -479,23 +496,12 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
             I::fold(ar, a0[i]);
             I::fold(ar, a1[i]);
         }
-        // the automorphism within the rows
-        T *l = (T *)lds;
-        const u32 first = d.g * (__brev((u32)j) >> 28) + carry;  // of value 0: brev8(16 j + i) = brev4(j) + 16 brev4(i)
-        auto permute = [&](const typename I::Acc *a, T *s) {
-#pragma unroll
-            for (int i = 0; i < 16; i++) l[rpad(rho * 256 + 16 * j + i)] = I::value(a[i]);
-            wave_lds_fence();
-#pragma unroll
-            for (int i = 0; i < 16; i++) {
-                const u32 brev4_i = (i & 1) * 8 + (i & 2) * 2 + (i & 4) / 2 + (i & 8) / 8;
-                const T v = l[rpad(rho * 256 + brev8(first + d.g * (16 * brev4_i)))];
-                s[i] = GROUP && mem > 0 ? I::join(ar, s[i], v) : v;
-            }
-            wave_lds_fence();
-        };
-        permute(a0, s0);
-        permute(a1, s1);
+        g = d.g;
+        carry = to_carry;
+        if (!GROUP || mem + 1 == members) {
+            move(a0, 1, 0);  // the automorphism within the rows
+            move(a1, 1, 0);
+        }
     }
     // inverse row pass of both sums: its twiddles are fetched once
     tw += 2 * N;
@@ -506,7 +512,9 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
     u64 *uo = u + ((size_t)grp * 2 * ext + e) * N + (size_t)r * 256 + j;
 #pragma unroll
     for (int poly = 0; poly < 2; poly++) {
-        T *v = poly ? s1 : s0;
+        T v[16];
+#pragma unroll
+        for (int i = 0; i < 16; i++) v[i] = (poly ? a1 : a0)[i].s;
         row_inv(ar, v, tab, twi, lds, rho, j);
         u64 *o = uo + (size_t)poly * ext * N;
 #pragma unroll

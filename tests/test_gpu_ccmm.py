@@ -130,6 +130,23 @@ def test_replicate_against_oracle(params):
     p.close()
 
 
+@pytest.mark.parametrize("params", [(12, 50, 4, 60, 2, 2, 40), (13, 45, 3, 48, 3, 3, 36), (12, 50, 3, 61, 2, 2, 40)], ids=["4K-wide", "8K-fp", "4K-61bit"])
+def test_fills_on_the_rings_of_the_register_transform(params):
+    """Groups of three rotations added before the inverse pass, and a last group of one: every kind of special primes."""
+    p = Pair(params)
+    l1 = p.pr.L
+    o_gks, g_gk = doubling_keys(p)
+    o_cts, g_ct = p.encrypt_both(p.rng.uniform(-1, 1, (2, p.n)), l1)
+    masks = p.o.one_hot_masks([5, p.n - 1], l1)
+    g_masks = p.ctx.pt_set_scale(p.ctx.pt_import(masks, l1), float(p.pr.q[l1 - 1]))
+    out = p.ctx.replicate(g_gk, g_ct, [0, 1, 1], g_masks, [1, 0, 1])
+    want = [p.o.replicate(o_cts[c], masks[k], o_gks) for c, k in ((0, 1), (1, 0), (1, 1))]
+    assert np.array_equal(out.export(), stack_cts(want))
+    for h in (g_ct, g_masks, out, g_gk):
+        h.free()
+    p.close()
+
+
 @pytest.mark.parametrize("params,d,m,period", [(TINY5, 3, 2, 4), (SMALL4, 5, 3, 8), (SMALL4, 8, 2, 8)], ids=["16-slots", "512-slots", "d-equals-period"])
 def test_ccmm_against_oracle_and_numpy(params, d, m, period):
     """CCMM section, C = A B, with the two-stage element extraction."""

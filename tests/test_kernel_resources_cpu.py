@@ -1,0 +1,32 @@
+"""Registers of the kernels that hold whole rows or columns of a transform: what the compiler could not place goes through scratch
+memory on every access, on the ring where it happens and nowhere else.  Read from the compiler's own report, ring by ring."""
+import os
+import re
+import subprocess
+from concurrent.futures import ThreadPoolExecutor
+
+import pytest
+
+from paper_2509_09424_amd import build
+
+
+def spilled(source):
+    """{mangled kernel name: vector registers spilled} of one source (file, or file:ring as in the build's list)."""
+    src, _, ring = source.partition(":")
+    cmd = [build.HIPCC] + build.FLAGS + ["-DKS_RING=" + ring] * bool(ring) + ["-I" + os.path.join(build.CSRC, "inc"), "--cuda-device-only",
+           "-Rpass-analysis=kernel-resource-usage", "-c", os.path.join(build.CSRC, src), "-o", os.devnull]
+    report = subprocess.run(cmd, capture_output=True, text=True, check=True).stderr
+    return {name: int(n) for name, n in re.findall(r"Function Name: (\S+).*?VGPRs Spill: (\d+)", report, re.S)}
+
+
+@pytest.fixture(scope="module")
+def rings():
+    with ThreadPoolExecutor(5) as pool:
+        return list(pool.map(spilled, ["keyswitch16_ring.hip:%d" % s for s in range(5)]))
+
+
+def test_inner_products_over_transformed_digits_do_not_spill(rings):
+    """Shared digits, of single rotations and of groups, for every kind of special primes."""
+    for s, kernels in enumerate(rings):
+        inner = {k: n for k, n in kernels.items() if "k_ks16_innerILi%dELb0E" % s in k}
+        assert len(inner) == 6 and not any(inner.values()), (s, inner)
