@@ -887,11 +887,12 @@ int raise_cts(ensi_ctx *ctx, int l1, const u64 *ct_base, size_t ct_stride_words,
 // Runs inner product -> inverse transform -> ModDown (+ phi_g(c0)) for n_rot descriptors already on the device.
 // members > 1: the descriptors come in groups of `members` rotations of one ciphertext (same source, digits and
 // destination); a group's inner products are added over the extended basis and brought back by one inverse
-// transform and one ModDown, and the destination receives sum_k phi_{g_k}(c0) with it.  h_desc: host copy of the
-// descriptors (needed by the unfused path of a grouped call only).
+// transform and one ModDown, and the destination receives sum_k phi_{g_k}(c0) with it; the raise must have been
+// RAISE_SHARED.  h_desc: host copy of the descriptors (needed by the unfused path of a grouped call only).
 int run_rotations(ensi_ctx *ctx, const RotDesc *d_desc, int n_rot, int l1, int limb_stride_in, int limb_stride_out, RaiseUse use, hipStream_t st,
                   int members, const RotDesc *h_desc, const KsWorkspace *ws) {
     int rc;
+    if (members > 1 && use == RAISE_ONE) ENSI_FAIL(ctx, ENSI_E_BADARG, "grouped rotations read transformed digits");
     u64 *u = ws ? ws->u : ctx->ws_u;
     if (ctx->ks16) {
         const Ks16Const *kc;

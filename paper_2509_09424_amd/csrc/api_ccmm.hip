@@ -321,7 +321,7 @@ static int doubling_steps(ensi_ctx *ctx, const ensi_gk *gk, ensi_ct *t, int r_be
     size_t k = 0;
     for (const auto &grp : groups) {
         const int members = (int)grp.size();
-        const RaiseUse use = members == 1 ? RAISE_ONE : RAISE_SHARED;
+        const RaiseUse use = raise_use(members, 1, members);
         for (int c0 = 0; c0 < n; c0 += chunk, k++) {
             const int cnt = std::min(chunk, n - c0);
             if ((rc = raise_cts(ctx, l1, t->d + (size_t)c0 * ct_words, ct_words, t->limbs_alloc, cnt, use, st))) return rc;

@@ -81,8 +81,11 @@ enum RaiseUse { RAISE_ONE, RAISE_SHARED };
 // partly hide, and the digits of neighbouring rotations come from L2.  Two rotations a raise: 96 ciphertexts
 // under Alg. 2 at 16 + 4 limbs 14.0 -> 12.6 ms; one: 64 columns of scores 90.7 -> 86.6; three: nothing in it (86.2, and 1152 rotations
 // of the 2^14 ring in 7.26 against 7.24).
+// Rotations in groups (members > 1: their inner products are added before one inverse pass) read transformed digits only.
 #define RAISE_ONE_MAX 2  // rotations per raise
-inline RaiseUse raise_use(size_t n_rot, size_t n_raised) { return n_rot <= RAISE_ONE_MAX * n_raised ? RAISE_ONE : RAISE_SHARED; }
+inline RaiseUse raise_use(size_t n_rot, size_t n_raised, int members = 1) {
+    return members == 1 && n_rot <= RAISE_ONE_MAX * n_raised ? RAISE_ONE : RAISE_SHARED;
+}
 size_t raised_words(const ensi_ctx *ctx, int l1);
 int get_modup(ensi_ctx *ctx, int l1, const ModUpConst **out);
 int get_moddown(ensi_ctx *ctx, int l1, const ModDownConst **out);

@@ -398,7 +398,7 @@ void launch_ks16_raise(ensi_ctx *ctx, const Ks16Const &kc, const u64 *ct_base, s
 // inner product + inverse transform + ModDown for n_rot descriptors (desc.digits = the ciphertext's block of dig)
 // members > 1: the descriptors come in groups of `members` rotations of one ciphertext (same digits and destination);
 // a group's inner products are added before one inverse transform and one ModDown
-// raw: the digits have been through their column pass only
+// raw: the digits have been through their column pass only (members = 1: the grouped kernel runs no row pass)
 void launch_ks16_switch(ensi_ctx *ctx, const Ks16Const &kc, const RotDesc *d_desc, int n_rot, u64 *u, int limb_stride_out, bool raw,
                         hipStream_t st, int members = 1);
 
