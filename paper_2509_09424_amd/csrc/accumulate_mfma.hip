@@ -81,6 +81,10 @@ typedef int v16i __attribute__((vector_size(64)));
 #define AM_BSLOT 8192           // plane tiles of one step (1 KiB each, PLANES of 8 used)
 #define AM_ASLOT 2048           // one wave's two weight fragments of one step
 
+// The word sums of an item are copied to one of two slots by all four waves while the item before it is multiplied: the slot's last
+// readers have finished only if an item is more than one group of steps (AM_RING), which more than AM_POS7_MIN operands fill.
+static_assert(AM_POS7_MIN >= AM_RING * AM_TILE_K, "an item with word sums must be more than one group of steps");
+
 #define AM_STORES 16            // stores of one item by one wave: 64 outputs x 32 words, 1 KiB each
 #define AM_OROW 144             // 16 words of an output, padded
 
