@@ -193,8 +193,10 @@ struct ScaleDown {
 };
 // Inverse column pass in place, plus the error polynomial and, on the first polynomial, the message: the ciphertext.
 // grid (TILES, 2 * limbs, n); errors: e0 of all ciphertexts, then (err_stride further) e1
+// As many blocks on a CU as its registers allow: asked for the four that its LDS holds, the rings 2^13 and 2^15 spilled 44 and 40
+// (64 x 6 limbs of 2^13 38.4 us, 26 so; 10 x 12 of 2^15 44.5, 31; 10 x 16 of 2^16 89.4, 87).
 template <int S>
-__global__ __launch_bounds__(CL_THREADS, 4) void k_cl_icols_add(u64 *ct, const int8_t *errors, size_t err_stride, const u64 *pt, int limbs,
+__global__ __launch_bounds__(CL_THREADS) void k_cl_icols_add(u64 *ct, const int8_t *errors, size_t err_stride, const u64 *pt, int limbs,
                                                              const PrimeConst *pcs, const u64 *tw_all) {
     typedef Ring<S> R;
     constexpr size_t N = R::N;
@@ -211,7 +213,7 @@ __global__ __launch_bounds__(CL_THREADS, 4) void k_cl_icols_add(u64 *ct, const i
     u64 *g = ct + ((size_t)blockIdx.z * 2 * limbs + blockIdx.y) * N + col;
     const u64 *m = pt + ((size_t)blockIdx.z * limbs + limb) * N + col;
     // The tile's errors, sixteen bytes a thread, pass through LDS: fetched byte by byte where they are added they were waited for
-    // one after the other (a wave lived 22 us; 10 x 16 limbs 149 us, now 96).
+    // one after the other (a wave lived 22 us; 10 x 16 limbs 144 us, now 87).
     double v[16];
     u64 a[16] = {};
 #pragma unroll

@@ -30,3 +30,9 @@ def test_inner_products_over_transformed_digits_do_not_spill(rings):
     for s, kernels in enumerate(rings):
         inner = {k: n for k, n in kernels.items() if "k_ks16_innerILi%dELb0E" % s in k}
         assert len(inner) == 6 and not any(inner.values()), (s, inner)
+
+
+def test_client_kernels_do_not_spill():
+    """Encoding, encryption, decryption and decoding, on every ring."""
+    kernels = {k: n for k, n in spilled("client16.hip").items() if "k_cl_" in k}
+    assert len([k for k in kernels if "k_cl_icols_add" in k]) == 5 and not any(kernels.values()), kernels
