@@ -14,8 +14,9 @@
 // w + 1 in {0, 1, 2}, and the sum of all operands, one per word (`word sums`), taken off again when the planes are
 // recombined.  An LDS-fed loop of the instruction alone: 19.8 ns each on signed bytes and weights, 19.3 with the weights shifted,
 // 17.0 with both (the same digits and signed weights: 19.8).  A step of the kernel: 0.312 us before, 0.276 with them.
-// Primes between (37 to 40 bits: five planes of 8 bits, seven of 7), primes above 2^50, and products of up to AM_POS7_MIN operands,
-// where an item is mostly its recombination, use 8-bit planes and signed weights (AM_FP8, AM_INT8).
+// Primes between (37 to 40 bits: five planes of 8 bits, seven of 7), primes above 2^50, products of up to AM_POS7_MIN operands,
+// where an item is mostly its recombination, and products of few outputs or few words, which the sum of the operands costs more than
+// it saves, use 8-bit planes and signed weights (AM_FP8, AM_INT8).
 //
 // The matrix pipe is signed: an 8-bit digit u is fed as u-128 (u xor 0x80), and 128 times the sum of the weights of output i
 // (`bias`) is added back to its plane when the planes are recombined.

@@ -87,10 +87,11 @@ static int build_plan(ensi_ctx *ctx, const int8_t *W, int s, int d, int m, int p
     std::vector<int32_t> bias;
     if (mfma_ok) {
         // Non-negative digits and weights cost the matrix cores least power: six planes of 7 bits and one of 8 hold 50 bits,
-        // four and one 36.  A prime of 37 to 40 bits would take seven planes that way and takes five of 8 bits instead; short sums
-        // do not gain.
+        // four and one 36.  A prime of 37 to 40 bits would take seven planes that way and takes five of 8 bits instead; short sums,
+        // few outputs and few words do not gain.
         p->planes = qbits <= 40 ? 5 : 7;  // qbits <= 56: never more than seven byte planes
-        const bool pos7 = n_v > AM_POS7_MIN && (qbits <= 36 || (qbits > 40 && qbits <= 50));
+        const long items = (long)2 * l1 * (ctx->N / 32) * (p->m_pad / 256);
+        const bool pos7 = n_v > AM_POS7_MIN && m > AM_POS7_MIN_OUT && items >= AM_POS7_MIN_ITEMS && (qbits <= 36 || (qbits > 40 && qbits <= 50));
         p->am_mode = qbits > 50 ? AM_INT8 : pos7 ? AM_POS7 : AM_FP8;
         wt.assign((size_t)p->m_pad * p->n_kpad, 0);
         bias.assign(p->m_pad, 0);

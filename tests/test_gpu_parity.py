@@ -215,16 +215,20 @@ def test_matmul_many_operands_and_wide_primes():
             p.close()
 
 
-@pytest.mark.parametrize("bits,operands,outputs", [(36, 513, 33), (36, 768, 257), (38, 769, 64), (50, 512, 33), (50, 513, 97), (50, 1100, 257), (54, 520, 40)])
-def test_signed_sums_by_digits(bits, operands, outputs):
-    """Every way the words of the signed sums are cut into digits (7 bits with shifted weights: more than 512 operands below
-    2^36 and 2^50; 8 bits: the others) on the smallest and largest residues, ragged operand and output counts, and with
-    the rescale between two layers applied on the way: plain integers, and the plain-ALU kernel on every word."""
+@pytest.mark.parametrize("bits,operands,outputs,L", [
+    (36, 513, 33, 3), (36, 768, 257, 3), (38, 769, 64, 3), (50, 512, 33, 3), (50, 513, 97, 3), (50, 1100, 257, 3), (54, 520, 40, 3),  # few words
+    (36, 513, 513, 7), (36, 800, 600, 7), (50, 513, 769, 7), (50, 1100, 513, 7),  # shifted weights
+    (36, 512, 513, 7), (50, 600, 512, 7), (50, 600, 600, 5), (38, 600, 600, 7)])  # one condition short of them
+def test_signed_sums_by_digits(bits, operands, outputs, L):
+    """Every way the words of the signed sums are cut into digits (7 bits with shifted weights: more than 512 operands and outputs
+    and at least 4096 pieces of 256 outputs x 32 words, below 2^36 and 2^50; 8 bits: the others) on the smallest and
+    largest residues, ragged operand and output counts, and with the rescale between two layers applied on the way: plain
+    integers, and the plain-ALU kernel on every word.  Only shifted weights need the sums of all operands."""
     import torch
 
     from paper_2509_09424_amd import binding
-    ctx = binding.Context(12, bits, 3, bits + 2, 1, 1, 20, seed=1)
-    L, N, q = 3, ctx.N, [int(x) for x in ctx.primes()[0]]
+    ctx = binding.Context(12, bits, L, bits + 2, 1, 1, 20, seed=1)
+    N, q = ctx.N, [int(x) for x in ctx.primes()[0]]
     W = np.random.default_rng(bits + operands).integers(-1, 2, (operands, outputs)).astype(np.int8)
     W[:, 0], W[:, 1] = 1, -1  # the largest sums of either sign
     x = torch.empty((operands, 2, L, N), dtype=torch.int64, device="cuda")
@@ -242,11 +246,16 @@ def test_signed_sums_by_digits(bits, operands, outputs):
         src, out = x.clone(), torch.full((outputs, 2, limbs, N), -1, dtype=torch.int64, device="cuda")
         h_in, h_out = ctx.ct_wrap(src.data_ptr(), operands, L, 1.0), ctx.ct_wrap(out.data_ptr(), outputs, limbs, 1.0)
         wt = ctx.weights_prepare(W, ctx.n_slots, operands, "zero", limbs)
+        ctx.profile_enable(True)
         if rescale:
             ctx.rescale_ternary_matmul_prepared(h_in, 2.0 ** -5, wt, h_out)
         else:
             ctx.ternary_matmul_prepared(None, h_in, wt, h_out)
         torch.cuda.synchronize()
+        items = 2 * limbs * (N // 32) * -(-outputs // 256)
+        shifted = mode == 2 and operands > 512 and outputs > 512 and items >= 4096 and (bits <= 36 or 40 < bits <= 50)
+        assert (ctx.profile_read().get("word_sums", (0, 0))[1] > 0) == shifted
+        ctx.profile_enable(False)
         for h in (wt, h_in, h_out):
             h.free()
         return out
