@@ -574,26 +574,30 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
                 }
             }
         };
-        piece(0, 0);
+        // (A wave whose outputs do not exist has nothing to recombine: 8 outputs of 32 to 512 operands 5 % of the kernel.  Leaving out
+        // the second block of 32 as well takes another 10 % there, and costs 1 to 4 % where all outputs exist.)
+        if (i0 < m) {
+            piece(0, 0);
 #pragma unroll
-        for (int mh = 0; mh < 4; mh++) {
-            const int ib = i0 + (mh >> 1) * 32, h = mh & 1;
+            for (int mh = 0; mh < 4; mh++) {
+                const int ib = i0 + (mh >> 1) * 32, h = mh & 1;
 #pragma unroll
-            for (int c = 0; c < 4; c++) *(ulonglong2 *)(o_lds + nl * AM_OROW + g * 64 + c * 16) = make_ulonglong2(res[c][0], res[c][1]);
-            wave_lds_fence();
-            ulonglong2 w[4];
+                for (int c = 0; c < 4; c++) *(ulonglong2 *)(o_lds + nl * AM_OROW + g * 64 + c * 16) = make_ulonglong2(res[c][0], res[c][1]);
+                wave_lds_fence();
+                ulonglong2 w[4];
 #pragma unroll
-            for (int k = 0; k < 4; k++) w[k] = *(const ulonglong2 *)(o_lds + (8 * k + (lane >> 3)) * AM_OROW + (lane & 7) * 16);
-            if (mh < 3) piece((mh + 1) >> 1, (mh + 1) & 1);
+                for (int k = 0; k < 4; k++) w[k] = *(const ulonglong2 *)(o_lds + (8 * k + (lane >> 3)) * AM_OROW + (lane & 7) * 16);
+                if (mh < 3) piece((mh + 1) >> 1, (mh + 1) & 1);
 #pragma unroll
-            for (int k = 0; k < 4; k++) {
-                const int row = 8 * k + (lane >> 3);
-                const ct_pair v = {w[k].x, w[k].y};
-                u64 *o = out + (size_t)(ib + row) * ct_words_out + off_out + 16 * h + (lane & 7) * 2;
-                if (whole) *(ct_pair *)o = v;
-                else if (ib + row < m) *(ct_pair *)o = v;
+                for (int k = 0; k < 4; k++) {
+                    const int row = 8 * k + (lane >> 3);
+                    const ct_pair v = {w[k].x, w[k].y};
+                    u64 *o = out + (size_t)(ib + row) * ct_words_out + off_out + 16 * h + (lane & 7) * 2;
+                    if (whole) *(ct_pair *)o = v;
+                    else if (ib + row < m) *(ct_pair *)o = v;
+                }
+                wave_lds_fence();
             }
-            wave_lds_fence();
         }
         stores_pending = whole;
         if (!whole) wait_vmcnt<0>();  // some stores were left out: start the next item from a known count
