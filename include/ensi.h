@@ -224,7 +224,8 @@ int ensi_set_accumulate_mode(ensi_ctx *ctx, int32_t mode);
 
 /* Diagnostics for the measurement of Alg. 1's contraction: runs a register-only
  * loop of the int8 matrix instruction the contraction is built from (one
- * workgroup of four waves per compute unit, no memory traffic) for about
+ * workgroup of four waves per compute unit, no memory traffic), on digits and
+ * weights like those of large products at the context's primes, for about
  * `seconds` (0 < seconds <= 2) and returns the operations per second the chip
  * sustains at the clock it holds under that load -- the ceiling the contraction
  * can be compared with besides the data-sheet peak.  ops_per_second: host

@@ -705,28 +705,33 @@ int launch_accumulate_mfma(ensi_ctx *ctx, const u64 *xbase, size_t xstride, int 
 }
 
 // ---------------------------------------------------------------- sustained rate of the matrix instruction
-// A register-only loop of V_MFMA_I32_32X32X32_I8, eight independent accumulator blocks per wave, one workgroup of four
-// waves per CU like the contraction: what the matrix pipes deliver at the clock the chip holds under that load.  No
-// memory is touched inside the loop; the operands come from `seed` words so that the compiler cannot fold the loop.
-__global__ __launch_bounds__(AM_THREADS) void k_matrix_rate(const int *seed, int iters, int *sink) {
-    v4i a, b;
+// A register-only loop of V_MFMA_I32_32X32X32_I8 on the digits and weights that the contraction has at the context's primes
+// (the clock the chip holds hangs on them), one accumulator block per plane, one workgroup of four waves per CU like the
+// contraction: what the matrix pipes deliver at the clock the chip holds under that load.  No memory is touched inside
+// the loop; the operands come from `seed` so that the compiler cannot fold the loop: [planes][1024] words of digits, then
+// RATE_WEIGHTS vectors of 1024 words of weights, taken in turn as an output's weights change from step to step.
+#define RATE_PLANES 7
+#define RATE_WEIGHTS 2
+__global__ __launch_bounds__(AM_THREADS) void k_matrix_rate(const v4i *seed, int iters, int *sink) {
+    v4i a[RATE_PLANES], b[RATE_WEIGHTS];
 #pragma unroll
-    for (int i = 0; i < 4; i++) {
-        a[i] = seed[(threadIdx.x * 4 + i) & 1023];
-        b[i] = seed[(threadIdx.x * 4 + i + 512) & 1023];
-    }
-    v16i d[8];
+    for (int p = 0; p < RATE_PLANES; p++) a[p] = seed[p * AM_THREADS + threadIdx.x];
 #pragma unroll
-    for (int j = 0; j < 8; j++)
+    for (int w = 0; w < RATE_WEIGHTS; w++) b[w] = seed[(RATE_PLANES + w) * AM_THREADS + threadIdx.x];
+    v16i d[RATE_PLANES];
 #pragma unroll
-        for (int r = 0; r < 16; r++) d[j][r] = 0;
+    for (int p = 0; p < RATE_PLANES; p++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) d[p][r] = 0;
     for (int it = 0; it < iters; it++) {
 #pragma unroll
-        for (int j = 0; j < 8; j++) d[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, d[j], 0, 0, 0);
+        for (int w = 0; w < RATE_WEIGHTS; w++)
+#pragma unroll
+            for (int p = 0; p < RATE_PLANES; p++) d[p] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[p], b[w], d[p], 0, 0, 0);
     }
     int t = 0;
 #pragma unroll
-    for (int j = 0; j < 8; j++) t += d[j][j];
+    for (int p = 0; p < RATE_PLANES; p++) t += d[p][p];
     if (t == 0x7fffffff) sink[0] = t;  // keeps the loop alive; never true for these operands in practice, harmless if it is
 }
 
@@ -737,25 +742,36 @@ int launch_matrix_rate(ensi_ctx *ctx, double seconds, double *ops_per_second, hi
         n_cu = hipGetDeviceProperties(&prop, ctx->device) == hipSuccess ? prop.multiProcessorCount : 256;
         if (n_cu < 8) n_cu = 8;
     }
-    std::vector<int> h(1024);
+    int qbits = 0;
+    for (int i = 0; i < ctx->L; i++) qbits = std::max(qbits, 64 - __builtin_clzll(ctx->primes[i]));
+    const bool pos7 = am_pos7_primes(qbits);
+    const size_t plane = (size_t)AM_THREADS * sizeof(v4i), n_digits = RATE_PLANES * plane, n_weights = RATE_WEIGHTS * plane;
+    std::vector<int8_t> h(n_digits + n_weights);
     u64 x = 0x9E3779B97F4A7C15ull;
-    for (int &v : h) {
+    for (size_t k = 0; k < h.size(); k++) {
         x = x * 6364136223846793005ull + 1442695040888963407ull;
-        v = (int)(x >> 32);
+        const u32 r = (u32)(x >> 32);
+        if (k < n_digits) {
+            h[k] = (int8_t)(pos7 && k / plane < RATE_PLANES - 1 ? r >> 25 : r >> 24);
+        } else {
+            const int w = r < 1288490189u ? -1 : r < 3006477107u ? 0 : 1;  // 3 : 4 : 3
+            h[k] = (int8_t)(pos7 ? w + 1 : w);
+        }
     }
-    int *d_seed = nullptr;
+    v4i *d_seed = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
-    hipError_t e = ctx->pool->alloc((void **)&d_seed, (h.size() + 1) * sizeof(int));
-    if (e == hipSuccess) e = hipMemcpy(d_seed, h.data(), h.size() * sizeof(int), hipMemcpyHostToDevice);
+    hipError_t e = ctx->pool->alloc((void **)&d_seed, h.size() + sizeof(int));
+    if (e == hipSuccess) e = hipMemcpy(d_seed, h.data(), h.size(), hipMemcpyHostToDevice);
+    int *sink = (int *)((char *)d_seed + h.size());
     if (e == hipSuccess) e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
     float ms = 0;
     // about 32 pipe cycles per instruction at roughly 1.6 GHz; the measured time is what counts
-    const int iters = (int)std::max(1000.0, seconds * 1.6e9 / (32.0 * 8.0));
+    const int iters = (int)std::max(1000.0, seconds * 1.6e9 / (32.0 * RATE_PLANES * RATE_WEIGHTS));
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_matrix_rate, dim3(n_cu), dim3(AM_THREADS), 0, st, d_seed, 1000, d_seed + 1024);
+        hipLaunchKernelGGL(k_matrix_rate, dim3(n_cu), dim3(AM_THREADS), 0, st, d_seed, 1000, sink);
         (void)hipEventRecord(e0, st);
-        hipLaunchKernelGGL(k_matrix_rate, dim3(n_cu), dim3(AM_THREADS), 0, st, d_seed, iters, d_seed + 1024);
+        hipLaunchKernelGGL(k_matrix_rate, dim3(n_cu), dim3(AM_THREADS), 0, st, d_seed, iters, sink);
         (void)hipEventRecord(e1, st);
         e = hipEventSynchronize(e1);
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
@@ -767,7 +783,7 @@ int launch_matrix_rate(ensi_ctx *ctx, double seconds, double *ops_per_second, hi
         ctx->err = "the matrix-rate probe failed";
         return ENSI_E_HIP;
     }
-    const double n_inst = (double)n_cu * 4 * (double)iters * 8;
+    const double n_inst = (double)n_cu * 4 * (double)iters * RATE_PLANES * RATE_WEIGHTS;
     *ops_per_second = n_inst * 2.0 * 32 * 32 * 32 / (ms * 1e-3);
     return ENSI_OK;
 }

@@ -91,7 +91,7 @@ static int build_plan(ensi_ctx *ctx, const int8_t *W, int s, int d, int m, int p
         // few outputs and few words do not gain.
         p->planes = qbits <= 40 ? 5 : 7;  // qbits <= 56: never more than seven byte planes
         const long items = (long)2 * l1 * (ctx->N / 32) * (p->m_pad / 256);
-        const bool pos7 = n_v > AM_POS7_MIN && m > AM_POS7_MIN_OUT && items >= AM_POS7_MIN_ITEMS && (qbits <= 36 || (qbits > 40 && qbits <= 50));
+        const bool pos7 = n_v > AM_POS7_MIN && m > AM_POS7_MIN_OUT && items >= AM_POS7_MIN_ITEMS && am_pos7_primes(qbits);
         p->am_mode = qbits > 50 ? AM_INT8 : pos7 ? AM_POS7 : AM_FP8;
         wt.assign((size_t)p->m_pad * p->n_kpad, 0);
         bias.assign(p->m_pad, 0);

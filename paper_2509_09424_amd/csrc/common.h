@@ -182,6 +182,9 @@ enum {
     AM_INT8 = 2,  // the same, recombined in 64-bit integers (primes of more than 50 bits)
 };
 
+// Primes whose words seven planes hold with a top one of 8 bits, or five (37 to 40 bits would take seven instead of five).
+inline bool am_pos7_primes(int qbits) { return qbits <= 36 || (qbits > 40 && qbits <= 50); }
+
 // Everything about one ternary_matmul that depends only on (W, s, d, m, placement).
 struct MatmulPlan {
     u64 hash;

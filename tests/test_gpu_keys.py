@@ -210,3 +210,16 @@ def test_matrix_rate_probe_reports_a_rate_below_the_data_sheet_peak():
             ctx.matrix_rate_probe(5.0)
     finally:
         ctx.close()
+
+
+def test_matrix_rate_probe_takes_the_digits_of_the_contexts_primes():
+    """Digits and weights that are never negative (primes of 41 to 50 bits) draw less power than signed ones (above 50 bits)."""
+    from paper_2509_09424_amd import binding
+    rates = []
+    for bits in (50, 54):
+        ctx = binding.Context(12, bits, 2, 60, 1, 1, 30, seed=1)
+        try:
+            rates.append(ctx.matrix_rate_probe(0.2))
+        finally:
+            ctx.close()
+    assert rates[0] > 1.03 * rates[1], rates
