@@ -403,22 +403,24 @@ extern "C" int ensi_gk_import(ensi_ctx *ctx, ensi_gk **gk_io, int32_t step, cons
     const u32 g = galois_element(ctx, step);
     LimbMap mext = make_map(ctx, ctx->L, true);
     u64 *key = nullptr;
-    DevBuf d_t;  // the key in position order (fused kernels only)
-    const size_t bytes = (size_t)beta * 2 * ext * N * 8;
-    if (ctx->pool->alloc((void **)&key, bytes) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation of a key failed");
-    if (ctx->ks16 && d_t.alloc(ctx, bytes) != hipSuccess) {
+    DevBuf d_t;  // one polynomial in position order (fused kernels only): beside a key of 84 MiB a second one may not find room
+    const size_t poly = (size_t)ext * N;
+    if (ctx->pool->alloc((void **)&key, (size_t)beta * 2 * poly * 8) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation of a key failed");
+    if (ctx->ks16 && d_t.alloc(ctx, poly * 8) != hipSuccess) {
         (void)hipFree(key);
         ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in gk_import");
     }
-    u64 *plain = ctx->ks16 ? d_t.as<u64>() : key;
-    int rc = upload_residues(ctx, plain, words, beta * 2 * ext, mext, "gk_import");
+    int rc = upload_residues(ctx, key, words, beta * 2 * ext, mext, "gk_import");
     if (rc) {
         (void)hipFree(key);
         return rc;
     }
-    launch_ntt(ctx, plain, beta * 2 * ext, mext, false, nullptr);
-    launch_to_mont(ctx, plain, beta * 2 * ext, mext, nullptr);
-    if (ctx->ks16) launch_ks16_key_format(ctx, plain, key, beta * 2 * ext, g, nullptr);
+    launch_ntt(ctx, key, beta * 2 * ext, mext, false, nullptr);
+    launch_to_mont(ctx, key, beta * 2 * ext, mext, nullptr);
+    for (int p = 0; p < beta * 2 && ctx->ks16; p++) {
+        (void)hipMemcpyAsync(d_t.p, key + p * poly, poly * 8, hipMemcpyDeviceToDevice, nullptr);
+        launch_ks16_key_format(ctx, d_t.as<u64>(), key + p * poly, ext, g, nullptr);
+    }
     if (hipStreamSynchronize(nullptr) != hipSuccess || hipGetLastError() != hipSuccess) {
         (void)hipFree(key);
         ENSI_FAIL(ctx, ENSI_E_HIP, "kernel failure in gk_import");

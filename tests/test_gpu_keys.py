@@ -104,6 +104,39 @@ def test_server_context_with_imported_public_keys_only(params):
         ctx.close()
 
 
+def test_key_import_needs_little_more_memory_than_the_key():
+    """A set of keys fills the card; the last one must not need the room of two.  The free memory is watched while a key of 24 MiB
+    is imported."""
+    import threading
+
+    import torch
+    p = Pair((16, 50, 6, 60, 2, 2, 40))
+    try:
+        _, g_gk = p.galois_keys([3])
+        words = p.ctx.gk_export(g_gk, 3)
+        torch.cuda.synchronize()
+        device = torch.cuda.current_device()
+        before, least, done = torch.cuda.mem_get_info(device)[0], [], threading.Event()
+
+        def watch():
+            while not done.is_set():
+                least.append(torch.cuda.mem_get_info(device)[0])
+        watcher = threading.Thread(target=watch)
+        watcher.start()
+        while not least:
+            pass
+        imported = p.ctx.gk_import(3, words)
+        done.set()
+        watcher.join()
+        used, key = before - min(least), words.nbytes
+        assert len(least) > 20 and key <= used + (2 << 20) and used < key + key // 2, (used, key, len(least))
+        assert np.array_equal(p.ctx.gk_export(imported, 3), words)
+        imported.free()
+        g_gk.free()
+    finally:
+        p.close()
+
+
 def test_null_randomness_comes_from_the_operating_system_when_the_seed_is_zero():
     """seed = 0: secret keys of two key generations differ, are ternary with all three values present, and the key
     pair works; a non-zero seed reproduces the same keys run after run (test mode)."""
