@@ -270,6 +270,56 @@ def test_signed_sums_by_digits(bits, operands, outputs, L):
         ctx.close()
 
 
+@pytest.mark.parametrize("bits,operands,kernel", [(50, 8192, "accumulate_mfma"), (50, 8193, "accumulate"), (36, 32768, "accumulate_mfma"),
+                                                  (36, 32769, "accumulate")])
+def test_signed_sums_at_the_most_operands(bits, operands, kernel):
+    """The most operands that the matrix cores are given: at 50 bits the sum of all operands of a word comes just under 2^63, at 36
+    bits a sum of one digit reaches 2^23.  Largest residues throughout, with a row of weights +1 and one of -1, so that every
+    bound of the recombination is met; one operand more goes to the plain-ALU kernel.  Plain integers."""
+    import torch
+
+    from paper_2509_09424_amd import binding
+    L, outputs = 6, 513
+    ctx = binding.Context(12, bits, L, bits + 2, 1, 1, 20, seed=1)
+    try:
+        N, q = ctx.N, [int(x) for x in ctx.primes()[0]]
+        W = np.random.default_rng(operands).integers(-1, 2, (operands, outputs)).astype(np.int8)
+        W[:, 0], W[:, 1], W[:, 2] = 1, -1, 0
+        x = torch.empty((operands, 2, L, N), dtype=torch.int64, device="cuda")
+        for i in range(L):
+            x[:, :, i] = q[i] - 1
+            x[:, :, i, 1::4] = 0
+            x[:, :, i, 2::4].random_(0, q[i], generator=torch.Generator(device="cuda").manual_seed(i))
+            x[:, :, i, 3::4] = (q[i] - 1) // 2
+        out = torch.full((outputs, 2, L, N), -1, dtype=torch.int64, device="cuda")
+        h_in, h_out = ctx.ct_wrap(x.data_ptr(), operands, L, 1.0), ctx.ct_wrap(out.data_ptr(), outputs, L, 1.0)
+        wt = ctx.weights_prepare(W, ctx.n_slots, operands, "zero", L)
+        ctx.profile_enable(True)
+        ctx.ternary_matmul_prepared(None, h_in, wt, h_out)
+        torch.cuda.synchronize()
+        ran = {k for k, v in ctx.profile_read().items() if v[1]}
+        assert kernel in ran and ("word_sums" in ran) == (kernel == "accumulate_mfma"), ran
+        # every word: three of four are the same for all operands; the others are taken as halves of 25 bits, whose sums a
+        # product of doubles has exactly
+        total = torch.from_numpy(W.sum(0, dtype=np.int64)).cuda()
+        Wd = torch.from_numpy(W).cuda().double()
+        for i in range(L):
+            for k, value in ((0, q[i] - 1), (1, 0), (3, (q[i] - 1) // 2)):
+                want = torch.tensor([int(t) * value % q[i] for t in total.tolist()], device="cuda")
+                assert torch.equal(out[:, :, i, k::4], want[:, None, None].expand(outputs, 2, N // 4)), (i, k)
+            r = x[:, :, i, 2::4].reshape(operands, -1)
+            low, high = (Wd.T @ (r & 0x1ffffff).double()).long(), (Wd.T @ (r >> 25).double()).long()
+            want = high % q[i]
+            for _ in range(5):  # times 2^25
+                want = want * 32 % q[i]
+            want = (want + low) % q[i]
+            assert torch.equal(out[:, :, i, 2::4].reshape(outputs, -1), want), i
+        for h in (wt, h_in, h_out):
+            h.free()
+    finally:
+        ctx.close()
+
+
 def test_mul_scalar_rescale_bit_exact_and_two_layer(small4):
     p = small4
     rng = np.random.default_rng(7)
