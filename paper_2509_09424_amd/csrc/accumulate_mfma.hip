@@ -269,10 +269,11 @@ __global__ __launch_bounds__(AM_THREADS) void k_byte_planes(const u64 *xbase, u3
 // the centred representative of limb l1), and the planes of the l1 remaining limbs written.  fc: [5][l1+1]
 // doubles: k mod q_i, that / q_i, q_l^-1 mod q_i, that / q_i, 1 / q_i.  grid (cw, nk / 4, 2): a block keeps
 // the centred last-limb residues of its 32 coefficients x 128 operands in registers and walks the limbs
-// (4 steps per block keep the register count low enough for four blocks per CU).
+// (4 steps per block keep the register count low enough for four blocks per CU, or for three where all digits are of 8 bits: two
+// registers more than four blocks have, 512 operands at 15 limbs 2.88 against 3.0 ms with those two spilled).
 #define AM_RS_STEPS 4
 template <int PLANES, bool POS7>
-__global__ __launch_bounds__(AM_THREADS, 4) void k_byte_planes_rescale(const u64 *xbase, u32 xstride, int n_v, int nk, int N, int l1,
+__global__ __launch_bounds__(AM_THREADS, POS7 ? 4 : 3) void k_byte_planes_rescale(const u64 *xbase, u32 xstride, int n_v, int nk, int N, int l1,
                                                                     int limb_stride_in, int c0, int cw, char *xp, const PrimeConst *pc,
                                                                     const double *fc, u64 *part) {
     __shared__ u32 stage[2][PLANES * 256];

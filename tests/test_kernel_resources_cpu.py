@@ -32,6 +32,12 @@ def test_inner_products_over_transformed_digits_do_not_spill(rings):
         assert len(inner) == 6 and not any(inner.values()), (s, inner)
 
 
+def test_plane_splits_do_not_spill():
+    """The splits of operands into planes, with and without the rescale, for every kind of digits, and the contraction."""
+    kernels = spilled("accumulate_mfma.hip")
+    assert len([k for k in kernels if "k_byte_planes_rescale" in k]) == 4 and not any(kernels.values()), kernels
+
+
 def test_client_kernels_do_not_spill():
     """Encoding, encryption, decryption and decoding, on every ring."""
     kernels = {k: n for k, n in spilled("client16.hip").items() if "k_cl_" in k}
