@@ -85,6 +85,7 @@ static int build_plan(ensi_ctx *ctx, const int8_t *W, int s, int d, int m, int p
     std::vector<u32> masks((size_t)tiles * std::max(n_v, 1) * 2, 0);
     std::vector<int8_t> wt;
     std::vector<int32_t> bias;
+    int8_t wt_zero = 0;
     if (mfma_ok) {
         // Non-negative digits and weights cost the matrix cores least power: six planes of 7 bits and one of 8 hold 50 bits,
         // four and one 36.  A prime of 37 to 40 bits would take seven planes that way and takes five of 8 bits instead; short sums,
@@ -93,8 +94,10 @@ static int build_plan(ensi_ctx *ctx, const int8_t *W, int s, int d, int m, int p
         const long items = (long)2 * l1 * (ctx->N / 32) * (p->m_pad / 256);
         const bool pos7 = n_v > AM_POS7_MIN && m > AM_POS7_MIN_OUT && items >= AM_POS7_MIN_ITEMS && am_pos7_primes(qbits);
         p->am_mode = qbits > 50 ? AM_INT8 : pos7 ? AM_POS7 : AM_FP8;
-        wt.assign((size_t)p->m_pad * p->n_kpad, 0);
-        bias.assign(p->m_pad, 0);
+        // AM_POS7: every weight plus one, also of the operands that fill the last step (zero words, whose top digit enters the bias)
+        wt_zero = pos7 ? 1 : 0;
+        wt.assign((size_t)p->m_pad * p->n_kpad, wt_zero);
+        bias.assign(p->m_pad, pos7 ? p->n_kpad : 0);
     }
     // the place of weight (v, i) in fragment order: [output tile of 256][step of 32 operands][wave][block of 32][lane][16 bytes],
     // lane = 32*(operand half of the step) + output within the block
@@ -103,11 +106,6 @@ static int build_plan(ensi_ctx *ctx, const int8_t *W, int s, int d, int m, int p
                             ((v % 32) / 16) * 32 + i % 32;
         return wt[cell * 16 + v % 16];
     };
-    if (mfma_ok && p->am_mode == AM_POS7)
-        for (int i = 0; i < m; i++) {
-            for (int v = 0; v < n_v; v += 16) memset(&wt_at(v, i), 1, std::min(16, n_v - v));
-            bias[i] = n_v;
-        }
     for (int j = 0; j < d; j++) {
         const int G = j / c_tot, b = j % c_tot;
         const int8_t *row = W + (size_t)j * m;
@@ -119,7 +117,7 @@ static int build_plan(ensi_ctx *ctx, const int8_t *W, int s, int d, int m, int p
             const int v = p->vid[(size_t)G * c_tot + rho];
             masks[((size_t)(i / 32) * n_v + v) * 2 + (row[i] > 0 ? 0 : 1)] |= 1u << (i % 32);
             if (mfma_ok) {
-                wt_at(v, i) += row[i];
+                wt_at(v, i) = (int8_t)(wt_zero + row[i]);
                 bias[i] += row[i];
             }
         }
