@@ -138,7 +138,7 @@ extern "C" int ensi_keygen(ensi_ctx *ctx, const int8_t *s, const int8_t *e, uint
     launch_ntt(ctx, d_a.as<u64>(), L, mq, false, st);
     launch_small_to_rns(ctx, d_small.as<int8_t>(), 1, mq, d_e.as<u64>(), st);
     launch_ntt(ctx, d_e.as<u64>(), L, mq, false, st);
-    launch_key_assemble(ctx, pk_b, d_a.as<u64>(), sk->d_s_hat, d_e.as<u64>(), nullptr, nullptr, mq, st);
+    launch_key_assemble(ctx, pk_b, d_a.as<u64>(), sk->d_s_hat, d_e.as<u64>(), nullptr, nullptr, mq, true, st);
     (void)hipMemcpyAsync(pk_a, d_a.p, (size_t)L * N * 8, hipMemcpyDeviceToDevice, st);
     launch_to_mont(ctx, pk_a, L, mq, st);
     if (hipStreamSynchronize(st) != hipSuccess || hipGetLastError() != hipSuccess) {
@@ -160,22 +160,30 @@ extern "C" void ensi_pk_free(ensi_pk *pk) {
     delete pk;
 }
 
-// Scratch of the switching-key generation (one secret, any number of keys).
+// Scratch of the switching-key generation (one secret, any number of keys), in one allocation: seven cost 0.6 of the 7.4 ms that eight
+// keys of 12 limbs take on the largest ring.  (Not kept between calls: it holds the secret.)
 struct KeygenScratch {
-    DevBuf d_s, d_target, d_e8, d_e, d_fac, d_s8;
-    DevBuf d_pair;  // one digit of a key on its way into the stored format (fused kernels only)
+    DevBuf all;
+    u64 *s, *target, *e, *fac, *pair;  // pair: one digit of a key on its way into the stored format (fused kernels only)
+    int8_t *e8, *s8;
 };
 static int keygen_scratch(ensi_ctx *ctx, const ensi_sk *sk, KeygenScratch &k, hipStream_t st) {
-    const int N = ctx->N, ext = ctx->L + ctx->K;
-    if (k.d_s.alloc(ctx, (size_t)ext * N * 8) != hipSuccess || k.d_target.alloc(ctx, (size_t)ext * N * 8) != hipSuccess || k.d_e8.alloc(ctx, N) != hipSuccess ||
-        k.d_e.alloc(ctx, (size_t)ext * N * 8) != hipSuccess || k.d_fac.alloc(ctx, (size_t)ext * 8) != hipSuccess || k.d_s8.alloc(ctx, N) != hipSuccess ||
-        (ctx->ks16 && k.d_pair.alloc(ctx, (size_t)2 * ext * N * 8) != hipSuccess))
+    const size_t N = ctx->N, ext = ctx->L + ctx->K, poly = ext * N, small = (N + 255) / 256 * 32;  // in words; every part 256-byte aligned
+    const size_t parts = poly + (32 - poly % 32) % 32;
+    if (k.all.alloc(ctx, (parts * (ctx->ks16 ? 5 : 3) + ENSI_MAX_EXT + 2 * small) * 8) != hipSuccess)
         ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in key generation");
-    (void)hipMemcpy(k.d_s8.p, sk->s.data(), N, hipMemcpyHostToDevice);
-    launch_small_to_rns(ctx, k.d_s8.as<int8_t>(), 1, make_map(ctx, ctx->L, true), k.d_s.as<u64>(), st);  // coefficient form of s
+    k.s = k.all.as<u64>();
+    k.target = k.s + parts;
+    k.e = k.target + parts;
+    k.fac = k.e + parts;
+    k.e8 = (int8_t *)(k.fac + ENSI_MAX_EXT);
+    k.s8 = k.e8 + small * 8;
+    k.pair = (u64 *)(k.s8 + small * 8);
+    (void)hipMemcpy(k.s8, sk->s.data(), N, hipMemcpyHostToDevice);
+    launch_small_to_rns(ctx, k.s8, 1, make_map(ctx, ctx->L, true), k.s, st);  // coefficient form of s
     return ENSI_OK;
 }
-// key <- hybrid key-switching key from the secret in k.d_target (transform domain, ordinary residues) to s:
+// key <- hybrid key-switching key from the secret in k.target (transform domain, ordinary residues) to s:
 // per digit j, (b_j, a_j) with b_j = -a_j s + e_j + [P]_{q_i} target on the limbs of digit j.  e: host
 // int8[beta][N] or NULL; a_j is the uniform stream stream_base | j.  g: the element the key is for.
 static int make_switch_key(ensi_ctx *ctx, const ensi_sk *sk, KeygenScratch &k, const int8_t *e, uint64_t seed_a, u64 stream_base, u32 g, u64 *key,
@@ -185,13 +193,13 @@ static int make_switch_key(ensi_ctx *ctx, const ensi_sk *sk, KeygenScratch &k, c
     LimbMap mext = make_map(ctx, L, true);
     std::vector<int8_t> ev(N);
     for (int j = 0; j < beta; j++) {
-        u64 *pair = key + (size_t)(j * 2) * ext * N, *kb = ctx->ks16 ? k.d_pair.as<u64>() : pair, *ka = kb + (size_t)ext * N;
+        u64 *pair = key + (size_t)(j * 2) * ext * N, *kb = ctx->ks16 ? k.pair : pair, *ka = kb + (size_t)ext * N;
         if (e) memcpy(ev.data(), e + (size_t)j * N, N);
         else if (sample_error(ctx, ev.data(), N)) return ENSI_E_BADARG;
-        (void)hipMemcpyAsync(k.d_e8.p, ev.data(), N, hipMemcpyHostToDevice, st);
+        (void)hipMemcpyAsync(k.e8, ev.data(), N, hipMemcpyHostToDevice, st);
         (void)hipStreamSynchronize(st);
-        launch_small_to_rns(ctx, k.d_e8.as<int8_t>(), 1, mext, k.d_e.as<u64>(), st);
-        launch_ntt(ctx, k.d_e.as<u64>(), ext, mext, false, st);
+        launch_small_to_rns(ctx, k.e8, 1, mext, k.e, st);
+        launch_ntt(ctx, k.e, ext, mext, false, st);
         launch_uniform(ctx, ka, mext, seed_a, stream_base | (u64)j, st);
         launch_ntt(ctx, ka, ext, mext, false, st);
         std::vector<u64> fac(ext, 0);
@@ -201,11 +209,11 @@ static int make_switch_key(ensi_ctx *ctx, const ensi_sk *sk, KeygenScratch &k, c
             for (int b = 0; b < K; b++) P = hm_mulmod(P, ctx->primes[L + b] % q, q);
             fac[i] = hm_to_mont(P, q);
         }
-        (void)hipMemcpyAsync(k.d_fac.p, fac.data(), ext * 8, hipMemcpyHostToDevice, st);
+        (void)hipMemcpyAsync(k.fac, fac.data(), ext * 8, hipMemcpyHostToDevice, st);
         (void)hipStreamSynchronize(st);
-        launch_key_assemble(ctx, kb, ka, sk->d_s_hat, k.d_e.as<u64>(), k.d_target.as<u64>(), k.d_fac.as<u64>(), mext, st);
-        launch_to_mont(ctx, ka, ext, mext, st);
+        launch_key_assemble(ctx, kb, ka, sk->d_s_hat, k.e, k.target, k.fac, mext, !ctx->ks16, st);
         if (ctx->ks16) launch_ks16_key_format(ctx, kb, pair, 2 * ext, g, st);
+        else launch_to_mont(ctx, ka, ext, mext, st);
     }
     return ENSI_OK;
 }
@@ -235,8 +243,8 @@ extern "C" int ensi_galois_keygen(ensi_ctx *ctx, const ensi_sk *sk, const int32_
         }
         gk->keys[g] = key;
         // phi_g(s), transform domain
-        launch_automorphism_coef(ctx, k.d_target.as<u64>(), k.d_s.as<u64>(), mext, inv_mod_2n(g, N), st);
-        launch_ntt(ctx, k.d_target.as<u64>(), ext, mext, false, st);
+        launch_automorphism_coef(ctx, k.target, k.s, mext, inv_mod_2n(g, N), st);
+        launch_ntt(ctx, k.target, ext, mext, false, st);
         if ((rc = make_switch_key(ctx, sk, k, e ? e + (size_t)t * beta * N : nullptr, seed_a, ((u64)2 << 56) | ((u64)g << 8), g, key, st))) {
             ensi_gk_free(gk);
             return rc;
@@ -273,8 +281,8 @@ extern "C" int ensi_relin_keygen(ensi_ctx *ctx, const ensi_sk *sk, const int8_t 
     }
     gk->keys[1u] = key;
     // s^2, transform domain: NTT(s) (.) NTT(s), the second factor in Montgomery form
-    launch_ntt(ctx, k.d_s.as<u64>(), ext, mext, false, st);
-    launch_mul_mont(ctx, k.d_target.as<u64>(), k.d_s.as<u64>(), sk->d_s_hat, ext, mext, st);
+    launch_ntt(ctx, k.s, ext, mext, false, st);
+    launch_mul_mont(ctx, k.target, k.s, sk->d_s_hat, ext, mext, st);
     if ((rc = make_switch_key(ctx, sk, k, e, seed_a, (u64)3 << 56, 1u, key, st))) {
         ensi_gk_free(gk);
         return rc;
@@ -403,10 +411,12 @@ extern "C" int ensi_gk_import(ensi_ctx *ctx, ensi_gk **gk_io, int32_t step, cons
     const u32 g = galois_element(ctx, step);
     LimbMap mext = make_map(ctx, ctx->L, true);
     u64 *key = nullptr;
-    DevBuf d_t;  // one polynomial in position order (fused kernels only): beside a key of 84 MiB a second one may not find room
+    // polynomials in position order (fused kernels only), 16 MiB of them: beside a key of 84 MiB a second one may not find room
+    KeptBuf d_t;
     const size_t poly = (size_t)ext * N;
+    const int chunk = (int)std::min<size_t>(beta * 2, std::max<size_t>(((size_t)16 << 20) / (poly * 8), 1));
     if (ctx->pool->alloc((void **)&key, (size_t)beta * 2 * poly * 8) != hipSuccess) ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation of a key failed");
-    if (ctx->ks16 && d_t.alloc(ctx, poly * 8) != hipSuccess) {
+    if (ctx->ks16 && d_t.take(ctx, chunk * poly * 8) != hipSuccess) {
         (void)hipFree(key);
         ENSI_FAIL(ctx, ENSI_E_NOMEM, "device allocation failed in gk_import");
     }
@@ -416,10 +426,11 @@ extern "C" int ensi_gk_import(ensi_ctx *ctx, ensi_gk **gk_io, int32_t step, cons
         return rc;
     }
     launch_ntt(ctx, key, beta * 2 * ext, mext, false, nullptr);
-    launch_to_mont(ctx, key, beta * 2 * ext, mext, nullptr);
-    for (int p = 0; p < beta * 2 && ctx->ks16; p++) {
-        (void)hipMemcpyAsync(d_t.p, key + p * poly, poly * 8, hipMemcpyDeviceToDevice, nullptr);
-        launch_ks16_key_format(ctx, d_t.as<u64>(), key + p * poly, ext, g, nullptr);
+    if (!ctx->ks16) launch_to_mont(ctx, key, beta * 2 * ext, mext, nullptr);
+    for (int p = 0; p < beta * 2 && ctx->ks16; p += chunk) {
+        const int n = std::min(chunk, beta * 2 - p);
+        (void)hipMemcpyAsync(d_t.p, key + p * poly, n * poly * 8, hipMemcpyDeviceToDevice, nullptr);
+        launch_ks16_key_format(ctx, (const u64 *)d_t.p, key + p * poly, n * ext, g, nullptr);
     }
     if (hipStreamSynchronize(nullptr) != hipSuccess || hipGetLastError() != hipSuccess) {
         (void)hipFree(key);

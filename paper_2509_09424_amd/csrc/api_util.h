@@ -18,6 +18,23 @@ struct DevBuf {
     T *as() { return (T *)p; }
 };
 
+// The same for memory that the next call of its kind wants again: kept by the pool in between (allocating and freeing 16 MiB takes
+// 0.4 ms).  Taking it waits for the device where a kept block serves, giving it back waits for nothing.
+struct KeptBuf {
+    DevPool *pool = nullptr;
+    void *p = nullptr;
+    size_t bytes = 0;
+    KeptBuf() {}
+    KeptBuf(const KeptBuf &) = delete;
+    ~KeptBuf() {
+        if (p) pool->give(p, bytes);
+    }
+    hipError_t take(ensi_ctx *ctx, size_t n) {
+        pool = ctx->pool.get();
+        return pool->take(&p, n, &bytes);
+    }
+};
+
 template <class T>
 inline hipError_t upload(ensi_ctx *ctx, T **d, const std::vector<T> &h) {
     hipError_t e = ctx->pool->alloc((void **)d, std::max<size_t>(h.size() * sizeof(T), 8));

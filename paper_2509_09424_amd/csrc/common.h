@@ -396,7 +396,7 @@ void launch_ntt16(ensi_ctx *ctx, u64 *data, int n_inst, const LimbMap &map, bool
 void launch_ntt16_gather(ensi_ctx *ctx, u64 *data, const MmOperand *ops, int n_ops, int l1, hipStream_t st);  // N >= 2^12
 
 // fused key switch (keyswitch16.hip)
-// rows (limb r % (L + K)) of the key of element g: Montgomery residues -> the stored format, and that -> residues; not in place
+// rows (limb r % (L + K)) of the key of element g: residues -> the stored format, and that -> residues; not in place
 void launch_ks16_key_format(ensi_ctx *ctx, const u64 *in, u64 *out, int n_rows, u32 g, hipStream_t st);
 void launch_ks16_key_plain(ensi_ctx *ctx, const u64 *in, u64 *out, int n_rows, u32 g, hipStream_t st);
 // raises n_ct ciphertexts: dig [n_ct][beta*ext + l1][N] receives the digits of c1 and P*c0, transformed (rows) or after their
@@ -467,9 +467,9 @@ void launch_from_mont(ensi_ctx *ctx, u64 *data, int n_rows, const LimbMap &map, 
 void launch_count_noncanonical(ensi_ctx *ctx, const u64 *data, int n_rows, const LimbMap &map, unsigned int *d_bad, hipStream_t st);
 // d_sums[c] += wrap-around sum of the active limb words of ciphertext c
 void launch_ct_checksum(ensi_ctx *ctx, const u64 *ct, int n, int l1, int limb_stride, u64 *d_sums, hipStream_t st);
-// b = -a*s + e (+ factor[row] * sg), all transform domain; s_mont in Montgomery form; writes b in Montgomery form
+// b = -a*s + e (+ factor[row] * sg), all transform domain; s_mont in Montgomery form; mont: writes b in Montgomery form
 void launch_key_assemble(ensi_ctx *ctx, u64 *b_out, const u64 *a, const u64 *s_mont, const u64 *e, const u64 *sg,
-                         const u64 *d_factor, const LimbMap &map, hipStream_t st);
+                         const u64 *d_factor, const LimbMap &map, bool mont, hipStream_t st);
 void launch_automorphism_coef(ensi_ctx *ctx, u64 *out, const u64 *in, const LimbMap &map, u32 g_inv, hipStream_t st);
 // plaintext y of the batch holds its n_slots values in slots [slot0 + y*slot_step, ...+n_slots), zeros elsewhere
 // (allocates its transform workspace, waits for the stream and frees it again; so does launch_decode)

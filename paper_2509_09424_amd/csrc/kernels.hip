@@ -477,9 +477,9 @@ void launch_ct_checksum(ensi_ctx *ctx, const u64 *ct, int n, int l1, int limb_st
 }
 
 // b = -a*s + e + factor[row]*sg  (transform domain); s_mont is in Montgomery form;
-// b is written in Montgomery form.  One row per limb of map.
+// mont: b is written in Montgomery form.  One row per limb of map.
 __global__ __launch_bounds__(EW_THREADS) void k_key_assemble(u64 *b_out, const u64 *a, const u64 *s_mont, const u64 *e, const u64 *sg,
-                                                             const u64 *factor, LimbMap map, const PrimeConst *pc, int N) {
+                                                             const u64 *factor, LimbMap map, const PrimeConst *pc, int N, bool mont) {
     const int idx = blockIdx.x * EW_THREADS + threadIdx.x;
     if (idx >= N) return;
     const int row = blockIdx.y;
@@ -491,12 +491,12 @@ __global__ __launch_bounds__(EW_THREADS) void k_key_assemble(u64 *b_out, const u
         // factor is stored in Montgomery form: mont_mul(sg, factor*R) = sg*factor
         b = add_mod(b, mont_mul(sg[o], factor[row], p.q, p.qneg_inv), p.q);
     }
-    b_out[o] = mont_mul(b, p.r2, p.q, p.qneg_inv);
+    b_out[o] = mont ? mont_mul(b, p.r2, p.q, p.qneg_inv) : b;
 }
 void launch_key_assemble(ensi_ctx *ctx, u64 *b_out, const u64 *a, const u64 *s_mont, const u64 *e, const u64 *sg,
-                         const u64 *d_factor, const LimbMap &map, hipStream_t st) {
+                         const u64 *d_factor, const LimbMap &map, bool mont, hipStream_t st) {
     dim3 grid((ctx->N + EW_THREADS - 1) / EW_THREADS, map.n);
-    hipLaunchKernelGGL(k_key_assemble, grid, dim3(EW_THREADS), 0, st, b_out, a, s_mont, e, sg, d_factor, map, ctx->d_pc, ctx->N);
+    hipLaunchKernelGGL(k_key_assemble, grid, dim3(EW_THREADS), 0, st, b_out, a, s_mont, e, sg, d_factor, map, ctx->d_pc, ctx->N, mont);
 }
 
 // Coefficient-form automorphism: out[k] = +-in[k * g^{-1} mod 2N].

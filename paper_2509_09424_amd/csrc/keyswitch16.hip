@@ -9,8 +9,8 @@ template <int S>
 void ks16_switch(ensi_ctx *ctx, const Ks16Const &kc, const RotDesc *d_desc, int n_rot, u64 *u, int limb_stride_out, bool raw, hipStream_t st, int members);
 
 // ---------------------------------------------------------------- key format
-// Montgomery residues in position order -> register order at the source positions of the element g (RowMap), limbs of primes
-// below 2^50 as doubles in [0,p), PRIME_WIDE limbs as split centred residues.  Row y of the two arrays is limb y % ext_full.
+// Residues in position order -> register order at the source positions of the element g (RowMap), limbs of primes below 2^50
+// as doubles in [0,p), PRIME_WIDE limbs as split centred residues, others as Montgomery residues.  Row y of the two arrays is limb y % ext_full.
 // A wave writes the 1024 words of four source rows; it reads the four rows they map to.  grid (N/1024, rows)
 template <int S>
 __global__ __launch_bounds__(64) void k_ks16_key_format(const u64 *in, u64 *out, const PrimeConst *pcs, int ext_full, u32 g, u32 g_inv) {
@@ -23,13 +23,13 @@ __global__ __launch_bounds__(64) void k_ks16_key_format(const u64 *in, u64 *out,
 #pragma unroll
     for (int i = 0; i < 16; i++) {
         u64 w = src[brev8((brev8(16 * j + i) - carry) * g_inv & 255)];
-        acc128 m = {w, 0};
-        const u64 k = mont_reduce(m, pc.q, pc.qneg_inv);
         if (pc.kind == PRIME_FP) {
-            w = (u64)__double_as_longlong((double)k);
+            w = (u64)__double_as_longlong((double)w);
         } else if (pc.kind == PRIME_WIDE) {
-            const int64_t c = (k > pc.q / 2 ? (int64_t)k - (int64_t)pc.q : (int64_t)k) + (1 << 29);
+            const int64_t c = (w > pc.q / 2 ? (int64_t)w - (int64_t)pc.q : (int64_t)w) + (1 << 29);
             w = ((u64)(u32)(u64)(c >> 30) << 32) | (u32)(((u32)c & 0x3fffffffu) - (1u << 29));
+        } else {
+            w = mont_mul(w, pc.r2, pc.q, pc.qneg_inv);
         }
         dst[64 * i + lane] = w;
     }

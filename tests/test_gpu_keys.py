@@ -105,12 +105,12 @@ def test_server_context_with_imported_public_keys_only(params):
 
 
 def test_key_import_needs_little_more_memory_than_the_key():
-    """A set of keys fills the card; the last one must not need the room of two.  The free memory is watched while a key of 24 MiB
+    """A set of keys fills the card; the last one must not need the room of two.  The free memory is watched while a key of 60 MiB
     is imported."""
     import threading
 
     import torch
-    p = Pair((16, 50, 6, 60, 2, 2, 40))
+    p = Pair((16, 50, 10, 60, 2, 2, 40))
     try:
         _, g_gk = p.galois_keys([3])
         words = p.ctx.gk_export(g_gk, 3)
