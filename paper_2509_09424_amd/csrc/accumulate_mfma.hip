@@ -35,7 +35,7 @@
 // contraction's inner loop.  The plane array of a whole operand array can exceed the
 // memory left, so the host works through the coefficients in slices (a slice holds a
 // range of 32-coefficient tiles of every limb of both polynomials).  The split can apply
-// the scalar-multiply + rescale step between two layers on the fly (k_byte_planes<.., true>):
+// the scalar-multiply + rescale step between two layers on the fly (k_byte_planes_rescale):
 // the rescaled operands then never exist as 64-bit words in memory.
 //
 // k_accumulate_mfma.  A work item is 256 outputs x 32 consecutive words; inside it each
@@ -118,9 +118,10 @@ __device__ __forceinline__ u64 reduce_signed(int64_t t, u64 q, double q_inv) {
 // per output and limb as a double in [0, q).  |S_p| <= 2^22 for up to 32768 operands, so planes are first paired
 // in 32-bit integers (S_p + 2^8 S_(p+1) < 2^31) and the pairs combined into lo + 2^32 hi with |lo| < 2^48 and
 // |hi| < 2^38.1 -- every product by a power of two and every sum below 2^53 is exact in a double.  One reduction:
-// k = rint((lo + B + 2^32 hi) / q) from two rounded products (off by far less than one half except within 2^-30 of
-// a tie), then 2^32 hi - k q, an integer below 2^52 in magnitude that the fused multiply-add returns exactly (as a multiple
-// of 2^-32: hi - k (q 2^-32)), plus lo + B: a representative within (1/2 + 2^-30) q of zero, shifted into [0, q).
+// k = rint((lo + B + 2^32 hi) / q), whose argument is off by its three roundings, 3 2^-53 |k| at most: below 2^-9 for the smallest
+// primes (2^13 < q, |k| < 2^42), 2^-26 at 41 bits and 32768 operands.  Then 2^32 hi - k q, an integer below 2^52 in magnitude
+// that the fused multiply-add returns exactly (as a multiple of 2^-32: hi - k (q 2^-32)), plus lo + B: a representative within
+// (1/2 + 2^-9) q of zero -- below q in magnitude is all that is needed -- shifted into [0, q).
 // AM_POS7: the same with 2^7 for 2^8.  Only the top plane has an offset; B is that offset 128 2^(7 (PLANES - 1)) (sum of the
 // weights) mod q less the word sum mod q, |B| < q.  |S_p| <= 2^23, so a pair stays below 2^31, lo below 2^45, hi below 2^38.
 struct AmModulus {
@@ -176,8 +177,8 @@ __device__ __forceinline__ void digits(u64 w, u32 *d) {
 // Slice-local word tile: nt_local = pl * cw + ctile, pl = poly * l1 + limb, ctile = coefficient tile - c0.
 // Thread (k4 = tid / 32, ln = tid % 32) handles operands 4*k4 .. 4*k4+3 of a step, word ln: its four
 // words give one dword (4 operand bytes) of every plane.  A plane tile is staged in LDS and written out as
-// whole 16-byte lane entries.  Bytes are stored as u - 128 (u xor 0x80); operands beyond n_v are zero
-// words (their weights are zero).
+// whole 16-byte lane entries.  Digits of 8 bits are stored as u - 128 (u xor 0x80), those of 7 as they are; operands beyond n_v
+// are zero words.
 // Row of the plane tile that holds word ln: accumulator register r of a lane is row 8*(r/4) + 4*(lane/32) + r%4 and holds
 // word 16*(r/8) + 8*(lane/32) + r%8, so that the two lanes of an output hold 16 consecutive words in eight registers.
 __device__ __forceinline__ int plane_row(int ln) { return ((ln >> 4) * 2 + ((ln >> 2) & 1)) * 8 + ((ln >> 3) & 1) * 4 + (ln & 3); }

@@ -160,7 +160,7 @@ extern "C" void ensi_pk_free(ensi_pk *pk) {
     delete pk;
 }
 
-// Scratch of the switching-key generation (one secret, any number of keys), in one allocation: seven cost 0.6 of the 7.4 ms that eight
+// Scratch of the switching-key generation (one secret, any number of keys), in one allocation: seven cost 0.9 of the 7.4 ms that eight
 // keys of 12 limbs take on the largest ring.  (Not kept between calls: it holds the secret.)
 struct KeygenScratch {
     DevBuf all;

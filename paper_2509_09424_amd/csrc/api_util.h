@@ -19,7 +19,7 @@ struct DevBuf {
 };
 
 // The same for memory that the next call of its kind wants again: kept by the pool in between (allocating and freeing 16 MiB takes
-// 0.4 ms).  Taking it waits for the device where a kept block serves, giving it back waits for nothing.
+// 0.3 ms).  Taking it waits for the device where a kept block serves, giving it back waits for nothing.
 struct KeptBuf {
     DevPool *pool = nullptr;
     void *p = nullptr;
@@ -97,7 +97,11 @@ enum RaiseUse { RAISE_ONE, RAISE_SHARED };
 // A row pass of its own takes the digits through memory twice more; one in the inner product costs arithmetic that the reads of keys
 // partly hide, and the digits of neighbouring rotations come from L2.  Two rotations a raise: 96 ciphertexts
 // under Alg. 2 at 16 + 4 limbs 14.0 -> 12.6 ms; one: 64 columns of scores 90.7 -> 86.6; three: nothing in it (86.2, and 1152 rotations
-// of the 2^14 ring in 7.26 against 7.24).
+// of the 2^14 ring in 7.26 against 7.24).  On every ring and for every kind of special primes: inner product and row pass of two
+// rotations a raise, in column form against rows, 0.98 and 1.22 ms (just below 2^60), 1.21 and 1.32 (others above 2^50), 1.07 and 1.20
+// (below 2^50) on 2^16; 0.245 and 0.288, 0.303 and 0.325, 0.273 and 0.282 on 2^14; 0.117 and 0.131, 0.145 and 0.158, 0.128 and 0.123
+// (the one that loses) on 2^13.  The row pass runs over everything that was raised, so it is the average that counts: one
+// of 32 inputs with 63 rotations, the others with none, 0.137 against 0.116 + 0.048 on 2^14.
 // Rotations in groups (members > 1: their inner products are added before one inverse pass) read transformed digits only.
 #define RAISE_ONE_MAX 2  // rotations per raise
 inline RaiseUse raise_use(size_t n_rot, size_t n_raised, int members = 1) {
