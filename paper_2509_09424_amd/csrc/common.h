@@ -171,10 +171,10 @@ struct RotDesc {
 // Digits and weights of the signed sums on the matrix cores (accumulate_mfma.hip).  AM_POS7 needs less power and more work per
 // output word: us per item of 256 x 32 words, 1536 to 4096 operands 18.5 to 40.8 against 19.2 to 44.8, 512 operands 9.9 against 9.8.
 // It also sums the operands of every word, once for all output tiles, in one launch more: whole products of 544 to 2560 operands
-// took, with these digits against the others, -5 to +1 % with six output tiles, -5 to +3 % with three or four, -5 to +4 % with two,
-// -2 to +8 % with one, and -3 to +15 % below 4096 items (2 and 3 limbs of the 2^12 ring), where the chip is not full for long.
+// took, with these digits against the others, -5 to +1 % with six output tiles, -5 to +3 % with three or four, -5 to +2 % with two full
+// ones, -2 to +4 % with 300 outputs, -2 to +8 % with one tile, and -3 to +15 % below 4096 items (2 and 3 limbs of the 2^12 ring), where the chip is not full for long.
 #define AM_POS7_MIN 512         // operands up to which the other digits are taken,
-#define AM_POS7_MIN_OUT 512     // outputs,
+#define AM_POS7_MIN_OUT 384     // outputs,
 #define AM_POS7_MIN_ITEMS 4096  // and items of 256 outputs x 32 words below which they are
 enum {
     AM_POS7 = 0,  // planes of 7 bits and a top one of 8, weights 0, 1, 2; recombined in double precision (primes below 2^36 or 2^50)

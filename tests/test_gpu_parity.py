@@ -217,10 +217,10 @@ def test_matmul_many_operands_and_wide_primes():
 
 @pytest.mark.parametrize("bits,operands,outputs,L", [
     (36, 513, 33, 3), (36, 768, 257, 3), (38, 769, 64, 3), (50, 512, 33, 3), (50, 513, 97, 3), (50, 1100, 257, 3), (54, 520, 40, 3),  # few words
-    (36, 513, 513, 7), (36, 800, 600, 7), (50, 513, 769, 7), (50, 1100, 513, 7),  # shifted weights
-    (36, 512, 513, 7), (50, 600, 512, 7), (50, 600, 600, 5), (38, 600, 600, 7)])  # one condition short of them
+    (36, 513, 513, 7), (36, 800, 600, 7), (50, 513, 769, 7), (50, 1100, 513, 7), (50, 700, 385, 8),  # shifted weights
+    (36, 512, 513, 7), (50, 600, 384, 8), (50, 600, 512, 7), (50, 600, 600, 5), (38, 600, 600, 7)])  # one condition short of them
 def test_signed_sums_by_digits(bits, operands, outputs, L):
-    """Every way the words of the signed sums are cut into digits (7 bits with shifted weights: more than 512 operands and outputs
+    """Every way the words of the signed sums are cut into digits (7 bits with shifted weights: more than 512 operands and 384 outputs
     and at least 4096 pieces of 256 outputs x 32 words, below 2^36 and 2^50; 8 bits: the others) on the smallest and
     largest residues, ragged operand and output counts, and with the rescale between two layers applied on the way: plain
     integers, and the plain-ALU kernel on every word.  Only shifted weights need the sums of all operands."""
@@ -253,7 +253,7 @@ def test_signed_sums_by_digits(bits, operands, outputs, L):
             ctx.ternary_matmul_prepared(None, h_in, wt, h_out)
         torch.cuda.synchronize()
         items = 2 * limbs * (N // 32) * -(-outputs // 256)
-        shifted = mode == 2 and operands > 512 and outputs > 512 and items >= 4096 and (bits <= 36 or 40 < bits <= 50)
+        shifted = mode == 2 and operands > 512 and outputs > 384 and items >= 4096 and (bits <= 36 or 40 < bits <= 50)
         assert (ctx.profile_read().get("word_sums", (0, 0))[1] > 0) == shifted
         ctx.profile_enable(False)
         for h in (wt, h_in, h_out):
