@@ -576,9 +576,11 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
                 }
             }
         };
-        // (A wave whose outputs do not exist has nothing to recombine: 8 outputs of 32 to 512 operands 5 % of the kernel.  Leaving out
-        // the second block of 32 as well takes another 10 % there, and costs 1 to 4 % where all outputs exist.)
-        if (i0 < m) {
+        // A wave whose outputs do not exist has nothing to recombine, and in products of one output tile does not: 8 outputs of 32 to 512
+        // operands 5 % of the kernel, 40 outputs 2 %.  (With more tiles it runs in step with the others: 825 outputs of 160
+        // operands took 3 % longer where the last tile's three idle waves skipped.  Leaving out the second block of 32 as well takes
+        // another 10 % at 8 outputs, and costs 1 to 4 % where all outputs exist.)
+        if (n_tiles_m > 1 || i0 < m) {
             piece(0, 0);
 #pragma unroll
             for (int mh = 0; mh < 4; mh++) {
