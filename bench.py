@@ -774,7 +774,7 @@ def run_leg(name, steps, warmup, separate_rescale=False, with_ntt=False):
         dom, roof = roofline_for(w, prof)
         if roof["bound"] == "mfma":
             # the data-sheet peak assumes 2.4 GHz; under matrix load the chip holds a lower clock.  A register-only loop of
-            # the same matrix instruction, run right after the timed steps, gives the rate the pipes sustain on this
+            # the same matrix instruction on digits and weights of the same kind, run right after the timed steps, gives the rate the pipes sustain on this
             # machine: the second ceiling the contraction is compared with.
             sustained = r.ctx.matrix_rate_probe(0.4) / 1e12
             roof["sustained_peak_measured"] = round(sustained, 1)
