@@ -12,6 +12,7 @@
 
 #include "common.h"
 #include "hostmath.h"
+#include "ntt16_core.h"
 
 #include "api_util.h"
 
@@ -207,24 +208,25 @@ extern "C" int ensi_ctx_create(const ensi_params *prm, ensi_ctx **out) {
         for (int k = 0; k < N; k++) {
             u32 rk = 0;
             for (int b = 0; b < ctx->log_n; b++) rk |= ((k >> b) & 1u) << (ctx->log_n - 1 - b);
+            const u32 at = ctx->log_n >= 12 && k >= N / 16 ? row_twiddle_place((u32)k, (u32)N) : (u32)k;
             if (fp) {
                 // fp64 path: the table holds the twiddle and twiddle/q as doubles
                 const double w = (double)pw[rk], wi = (double)ipw[rk];
                 const double wq = w / (double)q, wiq = wi / (double)q;
-                memcpy(&t[k], &w, 8);
-                memcpy(&t[N + k], &wq, 8);
-                memcpy(&t[2 * N + k], &wi, 8);
-                memcpy(&t[3 * N + k], &wiq, 8);
+                memcpy(&t[at], &w, 8);
+                memcpy(&t[N + at], &wq, 8);
+                memcpy(&t[2 * N + at], &wi, 8);
+                memcpy(&t[3 * N + at], &wiq, 8);
             } else if (wide) {
-                t[k] = hm_wide_pack(pw[rk], q);
-                t[N + k] = hm_wide_pack(hm_mulmod(pw[rk], (u64)1 << 32, q), q);
-                t[2 * N + k] = hm_wide_pack(ipw[rk], q);
-                t[3 * N + k] = hm_wide_pack(hm_mulmod(ipw[rk], (u64)1 << 32, q), q);
+                t[at] = hm_wide_pack(pw[rk], q);
+                t[N + at] = hm_wide_pack(hm_mulmod(pw[rk], (u64)1 << 32, q), q);
+                t[2 * N + at] = hm_wide_pack(ipw[rk], q);
+                t[3 * N + at] = hm_wide_pack(hm_mulmod(ipw[rk], (u64)1 << 32, q), q);
             } else {
-                t[k] = pw[rk];
-                t[N + k] = hm_shoup(pw[rk], q);
-                t[2 * N + k] = ipw[rk];
-                t[3 * N + k] = hm_shoup(ipw[rk], q);
+                t[at] = pw[rk];
+                t[N + at] = hm_shoup(pw[rk], q);
+                t[2 * N + at] = ipw[rk];
+                t[3 * N + at] = hm_shoup(ipw[rk], q);
             }
         }
     }

@@ -163,12 +163,12 @@ __global__ __launch_bounds__(64, 2) void k_cl_rows_key(const u64 *in, const u64 
     row_table_to_lds(tw1[0], twf, twf + N, R::ROWS + r, rho, j);
     row_table_to_lds(tw1[1], twi, twi + N, R::ROWS + r, rho, j);
     TwRegs tw2;
-    tw2.load(twf, twf + N, (R::ROWS + r) * 16u + j);
+    tw2.load(twf, twf + N, N, r, j);
     wave_lds_fence();
     row_fwd(ar, v, tw1[0] + rho * 16, tw2, lds, rho, j);
 #pragma unroll
     for (int i = 0; i < 16; i++) v[i] = ar.mid(v[i]);
-    tw2.load(twi, twi + N, (R::ROWS + r) * 16u + j);
+    tw2.load(twi, twi + N, N, r, j);
 #pragma unroll
     for (int p = 0; p < POLYS; p++) {
         const u64 *kp = key + ((size_t)p * key_limbs + limb) * N + (size_t)r * 256 + 16 * j;

@@ -10,7 +10,7 @@ void ks16_switch(ensi_ctx *ctx, const Ks16Const &kc, const RotDesc *d_desc, int 
 
 // ---------------------------------------------------------------- key format
 // Residues in position order -> register order at the source positions of the element g (RowMap), limbs of primes below 2^50
-// as doubles in [0,p), PRIME_WIDE limbs as split centred residues, others as Montgomery residues.  Row y of the two arrays is limb y % ext_full.
+// as centred doubles, PRIME_WIDE limbs as split centred residues, others as Montgomery residues.  Row y of the two arrays is limb y % ext_full.
 // A wave writes the 1024 words of four source rows; it reads the four rows they map to.  grid (N/1024, rows)
 template <int S>
 __global__ __launch_bounds__(64) void k_ks16_key_format(const u64 *in, u64 *out, const PrimeConst *pcs, int ext_full, u32 g, u32 g_inv) {
@@ -24,14 +24,14 @@ __global__ __launch_bounds__(64) void k_ks16_key_format(const u64 *in, u64 *out,
     for (int i = 0; i < 16; i++) {
         u64 w = src[brev8((brev8(16 * j + i) - carry) * g_inv & 255)];
         if (pc.kind == PRIME_FP) {
-            w = (u64)__double_as_longlong((double)w);
+            w = (u64)__double_as_longlong(w > pc.q / 2 ? (double)w - (double)pc.q : (double)w);
         } else if (pc.kind == PRIME_WIDE) {
             const int64_t c = (w > pc.q / 2 ? (int64_t)w - (int64_t)pc.q : (int64_t)w) + (1 << 29);
             w = ((u64)(u32)(u64)(c >> 30) << 32) | (u32)(((u32)c & 0x3fffffffu) - (1u << 29));
         } else {
             w = mont_mul(w, pc.r2, pc.q, pc.qneg_inv);
         }
-        dst[64 * i + lane] = w;
+        dst[reg_pos(i, lane)] = w;
     }
 }
 // The way back, to ordinary residues in position order.
@@ -45,9 +45,10 @@ __global__ __launch_bounds__(64) void k_ks16_key_plain(const u64 *in, u64 *out, 
     u64 *dst = out + (size_t)blockIdx.y * Ring<S>::N + (size_t)r * 256;
 #pragma unroll
     for (int i = 0; i < 16; i++) {
-        u64 w = src[64 * i + lane];
+        u64 w = src[reg_pos(i, lane)];
         if (pc.kind == PRIME_FP) {
-            w = (u64)__longlong_as_double((long long)w);
+            const double v = __longlong_as_double((long long)w);
+            w = (u64)(v < 0.0 ? v + (double)pc.q : v);
         } else if (pc.kind == PRIME_WIDE) {
             const int64_t v = (int64_t)(int32_t)(u32)(w >> 32) * (1 << 30) + (int32_t)(u32)w;
             w = v < 0 ? (u64)(v + (int64_t)pc.q) : (u64)v;

@@ -22,13 +22,13 @@
 //
 // Number formats between the kernels (workspaces only, never visible outside the library), by
 // the prime's kind:
-//   PRIME_FP    doubles (exact integers, |x| <= p/2); key: doubles in [0,p)
+//   PRIME_FP    doubles (exact integers, |x| <= p/2); key: the same
 //   PRIME_WIDE  signed 64-bit integers, |x| <= q/2 + 8 (2^60 - q); transformed digits and the key as two
 //               int32 halves high * 2^30 + low, so that the inner product is multiply-adds of 32-bit words
 //   PRIME_INT   canonical 64-bit residues; key: Montgomery residues
 // Transformed digits and the key are stored in the order a wave holds them in the row pass ("register order"): within
-// the four rows of a wave, value i of lane (rho, j) -- position 16 j + i of row rho -- at i * 64 + lane, so that reading
-// them needs no exchange and is contiguous.  The key of element g lies at the positions its words meet before the automorphism:
+// the four rows of a wave, value i of lane (rho, j) -- position 16 j + i of row rho -- at reg_pos(i, lane), so that reading
+// them needs no exchange and is contiguous, two values to a load.  The key of element g lies at the positions its words meet before the automorphism:
 // phi_g^-1 of it is stored.
 // All results that leave the last kernel are canonical residues and equal, word for word, what the unfused sequence
 // (ModUp, transform, inner product, inverse transform, ModDown, + phi_g(c0)) gives.
@@ -248,7 +248,7 @@ __device__ __forceinline__ void frows_body(u64 *g, size_t ct_stride, int n_here,
     const u64 *tws = tw + Ring<S>::N;
     row_table_to_lds(tw1, tw, tws, base, rho, j);
     TwRegs tw2;
-    tw2.load(tw, tws, base * 16u + j);
+    tw2.load(tw, tws, Ring<S>::N, r0 + rho, j);
     const ulonglong2 *tab = tw1 + rho * 16;
     typename A::T v[16], nv[16];
     {
@@ -268,9 +268,9 @@ __device__ __forceinline__ void frows_body(u64 *g, size_t ct_stride, int n_here,
             for (int i = 0; i < 16; i++) nv[i] = gt[rho * 256 + j + 16 * i];
         }
         row_fwd(ar, v, tab, tw2, lds, rho, j);
-        u64 *go = g + (size_t)c * ct_stride + lane;
+        u64 *go = g + (size_t)c * ct_stride;
 #pragma unroll
-        for (int i = 0; i < 16; i++) go[64 * i] = ar.store_ws_fwd(v[i]);
+        for (int i = 0; i < 16; i += 2) *(word_pair *)(go + reg_pos(i, lane)) = word_pair{ar.store_ws_fwd(v[i]), ar.store_ws_fwd(v[i + 1])};
     }
 }
 
@@ -296,47 +296,77 @@ __global__ __launch_bounds__(64, 2) void k_ks16_frows(Ks16Const kc, const PrimeC
 }
 
 // ---------------------------------------- automorphism + key inner product + inverse row pass
-// Sums of products of transformed digit words x with key words k, both as 64-bit words in their stored formats.
+// Sums of products of transformed digit words x with key words k, both as 64-bit words in their stored formats.  mac: onto a sum
+// that is reduced after each product.  Sum: the products of a whole inner product (at most 8 digits) are added first and
+// reduced once; it holds two or three words where the other holds one.
 template <class A>
 struct Inner;
 template <>
 struct Inner<ArithFp> {
-    struct Acc {
-        double s;
+    static __device__ __forceinline__ void mac(const ArithFp &ar, double &s, u64 x, u64 k) { s += ar.mulmod_np(as_f64(x), as_f64(k)); }
+    // h - 3 2^101 is the sum of the products rounded to multiples of 2^50, l what that rounding left: |x|, |k| <= p/2 < 2^49, so
+    // eight products stay below 2^101 and h between 2^102 and 2^103; what one addition leaves is within 2^49, an integer that the second
+    // multiply-add returns exactly, and |l| stays below 2^53 with P * c0 and the reduced h added.  Four instructions a product
+    // instead of seven.
+    struct Sum {
+        double h = 0x1.8p102, l = 0.0;
+        __device__ __forceinline__ void mac(u64 x, u64 k) {
+            const double n = fma(as_f64(x), as_f64(k), h);
+            l += fma(as_f64(x), as_f64(k), h - n);
+            h = n;
+        }
+        __device__ __forceinline__ void add(u64 x) { l += as_f64(x); }
+        __device__ __forceinline__ double reduced(const ArithFp &ar) const {
+            const double t = h - 0x1.8p102;
+            return ar.mid(fma(-rint(t * ar.pinv), ar.p, t) + l);
+        }
     };
-    static __device__ __forceinline__ void zero(Acc &a) { a.s = 0.0; }
-    static __device__ __forceinline__ void mac(const ArithFp &ar, Acc &a, u64 x, u64 k) { a.s += ar.mulmod_np(as_f64(x), as_f64(k)); }
-    static __device__ __forceinline__ void add(Acc &a, u64 x) { a.s += as_f64(x); }
-    // a rotation adds up to nine terms below 0.7 p to what those before it left: reduced after each, the sums stay exact integers
-    static __device__ __forceinline__ void fold(const ArithFp &ar, Acc &a) { a.s = ar.mid(a.s); }
+    static __device__ __forceinline__ double plus(const ArithFp &ar, double a, double b) { return ar.mid(a + b); }
+    static __device__ __forceinline__ void add(double &s, u64 x) { s += as_f64(x); }
+    static __device__ __forceinline__ void fold(const ArithFp &ar, double &s) { s = ar.mid(s); }
 };
 // x = xh 2^30 + xl, k = kh 2^30 + kl: xh kh 2^60 is taken apart into dwords and folded by 2^60 = d, 2^62 = 4 d, like the
-// middle sum m 2^30.  Every half is at most 2^29 (a little more for the high ones): within 6 q before the last fold.
+// middle sum m 2^30.  Every half is at most 2^29 (a little more for the high ones): within 6 q before the last fold, 6.6 q for the
+// sum of eight products.
 template <>
 struct Inner<ArithWide> {
-    struct Acc {
-        int64_t s;
-    };
-    static __device__ __forceinline__ void zero(Acc &a) { a.s = 0; }
-    static __device__ __forceinline__ void mac(const ArithWide &ar, Acc &a, u64 x, u64 k) {
-        const int xl = (int)(u32)x, xh = (int)(x >> 32), kl = (int)(u32)k, kh = (int)(k >> 32);
-        const int64_t h = mul_i(xh, kh);
-        const int64_t m = mad_i((int)(h >> 32), ar.d4, mad_i(xh, kl, mul_i(xl, kh)));
-        const int64_t l = mad_uu((u32)h, (u32)ar.d, mad_i(xl, kl, a.s));
-        a.s = ar.mid(mad_pow2<30>((u32)m, mad_i((int)(m >> 32), ar.d4, l)));
+    static __device__ __forceinline__ int64_t folded(const ArithWide &ar, int64_t h, int64_t m, int64_t l) {
+        m = mad_i((int)(h >> 32), ar.d4, m);
+        l = mad_uu((u32)h, (u32)ar.d, l);
+        return ar.mid(mad_pow2<30>((u32)m, mad_i((int)(m >> 32), ar.d4, l)));
     }
-    static __device__ __forceinline__ void add(Acc &, u64) {}
-    static __device__ __forceinline__ void fold(const ArithWide &, Acc &) {}
+    static __device__ __forceinline__ void mac(const ArithWide &ar, int64_t &s, u64 x, u64 k) {
+        const int xl = (int)(u32)x, xh = (int)(x >> 32), kl = (int)(u32)k, kh = (int)(k >> 32);
+        s = folded(ar, mul_i(xh, kh), mad_i(xh, kl, mul_i(xl, kh)), mad_i(xl, kl, s));
+    }
+    struct Sum {
+        int64_t h = 0, m = 0, l = 0;
+        __device__ __forceinline__ void mac(u64 x, u64 k) {
+            const int xl = (int)(u32)x, xh = (int)(x >> 32), kl = (int)(u32)k, kh = (int)(k >> 32);
+            h = mad_i(xh, kh, h);
+            m = mad_i(xh, kl, mad_i(xl, kh, m));
+            l = mad_i(xl, kl, l);
+        }
+        __device__ __forceinline__ void add(u64) {}
+        __device__ __forceinline__ int64_t reduced(const ArithWide &ar) const { return folded(ar, h, m, l); }
+    };
+    static __device__ __forceinline__ int64_t plus(const ArithWide &ar, int64_t a, int64_t b) { return ar.mid(a + b); }
+    static __device__ __forceinline__ void add(int64_t &, u64) {}
+    static __device__ __forceinline__ void fold(const ArithWide &, int64_t &) {}
 };
 template <>
 struct Inner<ArithInt> {
-    struct Acc {
-        u64 s;
+    static __device__ __forceinline__ void mac(const ArithInt &ar, u64 &s, u64 x, u64 k) { s = add_mod(s, mont_mul(x, k, ar.q, ar.qneg_inv), ar.q); }
+    // eight Montgomery products of residues below 2^61 and the sum of their high words fit 128 bits: one reduction
+    struct Sum {
+        acc128 s = {0, 0};
+        __device__ __forceinline__ void mac(u64 x, u64 k) { mac128(s, x, k); }
+        __device__ __forceinline__ void add(u64) {}
+        __device__ __forceinline__ u64 reduced(const ArithInt &ar) const { return mont_reduce(s, ar.q, ar.qneg_inv); }
     };
-    static __device__ __forceinline__ void zero(Acc &a) { a.s = 0; }
-    static __device__ __forceinline__ void mac(const ArithInt &ar, Acc &a, u64 x, u64 k) { a.s = add_mod(a.s, mont_mul(x, k, ar.q, ar.qneg_inv), ar.q); }
-    static __device__ __forceinline__ void add(Acc &, u64) {}
-    static __device__ __forceinline__ void fold(const ArithInt &, Acc &) {}
+    static __device__ __forceinline__ u64 plus(const ArithInt &ar, u64 a, u64 b) { return add_mod(a, b, ar.q); }
+    static __device__ __forceinline__ void add(u64 &, u64) {}
+    static __device__ __forceinline__ void fold(const ArithInt &, u64 &) {}
 };
 
 // Four rows of one limb of both accumulators, by one wave, and their inverse row passes.  Digits and keys are multiplied where they
@@ -345,7 +375,23 @@ struct Inner<ArithInt> {
 //   GROUP = false: one rotation; the wave takes source rows 4 tile .. 4 tile + 3 and writes the rows they map to.
 //   GROUP = true:  `members` rotations whose sums are added: the wave takes output rows 4 tile .. 4 tile + 3.
 // RAW (not GROUP): the digits have only been through their column pass; their row passes are run here.
-template <int S, bool RAW, bool GROUP, class A>
+//
+// What bounds the form that reads transformed digits (one rotation of the 2^16 ring at 16 + 4 limbs: 13 us, 14.6 before): the 21 MB of results
+// that it writes (a quarter of the time by themselves) and the words that come through a CU's L1, 106 KB a tile and rotation.  Those
+// come 16 bytes to a lane (8 bytes a lane reach 18 TB/s from L2, 16 bytes 34), keys once for the four rotations of a block (rotations that
+// use one key are neighbours), twiddles in the order they are read in.  An accumulator to each wave, four waves to a SIMD, takes 18 %
+// longer, as every digit is then read twice; two and three waves to a SIMD are within 4 %.
+template <bool RAW>
+struct InnerBlock {
+    static constexpr u32 WAVES = RAW ? 2 : 4;  // rotations of a block, one to a wave
+};
+// Values of a row that one pass over the digits adds up, and waves to a SIMD, by the arithmetic of the special primes: what its registers
+// allow without spilling.
+template <bool GROUP, class W>
+struct InnerShape {
+    static constexpr int VALUES = std::is_same<W, ArithInt>::value ? 2 : 4, PER_SIMD = !GROUP && std::is_same<W, ArithWide>::value ? 3 : 2;
+};
+template <int S, bool RAW, bool GROUP, int C, class A>
 __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *desc, const PrimeConst &pc, const u64 *tw_all, u64 *u, int prime, int e,
                                            int members, u32 grp, u32 tile, u64 *lds, ulonglong2 *tw1) {
     typedef Ring<S> R;
@@ -353,30 +399,30 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
     typedef Inner<A> I;
     typedef typename A::T T;
     constexpr size_t N = R::N;
-    const int lane = threadIdx.x, rho = lane >> 4, j = lane & 15;
+    const int lane = threadIdx.x & 63, rho = lane >> 4, j = lane & 15;
     const int l1 = kc.l1, ext = l1 + kc.K, beta = kc.beta;
     const size_t kstride = (size_t)(kc.L + kc.K) * N;  // words between b_j and a_j, and half the distance between digits
     const u64 *tw = tw_all + (size_t)prime * 4 * N;
     const ulonglong2 *tab = tw1 + rho * 16;
     A ar;
     ar.init(pc);
-    typename I::Acc a0[16], a1[16];
+    T a0[16], a1[16];
     u32 r = tile * 4 + rho, g = 1, carry = 0;
     // Moves a sum from the positions that the element g reads (carry: of this row) to those that the next rotation's element reads,
     // or, with 1 and 0, to the output's own order.  The rotations of a group add to one pair of sums in this way; a
     // second pair in the output's order took 14 to 58 registers more than there are (fills of 384 and 768 ciphertexts, 15 limbs: 48.7
     // and 79.1 ms of inner products with it, 46.0 and 75.0 so).
-    auto move = [&](typename I::Acc *a, u32 to_g_inv, u32 to_carry) {
+    auto move = [&](T *a, u32 to_g_inv, u32 to_carry) {
         T *l = (T *)lds;
         // value i of lane j, position p = 16 j + i with brev8(p) = brev4(j) + 16 brev4(i), is at brev8(h (brev8(p) - to_carry) + carry)
         const u32 h = g * to_g_inv, first = h * ((__brev((u32)j) >> 28) - to_carry) + carry;
 #pragma unroll
-        for (int i = 0; i < 16; i++) l[rpad(rho * 256 + 16 * j + i)] = a[i].s;
+        for (int i = 0; i < 16; i++) l[rpad(rho * 256 + 16 * j + i)] = a[i];
         wave_lds_fence();
 #pragma unroll
         for (int i = 0; i < 16; i++) {
             const u32 brev4_i = (i & 1) * 8 + (i & 2) * 2 + (i & 4) / 2 + (i & 8) / 8;
-            a[i].s = l[rpad(rho * 256 + brev8(first + h * (16 * brev4_i)))];
+            a[i] = l[rpad(rho * 256 + brev8(first + h * (16 * brev4_i)))];
         }
         wave_lds_fence();
     };
@@ -387,24 +433,21 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
         if (!GROUP) r = M::row(d.g_inv * M::exponent(rs));
         const u32 to_carry = M::carry(r, d.g);
         // byte offsets of value 0 from the wave's tile of digits and keys
-        const u32 reg_off = ((GROUP ? (rs >> 2) * 1024 + (rs & 3) * 16 : rho * 16) + j) * 8, row_off = (rho * 256 + j) * 8;
+        const u32 reg_off = ((GROUP ? (rs >> 2) * 1024 : 0) + reg_pos(0, (GROUP ? rs & 3 : rho) * 16 + j)) * 8, row_off = (rho * 256 + j) * 8;
         const u64 *src = d.digits + (size_t)e * N + (GROUP ? 0 : tile * 1024), *key = d.key + (size_t)prime * N + (GROUP ? 0 : tile * 1024);
         auto ld = [](const u64 *base, u32 off) { return *(decltype(as_global(base)))((decltype(as_global((const char *)base)))as_global(base) + off); };
-        if (!GROUP || mem == 0) {
-#pragma unroll
-            for (int i = 0; i < 16; i++) {
-                I::zero(a0[i]);
-                I::zero(a1[i]);
-            }
-        }
         const bool with_c0 = e < l1;  // P * c0 follows the digits
+        auto ld_pair = [](const u64 *base, u32 off) { return *(__attribute__((address_space(1))) const word_pair *)((decltype(as_global((const char *)base)))as_global(base) + off); };
         if (RAW) {
             TwRegs tw2;
             row_table_to_lds(tw1, tw, tw + N, R::ROWS + rs, rho, j);
-            tw2.load(tw, tw + N, (R::ROWS + rs) * 16u + j);
+            tw2.load(tw, tw + N, N, rs, j);
             u64 nv[16];
 #pragma unroll
-            for (int i = 0; i < 16; i++) nv[i] = ld(src + 16 * i, row_off);
+            for (int i = 0; i < 16; i++) {
+                a0[i] = a1[i] = 0;
+                nv[i] = ld(src + 16 * i, row_off);
+            }
             wave_lds_fence();
             const int nd = with_c0 ? beta + 1 : beta;
 #pragma unroll 1
@@ -424,9 +467,10 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
                     for (int h = 0; h < 16; h += 8) {
                         u64 k0[8], k1[8];
 #pragma unroll
-                        for (int i = 0; i < 8; i++) {
-                            k0[i] = ld(key + 64 * (h + i), reg_off);
-                            k1[i] = ld(key + kstride + 64 * (h + i), reg_off);
+                        for (int i = 0; i < 8; i += 2) {
+                            const word_pair p0 = ld_pair(key + reg_pos(h + i, 0), reg_off), p1 = ld_pair(key + kstride + reg_pos(h + i, 0), reg_off);
+                            k0[i] = p0[0], k0[i + 1] = p0[1];
+                            k1[i] = p1[0], k1[i + 1] = p1[1];
                         }
 #pragma unroll
                         for (int i = 0; i < 8; i++) {
@@ -442,59 +486,84 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
                 }
             }
         } else {
-            // C values at a time, the next C requested before the current ones are multiplied.
-            constexpr int C = 8;
-            u64 x[2][C], k0[2][C], k1[2][C];
-            auto fetch = [&](int i0, bool keys) {
-                const int b = i0 / C & 1;
+            // C values at a time over all digits (so that only theirs are sums of several words), the operands of the next product
+            // requested before the current one is formed.
+            u64 x[C], k0[C], k1[C];
+            auto fetch = [&](const u64 *s, const u64 *k, bool keys) {
+                auto get = [&](u64 *to, const u64 *from) {
 #pragma unroll
-                for (int i = 0; i < C; i++) x[b][i] = ld(src + 64 * (i0 + i), reg_off);
-                if (keys) {
-#pragma unroll
-                    for (int i = 0; i < C; i++) {
-                        k0[b][i] = ld(key + 64 * (i0 + i), reg_off);
-                        k1[b][i] = ld(key + kstride + 64 * (i0 + i), reg_off);
+                    for (int i = 0; i < C; i += 2) {
+                        const word_pair p = ld_pair(from + reg_pos(i, 0), reg_off);
+                        to[i] = p[0];
+                        to[i + 1] = p[1];
                     }
+                };
+                get(x, s);
+                if (keys) {
+                    get(k0, k);
+                    get(k1, k + kstride);
                 }
             };
-            fetch(0, true);
+            fetch(src, key, true);
             if (GROUP && mem > 0) {
                 move(a0, d.g_inv, to_carry);
                 move(a1, d.g_inv, to_carry);
             }
-#pragma unroll 1
-            for (int jd = 0; jd < beta; jd++) {
-                const bool more = jd + 1 < beta;
 #pragma unroll
-                for (int i0 = 0; i0 < 16; i0 += C) {
-                    if (i0 + C < 16) {
-                        fetch(i0 + C, true);
-                    } else {
-                        src += (size_t)ext * N;
-                        key += 2 * kstride;
-                        if (more || with_c0) fetch(0, more);
-                    }
+            for (int i0 = 0; i0 < 16; i0 += C) {
+                typename I::Sum s0[C], s1[C];
+                const u64 *s = src + reg_pos(i0, 0), *k = key + reg_pos(i0, 0);
+                auto product = [&](auto &&next) {
+                    u64 cx[C], c0[C], c1[C];
 #pragma unroll
                     for (int i = 0; i < C; i++) {
-                        const int b = i0 / C & 1;
-                        I::mac(ar, a0[i0 + i], x[b][i], k0[b][i]);
-                        I::mac(ar, a1[i0 + i], x[b][i], k1[b][i]);
+                        cx[i] = x[i];
+                        c0[i] = k0[i];
+                        c1[i] = k1[i];
                     }
-                }
-            }
-            if (with_c0) {
+                    next();
 #pragma unroll
-                for (int i0 = 0; i0 < 16; i0 += C) {
-                    if (i0 + C < 16) fetch(i0 + C, false);
-#pragma unroll
-                    for (int i = 0; i < C; i++) I::add(a0[i0 + i], x[i0 / C & 1][i]);
+                    for (int i = 0; i < C; i++) {
+                        s0[i].mac(cx[i], c0[i]);
+                        s1[i].mac(cx[i], c1[i]);
+                    }
+                };
+                auto fetch_next = [&] {
+                    if (i0 + C < 16) fetch(src + reg_pos(i0 + C, 0), key + reg_pos(i0 + C, 0), true);
+                };
+#pragma unroll 2
+                for (int jd = 1; jd < beta; jd++) {
+                    s += (size_t)ext * N;
+                    k += 2 * kstride;
+                    product([&] { fetch(s, k, true); });
                 }
+                if (with_c0) {
+                    product([&] { fetch(s + (size_t)ext * N, nullptr, false); });
+                    u64 cx[C];
+#pragma unroll
+                    for (int i = 0; i < C; i++) cx[i] = x[i];
+                    fetch_next();
+#pragma unroll
+                    for (int i = 0; i < C; i++) s0[i].add(cx[i]);
+                } else {
+                    product(fetch_next);
+                }
+#pragma unroll
+                for (int i = 0; i < C; i++) {
+                    T t0 = s0[i].reduced(ar), t1 = s1[i].reduced(ar);
+                    asm volatile("" : "+v"(t0), "+v"(t1));  // here, not where they are used: until then each would be two or three words
+                    a0[i0 + i] = GROUP && mem > 0 ? I::plus(ar, a0[i0 + i], t0) : t0;
+                    a1[i0 + i] = GROUP && mem > 0 ? I::plus(ar, a1[i0 + i], t1) : t1;
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
+        if (RAW) {
 #pragma unroll
-        for (int i = 0; i < 16; i++) {
-            I::fold(ar, a0[i]);
-            I::fold(ar, a1[i]);
+            for (int i = 0; i < 16; i++) {
+                I::fold(ar, a0[i]);
+                I::fold(ar, a1[i]);
+            }
         }
         g = d.g;
         carry = to_carry;
@@ -507,14 +576,14 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
     tw += 2 * N;
     row_table_to_lds(tw1, tw, tw + N, R::ROWS + r, rho, j);
     TwRegs twi;
-    twi.load(tw, tw + N, (R::ROWS + r) * 16u + j);
+    twi.load(tw, tw + N, N, r, j);
     wave_lds_fence();
     u64 *uo = u + ((size_t)grp * 2 * ext + e) * N + (size_t)r * 256 + j;
 #pragma unroll
     for (int poly = 0; poly < 2; poly++) {
         T v[16];
 #pragma unroll
-        for (int i = 0; i < 16; i++) v[i] = (poly ? a1 : a0)[i].s;
+        for (int i = 0; i < 16; i++) v[i] = (poly ? a1 : a0)[i];
         row_inv(ar, v, tab, twi, lds, rho, j);
         u64 *o = uo + (size_t)poly * ext * N;
 #pragma unroll
@@ -522,25 +591,28 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
     }
 }
 
-// grid (8 * ceil(4 TILES * ext / 8) * n_grp): the rotations of a tile of four rows of one limb run next to each other on one XCD
+// grid (8 * ceil(4 TILES * ext / 8) * ceil(n_grp / WAVES)): the rotations of a tile of four rows of one limb run next to each other on one XCD
 // (block b runs on XCD b % 8), whose L2 then serves the digits that several rotations of one ciphertext read and the keys
 // that several ciphertexts read.
 // GROUP: the block adds the inner products of `members` consecutive descriptors (rotations of one ciphertext: same digits,
 // their own Galois element and key) before the inverse pass, so that the group is brought back to the ciphertext basis
 // by one inverse transform and one ModDown; n_grp then counts groups.
 template <int S, bool RAW, bool GROUP, class W>
-__global__ __launch_bounds__(64, 2) void k_ks16_inner(Ks16Const kc, const RotDesc *desc, const PrimeConst *pcs, const u64 *tw_all, u64 *u, int members,
-                                                      u32 n_grp) {
-    __shared__ u64 lds[ROW_LDS];
-    __shared__ ulonglong2 tw1[4 * 16];
+__global__ __launch_bounds__((64 * InnerBlock<RAW>::WAVES), (RAW ? 2 : InnerShape<GROUP, W>::PER_SIMD)) void k_ks16_inner(
+    Ks16Const kc, const RotDesc *desc, const PrimeConst *pcs, const u64 *tw_all, u64 *u, int members, u32 n_grp) {
+    constexpr u32 WAVES = InnerBlock<RAW>::WAVES;
+    __shared__ u64 lds[WAVES][ROW_LDS];
+    __shared__ ulonglong2 tw1[WAVES][4 * 16];
     constexpr u32 TILES4 = 4 * Ring<S>::TILES;
+    constexpr int C = InnerShape<GROUP, W>::VALUES;
     const int ext = kc.l1 + kc.K;
-    const u32 k = blockIdx.x >> 3, q = k / n_grp * 8 + (blockIdx.x & 7), grp = k % n_grp;
-    if (q >= TILES4 * ext) return;
+    const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_blk = (n_grp + WAVES - 1) / WAVES;
+    const u32 k = blockIdx.x >> 3, q = k / n_blk * 8 + (blockIdx.x & 7), grp = k % n_blk * WAVES + wave;
+    if (q >= TILES4 * ext || grp >= n_grp) return;
     const int e = ext - 1 - (int)(q / TILES4), prime = ks_ext_prime(e, kc.l1, kc.L);  // the special limbs, which take longer, first
     const PrimeConst pc = load_prime(pcs, prime);
-    if (e < kc.l1) inner_body<S, RAW, GROUP, ArithFp>(kc, desc, pc, tw_all, u, prime, e, members, grp, q % TILES4, lds, tw1);
-    else inner_body<S, RAW, GROUP, W>(kc, desc, pc, tw_all, u, prime, e, members, grp, q % TILES4, lds, tw1);
+    if (e < kc.l1) inner_body<S, RAW, GROUP, C, ArithFp>(kc, desc, pc, tw_all, u, prime, e, members, grp, q % TILES4, lds[wave], tw1[wave]);
+    else inner_body<S, RAW, GROUP, C, W>(kc, desc, pc, tw_all, u, prime, e, members, grp, q % TILES4, lds[wave], tw1[wave]);
 }
 
 // ------------------------------------------------------ inverse column pass + ModDown
@@ -711,9 +783,10 @@ void ks16_switch(ensi_ctx *ctx, const Ks16Const &kc, const RotDesc *d_desc, int 
         typedef decltype(w) W;
         {
             ScopedTimer t(ctx, "ks_inner", st);
-            const unsigned blocks = (4u * TILES * ext + 7) / 8 * 8 * n_grp;
             auto inner = [&](auto raw_, auto group_) {
-                hipLaunchKernelGGL((k_ks16_inner<S, decltype(raw_)::value, decltype(group_)::value, W>), dim3(blocks), dim3(64), 0, st, kc, d_desc, ctx->d_pc,
+                constexpr unsigned WAVES = InnerBlock<decltype(raw_)::value>::WAVES;
+                const unsigned blocks = (4u * TILES * ext + 7) / 8 * 8 * ((n_grp + WAVES - 1) / WAVES);
+                hipLaunchKernelGGL((k_ks16_inner<S, decltype(raw_)::value, decltype(group_)::value, W>), dim3(blocks), dim3(64 * WAVES), 0, st, kc, d_desc, ctx->d_pc,
                                    ctx->d_tw, u, members, (u32)n_grp);
             };
             if (raw) inner(std::true_type(), std::false_type());

@@ -53,7 +53,7 @@ __device__ __forceinline__ void rows_body(u64 *g, size_t inst_stride, int n_here
     typename A::T v[16];
     row_table_to_lds(tw1, tw, tw + Ring<S>::N, base, rho, j);
     TwRegs tw2;
-    tw2.load(tw, tw + Ring<S>::N, base * 16u + j);
+    tw2.load(tw, tw + Ring<S>::N, Ring<S>::N, r0 + rho, j);
     const ulonglong2 *tab = tw1 + rho * 16;
     const int at = FWD ? rho * 256 + j : lane;  // forward: value i at j + 16 i of row rho; inverse: at lane + 64 i of the four rows
     constexpr int step = FWD ? 16 : 64;

@@ -280,7 +280,20 @@ __device__ __forceinline__ void ct4_tab(const A &ar, typename A::T *v, const TAB
         }
     }
 }
-// The 15 twiddles of a step with base index mbase, in ct4_tab's order.
+// The tables' last 15/16 serve the second steps of the row pass, 15 entries for each thread of a wave's four rows.  They lie in the
+// order in which waves read them: entry e (ct4_tab's order) of lane l of the four rows 4 t .. 4 t + 3 at N / 16 + 960 t +
+// row_twiddle_pos(e, l).  In the order of the network a load of the last stage's eight entries touched a line for every two lanes: 680 lines
+// a wave and table against the 120 that it reads, nearly as many as all operands of an inner product.
+ENSI_HD u32 row_twiddle_pos(u32 e, u32 l) { return e < 14 ? (e >> 1) * 128 + l * 2 + (e & 1) : 896 + l; }
+// place of entry k >= N / 16 of a table in the network's order, rows of 256
+ENSI_HD u32 row_twiddle_place(u32 k, u32 n) {
+    u32 stage = 0;
+    while (k >> stage >= n / 8) stage++;
+    const u32 rem = k - (n / 16 << stage), g = rem & ((1u << stage) - 1), rj = rem >> stage, r = rj >> 4;
+    return n / 16 + (r >> 2) * 960 + row_twiddle_pos((1u << stage) - 1 + g, (r & 3) * 16 + (rj & 15));
+}
+typedef u64 word_pair __attribute__((vector_size(16)));
+// The 15 twiddles of a thread in the second step of the row pass, in ct4_tab's order.
 struct TwRegs {
     ulonglong2 t[15];
     __device__ __forceinline__ const ulonglong2 &operator[](int i) const { return t[i]; }
@@ -293,11 +306,16 @@ struct TwRegs {
             t[i] = make_ulonglong2(x, y);
         }
     }
-    __device__ __forceinline__ void load(const u64 *tw, const u64 *tws, u32 mbase) {
+    // those of thread j of row r, second step, of a ring of n words
+    __device__ __forceinline__ void load(const u64 *tw, const u64 *tws, u32 n, u32 r, u32 j) {
+        const u32 at = n / 16 + (r >> 2) * 960, lane = (r & 3) * 16 + j;
 #pragma unroll
-        for (int k = 0; k < 4; k++)
-#pragma unroll
-            for (int g = 0; g < (1 << k); g++) t[(1 << k) - 1 + g] = make_ulonglong2(tw[(mbase << k) + g], tws[(mbase << k) + g]);
+        for (int e = 0; e < 14; e += 2) {
+            const word_pair a = *(const word_pair *)(tw + at + row_twiddle_pos(e, lane)), b = *(const word_pair *)(tws + at + row_twiddle_pos(e, lane));
+            t[e] = make_ulonglong2(a[0], b[0]);
+            t[e + 1] = make_ulonglong2(a[1], b[1]);
+        }
+        t[14] = make_ulonglong2(tw[at + row_twiddle_pos(14, lane)], tws[at + row_twiddle_pos(14, lane)]);
     }
 };
 
@@ -489,6 +507,9 @@ __device__ __forceinline__ void cols_inv_tab(const A &ar, typename A::T *v, cons
 //   forward: on entry v[i] = element j + 16 i of row rho, on exit v[i] = element 16 j + i.
 //   inverse: on entry v[i] = element 16 j + i, on exit v[i] = element j + 16 i.
 #define ROW_LDS (1024 + 64)
+// Register order of a wave's four rows in the key switch: where value i of a lane lies among their 1024 words.  A lane's even value and
+// the odd one behind it are neighbours: loads of 16 bytes a lane.
+__device__ __forceinline__ u32 reg_pos(int i, int lane) { return (u32)((i >> 1) * 128 + lane * 2 + (i & 1)); }
 __device__ __forceinline__ int rpad(int p) { return p + (p >> 4); }
 // Orders a wave's LDS writes before the reads of its other lanes that follow.
 __device__ __forceinline__ void wave_lds_fence() {

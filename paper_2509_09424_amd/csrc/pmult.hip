@@ -152,7 +152,7 @@ __global__ __launch_bounds__(64, 2) void k_pm16_rows_mac(PmGroup g, const PrimeC
     const u64 *twf = tw_all + (size_t)limb * 4 * N, *twi = twf + 2 * N;
     row_table_to_lds(tw1, twf, twf + N, R::ROWS + r, rho, j);
     TwRegs tw2;
-    tw2.load(twf, twf + N, (R::ROWS + r) * 16u + j);
+    tw2.load(twf, twf + N, N, r, j);
     const ulonglong2 *tab = tw1 + rho * 16;
     const int t0 = as_const(g.begin)[o], t1 = as_const(g.begin)[o + 1];
     double acc[16], nv[16];
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(64, 2) void k_pm16_rows_mac(PmGroup g, const PrimeC
         }
     }
     row_table_to_lds(tw1, twi, twi + N, R::ROWS + r, rho, j);
-    tw2.load(twi, twi + N, (R::ROWS + r) * 16u + j);
+    tw2.load(twi, twi + N, N, r, j);
     wave_lds_fence();
 #pragma unroll
     for (int i = 0; i < 16; i++) acc[i] = ar.mid(acc[i]);
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(64, 2) void k_pm16_rows(u64 *data, int n, int l1, c
     const u64 *tw = tw_all + (size_t)limb * 4 * N + (FWD ? 0 : 2 * N);
     row_table_to_lds(tw1, tw, tw + N, R::ROWS + r, rho, j);
     TwRegs tw2;
-    tw2.load(tw, tw + N, (R::ROWS + r) * 16u + j);
+    tw2.load(tw, tw + N, N, r, j);
     const ulonglong2 *tab = tw1 + rho * 16;
     const u32 row_off = (rho * 256 + j) * 8, reg_off = lane * 8;
     constexpr int in_step = FWD ? 16 : 64, out_step = FWD ? 64 : 16;

@@ -686,6 +686,35 @@ def test_register_transform_rings_bit_exact(params):
     p.close()
 
 
+@pytest.mark.parametrize("params", [(12, 50, 8, 60, 1, 1, 40), (12, 50, 7, 60, 2, 1, 40), (13, 45, 8, 48, 1, 1, 36), (12, 50, 8, 61, 1, 1, 40)],
+                         ids=["4K-wide-8", "4K-wide-7", "8K-fp-8", "4K-61bit-8"])
+def test_inner_products_of_one_to_eight_digits(params):
+    """Sums of up to eight products that are reduced once, over digits that several rotations share: every number of digits, for every kind of
+    special primes, and numbers of rotations around the four of a block; then groups of rotations (a fill)."""
+    p = Pair(params)
+    s = p.n // 8
+    fill = p.ctx.fill_steps(1, p.n)
+    o_gks, g_gk = p.galois_keys(sorted({r * s for r in range(1, 8)} | set(fill)))
+    rng = np.random.default_rng(12)
+    for limbs in range(p.pr.L, 0, -1):
+        d = 8 - limbs % 5
+        W = np.ones((d, 1), dtype=np.int8)
+        o_cts, g_ct = p.encrypt_both(wl.pack_columns(rng.uniform(-1, 1, (s, d)), p.n), limbs)
+        out = p.ctx.ternary_matmul(g_gk, g_ct, s, d, W, "zero")
+        want = p.o.ternary_matmul(o_cts, s, d, W, "zero", {r: o_gks[r * s] for r in range(1, d)})
+        assert np.array_equal(out.export(), stack_cts(want)), (limbs, d)
+        out.free()
+        g_ct.free()
+    o_cts, g_ct = p.encrypt_both(p.rng.uniform(-1, 1, (1, p.n)), p.pr.L)
+    masks = p.o.one_hot_masks([5], p.pr.L)
+    g_masks = p.ctx.pt_set_scale(p.ctx.pt_import(masks, p.pr.L), float(p.pr.q[-1]))
+    out = p.ctx.replicate(g_gk, g_ct, [0], g_masks, [0])
+    assert np.array_equal(out.export(), stack_cts([p.o.replicate(o_cts[0], masks[0], {st: o_gks[st] for st in fill})]))
+    for h in (g_ct, g_masks, out, g_gk):
+        h.free()
+    p.close()
+
+
 @pytest.mark.parametrize("log_n,n", [(12, 300), (13, 5), (14, 70), (15, 3), (16, 37)])
 def test_client_transforms_equal_the_length_2n_transform(log_n, n):
     """Encoding and decoding by the kernels of the register transform against the length-2N transform, which a context with
