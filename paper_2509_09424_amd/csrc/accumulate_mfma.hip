@@ -24,7 +24,8 @@
 // Operand v is the ciphertext at xbase + v*xstride words (the unpack phase writes its
 // rotations straight into that array).
 //
-// Two kernels.  k_byte_planes runs once per operand array: it splits every 32 x 32 tile
+// Products of few operands or few outputs run in one kernel, k_accumulate_direct, which keeps its digits in LDS; the others in two.
+// k_byte_planes runs once per operand array: it splits every 32 x 32 tile
 // (32 operands x 32 consecutive words) into its byte planes, already in the register
 // layout of the matrix instruction's first operand (lane = 32*(operand/16) + row, 16
 // operand bytes per lane; plane_row says which word a row is), so that the tile of one plane is 1 KiB that a single
@@ -610,6 +611,224 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
     wait_vmcnt<0>();  // no copy may still be in flight into LDS when the workgroup ends
 }
 
+// ---------------------------------------------------------------- few operands or few outputs: split and contraction in one kernel
+// A block takes one word tile: the digits of its operands go straight to LDS (no planes in memory, no filling up to whole groups of steps)
+// and each wave runs through blocks of 32 outputs.
+//   CHUNKED = false: all operands fit LDS together (AMD_MAX_OPERANDS); a wave takes every fourth block of outputs.
+//   CHUNKED = true:  one block of outputs a wave (AMD_MAX_OUTPUTS), which keeps its sums while the operands pass through LDS, AMD_CHUNK_STEPS
+//   steps at a time; two blocks on a CU, so that one reads while the other multiplies.
+// Bound by the reading of the operands and the writing of the outputs while the outputs are few, then by the fragment read from LDS that
+// every matrix instruction needs (in k_accumulate_mfma every second one does).  Four waves for up to 128 outputs, eight for 256, twelve
+// for 384: beyond that the sums do not fit the registers.
+#define AMD_MAX_OPERANDS 384
+#define AMD_MAX_OUTPUTS 384
+#define AMD_CHUNKED_MIN 256  // operands from which they pass through LDS in chunks, where the outputs allow it: 300 and 8 outputs 0.20 -> 0.14 ms
+                             // (2^14, 6 limbs), 300 and 256 0.38 -> 0.32; 200 and 256 0.22 -> 0.25
+#define AMD_CHUNK_STEPS 8
+#define AMD_AHEAD 4  // steps whose words, or weights, are requested together
+// RESCALE: the scalar-multiply + rescale step is applied to the operands on the way, as in k_byte_planes_rescale (fc: its constants); the limb that it
+// drops is read and rescaled once for every limb that stays, which pays for few operands only.
+template <int PLANES, int MODE, bool CHUNKED, int WAVES, bool RESCALE>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 12 ? 3 : 2) void k_accumulate_direct(const u64 *xbase, u32 xstride, int n_v, int nk, const v4i *wfrag, const void *bias,
+                                                                     int m, int m_pad, AmPrimes pr, int N, int l1, int limb_stride_in, u64 *out,
+                                                                     int limb_stride_out, const PrimeConst *pc, const double *fc) {
+    HIP_DYNAMIC_SHARED(char, smem)
+    static_assert(MODE != AM_POS7, "digits of 8 bits");
+    constexpr bool FP_EPI = MODE != AM_INT8;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5, nl = lane & 31;
+    const int steps = (n_v + AM_TILE_K - 1) / AM_TILE_K, cw = N / AM_TILE_N;
+    const int pl = blockIdx.x / cw, poly = pl >= l1, limb = poly ? pl - l1 : pl, ctile = blockIdx.x - pl * cw;
+    const u64 *xw = xbase + ((size_t)poly * limb_stride_in + limb) * N + (size_t)ctile * AM_TILE_N;
+    // digits of steps s0 .. s1 - 1 to LDS, the first of them at step 0
+    auto fill = [&](int s0, int s1) {
+        constexpr int PARTS = WAVES / 4;  // steps that the block's threads take at a time
+        const int k4 = tid >> 5 & 7, ln = tid & 31, part = tid >> 8;
+        u32 *dst = (u32 *)smem + ((k4 >> 2) * 32 + plane_row(ln)) * 4 + (k4 & 3);
+        AmFp mod, last;
+        double k, k_q, qi, qi_q, kl, kl_q;
+        const u64 *xl = xbase + ((size_t)poly * limb_stride_in + l1) * N + (size_t)ctile * AM_TILE_N;
+        if (RESCALE) {
+            const int lin = l1 + 1;
+            mod = {(double)as_const(&pc[limb].q)[0], as_const(fc)[4 * lin + limb]};
+            last = {(double)as_const(&pc[l1].q)[0], as_const(fc)[4 * lin + l1]};
+            k = as_const(fc)[limb], k_q = as_const(fc)[lin + limb], qi = as_const(fc)[2 * lin + limb], qi_q = as_const(fc)[3 * lin + limb];
+            kl = as_const(fc)[l1], kl_q = as_const(fc)[lin + l1];
+        }
+#pragma unroll 1
+        for (int sa = s0 + part; sa < s1; sa += AMD_AHEAD * PARTS) {
+            u64 w[AMD_AHEAD][4], wl[RESCALE ? AMD_AHEAD : 1][4];
+#pragma unroll
+            for (int s = 0; s < AMD_AHEAD; s++)
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const int v = (sa + s * PARTS) * AM_TILE_K + 4 * k4 + j;
+                    w[s][j] = v < n_v ? xw[(size_t)v * xstride + ln] : 0;
+                    if (RESCALE) wl[s][j] = v < n_v ? xl[(size_t)v * xstride + ln] : 0;  // (no operand: zero stays zero)
+                }
+            if (RESCALE) {
+#pragma unroll
+                for (int s = 0; s < AMD_AHEAD; s++)
+#pragma unroll
+                    for (int j = 0; j < 4; j++) {
+                        const double c = last.mid(last.mulmod((double)wl[s][j], kl, kl_q));
+                        const double t = mod.mulmod((double)w[s][j], k, k_q) - mod.mid(c);
+                        const double r = mod.mid(mod.mulmod(mod.mid(t), qi, qi_q));
+                        w[s][j] = (u64)(r < 0.0 ? r + mod.q : r);
+                    }
+            }
+#pragma unroll
+            for (int s = 0; s < AMD_AHEAD; s++) {
+                if (sa + s * PARTS < s1) {
+                    u32 d[8];
+                    transpose4((u32)w[s][0], (u32)w[s][1], (u32)w[s][2], (u32)w[s][3], d);
+                    transpose4((u32)(w[s][0] >> 32), (u32)(w[s][1] >> 32), (u32)(w[s][2] >> 32), (u32)(w[s][3] >> 32), d + 4);
+#pragma unroll
+                    for (int p = 0; p < PLANES; p++) dst[((sa + s * PARTS - s0) * PLANES + p) * 256] = d[p] ^ 0x80808080u;
+                }
+            }
+        }
+    };
+    const char *planes = smem + lane * 16;
+    // outputs ib .. ib + 31: adds the products of steps s0 .. s1 - 1, which lie in LDS from step 0 on
+    auto contract = [&](v16i *acc, int ib, int s0, int s1) {
+        const v4i *wp = wfrag + ((size_t)(ib / AM_TILE_M) * nk * 4 + ib % AM_TILE_M / 64) * 128 + ib % 64 / 32 * 64 + lane;
+#pragma unroll 1
+        for (int ka = s0; ka < s1; ka += AMD_AHEAD) {
+            v4i wf[AMD_AHEAD];
+#pragma unroll
+            for (int s = 0; s < AMD_AHEAD; s++)
+                if (ka + s < s1) wf[s] = wp[(size_t)(ka + s) * 512];
+#pragma unroll
+            for (int s = 0; s < AMD_AHEAD; s++) {
+                if (ka + s < s1) {
+#pragma unroll
+                    for (int p = 0; p < PLANES; p++)
+                        acc[p] = __builtin_amdgcn_mfma_i32_32x32x32_i8(*(const v4i *)(planes + ((ka + s - s0) * PLANES + p) * 1024), wf[s], acc[p], 0, 0, 0);
+                }
+            }
+        }
+    };
+    char *o_lds = smem + (CHUNKED ? AMD_CHUNK_STEPS : steps) * PLANES * 1024 + wv * 32 * AM_OROW;
+    const size_t ct_words_out = (size_t)2 * limb_stride_out * N;
+    const size_t off_out = ((size_t)poly * limb_stride_out + limb) * N + (size_t)ctile * AM_TILE_N;
+    const u64 q = pr.q[limb];
+    const double q_inv = pr.q_inv[limb], qd = (double)q;
+    const AmModulus md = {qd, q_inv, qd / AmDigits<false>::P4, q_inv * AmDigits<false>::P4};
+    u64 ones = 0;
+#pragma unroll
+    for (int p = 0; p < PLANES; p++) ones |= (u64)1 << (8 * p);
+    // the recombination and the stores as in k_accumulate_mfma: 32 outputs x 16 words at a time
+    auto finish = [&](const v16i *acc, int ib) {
+        double b_fp = 0.0;
+        int64_t b_int = 0;
+        if (FP_EPI) b_fp = ((const double *)bias)[(size_t)limb * m_pad + ib + nl];
+        else b_int = (int64_t)((u64)(int64_t)((const int *)bias)[ib + nl] * ones);
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                u64 res[2];
+#pragma unroll
+                for (int e = 0; e < 2; e++) {
+                    const int r = 8 * h + 2 * c + e;
+                    if (FP_EPI) {
+                        int S[PLANES];
+#pragma unroll
+                        for (int p = 0; p < PLANES; p++) S[p] = acc[p][r];
+                        res[e] = recombine_fp<PLANES, false>(S, b_fp, md);
+                    } else {
+                        int64_t t = b_int;
+#pragma unroll
+                        for (int p = 0; p < PLANES; p++) t += (int64_t)((u64)(int64_t)acc[p][r] << (8 * p));
+                        res[e] = reduce_signed(t, q, q_inv);
+                    }
+                }
+                *(ulonglong2 *)(o_lds + nl * AM_OROW + g * 64 + c * 16) = make_ulonglong2(res[0], res[1]);
+            }
+            wave_lds_fence();
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const int row = 8 * k + (lane >> 3);
+                const ulonglong2 w = *(const ulonglong2 *)(o_lds + row * AM_OROW + (lane & 7) * 16);
+                if (ib + row < m) *(ct_pair *)(out + (size_t)(ib + row) * ct_words_out + off_out + 16 * h + (lane & 7) * 2) = ct_pair{w.x, w.y};
+            }
+            wave_lds_fence();
+        }
+    };
+    if (CHUNKED) {
+        const int ib = wv * 32;
+        v16i acc[PLANES] = {};
+#pragma unroll 1
+        for (int s0 = 0; s0 < steps; s0 += AMD_CHUNK_STEPS) {
+            const int s1 = min(s0 + AMD_CHUNK_STEPS, steps);
+            if (s0) __syncthreads();  // every wave has read the chunk before
+            fill(s0, s1);
+            __syncthreads();
+            if (ib < m) contract(acc, ib, s0, s1);
+        }
+        if (ib < m) finish(acc, ib);
+    } else {
+        fill(0, steps);
+        __syncthreads();
+#pragma unroll 1
+        for (int ib = wv * 32; ib < m; ib += 32 * WAVES) {
+            v16i acc[PLANES] = {};
+            contract(acc, ib, 0, steps);
+            finish(acc, ib);
+        }
+    }
+}
+
+// Whether a product of n_v operands and m outputs takes the kernel above.  The other way keeps planes in memory, split for whole groups of 256
+// operands, and contracts them for whole tiles of 256 outputs.  Whole calls, planes in memory against here, on 3 limbs of the 2^12 ring in us, 6
+// of 2^14 in us and 16 of 2^16 in ms:
+//   operands x outputs   64 x 64 26, 8    64 x 40 220, 40     64 x 256 2.66, 1.47   256 x 1024 86, 68; 871, 686; 8.64, 6.90
+//   384 x 512 69, 55; 768, 669; 7.81, 7.11            450 x 512 (here all operands in LDS) 70, 72; 791, 797; 8.11, 8.10
+//   600 x 40 58, 33; 675, 260; 7.05, 2.72             1024 x 384 138, 92; 1290, 866; 13.4, 8.7     2560 x 384 325, 223; 2880, 1820
+// With the rescale (5 limbs of 2^14 and 11 of 2^16, both layers): 64 operands 442, 120 and 3.28, 1.10; 200 x 200 555, 527 and 3.99, 4.50.
+static bool am_direct(int n_v, int m, bool rescale) { return rescale ? n_v <= 128 : n_v <= AMD_MAX_OPERANDS || m <= AMD_MAX_OUTPUTS; }
+
+template <int P, int MODE>
+static void am_launch_direct(ensi_ctx *ctx, hipStream_t st, const u64 *xbase, u32 xstride, int n_v, int n_kpad, const v4i *wfrag, const void *bias, int m,
+                             int l1, int limb_stride_in, u64 *out, int limb_stride_out, int n_tiles_m, const double *d_rescale) {
+    AmPrimes pr;
+    for (int i = 0; i < ENSI_MAX_EXT; i++) {
+        pr.q[i] = i < l1 ? ctx->primes[i] : 1;
+        pr.q_inv[i] = 1.0 / (double)pr.q[i];
+    }
+    const int steps = (n_v + AM_TILE_K - 1) / AM_TILE_K;
+    ScopedTimer t(ctx, d_rescale ? "rescale_accumulate_direct" : "accumulate_direct", st);
+    auto launch = [&](auto chunked, auto waves, auto rescale) {
+        constexpr bool CHUNKED = decltype(chunked)::value, RESCALE = decltype(rescale)::value;
+        constexpr int WAVES = decltype(waves)::value;
+        auto lds = [](int s) { return s * P * 1024 + WAVES * 32 * AM_OROW; };
+        bool &attr_set = ctx->am_direct_attr_set[((2 * MODE + (P == 5 ? 0 : 1)) * 4 + (CHUNKED ? WAVES / 4 : 0)) * 2 + RESCALE];
+        if (!attr_set) {
+            (void)hipFuncSetAttribute((const void *)k_accumulate_direct<P, MODE, CHUNKED, WAVES, RESCALE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      lds(CHUNKED ? AMD_CHUNK_STEPS : AMD_MAX_OPERANDS / AM_TILE_K));
+            attr_set = true;
+        }
+        hipLaunchKernelGGL((k_accumulate_direct<P, MODE, CHUNKED, WAVES, RESCALE>), dim3(2 * l1 * (ctx->N / AM_TILE_N)), dim3(64 * WAVES),
+                           lds(CHUNKED ? AMD_CHUNK_STEPS : steps), st, xbase, xstride, n_v, n_kpad / AM_TILE_K, wfrag, bias, m, n_tiles_m * AM_TILE_M, pr, ctx->N,
+                           l1, limb_stride_in, out, limb_stride_out, ctx->d_pc, d_rescale);
+    };
+    typedef std::integral_constant<int, 4> Four;
+    typedef std::integral_constant<int, 8> Eight;
+    typedef std::integral_constant<int, 12> Twelve;
+    typedef std::false_type No;
+    typedef std::true_type Yes;
+    if (d_rescale) {
+        if constexpr (MODE == AM_FP8) launch(No(), Four(), Yes());  // (the rescale is fused for primes below 2^50 only)
+    } else if (n_v <= AMD_CHUNKED_MIN || m > AMD_MAX_OUTPUTS)
+        launch(No(), Four(), No());
+    else if (m <= 128)
+        launch(Yes(), Four(), No());
+    else if (m <= 256)
+        launch(Yes(), Eight(), No());
+    else
+        launch(Yes(), Twelve(), No());
+}
+
 template <int P, int MODE>
 static void am_launch(ensi_ctx *ctx, unsigned grid, hipStream_t st, const u64 *xbase, u32 xstride, int n_v, int n_kpad, const v4i *wfrag,
                       const void *bias, int m, int l1, int limb_stride_in, u64 *out, int limb_stride_out, int n_tiles_m, int workers,
@@ -678,6 +897,16 @@ int launch_accumulate_mfma(ensi_ctx *ctx, const u64 *xbase, size_t xstride, int 
     const v4i *wf = (const v4i *)d_wt;
     const int m_group = 8;  // 8 output tiles x 4 word tiles in flight per XCD
     const int P = planes <= 5 ? 5 : 7;
+    const void *bias = mode == AM_INT8 ? (const void *)d_bias : (const void *)d_bias_fp;
+    if (am_direct(n_v, m, d_rescale != nullptr)) {
+#define AMD_LAUNCH(PL, MODE) \
+    am_launch_direct<PL, MODE>(ctx, st, xbase, (u32)xstride, n_v, n_kpad, wf, bias, m, l1, limb_stride_in, out, limb_stride_out, n_tiles_m, d_rescale)
+        if (mode == AM_INT8) AMD_LAUNCH(7, AM_INT8);
+        else if (P == 5) AMD_LAUNCH(5, AM_FP8);
+        else AMD_LAUNCH(7, AM_FP8);
+#undef AMD_LAUNCH
+        return ENSI_OK;
+    }
     const int slice_ctiles = am_slice_ctiles(ctiles, l1, n_kpad, P);
     const size_t tiles = (size_t)slice_ctiles * 2 * l1, nk = n_kpad / AM_TILE_K;
     const size_t xp_words = tiles * nk * P * 128 + (mode == AM_POS7 ? tiles * (nk / AM_RS_STEPS + 1) * AM_TILE_N : 0);
@@ -691,7 +920,6 @@ int launch_accumulate_mfma(ensi_ctx *ctx, const u64 *xbase, size_t xstride, int 
         }
         ctx->ws_xp_words = xp_words;
     }
-    const void *bias = mode == AM_INT8 ? (const void *)d_bias : (const void *)d_bias_fp;
 #define AM_LAUNCH(PL, MODE)                                                                                                              \
     am_launch<PL, MODE>(ctx, grid, st, xbase, (u32)xstride, n_v, n_kpad, wf, bias, m, l1, limb_stride_in, out, limb_stride_out, n_tiles_m, \
                         workers, m_group, (char *)ctx->ws_xp, slice_ctiles, d_rescale)

@@ -309,7 +309,7 @@ struct ensi_ctx {
     StageSlot stage[ENSI_STAGE_SLOTS];
     int stage_next = 0;
     int n_cu = 0;                // compute units of the context's device (0: not queried yet)
-    bool am_attr_set[6] = {};    // dynamic LDS limit of the matrix-core accumulate kernels raised
+    bool am_attr_set[6] = {}, am_direct_attr_set[48] = {};  // dynamic LDS limit of the matrix-core accumulate kernels raised
     // timers
     bool profiling = false;
     std::vector<KernelTimer> timers;

@@ -270,6 +270,62 @@ def test_signed_sums_by_digits(bits, operands, outputs, L):
         ctx.close()
 
 
+@pytest.mark.parametrize("bits,operands,outputs", [
+    (50, 1, 1), (36, 31, 32), (50, 33, 33), (38, 128, 129), (54, 129, 40), (50, 256, 300),  # all operands in LDS
+    (50, 257, 128), (36, 300, 33), (38, 511, 129), (54, 257, 256), (50, 1025, 257), (54, 512, 384), (50, 2049, 8),  # in chunks
+    (50, 384, 385), (36, 384, 520), (50, 385, 385), (54, 400, 600)])  # many outputs, and one condition past it
+def test_signed_sums_of_few_operands_or_outputs(bits, operands, outputs):
+    """Up to 384 operands or outputs the digits are formed where they are multiplied (with the rescale: up to 128 operands); largest and
+    smallest residues among them, and one operand with weight +1 and one with -1 everywhere.  The plain-ALU kernel on every word, and plain
+    integers."""
+    import torch
+
+    from paper_2509_09424_amd import binding
+    L = 3
+    ctx = binding.Context(12, bits, L, bits + 2, 1, 1, 20, seed=1)
+    N, q = ctx.N, [int(x) for x in ctx.primes()[0]]
+    W = np.random.default_rng(bits + operands).integers(-1, 2, (operands, outputs)).astype(np.int8)
+    W[0], W[-1] = -1, 1
+    W[:, 0] = 1
+    x = torch.empty((operands, 2, L, N), dtype=torch.int64, device="cuda")
+    for i in range(L):
+        x[:, :, i].random_(0, q[i], generator=torch.Generator(device="cuda").manual_seed(i))
+        x[:, :, i, :40] = q[i] - 1
+    x[:, :, :, 40:80] = 0
+    words = x[:, 1, :, 30:100].cpu().numpy().astype(object)
+    want = sum(int(W[v, 0]) * words[v] for v in range(operands)) % np.array(q, dtype=object)[:, None]
+
+    def product(mode, rescale):
+        ctx.set_accumulate_mode(mode)
+        limbs = L - rescale
+        src, out = x.clone(), torch.full((outputs, 2, limbs, N), -1, dtype=torch.int64, device="cuda")
+        h_in, h_out = ctx.ct_wrap(src.data_ptr(), operands, L, 1.0), ctx.ct_wrap(out.data_ptr(), outputs, limbs, 1.0)
+        wt = ctx.weights_prepare(W, ctx.n_slots, operands, "zero", limbs)
+        ctx.profile_enable(True)
+        if rescale:
+            ctx.rescale_ternary_matmul_prepared(h_in, 2.0 ** -5, wt, h_out)
+        else:
+            ctx.ternary_matmul_prepared(None, h_in, wt, h_out)
+        torch.cuda.synchronize()
+        ran = {k for k, v in ctx.profile_read().items() if v[1]}
+        if mode == 2 and not (rescale and bits > 50):  # (wider primes: the rescale is a step of its own)
+            few = operands <= 128 if rescale else operands <= 384 or outputs <= 384
+            assert ("rescale_accumulate_direct" if rescale else "accumulate_direct") in ran if few else "accumulate_mfma" in ran, ran
+        ctx.profile_enable(False)
+        for h in (wt, h_in, h_out):
+            h.free()
+        return out
+
+    try:
+        for rescale in (False, True):
+            plain, matrix = product(1, rescale), product(2, rescale)
+            assert torch.equal(plain, matrix), "rescale %s" % rescale
+            if not rescale:
+                assert np.array_equal(matrix[0, 1, :, 30:100].cpu().numpy().astype(object), want)
+    finally:
+        ctx.close()
+
+
 @pytest.mark.parametrize("bits,operands,kernel", [(50, 8192, "accumulate_mfma"), (50, 8193, "accumulate"), (36, 32768, "accumulate_mfma"),
                                                   (36, 32769, "accumulate")])
 def test_signed_sums_at_the_most_operands(bits, operands, kernel):
