@@ -15,6 +15,9 @@
 //                  to centred residues y_k = [u (P/p_k)^-1]_{p_k}, held in registers, and then walks the
 //                  ciphertext limbs:  u P^-1 - sum_k y_k p_k^-1  mod q_i
 //
+// Few rotations, which do not fill the chip, take forms with more and shorter blocks: k_ks16_fcols_one (a limb to a block), k_ks16_specials
+// (the special limbs of the accumulators first) and k_ks16_inner_split (a wave to each digit); where the lines lie is said at the launchers.
+//
 // What bounds them: a row or column pass costs 40 to 60 instructions per word, the memory system about as much, so
 // neither can be wasted.  Holding y (fcols) and y_k (icols) in registers while the block walks the limbs is what
 // removed the re-reads: with a block per limb each word of y was fetched through L2 once per target limb and the
@@ -60,7 +63,8 @@ __device__ __forceinline__ RotDesc load_desc(const RotDesc *desc, int i) {
 // Basis conversion of values h .. h+7 of a column: sum_a y_a h_a over the 25-bit halves of y against split h and
 // h 2^25 is a1 2^b + a0 (b = 25 or 30: where the halves of h meet); four multiply-adds per source, one reduction
 // per word afterwards (a modular product per source in fp64 took twice the instructions).
-__device__ __forceinline__ void modup_sums(int64_t *a0, int64_t *a1, const u64 *hat, u64 (*y)[16], int ns, int h) {
+template <int Y>
+__device__ __forceinline__ void modup_sums(int64_t *a0, int64_t *a1, const u64 *hat, u64 (*y)[Y], int ns, int h) {
 #pragma unroll
     for (int a = 0; a < ENSI_MAX_ALPHA; a++) {
         if (a == 0 || a < ns) {  // (ns >= 1)
@@ -75,35 +79,41 @@ __device__ __forceinline__ void modup_sums(int64_t *a0, int64_t *a1, const u64 *
     }
 }
 
-__device__ __forceinline__ void modup_to(const ArithFp &ar, double *v, const u64 *hat, const u64 *, u64 (*y)[16], int ns, const PrimeConst &) {
+template <int Y>
+__device__ __forceinline__ void modup_half(const ArithFp &ar, double *v, const u64 *hat, const u64 *, u64 (*y)[Y], int ns, const PrimeConst &, int h) {
+    int64_t a0[8], a1[8];
+    modup_sums(a0, a1, hat, y, ns, h);
 #pragma unroll
-    for (int h = 0; h < 16; h += 8) {
-        int64_t a0[8], a1[8];
-        modup_sums(a0, a1, hat, y, ns, h);
-#pragma unroll
-        for (int i = 0; i < 8; i++) v[h + i] = ar.reduce25(a1[i], a0[i]);
-    }
+    for (int i = 0; i < 8; i++) v[i] = ar.reduce25(a1[i], a0[i]);
 }
 // |a0|, |a1| <= 2^57 leave the value within 1.14 q, as a forward step may start
-__device__ __forceinline__ void modup_to(const ArithWide &ar, int64_t *v, const u64 *hat, const u64 *, u64 (*y)[16], int ns, const PrimeConst &) {
+template <int Y>
+__device__ __forceinline__ void modup_half(const ArithWide &ar, int64_t *v, const u64 *hat, const u64 *, u64 (*y)[Y], int ns, const PrimeConst &, int h) {
+    int64_t a0[8], a1[8];
+    modup_sums(a0, a1, hat, y, ns, h);
 #pragma unroll
-    for (int h = 0; h < 16; h += 8) {
-        int64_t a0[8], a1[8];
-        modup_sums(a0, a1, hat, y, ns, h);
-#pragma unroll
-        for (int i = 0; i < 8; i++)
-            v[h + i] = mad_pow2<30>((u32)a1[i] & 0x3fffffffu, mad_i((int)(a1[i] >> 30), ar.d, a0[i]));
-    }
+    for (int i = 0; i < 8; i++) v[i] = mad_pow2<30>((u32)a1[i] & 0x3fffffffu, mad_i((int)(a1[i] >> 30), ar.d, a0[i]));
 }
-__device__ __forceinline__ void modup_to(const ArithInt &, u64 *v, const u64 *, const u64 *hat_mont, u64 (*y)[16], int ns, const PrimeConst &pc) {
+template <int Y>
+__device__ __forceinline__ void modup_half(const ArithInt &, u64 *v, const u64 *, const u64 *hat_mont, u64 (*y)[Y], int ns, const PrimeConst &pc, int h) {
 #pragma unroll
-    for (int i = 0; i < 16; i++) {
+    for (int i = 0; i < 8; i++) {
         acc128 acc = {0, 0};
 #pragma unroll
         for (int a = 0; a < ENSI_MAX_ALPHA; a++)
-            if (a < ns) mac128(acc, (y[a][i] >> 32 << 25) | (u32)y[a][i], as_const(hat_mont)[a]);
+            if (a < ns) mac128(acc, (y[a][h + i] >> 32 << 25) | (u32)y[a][h + i], as_const(hat_mont)[a]);
         v[i] = mont_reduce(acc, pc.q, pc.qneg_inv);
     }
+}
+template <class A>
+__device__ __forceinline__ void modup_to(const A &ar, typename A::T *v, const u64 *hat, const u64 *hat_mont, u64 (*y)[16], int ns, const PrimeConst &pc) {
+#pragma unroll
+    for (int h = 0; h < 16; h += 8) modup_half(ar, v + h, hat, hat_mont, y, ns, pc, h);
+}
+// y_a as two halves of 25 bits, from a word of c1
+__device__ __forceinline__ u64 modup_factor(u64 x, u64 inv, u64 inv_s, u64 q) {
+    const u64 t = mul_shoup(x, inv, inv_s, q);
+    return (t >> 25) << 32 | (t & 0x1ffffffu);
 }
 
 // LDS of a block that walks limbs, one barrier per pass.  A thread past the barrier of pass t may write the tile of pass
@@ -152,10 +162,7 @@ __global__ __launch_bounds__(KS_THREADS, 2) void k_ks16_fcols(Ks16Const kc, cons
 #pragma unroll
                 for (int i = 0; i < 16; i++) y[a][i] = ld_off(src + R::row(0, i) * 256, off_in);
 #pragma unroll
-                for (int i = 0; i < 16; i++) {
-                    const u64 t = mul_shoup(y[a][i], inv, inv_s, q);
-                    y[a][i] = (t >> 25) << 32 | (t & 0x1ffffffu);
-                }
+                for (int i = 0; i < 16; i++) y[a][i] = modup_factor(y[a][i], inv, inv_s, q);
             }
         }
         put_tab(0);
@@ -183,7 +190,7 @@ __global__ __launch_bounds__(KS_THREADS, 2) void k_ks16_fcols(Ks16Const kc, cons
 #pragma unroll
                     for (int i = 0; i < 16; i++) v[i] = ar.load(ld_off(c1 + (size_t)e * N + R::row(0, i) * 256, off_in));
                 } else {
-                    modup_to(ar, v, hat, nullptr, y, ns, pc);
+                    modup_to(ar, v, hat, (const u64 *)nullptr, y, ns, pc);
                 }
                 put_tab(tnxt);
                 cols_fwd_tab<S>(ar, v, tb, l, c, jj);
@@ -231,6 +238,86 @@ __global__ __launch_bounds__(KS_THREADS, 2) void k_ks16_fcols(Ks16Const kc, cons
             for (int i = 0; i < 16; i++) st_off(out + i * 256, off_out, ar.store_ws_cols(v[i]));
         }
     }
+}
+
+// The same for few ciphertexts, a limb to a block: the factors y_a are formed for the one target, half a column at a time, so that four
+// blocks fit a CU where a walk over limbs leaves room for two.  grid (TILES, beta * ext + l1, n_ct)
+struct ColLdsOne {
+    ulonglong2 tab[COL_TAB];
+    u64 tile[4096];
+};
+template <int S, class A>
+__device__ __forceinline__ void fcols_one_body(const Ks16Const &kc, const PrimeConst *pcs, const PrimeConst &pc, const u64 *c, u64 *out, int row, u32 off_in, u32 off_out,
+                                               ColLdsOne &sh, int col, int jj) {
+    typedef Ring<S> R;
+    constexpr size_t N = R::N;
+    const int l1 = kc.l1, ext = l1 + kc.K, j = row / ext, e = row - j * ext, first = j * kc.alpha, ns = kc.n_src[j];
+    A ar;
+    ar.init(pc);
+    typename A::T v[16];
+    const u64 *hat = kc.hat_sp + (size_t)row * kc.alpha * 2, *hat_mont = kc.hat_mont + (size_t)row * kc.alpha;
+#pragma unroll
+    for (int h = 0; h < 16; h += 8) {
+        u64 y[ENSI_MAX_ALPHA][8];
+#pragma unroll
+        for (int a = 0; a < ENSI_MAX_ALPHA; a++) {
+            if (a < ns) {
+#pragma unroll
+                for (int i = 0; i < 8; i++) y[a][i] = ld_off(c + (size_t)(first + a) * N + R::row(0, h + i) * 256, off_in);
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < ENSI_MAX_ALPHA; a++) {
+            if (a < ns) {
+                const u64 q = load_prime(pcs, first + a).q, inv = as_const(kc.inv)[first + a], inv_s = as_const(kc.inv_s)[first + a];
+#pragma unroll
+                for (int i = 0; i < 8; i++) y[a][i] = modup_factor(y[a][i], inv, inv_s, q);
+            }
+        }
+        modup_half(ar, v + h, hat, hat_mont, y, ns, pc, 0);
+    }
+    cols_fwd_tab<S>(ar, v, sh.tab, sh.tile, col, jj);
+#pragma unroll
+    for (int i = 0; i < 16; i++) st_off(out + i * 256, off_out, ar.store_ws_cols(v[i]));
+}
+template <int S, class W>
+__global__ __launch_bounds__(KS_THREADS, 4) void k_ks16_fcols_one(Ks16Const kc, const PrimeConst *pcs, const u64 *tw_all, const u64 *ct_base, size_t ct_stride,
+                                                                  int limb_stride, u64 *dig) {
+    typedef Ring<S> R;
+    constexpr size_t N = R::N;
+    __shared__ ColLdsOne sh;
+    const int tid = threadIdx.x, c = R::col(tid), jj = R::grp(tid), row = blockIdx.y;
+    const int l1 = kc.l1, ext = l1 + kc.K, rows = kc.beta * ext, limb = row < rows ? row % ext : row - rows, prime = row < rows ? ks_ext_prime(limb, l1, kc.L) : limb;
+    const u64 *c0 = ct_base + (size_t)blockIdx.z * ct_stride + (size_t)blockIdx.x * R::COLS, *c1 = c0 + (size_t)limb_stride * N;
+    u64 *out = dig + ((size_t)blockIdx.z * (rows + l1) + row) * N + (size_t)blockIdx.x * R::COLS;
+    const u32 off_in = (R::row(jj, 0) * 256 + c) * 8, off_out = (16 * jj * 256 + c) * 8;
+    const u64 *tw = tw_all + (size_t)prime * 4 * N;
+    u32 tidx = 0;
+    const int tplace = col_tab_index<S>(tid, &tidx);
+    if (tplace >= 0) sh.tab[tplace] = make_ulonglong2(tw[tidx], tw[N + tidx]);
+    const PrimeConst pc = load_prime(pcs, prime);
+    const int first = row < rows ? row / ext * kc.alpha : 0;
+    if (row >= rows || (limb >= first && limb < first + kc.n_src[row / ext])) {  // P * c0, or the digit's own limb
+        const bool is_c0 = row >= rows;
+        const double pm = as_const(kc.pmod_fp)[2 * limb], pm_p = as_const(kc.pmod_fp)[2 * limb + 1];
+        ArithFp ar;
+        ar.init(pc);
+        double v[16];
+#pragma unroll
+        for (int i = 0; i < 16; i++) v[i] = ar.load(ld_off((is_c0 ? c0 : c1) + (size_t)limb * N + R::row(0, i) * 256, off_in));
+        if (is_c0) {
+#pragma unroll
+            for (int i = 0; i < 16; i++) v[i] = ar.mulmod(v[i], pm, pm_p);
+        }
+        __syncthreads();
+        cols_fwd_tab<S>(ar, v, sh.tab, sh.tile, c, jj);
+#pragma unroll
+        for (int i = 0; i < 16; i++) st_off(out + i * 256, off_out, ar.store_ws_cols(v[i]));
+        return;
+    }
+    __syncthreads();
+    if (limb < l1) fcols_one_body<S, ArithFp>(kc, pcs, pc, c1, out, row, off_in, off_out, sh, c, jj);
+    else fcols_one_body<S, W>(kc, pcs, pc, c1, out, row, off_in, off_out, sh, c, jj);
 }
 
 // ------------------------------------------------------------------ forward row pass (in place)
@@ -322,8 +409,11 @@ struct Inner<ArithFp> {
         }
     };
     static __device__ __forceinline__ double plus(const ArithFp &ar, double a, double b) { return ar.mid(a + b); }
+    // up to nine terms, to be folded afterwards
+    static __device__ __forceinline__ double plus_lazy(const ArithFp &, double a, double b) { return a + b; }
     static __device__ __forceinline__ void add(double &s, u64 x) { s += as_f64(x); }
     static __device__ __forceinline__ void fold(const ArithFp &ar, double &s) { s = ar.mid(s); }
+    static __device__ __forceinline__ void settle(const ArithFp &ar, double &s) { s = ar.mid(s); }  // a sum of mac
 };
 // x = xh 2^30 + xl, k = kh 2^30 + kl: xh kh 2^60 is taken apart into dwords and folded by 2^60 = d, 2^62 = 4 d, like the
 // middle sum m 2^30.  Every half is at most 2^29 (a little more for the high ones): within 6 q before the last fold, 6.6 q for the
@@ -351,8 +441,10 @@ struct Inner<ArithWide> {
         __device__ __forceinline__ int64_t reduced(const ArithWide &ar) const { return folded(ar, h, m, l); }
     };
     static __device__ __forceinline__ int64_t plus(const ArithWide &ar, int64_t a, int64_t b) { return ar.mid(a + b); }
+    static __device__ __forceinline__ int64_t plus_lazy(const ArithWide &, int64_t a, int64_t b) { return a + b; }
     static __device__ __forceinline__ void add(int64_t &, u64) {}
-    static __device__ __forceinline__ void fold(const ArithWide &, int64_t &) {}
+    static __device__ __forceinline__ void fold(const ArithWide &ar, int64_t &s) { s = ar.mid(s); }
+    static __device__ __forceinline__ void settle(const ArithWide &, int64_t &) {}
 };
 template <>
 struct Inner<ArithInt> {
@@ -365,8 +457,10 @@ struct Inner<ArithInt> {
         __device__ __forceinline__ u64 reduced(const ArithInt &ar) const { return mont_reduce(s, ar.q, ar.qneg_inv); }
     };
     static __device__ __forceinline__ u64 plus(const ArithInt &ar, u64 a, u64 b) { return add_mod(a, b, ar.q); }
+    static __device__ __forceinline__ u64 plus_lazy(const ArithInt &ar, u64 a, u64 b) { return add_mod(a, b, ar.q); }
     static __device__ __forceinline__ void add(u64 &, u64) {}
     static __device__ __forceinline__ void fold(const ArithInt &, u64 &) {}
+    static __device__ __forceinline__ void settle(const ArithInt &, u64 &) {}
 };
 
 // Four rows of one limb of both accumulators, by one wave, and their inverse row passes.  Digits and keys are multiplied where they
@@ -561,8 +655,8 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
         if (RAW) {
 #pragma unroll
             for (int i = 0; i < 16; i++) {
-                I::fold(ar, a0[i]);
-                I::fold(ar, a1[i]);
+                I::settle(ar, a0[i]);
+                I::settle(ar, a1[i]);
             }
         }
         g = d.g;
@@ -615,6 +709,123 @@ __global__ __launch_bounds__((64 * InnerBlock<RAW>::WAVES), (RAW ? 2 : InnerShap
     else inner_body<S, RAW, GROUP, C, W>(kc, desc, pc, tw_all, u, prime, e, members, grp, q % TILES4, lds[wave], tw1[wave]);
 }
 
+// ------------------------------------------------ the same for few rotations: a wave to each digit
+// Where the waves of the form above (RAW) do not fill the chip, their serial chain of beta + 1 row passes and two inverse ones is what
+// takes the time.  Here a block takes four rows of one limb of one rotation, each of its waves the row pass and the two products of one digit (the
+// last one P * c0); the products meet in LDS, where the automorphism is applied, and two waves run an inverse row pass each.
+#define INNER_SPLIT_WAVES 5  // up to four digits
+template <int S, class A>
+__device__ __forceinline__ void inner_split_body(const Ks16Const &kc, const RotDesc *desc, const PrimeConst &pc, const u64 *tw_all, u64 *u, int prime, int e, u32 grp,
+                                                 u32 tile, u32 wave, u64 (*lds)[ROW_LDS], ulonglong2 *tw1) {
+    typedef Ring<S> R;
+    typedef RowMap<S> M;
+    typedef Inner<A> I;
+    typedef typename A::T T;
+    constexpr size_t N = R::N;
+    const int lane = threadIdx.x & 63, rho = lane >> 4, j = lane & 15;
+    const int l1 = kc.l1, ext = l1 + kc.K, beta = kc.beta, nd = e < l1 ? beta + 1 : beta;  // P * c0 follows the digits
+    const u64 *tw = tw_all + (size_t)prime * 4 * N;
+    A ar;
+    ar.init(pc);
+    const RotDesc d = load_desc(desc, grp);
+    const u32 rs = tile * 4 + rho, r = M::row(d.g_inv * M::exponent(rs)), carry = M::carry(r, d.g);
+    T *own = (T *)lds[wave];
+    T p1[16];
+    if ((int)wave < nd) {
+        const u64 *src = d.digits + (size_t)((int)wave * ext + e) * N + tile * 1024;
+        const u32 row_off = (rho * 256 + j) * 8, reg_off = reg_pos(0, lane) * 8;
+        T v[16];
+        auto ld = [](const u64 *base, u32 off) { return *(decltype(as_global(base)))((decltype(as_global((const char *)base)))as_global(base) + off); };
+        auto ld_pair = [](const u64 *base, u32 off) { return *(__attribute__((address_space(1))) const word_pair *)((decltype(as_global((const char *)base)))as_global(base) + off); };
+        row_table_to_lds(tw1, tw, tw + N, R::ROWS + rs, rho, j);
+        TwRegs tw2;
+        tw2.load(tw, tw + N, N, rs, j);
+#pragma unroll
+        for (int i = 0; i < 16; i++) v[i] = A::from_bits(ld(src + 16 * i, row_off));
+        wave_lds_fence();
+        row_fwd(ar, v, tw1 + rho * 16, tw2, lds[wave], rho, j);
+        if ((int)wave < beta) {
+            const size_t kstride = (size_t)(kc.L + kc.K) * N;
+            const u64 *key = d.key + 2 * wave * kstride + (size_t)prime * N + tile * 1024;
+#pragma unroll
+            for (int h = 0; h < 16; h += 4) {
+                word_pair k0[2], k1[2];
+#pragma unroll
+                for (int i = 0; i < 2; i++) {
+                    k0[i] = ld_pair(key + reg_pos(h + 2 * i, 0), reg_off);
+                    k1[i] = ld_pair(key + kstride + reg_pos(h + 2 * i, 0), reg_off);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const u64 x = ar.store_ws_fwd(v[h + i]);
+                    T p0 = 0;
+                    p1[h + i] = 0;
+                    I::mac(ar, p0, x, k0[i / 2][i & 1]);
+                    I::mac(ar, p1[h + i], x, k1[i / 2][i & 1]);
+                    own[rpad(rho * 256 + 16 * j + h + i)] = p0;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; i++) {
+                T p0 = 0;
+                I::add(p0, ar.store_ws_fwd(v[i]));
+                own[rpad(rho * 256 + 16 * j + i)] = p0;
+            }
+        }
+    }
+    T a[16];
+    // value i of lane j, position p = 16 j + i of the output row with brev8(p) = brev4(j) + 16 brev4(i), comes from brev8(g brev8(p) + carry)
+    auto sum = [&](int n) {
+        const u32 first = d.g * (__brev((u32)j) >> 28) + carry;
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const u32 brev4_i = (i & 1) * 8 + (i & 2) * 2 + (i & 4) / 2 + (i & 8) / 8;
+            const int at = rpad(rho * 256 + brev8(first + d.g * (16 * brev4_i)));
+            a[i] = ((const T *)lds[0])[at];
+            for (int w = 1; w < n; w++) a[i] = I::plus_lazy(ar, a[i], ((const T *)lds[w])[at]);
+            I::fold(ar, a[i]);
+        }
+    };
+    __syncthreads();
+    if (wave == 0) sum(nd);
+    __syncthreads();
+    if ((int)wave < beta) {
+#pragma unroll
+        for (int i = 0; i < 16; i++) own[rpad(rho * 256 + 16 * j + i)] = p1[i];
+    }
+    __syncthreads();
+    if (wave == 1) sum(beta);
+    __syncthreads();
+    if (wave < 2) {
+        tw += 2 * N;
+        row_table_to_lds(tw1, tw, tw + N, R::ROWS + r, rho, j);
+        TwRegs twi;
+        twi.load(tw, tw + N, N, r, j);
+        wave_lds_fence();
+        row_inv(ar, a, tw1 + rho * 16, twi, lds[wave], rho, j);
+        u64 *o = u + ((size_t)(grp * 2 + wave) * ext + e) * N + (size_t)r * 256 + j;
+#pragma unroll
+        for (int i = 0; i < 16; i++) o[16 * i] = ar.store_ws_inv(a[i]);
+    }
+}
+// grid (8 * ceil(4 TILES * ext / 8) * n_rot), 64 (beta + 1) threads (at least two waves)
+template <int S, class W>
+__global__ __launch_bounds__((64 * INNER_SPLIT_WAVES), (std::is_same<W, ArithInt>::value ? 3 : 4)) void k_ks16_inner_split(Ks16Const kc, const RotDesc *desc, const PrimeConst *pcs, const u64 *tw_all, u64 *u,
+                                                                                u32 n_rot) {
+    __shared__ u64 lds[INNER_SPLIT_WAVES][ROW_LDS];
+    __shared__ ulonglong2 tw1[INNER_SPLIT_WAVES][4 * 16];
+    constexpr u32 TILES4 = 4 * Ring<S>::TILES;
+    const int ext = kc.l1 + kc.K;
+    const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const u32 k = blockIdx.x >> 3, q = k / n_rot * 8 + (blockIdx.x & 7), grp = k % n_rot;
+    if (q >= TILES4 * ext) return;
+    const int e = ext - 1 - (int)(q / TILES4), prime = ks_ext_prime(e, kc.l1, kc.L);
+    const PrimeConst pc = load_prime(pcs, prime);
+    if (e < kc.l1) inner_split_body<S, ArithFp>(kc, desc, pc, tw_all, u, prime, e, grp, q % TILES4, wave, lds, tw1[wave]);
+    else inner_split_body<S, W>(kc, desc, pc, tw_all, u, prime, e, grp, q % TILES4, wave, lds, tw1[wave]);
+}
+
 // ------------------------------------------------------ inverse column pass + ModDown
 // Special limb k of one column tile: inverse column pass and the centred residue of u (P/p_k)^-1, as hi * 2^30 + lo (lo in
 // [0, 2^30), hi signed).
@@ -628,9 +839,34 @@ __device__ __forceinline__ int64_t special_centred(const ArithInt &ar, u64 v, co
     const u64 y = mul_shoup(v, as_const(kc.down_p)[2 * k], as_const(kc.down_p)[2 * k + 1], ar.q);
     return y > ar.q / 2 ? (int64_t)y - (int64_t)ar.q : (int64_t)y;
 }
+// y_k as two int32 words
+__device__ __forceinline__ u64 special_word(int64_t z) { return ((u64)(u32)(int32_t)(z >> 30) << 32) | (u32)(z & 0x3fffffff); }
+// The special limbs of few rotations, a block each: y_k in place of the limb of the accumulator, at the rows where the ciphertext limbs of a
+// column tile have theirs.  grid (TILES, 2 * K, n_rot / members)
+template <int S, class W>
+__global__ __launch_bounds__(KS_THREADS, 4) void k_ks16_specials(Ks16Const kc, const PrimeConst *pcs, const u64 *tw_all, u64 *u) {
+    typedef Ring<S> R;
+    constexpr size_t N = R::N;
+    __shared__ ColLdsOne sh;
+    const int tid = threadIdx.x, c = R::col(tid), jj = R::grp(tid), poly = blockIdx.y / kc.K, k = blockIdx.y - poly * kc.K, ext = kc.l1 + kc.K;
+    u64 *at = u + (((size_t)blockIdx.z * 2 + poly) * ext + kc.l1 + k) * N + (size_t)blockIdx.x * R::COLS;
+    const u64 *tw = tw_all + (size_t)(kc.L + k) * 4 * N + 2 * N;
+    u32 tidx = 0;
+    const int tplace = col_tab_index<S>(tid, &tidx);
+    if (tplace >= 0) sh.tab[tplace] = make_ulonglong2(tw[tidx], tw[N + tidx]);
+    W ar;
+    ar.init(load_prime(pcs, kc.L + k));
+    typename W::T v[16];
+#pragma unroll
+    for (int i = 0; i < 16; i++) v[i] = W::from_bits(ld_off(at + i * 256, (16 * jj * 256 + c) * 8));
+    __syncthreads();
+    cols_inv_tab<S>(ar, v, sh.tab, sh.tile, c, jj);  // (its barrier comes after every thread's reads of the tile)
+#pragma unroll
+    for (int i = 0; i < 16; i++) st_off(at + R::row(0, i) * 256, (R::row(jj, 0) * 256 + c) * 8, special_word(special_centred(ar, v[i], kc, k)));
+}
 // grid (TILES, 2 * parts, n_rot / members): a block brings the special limbs of one column tile of one accumulator back
-// and then `per` ciphertext limbs.  K: the number of special primes.
-template <int S, class W, int K>
+// and then `per` ciphertext limbs.  K: the number of special primes.  READY: k_ks16_specials has brought them back (W has no say then).
+template <int S, class W, int K, bool READY>
 __global__ __launch_bounds__(KS_THREADS, 2) void k_ks16_icols(Ks16Const kc, const RotDesc *desc, const PrimeConst *pcs, const u64 *tw_all, const u64 *u,
                                                               int limb_stride_out, int members, int per) {
     typedef Ring<S> R;
@@ -657,10 +893,16 @@ __global__ __launch_bounds__(KS_THREADS, 2) void k_ks16_icols(Ks16Const kc, cons
     auto put_tab = [&](int buf) {
         if (tplace >= 0) sh.tab[buf][tplace] = tnext;
     };
-    fetch(0);
-    put_tab(0);
-    __syncthreads();
+    fetch(READY ? K : 0);
+    put_tab(READY ? K % 3 : 0);
     u64 y[K][16];
+    if (READY) {
+#pragma unroll
+        for (int k = 0; k < K; k++)
+#pragma unroll
+            for (int i = 0; i < 16; i++) y[k][i] = ld_off(src + (size_t)(l1 + k) * N + R::row(0, i) * 256, off_out);
+    }
+    __syncthreads();
     auto special = [&](u64 *yk, int k) {
         W ar;
         ar.init(load_prime(pcs, kc.L + k));
@@ -672,15 +914,16 @@ __global__ __launch_bounds__(KS_THREADS, 2) void k_ks16_icols(Ks16Const kc, cons
         cols_inv_tab<S>(ar, v, sh.tab[k % 3], sh.tile[k & 1], c, jj);
 #pragma unroll
         for (int i = 0; i < 16; i++) {
-            const int64_t z = special_centred(ar, v[i], kc, k);
-            yk[i] = ((u64)(u32)(int32_t)(z >> 30) << 32) | (u32)(z & 0x3fffffff);
+            yk[i] = special_word(special_centred(ar, v[i], kc, k));
             keep_narrow(yk[i]);
         }
     };
-    special(y[0], 0);
-    if constexpr (K > 1) special(y[1], 1);
-    if constexpr (K > 2) special(y[2], 2);
-    if constexpr (K > 3) special(y[3], 3);
+    if constexpr (!READY) {
+        special(y[0], 0);
+        if constexpr (K > 1) special(y[1], 1);
+        if constexpr (K > 2) special(y[2], 2);
+        if constexpr (K > 3) special(y[3], 3);
+    }
     const RotDesc dl = load_desc(desc, blockIdx.z * members);  // the group's first descriptor carries the destination
     auto out_at = [&](u64 *out, int i) { return (decltype(as_global(out)))((decltype(as_global((char *)out)))as_global(out + R::row(0, i) * 256) + off_out); };
     int tcur = K % 3;
@@ -744,6 +987,20 @@ static int limbs_per_block(long blocks, int limbs) {
     return (int)((limbs + parts - 1) / parts);
 }
 
+// Few rotations, which do not fill the chip.  Whole calls of ensi_rotate, without and with each form, in us, on 2^16 with 10 + 3 limbs (and 16 + 4),
+// 2^14 with 6 + 2 and 2^12 with 3 + 1:
+// Raise with a limb to a block (k_ks16_fcols_one), where the blocks of a limb each are more than the two to a CU that the walking form
+// has room for, and up to three times as many: one rotation 91, 82 (118, 116); two 127, 128; 2^14: no difference.
+#define FCOLS_ONE_MIN 512
+#define FCOLS_ONE_MAX 1536
+// Special limbs first (k_ks16_specials), where otherwise several blocks would bring the same ones back, by column tiles of accumulators: one
+// rotation 91, 84 (118, 105), two 127, 113 (210, 175), eight 348, 343, 16 578, 585; 2^14: one 45, 45, 24 141, 133; a single special prime
+// is not worth the launch (2^12: 36, 39).
+#define SPECIALS_FIRST_MAX 256
+// Inner products with a wave to each digit (k_ks16_inner_split), by waves of the form with one to a tile: on 2^12 one rotation 36, 30, 32
+// 55, 43, 64 (1024 waves) 65, 67; on 2^14 four 55, 53, eight 75, 79; on 2^16 one with 5 limbs (512) 57, 57, with 10 (832) 91, 102.
+#define INNER_SPLIT_MAX 512
+
 // Calls f with the arithmetic of the special primes.
 template <class F>
 static void special_dispatch(const ensi_ctx *ctx, F f) {
@@ -761,9 +1018,15 @@ void ks16_raise(ensi_ctx *ctx, const Ks16Const &kc, const u64 *ct_base, size_t c
         typedef decltype(w) W;
         {
             ScopedTimer t(ctx, "ks_modup_fcols", st);
-            const int per = limbs_per_block((long)TILES * (kc.beta + 1) * n_ct, ext);
-            hipLaunchKernelGGL((k_ks16_fcols<S, W>), dim3(TILES, kc.beta * ((ext + per - 1) / per) + (kc.l1 + per - 1) / per, n_ct), dim3(KS_THREADS), 0, st, kc,
-                               ctx->d_pc, ctx->d_tw, ct_base, ct_stride_words, limb_stride, dig, per);
+            const long limbs = (long)TILES * n_rows * n_ct;
+            if (limbs > FCOLS_ONE_MIN && limbs <= FCOLS_ONE_MAX) {
+                hipLaunchKernelGGL((k_ks16_fcols_one<S, W>), dim3(TILES, n_rows, n_ct), dim3(KS_THREADS), 0, st, kc, ctx->d_pc, ctx->d_tw, ct_base, ct_stride_words,
+                                   limb_stride, dig);
+            } else {
+                const int per = limbs_per_block((long)TILES * (kc.beta + 1) * n_ct, ext);
+                hipLaunchKernelGGL((k_ks16_fcols<S, W>), dim3(TILES, kc.beta * ((ext + per - 1) / per) + (kc.l1 + per - 1) / per, n_ct), dim3(KS_THREADS), 0, st, kc,
+                                   ctx->d_pc, ctx->d_tw, ct_base, ct_stride_words, limb_stride, dig, per);
+            }
         }
         if (rows) {
             ScopedTimer t(ctx, "ks_frows", st);
@@ -789,15 +1052,24 @@ void ks16_switch(ensi_ctx *ctx, const Ks16Const &kc, const RotDesc *d_desc, int 
                 hipLaunchKernelGGL((k_ks16_inner<S, decltype(raw_)::value, decltype(group_)::value, W>), dim3(blocks), dim3(64 * WAVES), 0, st, kc, d_desc, ctx->d_pc,
                                    ctx->d_tw, u, members, (u32)n_grp);
             };
-            if (raw) inner(std::true_type(), std::false_type());
+            if (raw && kc.beta < INNER_SPLIT_WAVES && 4l * TILES * ext * n_rot <= INNER_SPLIT_MAX)
+                hipLaunchKernelGGL((k_ks16_inner_split<S, W>), dim3((4u * TILES * ext + 7) / 8 * 8 * n_rot), dim3(64 * (kc.beta + 1)), 0, st, kc, d_desc, ctx->d_pc,
+                                   ctx->d_tw, u, (u32)n_rot);
+            else if (raw) inner(std::true_type(), std::false_type());
             else if (members > 1) inner(std::false_type(), std::true_type());
             else inner(std::false_type(), std::false_type());
         }
         ScopedTimer t(ctx, "ks_icols_moddown", st);
         const int per = limbs_per_block((long)TILES * 2 * n_grp, kc.l1);
+        const bool ready = kc.K > 1 && per < kc.l1 && (long)TILES * 2 * n_grp <= SPECIALS_FIRST_MAX;
+        if (ready) hipLaunchKernelGGL((k_ks16_specials<S, W>), dim3(TILES, 2 * kc.K, n_grp), dim3(KS_THREADS), 0, st, kc, ctx->d_pc, ctx->d_tw, u);
         auto icols = [&](auto k) {
-            hipLaunchKernelGGL((k_ks16_icols<S, W, decltype(k)::value>), dim3(TILES, 2 * ((kc.l1 + per - 1) / per), n_grp), dim3(KS_THREADS), 0, st, kc, d_desc,
-                               ctx->d_pc, ctx->d_tw, u, limb_stride_out, members, per);
+            if (ready)
+                hipLaunchKernelGGL((k_ks16_icols<S, ArithFp, decltype(k)::value, true>), dim3(TILES, 2 * ((kc.l1 + per - 1) / per), n_grp), dim3(KS_THREADS), 0, st, kc,
+                                   d_desc, ctx->d_pc, ctx->d_tw, u, limb_stride_out, members, per);
+            else
+                hipLaunchKernelGGL((k_ks16_icols<S, W, decltype(k)::value, false>), dim3(TILES, 2 * ((kc.l1 + per - 1) / per), n_grp), dim3(KS_THREADS), 0, st, kc, d_desc,
+                                   ctx->d_pc, ctx->d_tw, u, limb_stride_out, members, per);
         };
         if (kc.K == 1) icols(std::integral_constant<int, 1>{});
         else if (kc.K == 2) icols(std::integral_constant<int, 2>{});

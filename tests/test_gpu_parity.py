@@ -771,6 +771,29 @@ def test_inner_products_of_one_to_eight_digits(params):
     p.close()
 
 
+@pytest.mark.parametrize("params", [(12, 50, 5, 60, 3, 2, 40), (12, 45, 4, 48, 2, 2, 36), (13, 50, 3, 61, 2, 1, 40), (12, 50, 8, 60, 1, 1, 40), (12, 50, 4, 55, 4, 1, 36)],
+                         ids=["4K-wide3", "4K-fp2", "8K-61bit2", "4K-eight-digits", "4K-55bit4"])
+def test_rotations_of_few_and_more_ciphertexts(params):
+    """The forms of the key switch that few rotations take (a limb to a block, special limbs first, a wave to each digit) and the
+    ones beyond, around the batch sizes where they change, for every kind and number of special primes."""
+    p = Pair(params)
+    steps = [1, -1, p.n // 2]
+    o_gks, g_gk = p.galois_keys(steps)
+    o_cts, g_ct = p.encrypt_both(p.rng.uniform(-1, 1, (2, p.n)), p.pr.L)
+    both = stack_cts(o_cts)
+    want = np.stack([stack_cts([p.o.rotate(c, o_gks[st]) for c in o_cts]) for st in steps])
+    for n in (1, 2, 9, 16, 17, 33, 47, 65, 128, 129):
+        which, st = np.arange(n) % 2, np.arange(n) // 2 % 3
+        batch = p.ctx.ct_import(np.ascontiguousarray(both[which]), g_ct.scale)
+        out = p.ctx.rotate(g_gk, batch, [steps[k] for k in st])
+        assert np.array_equal(out.export(), want[st, which]), n
+        out.free()
+        batch.free()
+    for h in (g_ct, g_gk):
+        h.free()
+    p.close()
+
+
 @pytest.mark.parametrize("log_n,n", [(12, 300), (13, 5), (14, 70), (15, 3), (16, 37)])
 def test_client_transforms_equal_the_length_2n_transform(log_n, n):
     """Encoding and decoding by the kernels of the register transform against the length-2N transform, which a context with
