@@ -330,6 +330,9 @@ extern "C" void ensi_ctx_free(ensi_ctx *ctx) {
         if (sl.host) (void)hipHostFree(sl.host);
         if (sl.ev) (void)hipEventDestroy(sl.ev);
     }
+    if (ctx->side_done) (void)hipEventDestroy(ctx->side_done);
+    if (ctx->side_free) (void)hipEventDestroy(ctx->side_free);
+    if (ctx->side) (void)hipStreamDestroy(ctx->side);
     for (auto &p : ctx->pending) {
         (void)hipEventDestroy(p.second.first);
         (void)hipEventDestroy(p.second.second);
@@ -715,6 +718,15 @@ extern "C" int ensi_ct_checksum(ensi_ctx *ctx, const ensi_ct *ct, uint64_t *sums
     return ENSI_OK;
 }
 
+// The second stream and its events, created on first use.
+static hipError_t side_stream(ensi_ctx *ctx) {
+    hipError_t e = hipSuccess;
+    if (!ctx->side) e = hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking);
+    if (e == hipSuccess && !ctx->side_done) e = hipEventCreateWithFlags(&ctx->side_done, hipEventDisableTiming);
+    if (e == hipSuccess && !ctx->side_free) e = hipEventCreateWithFlags(&ctx->side_free, hipEventDisableTiming);
+    return e;
+}
+
 extern "C" int ensi_encrypt(ensi_ctx *ctx, const ensi_pk *pk, const ensi_pt *pt, const int8_t *v, const int8_t *e0, const int8_t *e1,
                             ensi_ct **out) {
     if (!ctx || !pk || !pt || !out) return ENSI_E_BADARG;
@@ -740,15 +752,23 @@ extern "C" int ensi_encrypt(ensi_ctx *ctx, const ensi_pk *pk, const ensi_pt *pt,
         const size_t chunk_rows = (size_t)std::min(n, per), ws_words = chunk_rows * l1 * N;
         rc = grow(ctx, &ctx->ws_cl, &ctx->ws_cl_words, ws_words + (3 * chunk_rows * N + 7) / 8);
         int8_t *d_small = (int8_t *)(ctx->ws_cl + ws_words);
-        hipError_t e = hipSuccess;
+        hipError_t e = rc ? hipSuccess : side_stream(ctx);
         for (int c0 = 0; c0 < n && !rc && e == hipSuccess; c0 += per) {
             const size_t cn = (size_t)std::min(per, n - c0) * N, at = (size_t)c0 * N;
+            u64 *out_ct = ct->d + (size_t)c0 * 2 * l1 * N;
             e = host_to_device(ctx, d_small, v + at, cn, st);
-            if (e == hipSuccess) e = host_to_device(ctx, d_small + cn, e0 + at, cn, st);
-            if (e == hipSuccess) e = host_to_device(ctx, d_small + 2 * cn, e1 + at, cn, st);
-            if (e == hipSuccess)
-                launch_cl_encrypt(ctx, pk->d_pk, d_small, pt->d + (size_t)c0 * l1 * N, (int)(cn / N), l1, ctx->ws_cl, ct->d + (size_t)c0 * 2 * l1 * N, st);
+            // The errors, which only the last kernel adds, are copied while the mask is transformed and multiplied: on the second stream, once
+            // the chunk before has added its own (10 ciphertexts of 16 limbs: 309 us in one stream, now 261).
+            if (e == hipSuccess) launch_cl_encrypt_mask(ctx, pk->d_pk, d_small, (int)(cn / N), l1, ctx->ws_cl, out_ct, st);
+            if (e == hipSuccess && c0) e = hipStreamWaitEvent(ctx->side, ctx->side_free, 0);
+            if (e == hipSuccess) e = host_to_device(ctx, d_small + cn, e0 + at, cn, ctx->side);
+            if (e == hipSuccess) e = host_to_device(ctx, d_small + 2 * cn, e1 + at, cn, ctx->side);
+            if (e == hipSuccess) e = hipEventRecord(ctx->side_done, ctx->side);
+            if (e == hipSuccess) e = hipStreamWaitEvent(st, ctx->side_done, 0);
+            if (e == hipSuccess) launch_cl_encrypt_add(ctx, d_small + cn, pt->d + (size_t)c0 * l1 * N, (int)(cn / N), l1, out_ct, st);
+            if (e == hipSuccess) e = hipEventRecord(ctx->side_free, st);
         }
+        if (e != hipSuccess && ctx->side) (void)hipStreamSynchronize(ctx->side);  // its copies may not outlive the call
         if (!rc && e == hipSuccess) e = hipStreamSynchronize(st);
         if (!rc && e == hipSuccess) e = hipGetLastError();
         if (rc || e != hipSuccess) {

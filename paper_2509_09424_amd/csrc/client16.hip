@@ -138,7 +138,7 @@ __global__ __launch_bounds__(CL_THREADS) void k_cl_fcols_small(const int8_t *sma
 // kernel scales by) and inverse row pass of each product.  A wave runs four rows of one limb of one of the n polynomials.  The
 // twiddles of both directions and the key words are five times the bytes of the rows themselves: the waves of the n polynomials
 // that share them run next to each other on one XCD (block b runs on XCD b % 8) and find them in its L2.  (Polynomials launched
-// one after the other fetched 540 MB for 10 x 16 limbs: 116 us, now 94.  Waves that keep the twiddles for five polynomials in registers: 100.)
+// one after the other fetched 540 MB for 10 x 16 limbs: 116 us, then 94.  Waves that keep the twiddles for five polynomials in registers: 100.)
 // grid (8 * ceil(4 TILES * limbs / 8) * n); in: [n][limbs][N], out: [n][POLYS][limbs][N] doubles (may be the same array if
 // POLYS is 1)
 template <int S, int POLYS>
@@ -164,6 +164,15 @@ __global__ __launch_bounds__(64, 2) void k_cl_rows_key(const u64 *in, const u64 
     row_table_to_lds(tw1[1], twi, twi + N, R::ROWS + r, rho, j);
     TwRegs tw2;
     tw2.load(twf, twf + N, N, r, j);
+    // The key's rows are read like the polynomial's, a line to sixteen lanes, and brought to the places of the products through LDS: read
+    // in place every load touches 64 lines (10 x 16 limbs, two polynomials: 91 to 95 us so, now 86).
+    u64 kw[16];
+    auto fetch_key = [&](int p) {
+        const u64 *kp = key + ((size_t)p * key_limbs + limb) * N + (size_t)r * 256 + j;
+#pragma unroll
+        for (int i = 0; i < 16; i++) kw[i] = kp[16 * i];
+    };
+    fetch_key(0);
     wave_lds_fence();
     row_fwd(ar, v, tw1[0] + rho * 16, tw2, lds, rho, j);
 #pragma unroll
@@ -171,10 +180,14 @@ __global__ __launch_bounds__(64, 2) void k_cl_rows_key(const u64 *in, const u64 
     tw2.load(twi, twi + N, N, r, j);
 #pragma unroll
     for (int p = 0; p < POLYS; p++) {
-        const u64 *kp = key + ((size_t)p * key_limbs + limb) * N + (size_t)r * 256 + 16 * j;
+#pragma unroll
+        for (int i = 0; i < 16; i++) lds[rpad(rho * 256 + j + 16 * i)] = kw[i];
+        wave_lds_fence();
         double x[16];
 #pragma unroll
-        for (int i = 0; i < 16; i++) x[i] = ar.mid(ar.mulmod_np(v[i], ar.load(kp[i])));
+        for (int i = 0; i < 16; i++) x[i] = ar.mid(ar.mulmod_np(v[i], ar.load(lds[rpad(rho * 256 + 16 * j + i)])));
+        wave_lds_fence();
+        if (p + 1 < POLYS) fetch_key(p + 1);
         row_inv(ar, x, tw1[1] + rho * 16, tw2, lds, rho, j);
         u64 *o = out + (((size_t)z * POLYS + p) * limbs + limb) * N + (size_t)r * 256 + j;
 #pragma unroll
@@ -340,13 +353,18 @@ static void launch_rows_key(ensi_ctx *ctx, const u64 *in, const u64 *key, int ke
     hipLaunchKernelGGL((k_cl_rows_key<S, POLYS>), dim3(tiles * n), dim3(64), 0, st, in, key, key_limbs, limbs, (u32)n, ctx->d_pc, ctx->d_tw, out);
 }
 
-void launch_cl_encrypt(ensi_ctx *ctx, const u64 *d_pk, const int8_t *d_small, const u64 *pt, int n, int limbs, u64 *ws, u64 *ct, hipStream_t st) {
-    const size_t pn = (size_t)n * ctx->N;
+void launch_cl_encrypt_mask(ensi_ctx *ctx, const u64 *d_pk, const int8_t *d_mask, int n, int limbs, u64 *ws, u64 *ct, hipStream_t st) {
     ring_dispatch(ctx->log_n, [&](auto s) {
         constexpr int S = decltype(s)::value, TILES = Ring<S>::TILES;
-        hipLaunchKernelGGL((k_cl_fcols_small<S>), dim3(TILES, limbs, n), dim3(CL_THREADS), 0, st, d_small, ctx->d_pc, ctx->d_tw, ws);
+        hipLaunchKernelGGL((k_cl_fcols_small<S>), dim3(TILES, limbs, n), dim3(CL_THREADS), 0, st, d_mask, ctx->d_pc, ctx->d_tw, ws);
         launch_rows_key<S, 2>(ctx, ws, d_pk, ctx->L, limbs, n, ct, st);
-        hipLaunchKernelGGL((k_cl_icols_add<S>), dim3(TILES, 2 * limbs, n), dim3(CL_THREADS), 0, st, ct, d_small + pn, pn, pt, limbs, ctx->d_pc, ctx->d_tw);
+    });
+}
+void launch_cl_encrypt_add(ensi_ctx *ctx, const int8_t *d_errors, const u64 *pt, int n, int limbs, u64 *ct, hipStream_t st) {
+    ring_dispatch(ctx->log_n, [&](auto s) {
+        constexpr int S = decltype(s)::value;
+        hipLaunchKernelGGL((k_cl_icols_add<S>), dim3(Ring<S>::TILES, 2 * limbs, n), dim3(CL_THREADS), 0, st, ct, d_errors, (size_t)n * ctx->N, pt, limbs, ctx->d_pc,
+                           ctx->d_tw);
     });
 }
 

@@ -275,6 +275,9 @@ struct ensi_ctx {
     std::shared_ptr<DevPool> pool = std::make_shared<DevPool>();
     u64 *ws_cl = nullptr; size_t ws_cl_words = 0;       // client side: one chunk's intermediates
     void *pinned_out = nullptr; size_t pinned_out_bytes = 0;  // decoded slots on their way to the caller
+    // a second stream for copies that run beside the kernels of a call (created on first use), and the events between the two
+    hipStream_t side = nullptr;
+    hipEvent_t side_done = nullptr, side_free = nullptr;
     std::vector<u32> rot_exp;
     std::map<int, ModUpConst> modup;      // by l1
     std::map<int, ModDownConst> moddown;  // by l1
@@ -440,8 +443,9 @@ void launch_pm16_pt_format(ensi_ctx *ctx, const u64 *ntt_form, int n_rows, u64 *
 // the client's side on the register transform (client16.hip): N >= 2^12, ciphertext primes below 2^50
 void launch_cl_encode(ensi_ctx *ctx, const double *d_slots, int n_pt, int n_slots, int slot0, int slot_step, int y0, double scale, int limbs, double2 *ws,
                       u64 *out, hipStream_t st);  // ws: n_pt * N / 2 values
-// d_small: int8 [3][n][N] (mask, two error polynomials); pt: [n][limbs][N]; ws: n * limbs * N words
-void launch_cl_encrypt(ensi_ctx *ctx, const u64 *d_pk, const int8_t *d_small, const u64 *pt, int n, int limbs, u64 *ws, u64 *ct, hipStream_t st);
+// encryption in two parts.  d_mask: int8 [n][N]; ws: n * limbs * N words; d_errors: int8 [2][n][N], added to the ciphertexts with pt: [n][limbs][N]
+void launch_cl_encrypt_mask(ensi_ctx *ctx, const u64 *d_pk, const int8_t *d_mask, int n, int limbs, u64 *ws, u64 *ct, hipStream_t st);
+void launch_cl_encrypt_add(ensi_ctx *ctx, const int8_t *d_errors, const u64 *pt, int n, int limbs, u64 *ct, hipStream_t st);
 // ws: n * use * N words; f: n * N / 2 values
 void launch_cl_decrypt(ensi_ctx *ctx, const u64 *d_s_hat, const u64 *ct, int n, int limbs_alloc, int use, const CrtPair &crt, int slot_begin, int n_slots,
                        double inv_scale, u64 *ws, double2 *f, double *out, hipStream_t st);

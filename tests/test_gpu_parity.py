@@ -782,7 +782,7 @@ def test_rotations_of_few_and_more_ciphertexts(params):
     o_cts, g_ct = p.encrypt_both(p.rng.uniform(-1, 1, (2, p.n)), p.pr.L)
     both = stack_cts(o_cts)
     want = np.stack([stack_cts([p.o.rotate(c, o_gks[st]) for c in o_cts]) for st in steps])
-    for n in (1, 2, 9, 16, 17, 33, 47, 65, 128, 129):
+    for n in (1, 2, 9, 16, 17, 33, 47, 64, 65, 128, 129):
         which, st = np.arange(n) % 2, np.arange(n) // 2 % 3
         batch = p.ctx.ct_import(np.ascontiguousarray(both[which]), g_ct.scale)
         out = p.ctx.rotate(g_gk, batch, [steps[k] for k in st])
