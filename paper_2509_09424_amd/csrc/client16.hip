@@ -174,7 +174,7 @@ __global__ __launch_bounds__(64, 2) void k_cl_rows_key(const u64 *in, const u64 
     };
     fetch_key(0);
     wave_lds_fence();
-    row_fwd(ar, v, tw1[0] + rho * 16, tw2, lds, rho, j);
+    row_fwd<true>(ar, v, tw1[0] + rho * 16, tw2, lds, rho, j);
 #pragma unroll
     for (int i = 0; i < 16; i++) v[i] = ar.mid(v[i]);
     tw2.load(twi, twi + N, N, r, j);

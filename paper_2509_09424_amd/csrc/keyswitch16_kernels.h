@@ -25,10 +25,10 @@
 //
 // Number formats between the kernels (workspaces only, never visible outside the library), by
 // the prime's kind:
-//   PRIME_FP    doubles (exact integers, |x| <= p/2); key: the same
-//   PRIME_WIDE  signed 64-bit integers, |x| <= q/2 + 8 (2^60 - q); transformed digits and the key as two
+//   PRIME_FP    doubles (exact integers, |x| <= p/2; after a forward column pass below 8 p); key: the same
+//   PRIME_WIDE  signed 64-bit integers, |x| <= q/2 + 8 (2^60 - q) (after a forward column pass below 7.5 2^60); transformed digits and the key as two
 //               int32 halves high * 2^30 + low, so that the inner product is multiply-adds of 32-bit words
-//   PRIME_INT   canonical 64-bit residues; key: Montgomery residues
+//   PRIME_INT   canonical 64-bit residues (after a forward column pass below 4 q); key: Montgomery residues
 // Transformed digits and the key are stored in the order a wave holds them in the row pass ("register order"): within
 // the four rows of a wave, value i of lane (rho, j) -- position 16 j + i of row rho -- at reg_pos(i, lane), so that reading
 // them needs no exchange and is contiguous, two values to a load.  The key of element g lies at the positions its words meet before the automorphism:
@@ -105,10 +105,15 @@ __device__ __forceinline__ void modup_half(const ArithInt &, u64 *v, const u64 *
         v[i] = mont_reduce(acc, pc.q, pc.qneg_inv);
     }
 }
+// what the first stage of the column pass asks of the sums
+__device__ __forceinline__ void modup_fold(const ArithFp &ar, double *v) { fold_first(ar, v); }
+template <class A>
+__device__ __forceinline__ void modup_fold(const A &, typename A::T *) {}
 template <class A>
 __device__ __forceinline__ void modup_to(const A &ar, typename A::T *v, const u64 *hat, const u64 *hat_mont, u64 (*y)[16], int ns, const PrimeConst &pc) {
 #pragma unroll
     for (int h = 0; h < 16; h += 8) modup_half(ar, v + h, hat, hat_mont, y, ns, pc, h);
+    modup_fold(ar, v);
 }
 // y_a as two halves of 25 bits, from a word of c1
 __device__ __forceinline__ u64 modup_factor(u64 x, u64 inv, u64 inv_s, u64 q) {
@@ -276,6 +281,7 @@ __device__ __forceinline__ void fcols_one_body(const Ks16Const &kc, const PrimeC
         }
         modup_half(ar, v + h, hat, hat_mont, y, ns, pc, 0);
     }
+    modup_fold(ar, v);
     cols_fwd_tab<S>(ar, v, sh.tab, sh.tile, col, jj);
 #pragma unroll
     for (int i = 0; i < 16; i++) st_off(out + i * 256, off_out, ar.store_ws_cols(v[i]));
@@ -354,7 +360,7 @@ __device__ __forceinline__ void frows_body(u64 *g, size_t ct_stride, int n_here,
 #pragma unroll
             for (int i = 0; i < 16; i++) nv[i] = gt[rho * 256 + j + 16 * i];
         }
-        row_fwd(ar, v, tab, tw2, lds, rho, j);
+        row_fwd<true>(ar, v, tab, tw2, lds, rho, j);
         u64 *go = g + (size_t)c * ct_stride;
 #pragma unroll
         for (int i = 0; i < 16; i += 2) *(word_pair *)(go + reg_pos(i, lane)) = word_pair{ar.store_ws_fwd(v[i]), ar.store_ws_fwd(v[i + 1])};
@@ -555,7 +561,7 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
 #pragma unroll
                     for (int i = 0; i < 16; i++) nv[i] = ld(src + 16 * i, row_off);
                 }
-                row_fwd(ar, v, tab, tw2, lds, rho, j);
+                row_fwd<true>(ar, v, tab, tw2, lds, rho, j);
                 if (jd < beta) {
 #pragma unroll
                     for (int h = 0; h < 16; h += 8) {
@@ -743,7 +749,7 @@ __device__ __forceinline__ void inner_split_body(const Ks16Const &kc, const RotD
 #pragma unroll
         for (int i = 0; i < 16; i++) v[i] = A::from_bits(ld(src + 16 * i, row_off));
         wave_lds_fence();
-        row_fwd(ar, v, tw1 + rho * 16, tw2, lds[wave], rho, j);
+        row_fwd<true>(ar, v, tw1 + rho * 16, tw2, lds[wave], rho, j);
         if ((int)wave < beta) {
             const size_t kstride = (size_t)(kc.L + kc.K) * N;
             const u64 *key = d.key + 2 * wave * kstride + (size_t)prime * N + tile * 1024;

@@ -78,7 +78,7 @@ __device__ __forceinline__ void rows_body(u64 *g, size_t inst_stride, int n_here
         }
         u64 *go = g + (size_t)c * inst_stride;
         if (FWD) {
-            row_fwd(ar, v, tab, tw2, lds, rho, j);
+            row_fwd<false>(ar, v, tab, tw2, lds, rho, j);
 #pragma unroll
             for (int i = 0; i < 16; i++) lds[rpad(rho * 256 + 16 * j + i)] = ar.store_fwd(v[i]);
             wave_lds_fence();

@@ -11,7 +11,8 @@
 //   ArithFp   primes below 2^50: residues are exact integers held in doubles; a product
 //             x*w mod p is  h = x*w; l = fma(x,w,-h); q = rint(x*(w/p)); r = fma(-q,p,h)+l
 //             (exact: h - q*p and l are integers below 2^53).  Values stay within +-8p and
-//             are brought back to |x| <= p/2 with x - rint(x/p)*p between steps.
+//             are brought back to |x| <= p/2 with x - rint(x/p)*p between inverse steps, half of them between
+//             forward ones (fold_first).
 //   ArithWide primes q = 2^60 - d, d < 2^26: signed 64-bit integers.  A multiplier w is stored as two centred residues w and
 //             w 2^32 mod q, each split at 28 bits, so that x = xh 2^32 + xl (xl signed) times w is congruent to
 //             B 2^28 + A with A, B two-term sums of 32 x 32 bit products; B's upper dword times 2^60 is folded with
@@ -99,8 +100,8 @@ struct ArithInt {
     __device__ __forceinline__ u64 store_fwd(T x) const { return csub(csub(x, two_q), q); }
     __device__ __forceinline__ u64 store_inv(T x) const { return csub(x, q); }
     __device__ __forceinline__ u64 store_inv_scaled(T x) const { return mul_shoup(x, ninv, ninv_s, q); }
-    // workspace words after a forward column pass, a whole forward pass and an inverse row pass: the canonical residue
-    __device__ __forceinline__ u64 store_ws_cols(T x) const { return store_fwd(x); }
+    // workspace words after a whole forward pass and an inverse row pass: the canonical residue; after a forward column pass: below 4 q
+    __device__ __forceinline__ u64 store_ws_cols(T x) const { return x; }
     __device__ __forceinline__ u64 store_ws_fwd(T x) const { return store_fwd(x); }
     __device__ __forceinline__ u64 store_ws_inv(T x) const { return store_inv(x); }
     __device__ __forceinline__ void gs_fix(T *) const {}
@@ -170,7 +171,7 @@ struct ArithWide {
         const u32 hi = (u32)(u64)(r >> 30), lo = ((u32)r & 0x3fffffffu) - (1u << 29);
         return ((u64)hi << 32) | lo;
     }
-    __device__ __forceinline__ u64 store_ws_cols(T x) const { return (u64)mid(x); }
+    __device__ __forceinline__ u64 store_ws_cols(T x) const { return (u64)x; }
     __device__ __forceinline__ u64 store_ws_inv(T x) const { return (u64)mid(x); }
 };
 
@@ -222,16 +223,16 @@ struct ArithFp {
     __device__ __forceinline__ u64 store_fwd(T x) const { return canon(x); }
     __device__ __forceinline__ u64 store_inv(T x) const { return canon(x); }
     __device__ __forceinline__ u64 store_inv_scaled(T x) const { return canon(mulmod(x, ninv, ninv_p)); }
-    // workspace words: the bits of the double, |x| <= p/2
+    // workspace words: the bits of the double, |x| <= p/2 (after a forward column pass: below 8 p)
     __device__ __forceinline__ u64 store_ws_fwd(T x) const { return (u64)__double_as_longlong(mid(x)); }
-    __device__ __forceinline__ u64 store_ws_cols(T x) const { return store_ws_fwd(x); }
+    __device__ __forceinline__ u64 store_ws_cols(T x) const { return (u64)__double_as_longlong(x); }
     __device__ __forceinline__ u64 store_ws_inv(T x) const { return store_ws_fwd(x); }
     __device__ __forceinline__ void gs_fix(T *) const {}
-    // a1 2^25 + a0 mod p for |a1| <= 2^53, |a0| <= 2^52
+    // a number congruent to a1 2^25 + a0 mod p for |a1| <= 2^53, |a0| <= 2^52: within p + 2^52
     __device__ __forceinline__ T reduce25(int64_t a1, int64_t a0) const {
         const double x = fma((double)(int)(a1 >> 32), 4294967296.0, (double)(u32)a1) * 33554432.0;
         const double y = fma((double)(int)(a0 >> 32), 4294967296.0, (double)(u32)a0);
-        return mid(fma(-rint(x * pinv), p, x) + y);
+        return fma(-rint(x * pinv), p, x) + y;
     }
     // the same for |a1|, |a0| < 2^60: their dwords are taken apart, |result| <= p + 2^32
     __device__ __forceinline__ T reduce25_long(int64_t a1, int64_t a0) const {
@@ -381,6 +382,18 @@ struct Ring {
     static __device__ __forceinline__ int row(int jj, int i) { return ((i >> (4 - S)) << 4) + (jj << (4 - S)) + (i & ((1 << (4 - S)) - 1)); }
 };
 
+// Brings the first eight of a forward step's values back to their range.  In the step's first stage value i + 8 is multiplied, which leaves
+// it small whatever it was, and added to and subtracted from value i: reducing the ones that are added to is enough.  In units of p (ArithFp,
+// primes just below 2^50; a product of y is within 1/2 + |y| / 4, its quotient's rounding): the first step of a column pass starts within 1 (or, folded, within 1/2 and 5 after
+// the basis conversion) and ends within 6.1, the ones after it start within 1/2 and 7.4 and end within 7.4 again, below the 8 = 2^53
+// that a double holds.  (ArithWide, units of 2^60: 1/2 and 6.9, ending within 6.5, below 7.5.)  Reducing all sixteen took 3 instructions a word
+// more per pass.
+template <class A>
+__device__ __forceinline__ void fold_first(const A &ar, typename A::T *v) {
+#pragma unroll
+    for (int i = 0; i < 8; i++) v[i] = ar.mid(v[i]);
+}
+
 // The first ST stages of a forward step and the last ST of an inverse one, all over the same 15 twiddles.
 template <int ST, class A, class TAB>
 __device__ __forceinline__ void ct_first_tab(const A &ar, typename A::T *v, const TAB &tab) {
@@ -432,10 +445,11 @@ __device__ __forceinline__ void cols_fwd_regs(const A &ar, typename A::T *v, con
         typename A::T *l = (typename A::T *)lds;
         ct_first_tab<S>(ar, v, TwFirst{tw, tws});
 #pragma unroll
-        for (int i = 0; i < 16; i++) l[R::row(jj, i) * R::COLS + c] = ar.mid(v[i]);
+        for (int i = 0; i < 16; i++) l[R::row(jj, i) * R::COLS + c] = v[i];
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < 16; i++) v[i] = l[(16 * jj + i) * R::COLS + c];
+        fold_first(ar, v);
     }
     ct4(ar, v, tw, tws, (1u << S) + jj);
 }
@@ -475,10 +489,11 @@ __device__ __forceinline__ void cols_fwd_tab(const A &ar, typename A::T *v, cons
         typename A::T *l = (typename A::T *)lds;
         ct_first_tab<S>(ar, v, tab);
 #pragma unroll
-        for (int i = 0; i < 16; i++) l[R::row(jj, i) * R::COLS + c] = ar.mid(v[i]);
+        for (int i = 0; i < 16; i++) l[R::row(jj, i) * R::COLS + c] = v[i];
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < 16; i++) v[i] = l[(16 * jj + i) * R::COLS + c];
+        fold_first(ar, v);
     } else {
         __syncthreads();
     }
@@ -518,15 +533,18 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 // tab1: the row's first-step twiddles (row_table_to_lds), tab2: the thread's second-step twiddles, in ct4_tab's order
-template <class A, class TAB1, class TAB2>
+// FROM_COLS: the values are as a forward column pass left them (store_ws_cols), else canonical residues
+template <bool FROM_COLS, class A, class TAB1, class TAB2>
 __device__ __forceinline__ void row_fwd(const A &ar, typename A::T *v, const TAB1 &tab1, const TAB2 &tab2, u64 *lds, int rho, int j) {
     typename A::T *l = (typename A::T *)lds;
+    if (FROM_COLS) fold_first(ar, v);
     ct4_tab(ar, v, tab1);
 #pragma unroll
-    for (int i = 0; i < 16; i++) l[rpad(rho * 256 + j + 16 * i)] = ar.mid(v[i]);
+    for (int i = 0; i < 16; i++) l[rpad(rho * 256 + j + 16 * i)] = v[i];
     wave_lds_fence();
 #pragma unroll
     for (int i = 0; i < 16; i++) v[i] = l[rpad(rho * 256 + 16 * j + i)];
+    fold_first(ar, v);
     ct4_tab(ar, v, tab2);
     wave_lds_fence();
 }

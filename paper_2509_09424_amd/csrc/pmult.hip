@@ -127,7 +127,7 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm16_fcols(PmGroup g, const Prim
     for (int k = 0; k < 16; k++) v[k] = ar.load(src[(size_t)R::row(jj, k) * 256]);
     cols_fwd_regs<S>(ar, v, tw, tw + PM_N, lds, c16, jj);
 #pragma unroll
-    for (int k = 0; k < 16; k++) out[(size_t)(16 * jj + k) * 256] = pm_u64(ar.mid(v[k]));
+    for (int k = 0; k < 16; k++) out[(size_t)(16 * jj + k) * 256] = ar.store_ws_cols(v[k]);
 }
 
 // Row passes and products where (nearly) every source enters one product.  A wave takes four rows of one limb of one
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(64, 2) void k_pm16_rows_mac(PmGroup g, const PrimeC
 #pragma unroll
             for (int i = 0; i < 16; i++) nv[i] = pm_f64(ld_off(s + 16 * i, a_off));
         }
-        row_fwd(ar, v, tab, tw2, lds, rho, j);
+        row_fwd<true>(ar, v, tab, tw2, lds, rho, j);
 #pragma unroll
         for (int i = 0; i < 16; i++) acc[i] += ar.mulmod_np(ar.mid(v[i]), w[i]);
         // a product is below 0.7 q in magnitude: eight of them stay exact in a double
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(64, 2) void k_pm16_rows(u64 *data, int n, int l1, c
 #pragma unroll
             for (int i = 0; i < 16; i++) nv[i] = pm_f64(ld_off(g + ct + in_step * i, FWD ? row_off : reg_off));
         }
-        if (FWD) row_fwd(ar, v, tab, tw2, lds, rho, j);
+        if (FWD) row_fwd<true>(ar, v, tab, tw2, lds, rho, j);
         else row_inv(ar, v, tab, tw2, lds, rho, j);
 #pragma unroll
         for (int i = 0; i < 16; i++) st_off(g + out_step * i, FWD ? reg_off : row_off, pm_u64(ar.mid(v[i])));
