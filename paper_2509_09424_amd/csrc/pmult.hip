@@ -30,6 +30,13 @@
 
 __device__ __forceinline__ double pm_f64(u64 x) { return __longlong_as_double((long long)x); }
 __device__ __forceinline__ u64 pm_u64(double x) { return (u64)__double_as_longlong(x); }
+// two neighbouring words, 16 bytes to a lane
+__device__ __forceinline__ void ld_two(const u64 *base, u32 bytes, double *d) {
+    const word_pair p = *(const word_pair *)((const char *)base + bytes);
+    d[0] = pm_f64(p[0]);
+    d[1] = pm_f64(p[1]);
+}
+__device__ __forceinline__ void st_two(u64 *base, u32 bytes, double x, double y) { *(word_pair *)((char *)base + bytes) = word_pair{pm_u64(x), pm_u64(y)}; }
 
 // ===================================================================== generic path
 // grid (ceil(N/256), 2*l1, n_src): ws_a[slot][c*l1+i][N] <- limb i of component c of the group's distinct source `slot`
@@ -96,13 +103,14 @@ void launch_pm_generic(ensi_ctx *ctx, const PmGroup &g, const u64 *d_consts, con
 
 // ===================================================================== N = 2^12 .. 2^16, fp64 arithmetic
 // Plaintext in the order a wave holds it in the row pass: within the four rows b, lane (rho, j) owns, as its i-th
-// value, position 16 j + i of row rho; that value is stored at b*1024 + i*64 + lane, as a double.
+// value, position 16 j + i of row rho; that value is stored at b*1024 + reg_pos(i, lane), as a double.
 // grid (N / 1024, n_rows)
 __global__ __launch_bounds__(64) void k_pm16_pt_format(const u64 *in, u64 *out, int N) {
     const int tid = threadIdx.x, rho = tid >> 4, j = tid & 15;
     const size_t base = (size_t)blockIdx.y * N + (size_t)blockIdx.x * 1024;
 #pragma unroll
-    for (int i = 0; i < 16; i++) out[base + i * 64 + tid] = pm_u64((double)in[base + rho * 256 + 16 * j + i]);
+    for (int i = 0; i < 16; i += 2)
+        *(word_pair *)(out + base + reg_pos(i, tid)) = word_pair{pm_u64((double)in[base + rho * 256 + 16 * j + i]), pm_u64((double)in[base + rho * 256 + 16 * j + i + 1])};
 }
 void launch_pm16_pt_format(ensi_ctx *ctx, const u64 *ntt_form, int n_rows, u64 *out, hipStream_t st) {
     hipLaunchKernelGGL(k_pm16_pt_format, dim3(ctx->N / 1024, n_rows), dim3(64), 0, st, ntt_form, out, ctx->N);
@@ -160,7 +168,7 @@ __global__ __launch_bounds__(64, 2) void k_pm16_rows_mac(PmGroup g, const PrimeC
     for (int i = 0; i < 16; i++) acc[i] = 0.0;
     const size_t term = (size_t)2 * g.l1 * N, at = (size_t)(p * g.l1 + limb) * N + (size_t)tile * 1024;  // words per source; place in it
     const u64 *a = g.ws_a + at, *b = g.pt + (size_t)limb * N + (size_t)tile * 1024;
-    const u32 a_off = (rho * 256 + j) * 8, b_off = lane * 8;
+    const u32 a_off = (rho * 256 + j) * 8, b_off = reg_pos(0, lane) * 8;
     auto slot_and_pt = [&](int t) { return as_const((const u64 *)(g.terms + t))[1]; };
     if (t0 < t1) {
         const u64 *s = a + (slot_and_pt(t0) >> 32) * term;
@@ -173,7 +181,7 @@ __global__ __launch_bounds__(64, 2) void k_pm16_rows_mac(PmGroup g, const PrimeC
         const u64 *w_src = b + (size_t)(u32)slot_and_pt(t) * g.pt_limbs * N;
         double v[16], w[16];
 #pragma unroll
-        for (int i = 0; i < 16; i++) w[i] = pm_f64(ld_off(w_src + 64 * i, b_off));
+        for (int i = 0; i < 16; i += 2) ld_two(w_src + reg_pos(i, 0), b_off, w + i);
 #pragma unroll
         for (int i = 0; i < 16; i++) v[i] = nv[i];
         if (t + 1 < t1) {
@@ -203,7 +211,7 @@ __global__ __launch_bounds__(64, 2) void k_pm16_rows_mac(PmGroup g, const PrimeC
 
 // Where sources enter several products each, their row passes are run once (k_pm16_rows<true>), the products are formed
 // on whole tiles (k_pm16_mac) and the sums brought back (k_pm16_rows<false>).  Between these the words of a wave's four rows
-// are in register order: value i of lane l at 64 i + l.
+// are in register order (reg_pos).
 // grid (4 TILES, 2 * l1 * ceil(n / PM_ROWS_GROUP)): a wave takes four rows of polynomial-limb y for up to PM_ROWS_GROUP of the n
 // ciphertexts (the twiddles are fetched once), in place.
 #define PM_ROWS_GROUP 8
@@ -223,27 +231,41 @@ __global__ __launch_bounds__(64, 2) void k_pm16_rows(u64 *data, int n, int l1, c
     TwRegs tw2;
     tw2.load(tw, tw + N, N, r, j);
     const ulonglong2 *tab = tw1 + rho * 16;
-    const u32 row_off = (rho * 256 + j) * 8, reg_off = lane * 8;
-    constexpr int in_step = FWD ? 16 : 64, out_step = FWD ? 64 : 16;
+    const u32 row_off = (rho * 256 + j) * 8, reg_off = reg_pos(0, lane) * 8;
     const size_t ct = (size_t)2 * l1 * N;
     u64 *g = data + c0 * ct + (size_t)y * N + (size_t)blockIdx.x * 1024;
     const int n_here = min(PM_ROWS_GROUP, n - c0);
     double v[16], nv[16];
+    auto fetch = [&](const u64 *src) {
 #pragma unroll
-    for (int i = 0; i < 16; i++) nv[i] = pm_f64(ld_off(g + in_step * i, FWD ? row_off : reg_off));
+        for (int i = 0; i < 16; i += 2) {
+            if (FWD) {
+                nv[i] = pm_f64(ld_off(src + 16 * i, row_off));
+                nv[i + 1] = pm_f64(ld_off(src + 16 * i + 16, row_off));
+            } else {
+                ld_two(src + reg_pos(i, 0), reg_off, nv + i);
+            }
+        }
+    };
+    fetch(g);
     wave_lds_fence();
 #pragma unroll 1
     for (int c = 0; c < n_here; c++) {
 #pragma unroll
         for (int i = 0; i < 16; i++) v[i] = nv[i];
-        if (c + 1 < n_here) {
-#pragma unroll
-            for (int i = 0; i < 16; i++) nv[i] = pm_f64(ld_off(g + ct + in_step * i, FWD ? row_off : reg_off));
-        }
+        if (c + 1 < n_here) fetch(g + ct);
         if (FWD) row_fwd<true>(ar, v, tab, tw2, lds, rho, j);
         else row_inv(ar, v, tab, tw2, lds, rho, j);
 #pragma unroll
-        for (int i = 0; i < 16; i++) st_off(g + out_step * i, FWD ? reg_off : row_off, pm_u64(ar.mid(v[i])));
+        for (int i = 0; i < 16; i += 2) {
+            const double x = ar.mid(v[i]), y = ar.mid(v[i + 1]);
+            if (FWD) {
+                st_two(g + reg_pos(i, 0), reg_off, x, y);
+            } else {
+                st_off(g + 16 * i, row_off, pm_u64(x));
+                st_off(g + 16 * i + 16, row_off, pm_u64(y));
+            }
+        }
         g += ct;
     }
 }
@@ -263,7 +285,7 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm16_mac(PmGroup g, const PmEntr
     ar.init(load_prime(pcs, limb));
     const size_t poly = (size_t)g.l1 * N;
     const u64 *a = g.ws_a + (size_t)limb * N + (size_t)tile * 1024, *b = g.pt + (size_t)limb * N + (size_t)tile * 1024;
-    const u32 off = threadIdx.x * 8;
+    const u32 off = threadIdx.x * 16;  // two words to a load: values i and i + 1 of a thread are neighbours
     double acc[PM_MAC_OUT][2][4];
 #pragma unroll
     for (int o = 0; o < PM_MAC_OUT; o++)
@@ -274,9 +296,9 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm16_mac(PmGroup g, const PmEntr
     auto fetch = [&](int slot) {
         const u64 *s = a + (size_t)slot * 2 * poly;
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-            x[0][i] = pm_f64(ld_off(s + 256 * i, off));
-            x[1][i] = pm_f64(ld_off(s + poly + 256 * i, off));
+        for (int i = 0; i < 4; i += 2) {
+            ld_two(s + 256 * i, off, x[0] + i);
+            ld_two(s + poly + 256 * i, off, x[1] + i);
         }
     };
     auto entry = [&](int e, int w) { return as_const((const int32_t *)(entries + e))[w]; };
@@ -289,7 +311,7 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm16_mac(PmGroup g, const PmEntr
             const int pt = entry(e, 1 + o);
             if (pt >= 0) {
 #pragma unroll
-                for (int i = 0; i < 4; i++) w[o][i] = pm_f64(ld_off(b + (size_t)pt * g.pt_limbs * N + 256 * i, off));
+                for (int i = 0; i < 4; i += 2) ld_two(b + (size_t)pt * g.pt_limbs * N + 256 * i, off, w[o] + i);
             }
         }
 #pragma unroll
@@ -325,9 +347,9 @@ __global__ __launch_bounds__(PM_THREADS) void k_pm16_mac(PmGroup g, const PmEntr
         if (out_idx < (u32)g.n_out) {
             u64 *d = g.ws_b + (size_t)out_idx * 2 * poly + (size_t)limb * N + (size_t)tile * 1024;
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                st_off(d + 256 * i, off, pm_u64(ar.mid(acc[o][0][i])));
-                st_off(d + poly + 256 * i, off, pm_u64(ar.mid(acc[o][1][i])));
+            for (int i = 0; i < 4; i += 2) {
+                st_two(d + 256 * i, off, ar.mid(acc[o][0][i]), ar.mid(acc[o][0][i + 1]));
+                st_two(d + poly + 256 * i, off, ar.mid(acc[o][1][i]), ar.mid(acc[o][1][i + 1]));
             }
         }
     }
