@@ -165,14 +165,15 @@ __global__ __launch_bounds__(64, 2) void k_cl_rows_key(const u64 *in, const u64 
     TwRegs tw2;
     tw2.load(twf, twf + N, N, r, j);
     // The key's rows are read like the polynomial's, a line to sixteen lanes, and brought to the places of the products through LDS: read
-    // in place every load touches 64 lines (10 x 16 limbs, two polynomials: 91 to 95 us so, now 86).
+    // in place every load touches 64 lines (10 x 16 limbs, two polynomials: 91 to 95 us so, now 86; one polynomial of few limbs waits for
+    // the exchange instead, 12 us so and 14).
     u64 kw[16];
     auto fetch_key = [&](int p) {
         const u64 *kp = key + ((size_t)p * key_limbs + limb) * N + (size_t)r * 256 + j;
 #pragma unroll
         for (int i = 0; i < 16; i++) kw[i] = kp[16 * i];
     };
-    fetch_key(0);
+    if (POLYS > 1) fetch_key(0);
     wave_lds_fence();
     row_fwd<true>(ar, v, tw1[0] + rho * 16, tw2, lds, rho, j);
 #pragma unroll
@@ -180,13 +181,21 @@ __global__ __launch_bounds__(64, 2) void k_cl_rows_key(const u64 *in, const u64 
     tw2.load(twi, twi + N, N, r, j);
 #pragma unroll
     for (int p = 0; p < POLYS; p++) {
+        if (POLYS > 1) {
 #pragma unroll
-        for (int i = 0; i < 16; i++) lds[rpad(rho * 256 + j + 16 * i)] = kw[i];
-        wave_lds_fence();
+            for (int i = 0; i < 16; i++) lds[rpad(rho * 256 + j + 16 * i)] = kw[i];
+            wave_lds_fence();
+#pragma unroll
+            for (int i = 0; i < 16; i++) kw[i] = lds[rpad(rho * 256 + 16 * j + i)];
+            wave_lds_fence();
+        } else {
+            const u64 *kp = key + ((size_t)p * key_limbs + limb) * N + (size_t)r * 256 + 16 * j;
+#pragma unroll
+            for (int i = 0; i < 16; i++) kw[i] = kp[i];
+        }
         double x[16];
 #pragma unroll
-        for (int i = 0; i < 16; i++) x[i] = ar.mid(ar.mulmod_np(v[i], ar.load(lds[rpad(rho * 256 + 16 * j + i)])));
-        wave_lds_fence();
+        for (int i = 0; i < 16; i++) x[i] = ar.mid(ar.mulmod_np(v[i], ar.load(kw[i])));
         if (p + 1 < POLYS) fetch_key(p + 1);
         row_inv(ar, x, tw1[1] + rho * 16, tw2, lds, rho, j);
         u64 *o = out + (((size_t)z * POLYS + p) * limbs + limb) * N + (size_t)r * 256 + j;
