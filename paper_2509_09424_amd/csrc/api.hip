@@ -741,6 +741,8 @@ extern "C" int ensi_ct_checksum(ensi_ctx *ctx, const ensi_ct *ct, uint64_t *sums
     return ENSI_OK;
 }
 
+#define ENCRYPT_BESIDE_BYTES 16384  // of one of the small polynomials of a chunk: beyond it the errors travel on the second stream
+
 // The second stream and its events, created on first use.
 static hipError_t side_stream(ensi_ctx *ctx) {
     hipError_t e = hipSuccess;
@@ -775,23 +777,26 @@ extern "C" int ensi_encrypt(ensi_ctx *ctx, const ensi_pk *pk, const ensi_pt *pt,
         const size_t chunk_rows = (size_t)std::min(n, per), ws_words = chunk_rows * l1 * N;
         rc = grow(ctx, &ctx->ws_cl, &ctx->ws_cl_words, ws_words + (3 * chunk_rows * N + 7) / 8);
         int8_t *d_small = (int8_t *)(ctx->ws_cl + ws_words);
-        hipError_t e = rc ? hipSuccess : side_stream(ctx);
+        // The errors, which only the last kernel adds, are copied while the mask is transformed and multiplied: on the second stream, once the chunk
+        // before has added its own.  One stream against two, nothing else changed, in us: polynomials of 64 KiB of 16 limbs 101, 80 (one) and 304, 250
+        // (ten); 24 and 32 KiB of three limbs 94, 71 and 91, 72.  Copies of up to 16 KiB do not go through the copy engine: 60, 63.
+        const bool beside = chunk_rows * N > ENCRYPT_BESIDE_BYTES;
+        hipError_t e = rc || !beside ? hipSuccess : side_stream(ctx);
+        hipStream_t st_e = beside ? ctx->side : st;
         for (int c0 = 0; c0 < n && !rc && e == hipSuccess; c0 += per) {
             const size_t cn = (size_t)std::min(per, n - c0) * N, at = (size_t)c0 * N;
             u64 *out_ct = ct->d + (size_t)c0 * 2 * l1 * N;
             e = host_to_device(ctx, d_small, v + at, cn, st);
-            // The errors, which only the last kernel adds, are copied while the mask is transformed and multiplied: on the second stream, once
-            // the chunk before has added its own (10 ciphertexts of 16 limbs: 309 us in one stream, now 261).
             if (e == hipSuccess) launch_cl_encrypt_mask(ctx, pk->d_pk, d_small, (int)(cn / N), l1, ctx->ws_cl, out_ct, st);
-            if (e == hipSuccess && c0) e = hipStreamWaitEvent(ctx->side, ctx->side_free, 0);
-            if (e == hipSuccess) e = host_to_device(ctx, d_small + cn, e0 + at, cn, ctx->side);
-            if (e == hipSuccess) e = host_to_device(ctx, d_small + 2 * cn, e1 + at, cn, ctx->side);
-            if (e == hipSuccess) e = hipEventRecord(ctx->side_done, ctx->side);
-            if (e == hipSuccess) e = hipStreamWaitEvent(st, ctx->side_done, 0);
+            if (e == hipSuccess && beside && c0) e = hipStreamWaitEvent(st_e, ctx->side_free, 0);
+            if (e == hipSuccess) e = host_to_device(ctx, d_small + cn, e0 + at, cn, st_e);
+            if (e == hipSuccess) e = host_to_device(ctx, d_small + 2 * cn, e1 + at, cn, st_e);
+            if (e == hipSuccess && beside) e = hipEventRecord(ctx->side_done, st_e);
+            if (e == hipSuccess && beside) e = hipStreamWaitEvent(st, ctx->side_done, 0);
             if (e == hipSuccess) launch_cl_encrypt_add(ctx, d_small + cn, pt->d + (size_t)c0 * l1 * N, (int)(cn / N), l1, out_ct, st);
-            if (e == hipSuccess) e = hipEventRecord(ctx->side_free, st);
+            if (e == hipSuccess && beside && c0 + per < n) e = hipEventRecord(ctx->side_free, st);
         }
-        if (e != hipSuccess && ctx->side) (void)hipStreamSynchronize(ctx->side);
+        if (e != hipSuccess && beside && ctx->side) (void)hipStreamSynchronize(ctx->side);
         if (!rc) e = wait_client(st, e);
         if (!rc && e == hipSuccess) e = hipGetLastError();
         if (rc || e != hipSuccess) {

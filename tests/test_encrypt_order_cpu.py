@@ -51,3 +51,21 @@ def test_nothing_of_a_failed_call_runs_beside_the_next(tmp_path, call, fail):
     assert any(c[0] == "copy" and c[1] != "(nil)" for c in calls[at["second"]:])
     crossing = [(calls[i], calls[k]) for i, k in pairs if i < at["second"] < k]
     assert not crossing, crossing[:3]
+
+
+def test_small_batches_keep_to_one_stream(tmp_path):
+    """Up to 16 KiB a polynomial a second stream costs more than it hides; whole calls at both sides of the line."""
+    calls = simhip.run(tmp_path, """
+ctx = binding.Context(12, 36, 3, 37, 1, 1, 30, seed=1)
+sk, pk = ctx.keygen(None, None, 3)
+pts = [ctx.pt_import(np.zeros((n, ctx.N), dtype=np.int64), 3) for n in (4, 5)]
+zero = np.zeros((5, ctx.N), dtype=np.int8)
+for n, pt in zip((4, 5), pts):
+    mark("%d" % n)
+    ctx.encrypt(pk, pt, zero[:n], zero[:n], zero[:n])
+mark("end")
+""")
+    at = {c[1]: k for k, c in enumerate(calls) if c[0] == "mark"}
+    streams = [{c[1] for c in calls[at[a]:at[b]] if c[0] in ("copy", "launch")} for a, b in (("4", "5"), ("5", "end"))]
+    assert [len(s) for s in streams] == [1, 2] and not any(c[0] in ("record", "wait") and c[1] != "(nil)" for c in calls[at["4"]:at["5"]])
+    assert not [p for p in simhip.unordered(calls) if at["4"] < p[1] < at["5"]]
