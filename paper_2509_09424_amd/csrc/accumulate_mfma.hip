@@ -786,7 +786,10 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 12 ? 3 : 2) void k_accumulate_
 //   384 x 512 69, 55; 768, 669; 7.81, 7.11            450 x 512 (here all operands in LDS) 70, 72; 791, 797; 8.11, 8.10
 //   600 x 40 58, 33; 675, 260; 7.05, 2.72             1024 x 384 138, 92; 1290, 866; 13.4, 8.7     2560 x 384 325, 223; 2880, 1820
 // With the rescale (5 limbs of 2^14 and 11 of 2^16, both layers): 64 operands 442, 120 and 3.28, 1.10; 200 x 200 555, 527 and 3.99, 4.50.
-static bool am_direct(int n_v, int m, bool rescale) { return rescale ? n_v <= 128 : n_v <= AMD_MAX_OPERANDS || m <= AMD_MAX_OUTPUTS; }
+// Its digits are of 8 bits and its weights signed: weights prepared for the digits of AM_POS7 are not for it, whatever the sizes.
+static bool am_direct(int mode, int n_v, int m, bool rescale) {
+    return mode != AM_POS7 && (rescale ? n_v <= 128 : n_v <= AMD_MAX_OPERANDS || m <= AMD_MAX_OUTPUTS);
+}
 
 template <int P, int MODE>
 static void am_launch_direct(ensi_ctx *ctx, hipStream_t st, const u64 *xbase, u32 xstride, int n_v, int n_kpad, const v4i *wfrag, const void *bias, int m,
@@ -818,7 +821,7 @@ static void am_launch_direct(ensi_ctx *ctx, hipStream_t st, const u64 *xbase, u3
     typedef std::false_type No;
     typedef std::true_type Yes;
     if (d_rescale) {
-        if constexpr (MODE == AM_FP8) launch(No(), Four(), Yes());  // (the rescale is fused for primes below 2^50 only)
+        if constexpr (MODE == AM_FP8) launch(No(), Four(), Yes());  // (the only mode that comes here with a rescale)
     } else if (n_v <= AMD_CHUNKED_MIN || m > AMD_MAX_OUTPUTS)
         launch(No(), Four(), No());
     else if (m <= 128)
@@ -884,6 +887,10 @@ static int am_slice_ctiles(int ctiles, int l1, int n_kpad, int planes) {
 int launch_accumulate_mfma(ensi_ctx *ctx, const u64 *xbase, size_t xstride, int n_v, int n_kpad, const int8_t *d_wt, const int32_t *d_bias,
                            const double *d_bias_fp, int planes, int mode, int m, int l1, int limb_stride_in, u64 *out, int limb_stride_out, const double *d_rescale,
                            hipStream_t st) {
+    if (d_rescale && mode == AM_INT8) {  // (the rescale on the way works in double precision)
+        ctx->err = "the rescale is fused with the signed sums for primes below 2^50 only";
+        return ENSI_E_BADARG;
+    }
     const int ctiles = ctx->N / AM_TILE_N;
     const int n_tiles_m = (m + AM_TILE_M - 1) / AM_TILE_M;
     int &n_cu = ctx->n_cu;
@@ -898,7 +905,7 @@ int launch_accumulate_mfma(ensi_ctx *ctx, const u64 *xbase, size_t xstride, int 
     const int m_group = 8;  // 8 output tiles x 4 word tiles in flight per XCD
     const int P = planes <= 5 ? 5 : 7;
     const void *bias = mode == AM_INT8 ? (const void *)d_bias : (const void *)d_bias_fp;
-    if (am_direct(n_v, m, d_rescale != nullptr)) {
+    if (am_direct(mode, n_v, m, d_rescale != nullptr)) {
 #define AMD_LAUNCH(PL, MODE) \
     am_launch_direct<PL, MODE>(ctx, st, xbase, (u32)xstride, n_v, n_kpad, wf, bias, m, l1, limb_stride_in, out, limb_stride_out, n_tiles_m, d_rescale)
         if (mode == AM_INT8) AMD_LAUNCH(7, AM_INT8);

@@ -84,15 +84,18 @@ def mark(text): sim.simhip_mark(text.encode())
 """ % ROOT
 
 
-def run(tmp_path, body):
-    """Runs a Python program on the simulated runtime and returns what it called: a list of [what, stream, ...]."""
+def run(tmp_path, body=None, command=None):
+    """Runs a Python program, or a command, on the simulated runtime and returns what it called: a list of [what, stream, ...]."""
     src, lib, log, prog = tmp_path / "simhip.cpp", tmp_path / "libsimhip.so", tmp_path / "log", tmp_path / "prog.py"
     if not lib.exists():
         src.write_text(SOURCE)
         subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", str(src), "-o", str(lib)], check=True)
-    prog.write_text(PREAMBLE + body)
+    if body is not None:
+        prog.write_text(PREAMBLE + body)
+        command = [sys.executable, str(prog)]
+    log.write_text("")
     env = dict(os.environ, SIMHIP=str(lib), SIMHIP_LOG=str(log), LD_PRELOAD=str(lib) + ":" + os.environ.get("LD_PRELOAD", ""))
-    r = subprocess.run([sys.executable, str(prog)], env=env, capture_output=True, text=True, timeout=120)
+    r = subprocess.run(command, env=env, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
     return [line.split() for line in log.read_text().splitlines()]
 
