@@ -624,7 +624,9 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
 #define AMD_MAX_OUTPUTS 384
 #define AMD_CHUNKED_MIN 256  // operands from which they pass through LDS in chunks, where the outputs allow it: 300 and 8 outputs 0.20 -> 0.14 ms
                              // (2^14, 6 limbs), 300 and 256 0.38 -> 0.32; 200 and 256 0.22 -> 0.25
+#define AMD_MAX_RESCALED 128  // operands that are rescaled on the way
 #define AMD_CHUNK_STEPS 8
+#define AM_LDS (160 << 10)  // of a CU
 #define AMD_AHEAD 4  // steps whose words, or weights, are requested together
 // RESCALE: the scalar-multiply + rescale step is applied to the operands on the way, as in k_byte_planes_rescale (fc: its constants); the limb that it
 // drops is read and rescaled once for every limb that stays, which pays for few operands only.
@@ -779,16 +781,39 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 12 ? 3 : 2) void k_accumulate_
     }
 }
 
-// Whether a product of n_v operands and m outputs takes the kernel above.  The other way keeps planes in memory, split for whole groups of 256
-// operands, and contracts them for whole tiles of 256 outputs.  Whole calls, planes in memory against here, on 3 limbs of the 2^12 ring in us, 6
-// of 2^14 in us and 16 of 2^16 in ms:
-//   operands x outputs   64 x 64 26, 8    64 x 40 220, 40     64 x 256 2.66, 1.47   256 x 1024 86, 68; 871, 686; 8.64, 6.90
-//   384 x 512 69, 55; 768, 669; 7.81, 7.11            450 x 512 (here all operands in LDS) 70, 72; 791, 797; 8.11, 8.10
-//   600 x 40 58, 33; 675, 260; 7.05, 2.72             1024 x 384 138, 92; 1290, 866; 13.4, 8.7     2560 x 384 325, 223; 2880, 1820
-// With the rescale (5 limbs of 2^14 and 11 of 2^16, both layers): 64 operands 442, 120 and 3.28, 1.10; 200 x 200 555, 527 and 3.99, 4.50.
+static bool amd_chunked(int n_v, int m) { return n_v > AMD_CHUNKED_MIN && m <= AMD_MAX_OUTPUTS; }
+// LDS of a block: the digits of `steps` steps and each wave's results.
+static constexpr int amd_lds(int planes, int steps, int waves) { return steps * planes * 1024 + waves * 32 * AM_OROW; }
+
+// Whether a product of n_v operands and m outputs over `tiles` word tiles takes the kernel above.  The other way keeps planes in memory, split for
+// whole groups of 256 operands, and contracts them for whole tiles of 256 outputs, item by item on all CUs.  Whole calls, this way over that one (the lower
+// the better), on 2 limbs of the 2^10 ring (128 tiles), 3 of 2^11 (384), 3 of 2^12 (768), 6 of 2^14 (6144) and 16 of 2^16 (65536), primes of 50 bits:
+//   operands x outputs   64 x 8 .38 .25 .19 .15 .15      64 x 512 .74 .56 .48 .48 .55      64 x 4096 1.32 .83 .60 .53 .50
+//                        256 x 8 .50 .32 .51 .43 .42     256 x 1024 1.36 .82 .82 .71 .78   256 x 4096 1.95 1.03 1.00 .84 .84
+//                        384 x 384 .70 .73 .64 .59 .69   384 x 1024 1.42 1.25 .94 .91 .94  384 x 4096 1.86 1.32 .93 .93 1.06
+//                        1024 x 8 .83 .46 .47 .38 .41    1024 x 384 1.00 .83 .60 .63 .64   4096 x 384 1.06 .75 .62 .61
+// A block runs through all outputs of its word tile: what costs is CUs that have no block, or none in the last round, as long as that takes.  m times the idle
+// share of the rounds is a measure of it.
+//   - Few outputs (a block of 32 a wave): as many tiles as three quarters of the CUs, or few enough operands.
+//   - All operands in LDS, fewer tiles than CUs: up to 480 idle outputs (16 x 1024, 128 tiles: .83; 128 x 1024: 1.04), of more than 128 operands 192
+//     (384 x 768, 192 tiles: .92; 384 x 1024: 1.10) or 384 outputs in all.  With as many tiles as CUs: up to 128 operands always;
+//     two blocks to a CU: up to 512 idle outputs, 640 where the planes take a second group of operands (256 x 2048, 640 tiles: .95; 256 x 4096: 1.05);
+//     one block to a CU: up to 64 (257 x 1024, 576 tiles: 1.12; 257 x 640: .97), and up to 1.4 million weights (6 limbs of 2^14: 384 x 3072 .92, 350 x 4096
+//     .94, 384 x 4096 .97, 257 x 6144 1.03, 384 x 6144 1.14; 16 of 2^16: .98, 1.02, 1.05, 1.01, 1.10).
+//   - With the rescale: up to 128 operands as above (16 limbs of 2^16, 128 x 512 .90, 128 x 4096 .74; 200 x 200 1.13).
 // Its digits are of 8 bits and its weights signed: weights prepared for the digits of AM_POS7 are not for it, whatever the sizes.
-static bool am_direct(int mode, int n_v, int m, bool rescale) {
-    return mode != AM_POS7 && (rescale ? n_v <= 128 : n_v <= AMD_MAX_OPERANDS || m <= AMD_MAX_OUTPUTS);
+bool am_direct(int n_cu, int tiles, int planes, int mode, int n_v, int m, bool rescale) {
+    if (mode == AM_POS7 || (rescale && n_v > AMD_MAX_RESCALED)) return false;
+    if (amd_chunked(n_v, m)) return 4l * tiles >= 3l * n_cu || n_v <= 512 + 2 * tiles;
+    if (n_v > AMD_MAX_OPERANDS) return false;
+    const auto idle = [&](int places, long outputs) {  // whether the places of the last round that are empty would have done more than `outputs`
+        const long all = (long)((tiles + places - 1) / places) * places;
+        return m * (all - tiles) > outputs * all;
+    };
+    if (n_v <= 128) return tiles >= n_cu || !idle(n_cu, 480);
+    if (tiles < n_cu) return m <= AMD_MAX_OUTPUTS || !idle(n_cu, 192);
+    if (2 * amd_lds(planes, (n_v + AM_TILE_K - 1) / AM_TILE_K, 4) <= AM_LDS) return !idle(2 * n_cu, n_v > 256 ? 640 : 512);
+    return !idle(n_cu, 64) && (long)n_v * m <= 1400000;
 }
 
 template <int P, int MODE>
@@ -804,7 +829,7 @@ static void am_launch_direct(ensi_ctx *ctx, hipStream_t st, const u64 *xbase, u3
     auto launch = [&](auto chunked, auto waves, auto rescale) {
         constexpr bool CHUNKED = decltype(chunked)::value, RESCALE = decltype(rescale)::value;
         constexpr int WAVES = decltype(waves)::value;
-        auto lds = [](int s) { return s * P * 1024 + WAVES * 32 * AM_OROW; };
+        auto lds = [](int s) { return amd_lds(P, s, WAVES); };
         bool &attr_set = ctx->am_direct_attr_set[((2 * MODE + (P == 5 ? 0 : 1)) * 4 + (CHUNKED ? WAVES / 4 : 0)) * 2 + RESCALE];
         if (!attr_set) {
             (void)hipFuncSetAttribute((const void *)k_accumulate_direct<P, MODE, CHUNKED, WAVES, RESCALE>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -822,7 +847,7 @@ static void am_launch_direct(ensi_ctx *ctx, hipStream_t st, const u64 *xbase, u3
     typedef std::true_type Yes;
     if (d_rescale) {
         if constexpr (MODE == AM_FP8) launch(No(), Four(), Yes());  // (the only mode that comes here with a rescale)
-    } else if (n_v <= AMD_CHUNKED_MIN || m > AMD_MAX_OUTPUTS)
+    } else if (!amd_chunked(n_v, m))
         launch(No(), Four(), No());
     else if (m <= 128)
         launch(Yes(), Four(), No());
@@ -905,7 +930,7 @@ int launch_accumulate_mfma(ensi_ctx *ctx, const u64 *xbase, size_t xstride, int 
     const int m_group = 8;  // 8 output tiles x 4 word tiles in flight per XCD
     const int P = planes <= 5 ? 5 : 7;
     const void *bias = mode == AM_INT8 ? (const void *)d_bias : (const void *)d_bias_fp;
-    if (am_direct(mode, n_v, m, d_rescale != nullptr)) {
+    if (am_direct(n_cu, 2 * l1 * ctiles, P, mode, n_v, m, d_rescale != nullptr)) {
 #define AMD_LAUNCH(PL, MODE) \
     am_launch_direct<PL, MODE>(ctx, st, xbase, (u32)xstride, n_v, n_kpad, wf, bias, m, l1, limb_stride_in, out, limb_stride_out, n_tiles_m, d_rescale)
         if (mode == AM_INT8) AMD_LAUNCH(7, AM_INT8);

@@ -424,6 +424,8 @@ void launch_accumulate(ensi_ctx *ctx, const u64 *xbase, size_t xstride, int n_v,
 // d_fconsts != nullptr selects the fp64 kernel (all active primes below 2^50)
 void launch_rescale(ensi_ctx *ctx, u64 *ct, int n_ct, int l1, int limb_stride, const u64 *d_consts, const double *d_fconsts,
                     hipStream_t st);
+// whether the signed sums of n_v operands into m outputs over `tiles` tiles of 32 words keep their digits in LDS
+bool am_direct(int n_cu, int tiles, int planes, int mode, int n_v, int m, bool rescale);
 // planes: 5 or 7 byte planes contracted; weights d_wt in fragment order [m_pad/256][n_kpad/32][4][2][64][16], n_kpad a
 // multiple of 256, and their mode AM_*.  Grows ctx->ws_xp (byte planes of a slice of the operand words); returns an ENSI_E_* code.
 // d_rescale != nullptr: operands are read at l1 + 1 limbs and multiplied/rescaled on the fly (fp64 constants [5][l1+1]).

@@ -326,6 +326,38 @@ def test_signed_sums_of_few_operands_or_outputs(bits, operands, outputs):
         ctx.close()
 
 
+@pytest.mark.parametrize("bits,operands,outputs,kernel", [(50, 256, 384, "accumulate_direct"), (50, 256, 385, "accumulate_mfma"), (36, 16, 960, "accumulate_direct"),
+                                                          (36, 16, 961, "accumulate_mfma"), (54, 300, 600, "accumulate_mfma"), (50, 769, 40, "accumulate_mfma")])
+def test_signed_sums_of_fewer_word_tiles_than_compute_units(bits, operands, outputs, kernel):
+    """Two limbs of the 2^10 ring, on both sides of the lines: the plain-ALU kernel on every word."""
+    import torch
+
+    from paper_2509_09424_amd import binding
+    ctx = binding.Context(10, bits, 2, bits + 2, 1, 1, 20, seed=1)
+    q = [int(x) for x in ctx.primes()[0]]
+    W = np.random.default_rng(operands).integers(-1, 2, (operands, outputs)).astype(np.int8)
+    x = torch.empty((operands, 2, 2, ctx.N), dtype=torch.int64, device="cuda")
+    for i in range(2):
+        x[:, :, i].random_(0, q[i], generator=torch.Generator(device="cuda").manual_seed(i))
+    got = []
+    for mode in (1, 2):
+        ctx.set_accumulate_mode(mode)
+        out = torch.full((outputs, 2, 2, ctx.N), -1, dtype=torch.int64, device="cuda")
+        h_in, h_out = ctx.ct_wrap(x.data_ptr(), operands, 2, 1.0), ctx.ct_wrap(out.data_ptr(), outputs, 2, 1.0)
+        wt = ctx.weights_prepare(W, ctx.n_slots, operands, "zero", 2)
+        ctx.profile_enable(True)
+        ctx.ternary_matmul_prepared(None, h_in, wt, h_out)
+        torch.cuda.synchronize()
+        ran = {k for k, v in ctx.profile_read().items() if v[1]}
+        assert mode == 1 or kernel in ran, ran
+        ctx.profile_enable(False)
+        got.append(out)
+        for h in (wt, h_in, h_out):
+            h.free()
+    assert torch.equal(*got)
+    ctx.close()
+
+
 @pytest.mark.parametrize("bits,operands,kernel", [(50, 8192, "accumulate_mfma"), (50, 8193, "accumulate"), (36, 32768, "accumulate_mfma"),
                                                   (36, 32769, "accumulate")])
 def test_signed_sums_at_the_most_operands(bits, operands, kernel):
