@@ -616,7 +616,8 @@ __global__ __launch_bounds__(AM_THREADS) void k_accumulate_mfma(const char *xp, 
 // and each wave runs through blocks of 32 outputs.
 //   CHUNKED = false: all operands fit LDS together (AMD_MAX_OPERANDS); a wave takes every fourth block of outputs.
 //   CHUNKED = true:  one block of outputs a wave (AMD_MAX_OUTPUTS), which keeps its sums while the operands pass through LDS, AMD_CHUNK_STEPS
-//   steps at a time; two blocks on a CU, so that one reads while the other multiplies.
+//   steps at a time.  Four waves, or eight over five planes, leave room for two blocks on a CU, so that one reads while the other multiplies; the others
+//   read and multiply by turns.
 // Bound by the reading of the operands and the writing of the outputs while the outputs are few, then by the fragment read from LDS that
 // every matrix instruction needs (in k_accumulate_mfma every second one does).  Four waves for up to 128 outputs, eight for 256, twelve
 // for 384: beyond that the sums do not fit the registers.
@@ -644,7 +645,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 12 ? 3 : 2) void k_accumulate_
     // digits of steps s0 .. s1 - 1 to LDS, the first of them at step 0
     auto fill = [&](int s0, int s1) {
         constexpr int PARTS = WAVES / 4;  // steps that the block's threads take at a time
-        const int k4 = tid >> 5 & 7, ln = tid & 31, part = tid >> 8;
+        const int k4 = tid >> 5 & 7, ln = tid & 31, part = wv >> 2;
         u32 *dst = (u32 *)smem + ((k4 >> 2) * 32 + plane_row(ln)) * 4 + (k4 & 3);
         AmFp mod, last;
         double k, k_q, qi, qi_q, kl, kl_q;
@@ -660,13 +661,16 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 12 ? 3 : 2) void k_accumulate_
         for (int sa = s0 + part; sa < s1; sa += AMD_AHEAD * PARTS) {
             u64 w[AMD_AHEAD][4], wl[RESCALE ? AMD_AHEAD : 1][4];
 #pragma unroll
-            for (int s = 0; s < AMD_AHEAD; s++)
+            for (int s = 0; s < AMD_AHEAD; s++) {
+                if (AMD_CHUNK_STEPS % (AMD_AHEAD * PARTS) && sa + s * PARTS >= s1) break;  // the next chunk's (read twice, 384 x 384 on 16 limbs of
+                                                                                           // 2^16 took 4.97 ms, now 4.11; 2560 x 384 19.7, 18.7)
 #pragma unroll
                 for (int j = 0; j < 4; j++) {
                     const int v = (sa + s * PARTS) * AM_TILE_K + 4 * k4 + j;
                     w[s][j] = v < n_v ? xw[(size_t)v * xstride + ln] : 0;
                     if (RESCALE) wl[s][j] = v < n_v ? xl[(size_t)v * xstride + ln] : 0;  // (no operand: zero stays zero)
                 }
+            }
             if (RESCALE) {
 #pragma unroll
                 for (int s = 0; s < AMD_AHEAD; s++)
