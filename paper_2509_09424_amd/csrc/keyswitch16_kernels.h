@@ -478,12 +478,19 @@ struct Inner<ArithInt> {
 //
 // What bounds the form that reads transformed digits (one rotation of the 2^16 ring at 16 + 4 limbs: 13 us, 14.6 before): the 21 MB of results
 // that it writes (a quarter of the time by themselves) and the words that come through a CU's L1, 106 KB a tile and rotation.  Those
-// come 16 bytes to a lane (8 bytes a lane reach 18 TB/s from L2, 16 bytes 34), keys once for the four rotations of a block (rotations that
+// come 16 bytes to a lane (8 bytes a lane reach 18 TB/s from L2, 16 bytes 34), keys once for the rotations of a block (those that
 // use one key are neighbours), twiddles in the order they are read in.  An accumulator to each wave, four waves to a SIMD, takes 18 %
 // longer, as every digit is then read twice; two and three waves to a SIMD are within 4 %.
-template <bool RAW>
-struct InnerBlock {
-    static constexpr u32 WAVES = RAW ? 2 : 4;  // rotations of a block, one to a wave
+// Rotations of a block, one to a wave: four where there are many, which share the lines of a key in the L1 of their CU; one where there are few, as a block
+// of waves that have no rotation keeps its LDS, and one of waves that have leaves other CUs empty.  Inner products against one wave and
+// four, over special primes of all kinds (geometric means, the kernel before blocks of four = 1): fills of one ciphertext on 2^15 and 2^16 1.07, 1.11, of five
+// 0.95, 1.18, of 17 1.00, 1.01, of 40 0.955, 0.926; 3 to 15 rotations of a ciphertext 0.92 to 1.04, 0.94 to 1.05, 30 0.984, 0.990, 60 0.966, 0.910; on 2^12 to 2^14 five
+// 0.91, 0.95, 30 0.941, 0.953, 60 0.933, 0.924.  The row-pass form never gains by a second wave (nine rotations 0.99, 1.03, 64 0.995, 0.998).
+#define INNER_WAVES 4
+#define INNER_WAVES_MIN 32  // rotations, or groups, from which a block has INNER_WAVES
+struct InnerLds {  // of a wave
+    u64 row[ROW_LDS];
+    ulonglong2 tw1[4 * 16];
 };
 // Values of a row that one pass over the digits adds up, and waves to a SIMD, by the arithmetic of the special primes: what its registers
 // allow without spilling.
@@ -691,28 +698,26 @@ __device__ __forceinline__ void inner_body(const Ks16Const &kc, const RotDesc *d
     }
 }
 
-// grid (8 * ceil(4 TILES * ext / 8) * ceil(n_grp / WAVES)): the rotations of a tile of four rows of one limb run next to each other on one XCD
+// grid (8 * ceil(4 TILES * ext / 8) * ceil(n_grp / waves)), 64 waves threads: the rotations of a tile of four rows of one limb run next to each other on one XCD
 // (block b runs on XCD b % 8), whose L2 then serves the digits that several rotations of one ciphertext read and the keys
 // that several ciphertexts read.
 // GROUP: the block adds the inner products of `members` consecutive descriptors (rotations of one ciphertext: same digits,
 // their own Galois element and key) before the inverse pass, so that the group is brought back to the ciphertext basis
 // by one inverse transform and one ModDown; n_grp then counts groups.
 template <int S, bool RAW, bool GROUP, class W>
-__global__ __launch_bounds__((64 * InnerBlock<RAW>::WAVES), (RAW ? 2 : InnerShape<GROUP, W>::PER_SIMD)) void k_ks16_inner(
-    Ks16Const kc, const RotDesc *desc, const PrimeConst *pcs, const u64 *tw_all, u64 *u, int members, u32 n_grp) {
-    constexpr u32 WAVES = InnerBlock<RAW>::WAVES;
-    __shared__ u64 lds[WAVES][ROW_LDS];
-    __shared__ ulonglong2 tw1[WAVES][4 * 16];
+__global__ __launch_bounds__((RAW ? 64 : 64 * INNER_WAVES), (RAW ? 2 : InnerShape<GROUP, W>::PER_SIMD)) void k_ks16_inner(
+    Ks16Const kc, const RotDesc *desc, const PrimeConst *pcs, const u64 *tw_all, u64 *u, int members, u32 n_grp, u32 waves) {
+    HIP_DYNAMIC_SHARED(InnerLds, lds)
     constexpr u32 TILES4 = 4 * Ring<S>::TILES;
     constexpr int C = InnerShape<GROUP, W>::VALUES;
     const int ext = kc.l1 + kc.K;
-    const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_blk = (n_grp + WAVES - 1) / WAVES;
-    const u32 k = blockIdx.x >> 3, q = k / n_blk * 8 + (blockIdx.x & 7), grp = k % n_blk * WAVES + wave;
+    const u32 wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_blk = (n_grp + waves - 1) / waves;
+    const u32 k = blockIdx.x >> 3, q = k / n_blk * 8 + (blockIdx.x & 7), grp = k % n_blk * waves + wave;
     if (q >= TILES4 * ext || grp >= n_grp) return;
     const int e = ext - 1 - (int)(q / TILES4), prime = ks_ext_prime(e, kc.l1, kc.L);  // the special limbs, which take longer, first
     const PrimeConst pc = load_prime(pcs, prime);
-    if (e < kc.l1) inner_body<S, RAW, GROUP, C, ArithFp>(kc, desc, pc, tw_all, u, prime, e, members, grp, q % TILES4, lds[wave], tw1[wave]);
-    else inner_body<S, RAW, GROUP, C, W>(kc, desc, pc, tw_all, u, prime, e, members, grp, q % TILES4, lds[wave], tw1[wave]);
+    if (e < kc.l1) inner_body<S, RAW, GROUP, C, ArithFp>(kc, desc, pc, tw_all, u, prime, e, members, grp, q % TILES4, lds[wave].row, lds[wave].tw1);
+    else inner_body<S, RAW, GROUP, C, W>(kc, desc, pc, tw_all, u, prime, e, members, grp, q % TILES4, lds[wave].row, lds[wave].tw1);
 }
 
 // ------------------------------------------------ the same for few rotations: a wave to each digit
@@ -1053,10 +1058,10 @@ void ks16_switch(ensi_ctx *ctx, const Ks16Const &kc, const RotDesc *d_desc, int 
         {
             ScopedTimer t(ctx, "ks_inner", st);
             auto inner = [&](auto raw_, auto group_) {
-                constexpr unsigned WAVES = InnerBlock<decltype(raw_)::value>::WAVES;
-                const unsigned blocks = (4u * TILES * ext + 7) / 8 * 8 * ((n_grp + WAVES - 1) / WAVES);
-                hipLaunchKernelGGL((k_ks16_inner<S, decltype(raw_)::value, decltype(group_)::value, W>), dim3(blocks), dim3(64 * WAVES), 0, st, kc, d_desc, ctx->d_pc,
-                                   ctx->d_tw, u, members, (u32)n_grp);
+                const unsigned waves = decltype(raw_)::value || n_grp < INNER_WAVES_MIN ? 1 : INNER_WAVES;
+                const unsigned blocks = (4u * TILES * ext + 7) / 8 * 8 * ((n_grp + waves - 1) / waves);
+                hipLaunchKernelGGL((k_ks16_inner<S, decltype(raw_)::value, decltype(group_)::value, W>), dim3(blocks), dim3(64 * waves), waves * sizeof(InnerLds), st, kc,
+                                   d_desc, ctx->d_pc, ctx->d_tw, u, members, (u32)n_grp, waves);
             };
             if (raw && kc.beta < INNER_SPLIT_WAVES && 4l * TILES * ext * n_rot <= INNER_SPLIT_MAX)
                 hipLaunchKernelGGL((k_ks16_inner_split<S, W>), dim3((4u * TILES * ext + 7) / 8 * 8 * n_rot), dim3(64 * (kc.beta + 1)), 0, st, kc, d_desc, ctx->d_pc,
