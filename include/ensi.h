@@ -191,7 +191,7 @@ int ensi_rotate(ensi_ctx *ctx, const ensi_gk *gk, const ensi_ct *in, const int32
  * ensi_rotate, but every intermediate (descriptors, raised digits, accumulators, conversion residues) lives in a
  * workspace that is linked into the library as a device array instead of being allocated: 96 MiB, held by every GPU
  * the library runs on from load time to the end of the process.  The call allocates and frees nothing (the
- * constants of every level, the pinned staging ring and the workspace's address are set up by ensi_ctx_create);
+ * constants of every level and the workspace's address are set up by ensi_ctx_create, descriptors travel as a kernel's arguments);
  * the per-kernel timers must be off.  Limits: at most 64 ciphertexts per call and
  *   n * (beta (l+K) + 3 l + 4 K) * 8 N  (+ n * l * 8 N on rings of 2^16 with ciphertext primes below 2^50)  bytes
  * <= 96 MiB, l = in.limbs, beta = ceil(l / alpha) -- one ciphertext of the 2^16 ring at 16 + 4 limbs (80 MiB), the

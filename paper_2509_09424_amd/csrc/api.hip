@@ -19,7 +19,6 @@
 // ------------------------------------------------------------ staged uploads
 // Up to UPLOAD_BYTES travel as a kernel's arguments: the kernels behind them need not wait for a copy engine (one rotation 74.9 -> 71.4 us, 64 x 64
 // on the 2^12 ring 57.4 -> 53.5).
-#define UPLOAD_BYTES 3072
 struct UploadWords {
     u32 w[UPLOAD_BYTES / 4];
 };

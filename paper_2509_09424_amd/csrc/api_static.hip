@@ -79,8 +79,8 @@ extern "C" int ensi_rotate_static(ensi_ctx *ctx, const ensi_gk *gk, const ensi_c
         desc[c].g = g;
         desc[c].g_inv = inv_mod_2n(g, N);
     }
-    // through the pinned ring the context allocated at creation (a slot holds 64 KiB, the descriptors at most 3 KiB)
-    if ((size_t)n * sizeof(RotDesc) > ctx->stage[ctx->stage_next].cap) ENSI_FAIL(ctx, ENSI_E_SHAPE, "descriptor table larger than a staging slot");
+    // as a kernel's arguments: no staging slot, which might have to grow, and no copy
+    static_assert(ENSI_STATIC_MAX_BATCH * sizeof(RotDesc) <= UPLOAD_BYTES, "the descriptors of a call travel as a kernel's arguments");
     ENSI_HIP(ctx, host_to_device(ctx, d_desc, desc, (size_t)n * sizeof(RotDesc), st));
     int rc;
     // every word of the workspace that a kernel reads is written earlier in this same call (digits by the raise, accumulators

@@ -81,8 +81,9 @@ inline int grow(ensi_ctx *ctx, u64 **p, size_t *have, size_t need) {
 int sample_ternary(ensi_ctx *ctx, int8_t *out, size_t n);
 int sample_error(ensi_ctx *ctx, int8_t *out, size_t n);
 
-// dst (device) <- src (host, any memory) on the stream, through the context's ring of pinned buffers: returns at once,
-// never waits for the stream, and src may be reused or freed as soon as the call returns.
+// dst (device) <- src (host, any memory) on the stream: returns at once, never waits for the stream, and src may be reused or freed as soon as the
+// call returns.  Up to UPLOAD_BYTES of whole words travel as a kernel's arguments, the rest through the context's ring of pinned buffers.
+#define UPLOAD_BYTES 3072
 hipError_t host_to_device(ensi_ctx *ctx, void *dst, const void *src, size_t bytes, hipStream_t st);
 
 // ---- key switching, shared by the entry points (api.hip) -------------------------------------------------

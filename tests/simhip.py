@@ -42,9 +42,9 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_t *p, int) { memset(p, 0, s
 const char *hipGetErrorString(hipError_t) { return "simulated"; }
 hipError_t hipGetLastError() { hipError_t e = last; last = hipSuccess; return e; }
 hipError_t hipGetSymbolAddress(void **p, const void *) { static void *scratch = calloc(96, 1 << 20); *p = scratch; return hipSuccess; }
-hipError_t hipMalloc(void **p, size_t n) { *p = calloc(n ? n : 1, 1); return hipSuccess; }
+hipError_t hipMalloc(void **p, size_t n) { LOG("alloc"); *p = calloc(n ? n : 1, 1); return hipSuccess; }
 hipError_t hipFree(void *p) { LOG("sync all"); free(p); return hipSuccess; }
-hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = calloc(n, 1); return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { LOG("alloc"); *p = calloc(n, 1); return hipSuccess; }
 hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { LOG("sync (nil)"); memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemcpy2D(void *d, size_t dp, const void *s, size_t sp, size_t w, size_t h, hipMemcpyKind) {
@@ -61,11 +61,11 @@ hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipSt
 hipError_t hipMemset(void *d, int v, size_t n) { memset(d, v, n); return hipSuccess; }
 hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t st) { LOG("fill %p", (void *)st); memset(d, v, n); return hipSuccess; }
 hipError_t hipDeviceSynchronize() { LOG("sync all"); return hipSuccess; }
-hipError_t hipStreamCreateWithFlags(hipStream_t *st, unsigned) { *st = (hipStream_t)malloc(8); return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *st, unsigned) { LOG("alloc"); *st = (hipStream_t)malloc(8); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t st) { free((void *)st); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t st) { LOG("sync %p", (void *)st); return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t st, hipEvent_t e, unsigned) { LOG("wait %p %p", (void *)st, (void *)e); return hipSuccess; }
-hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)malloc(8); return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { LOG("alloc"); *e = (hipEvent_t)malloc(8); return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
 hipError_t hipEventDestroy(hipEvent_t e) { free((void *)e); return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t st) { LOG("record %p %p", (void *)st, (void *)e); return hipSuccess; }
