@@ -385,7 +385,7 @@ struct Ring {
 // Brings the first eight of a forward step's values back to their range.  In the step's first stage value i + 8 is multiplied, which leaves
 // it small whatever it was, and added to and subtracted from value i: reducing the ones that are added to is enough.  In units of p (ArithFp,
 // primes just below 2^50; a product of y is within 1/2 + |y| / 4, its quotient's rounding): the first step of a column pass starts within 1 (or, folded, within 1/2 and 5 after
-// the basis conversion) and ends within 6.1, the ones after it start within 1/2 and 7.4 and end within 7.4 again, below the 8 = 2^53
+// the basis conversion) and ends within 6.31, the ones after it start within 1/2 and 7.4 and end within 7.4 again, below the 8 = 2^53
 // that a double holds.  (ArithWide, units of 2^60: 1/2 and 6.9, ending within 6.5, below 7.5.)  Reducing all sixteen took 3 instructions a word
 // more per pass.
 template <class A>
