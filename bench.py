@@ -568,12 +568,14 @@ def roofline_for(w, prof):
         "pm_icols_rescale": pm_sum(lambda l, t, o, src: o * (2 * (l - 1) + 2 + 2 * (l - 1))),
     }
     members = {"ntt": ["ntt_fwd_cols", "ntt_fwd_rows", "ntt_inv_rows", "ntt_inv_cols"]}
-    classes = list(hbm) + ["accumulate", "accumulate_mfma"]
+    # the products of few operands or outputs form their digits where they multiply them: one kernel, with the rescale or without
+    members["accumulate_direct"] = ["accumulate_direct", "rescale_accumulate_direct"]
+    classes = list(hbm) + ["accumulate", "accumulate_mfma", "accumulate_direct"]
     tot = {g: sum(prof.get(k, (0.0, 0))[0] for k in members.get(g, [g])) for g in classes}
     dom = max(tot, key=tot.get)
     ms = tot[dom]
     launches = sum(prof.get(k, (0.0, 0))[1] for k in members.get(dom, [dom]))
-    if dom == "accumulate_mfma":
+    if dom in ("accumulate_mfma", "accumulate_direct"):
         # Alg. 1 on the matrix cores: one int8 multiply-add per (output, operand, limb word, byte plane); 7 planes at 50 bits
         planes = -(-w.q_bits // 8)
         planes = 5 if planes <= 5 else 7 if planes <= 7 else 8

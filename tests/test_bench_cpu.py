@@ -53,6 +53,15 @@ def test_matrix_core_operation_count():
     assert abs(roof["achieved"] - 2.0 * 2560 * 2560 * 2 * 16 * 65536 * 7 / 0.05 / 1e12) < 1e-6
 
 
+def test_sums_in_one_kernel_are_the_dominant_one_where_they_are():
+    """The 2^12 workload forms its digits where it multiplies them: named, and counted like the contraction of planes."""
+    w = wl.BY_NAME["tiny"]
+    dom, roof = bench.roofline_for(w, {"accumulate_direct": (0.02, 2), "ks_inner": (0.01, 2)})
+    assert dom == roof["kernel"] == "accumulate_direct" and roof["bound"] == "mfma" and roof["launches"] == 2
+    assert abs(roof["achieved"] - 2.0 * 64 * 64 * 2 * 3 * 4096 * 5 / 2e-5 / 1e12) < 1e-6
+    assert bench.roofline_for(w, {"accumulate_direct": (0.02, 2), "ks_inner": (0.03, 2)})[0] == "ks_inner"
+
+
 def test_profile_facts_come_from_the_tracked_summary_or_not_at_all(tmp_path, monkeypatch):
     monkeypatch.setattr(bench, "ROOT", str(tmp_path))
     assert bench.profile_facts("ffn2560", "accumulate_mfma") == {}
