@@ -326,27 +326,35 @@ def test_signed_sums_of_few_operands_or_outputs(bits, operands, outputs):
         ctx.close()
 
 
-@pytest.mark.parametrize("bits,operands,outputs,kernel", [(50, 256, 384, "accumulate_direct"), (50, 256, 385, "accumulate_mfma"), (36, 16, 960, "accumulate_direct"),
-                                                          (36, 16, 961, "accumulate_mfma"), (54, 300, 600, "accumulate_mfma"), (50, 769, 40, "accumulate_mfma")])
-def test_signed_sums_of_fewer_word_tiles_than_compute_units(bits, operands, outputs, kernel):
-    """Two limbs of the 2^10 ring, on both sides of the lines: the plain-ALU kernel on every word."""
+@pytest.mark.parametrize("log_n,bits,operands,outputs,rescale,kernel", [
+    (10, 50, 256, 384, 0, "accumulate_direct"), (10, 50, 256, 385, 0, "accumulate_mfma"), (10, 36, 16, 960, 0, "accumulate_direct"), (10, 36, 16, 961, 0, "accumulate_mfma"),
+    (10, 54, 300, 600, 0, "accumulate_mfma"), (10, 50, 769, 40, 0, "accumulate_mfma"),
+    (16, 50, 128, 129, 1, "rescale_accumulate_direct"), (16, 36, 31, 600, 1, "rescale_accumulate_direct"), (16, 50, 129, 40, 1, "accumulate_mfma"),
+    (16, 50, 384, 390, 0, "accumulate_direct"), (16, 36, 300, 33, 0, "accumulate_direct")])
+def test_signed_sums_on_the_smallest_and_largest_rings(log_n, bits, operands, outputs, rescale, kernel):
+    """Two limbs: fewer word tiles than compute units, on both sides of the lines, and many, also with the rescale.  The plain-ALU kernel on every word."""
     import torch
 
     from paper_2509_09424_amd import binding
-    ctx = binding.Context(10, bits, 2, bits + 2, 1, 1, 20, seed=1)
+    L = 2 + rescale
+    ctx = binding.Context(log_n, bits, L, bits + 2, 1, 1, 20, seed=1)
     q = [int(x) for x in ctx.primes()[0]]
     W = np.random.default_rng(operands).integers(-1, 2, (operands, outputs)).astype(np.int8)
-    x = torch.empty((operands, 2, 2, ctx.N), dtype=torch.int64, device="cuda")
-    for i in range(2):
+    x = torch.empty((operands, 2, L, ctx.N), dtype=torch.int64, device="cuda")
+    for i in range(L):
         x[:, :, i].random_(0, q[i], generator=torch.Generator(device="cuda").manual_seed(i))
     got = []
     for mode in (1, 2):
         ctx.set_accumulate_mode(mode)
         out = torch.full((outputs, 2, 2, ctx.N), -1, dtype=torch.int64, device="cuda")
-        h_in, h_out = ctx.ct_wrap(x.data_ptr(), operands, 2, 1.0), ctx.ct_wrap(out.data_ptr(), outputs, 2, 1.0)
+        src = x.clone()
+        h_in, h_out = ctx.ct_wrap(src.data_ptr(), operands, L, 1.0), ctx.ct_wrap(out.data_ptr(), outputs, 2, 1.0)
         wt = ctx.weights_prepare(W, ctx.n_slots, operands, "zero", 2)
         ctx.profile_enable(True)
-        ctx.ternary_matmul_prepared(None, h_in, wt, h_out)
+        if rescale:
+            ctx.rescale_ternary_matmul_prepared(h_in, 2.0 ** -5, wt, h_out)
+        else:
+            ctx.ternary_matmul_prepared(None, h_in, wt, h_out)
         torch.cuda.synchronize()
         ran = {k for k, v in ctx.profile_read().items() if v[1]}
         assert mode == 1 or kernel in ran, ran
@@ -816,6 +824,28 @@ def test_rotations_of_few_and_more_ciphertexts(params):
     want = np.stack([stack_cts([p.o.rotate(c, o_gks[st]) for c in o_cts]) for st in steps])
     for n in (1, 2, 9, 16, 17, 33, 47, 64, 65, 128, 129):
         which, st = np.arange(n) % 2, np.arange(n) // 2 % 3
+        batch = p.ctx.ct_import(np.ascontiguousarray(both[which]), g_ct.scale)
+        out = p.ctx.rotate(g_gk, batch, [steps[k] for k in st])
+        assert np.array_equal(out.export(), want[st, which]), n
+        out.free()
+        batch.free()
+    for h in (g_ct, g_gk):
+        h.free()
+    p.close()
+
+
+@pytest.mark.parametrize("params", [(14, 50, 6, 60, 2, 2, 40), (14, 45, 4, 48, 2, 1, 36), (15, 50, 4, 61, 2, 2, 40), (15, 50, 3, 60, 1, 1, 40), (16, 50, 5, 60, 3, 2, 40),
+                                    (16, 45, 4, 48, 2, 1, 36), (16, 50, 3, 61, 2, 1, 40)], ids=["16K", "16K-fp", "32K-61bit", "32K", "64K", "64K-fp", "64K-61bit"])
+def test_few_rotations_on_large_rings(params):
+    """The same forms on the rings from 2^14: up to 512 waves of four rows a digit to a wave, then two and three ciphertexts past them."""
+    p = Pair(params)
+    steps = [1, -1]
+    o_gks, g_gk = p.galois_keys(steps)
+    o_cts, g_ct = p.encrypt_both(p.rng.uniform(-1, 1, (2, p.n)), p.pr.L)
+    both = stack_cts(o_cts)
+    want = np.stack([stack_cts([p.o.rotate(c, o_gks[st]) for c in o_cts]) for st in steps])
+    for n in (1, 2, 3, 9):
+        which, st = np.arange(n) % 2, np.arange(n) // 2 % 2
         batch = p.ctx.ct_import(np.ascontiguousarray(both[which]), g_ct.scale)
         out = p.ctx.rotate(g_gk, batch, [steps[k] for k in st])
         assert np.array_equal(out.export(), want[st, which]), n

@@ -32,9 +32,21 @@ def test_inner_products_over_transformed_digits_do_not_spill(rings):
         assert len(inner) == 6 and not any(inner.values()), (s, inner)
 
 
+def test_forms_for_few_rotations_do_not_spill(rings):
+    """A limb to a block, special limbs first, a wave to each digit; and the inverse column pass of up to three special primes (four take 128 registers for
+    their residues alone, and some of the rest goes through scratch memory: 18, or 9 where the special limbs come first)."""
+    for s, kernels in enumerate(rings):
+        few = {k: n for k, n in kernels.items() if any(name + "ILi%d" % s in k for name in ("k_ks16_fcols_one", "k_ks16_specials", "k_ks16_inner_split"))}
+        assert len(few) == 9 and not any(few.values()), (s, few)
+        icols = {k: n for k, n in kernels.items() if "k_ks16_icolsILi%d" % s in k}
+        assert len(icols) == 16, icols
+        assert all(n <= (18 if "Li4E" in k.split("Arith")[1] else 0) for k, n in icols.items()), (s, icols)
+
+
 def test_plane_splits_do_not_spill():
-    """The splits of operands into planes, with and without the rescale, for every kind of digits, and the contraction."""
+    """The splits of operands into planes, with and without the rescale, for every kind of digits, the contraction, and both in one kernel."""
     kernels = spilled("accumulate_mfma.hip")
+    assert len([k for k in kernels if "k_accumulate_direct" in k]) == 14
     assert len([k for k in kernels if "k_byte_planes_rescale" in k]) == 4 and not any(kernels.values()), kernels
 
 
