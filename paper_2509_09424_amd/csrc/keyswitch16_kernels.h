@@ -256,7 +256,7 @@ __device__ __forceinline__ void fcols_one_body(const Ks16Const &kc, const PrimeC
                                                ColLdsOne &sh, int col, int jj) {
     typedef Ring<S> R;
     constexpr size_t N = R::N;
-    const int l1 = kc.l1, ext = l1 + kc.K, j = row / ext, e = row - j * ext, first = j * kc.alpha, ns = kc.n_src[j];
+    const int l1 = kc.l1, ext = l1 + kc.K, j = row / ext, first = j * kc.alpha, ns = kc.n_src[j];
     A ar;
     ar.init(pc);
     typename A::T v[16];
